@@ -50,6 +50,8 @@ struct DevJob {
   int32_t steps;             // steps of this launch
   int32_t degree;            // kernel variant shared by all instances of the job
   int32_t bounded;           // 1: the instances reset their boundary layers after every step
+  int32_t nodes;             // register kernels: nodes per lane (2, 4 or 8)
+  int32_t s_per;             // register kernels: steps between wave exchanges (even)
   int32_t pad_;
 };
 struct DevJobInst {
@@ -66,6 +68,34 @@ struct DevJobInst {
   int32_t bkind;             // 0 periodic, 1 equilibrium layers, 2 non-equilibrium extrapolation
   int32_t layers;            // boundary layers at each end (bounded)
   int32_t pad_;
+};
+
+// Register-resident path: queue items.  A job's steps are split into parts (one
+// for most jobs), taken in the order of the list; part p waits for part p - 1.
+struct DevItem {
+  int32_t job;               // index into the launch's jobs
+  int32_t part;
+  int32_t steps;
+  int32_t more;              // 1: the job has a further part
+};
+
+// Register-resident path: a segment is a run of consecutive nodes of an
+// instance advanced by `waves` waves of one workgroup, R nodes per lane.
+struct DevSeg {
+  uint64_t in;               // device address of row 0 of the state read ...
+  uint64_t out;              // ... and written
+  int32_t n;                 // nodes of the instance
+  int32_t stride;            // row stride in elements
+  int32_t inst;              // index into coefficients / status
+  int32_t kind;              // 0 ring: the whole instance, its ends joined
+  int32_t x0;                // first node owned
+  int32_t len;               // nodes owned (written back)
+  int32_t lanes;             // lanes advanced: the owned nodes' and `extra` at each end
+  int32_t extra;
+  int32_t over;              // nodes by which the owned lanes exceed the ring (< R)
+  int32_t w0;                // first wave of the workgroup
+  int32_t waves;
+  int32_t lds_off;           // element offset of the segment's strips in LDS
 };
 
 // Slab path: an instance split over several co-resident workgroups (one slab
@@ -399,14 +429,17 @@ template <typename T, typename A> struct Relax;
 template <> struct Relax<double, double> {
   __device__ static const double* coef(const DevCoef* c) { return &c->wc[0][0]; }
   __device__ static double w0(const DevCoef* c) { return c->w0; }
+  __device__ static const double* w0p(const DevCoef* c) { return &c->w0; }
 };
 template <> struct Relax<float, double> {
   __device__ static const double* coef(const DevCoef* c) { return &c->wc[0][0]; }
   __device__ static double w0(const DevCoef* c) { return c->w0; }
+  __device__ static const double* w0p(const DevCoef* c) { return &c->w0; }
 };
 template <> struct Relax<float, float> {
   __device__ static const float* coef(const DevCoef* c) { return &c->wHf[0][0]; }
   __device__ static float w0(const DevCoef* c) { return c->w0f; }
+  __device__ static const float* w0p(const DevCoef* c) { return &c->w0f; }
 };
 
 template <int Q, int D, int P, typename T, typename A, bool V = false>

@@ -61,6 +61,11 @@ const void* resident_kernel(int q, int prec, int code) {
   return t ? t->resident_fn(prec, code) : nullptr;
 }
 
+const void* reg_kernel(int q, int prec, int code, bool wide) {
+  const QKernels* t = table(q);
+  return t ? t->reg_fn(prec, code, wide) : nullptr;
+}
+
 const void* tile_kernel(int q, int prec) {
   const QKernels* t = table(q);
   return t ? t->tile_fn(prec) : nullptr;
@@ -109,6 +114,26 @@ hipError_t launch_resident(int q, int prec, int code, const DevJob* jobs, const 
   return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
 }
 
+hipError_t launch_reg(int q, int prec, int code, bool wide, const DevItem* items, int nitems, const DevJob* jobs,
+                      const DevSeg* segs, int* counter, int* done, const DevCoef* coefs, int* status,
+                      long long wait_ticks, int stall_item, int grid, int block, size_t lds, hipStream_t s) {
+  const void* fn = reg_kernel(q, prec, code, wide);
+  if (!fn) return hipErrorInvalidValue;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  void* args[] = {(void*)&items, (void*)&nitems, (void*)&jobs,   (void*)&segs,       (void*)&counter,
+                  (void*)&done,  (void*)&coefs,  (void*)&status, (void*)&wait_ticks, (void*)&stall_item};
+  return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
+}
+
+hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu) {
+  const void* fn = reg_kernel(q, prec, code, wide);
+  if (!fn) return hipErrorInvalidValue;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, block, lds);
+}
+
 namespace {
 // kernel attributes, queried once per kernel (the planner asks per instance)
 bool kernel_attributes(const void* fn, hipFuncAttributes* out) {
@@ -136,7 +161,8 @@ int resident_vgprs(int q, int prec, int code) {
 size_t resident_static_lds(int q, int prec, int code) {
   hipFuncAttributes a;
   const void* fn = resident_kernel(q, prec, code);
-  if (!fn || !kernel_attributes(fn, &a)) return 1024;
+  if (!fn) return 0;
+  if (!kernel_attributes(fn, &a)) return 1024;
   return a.sharedSizeBytes;
 }
 

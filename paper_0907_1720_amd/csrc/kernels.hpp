@@ -11,22 +11,24 @@
 // sums with real exponents (P = 2): degree 2, 5, 7 or 11 of each class's
 // polynomial in phi^step (its strided layout); P = 3: the same for exactly the
 // classes phi^0 and phi^(1/2), degree 2 or 5.
-#define LBM_VARIANT_CASES \
-  LBM_CASE(5, 0)          \
-  LBM_CASE(7, 0)          \
-  LBM_CASE(9, 0)          \
-  LBM_CASE(13, 0)         \
-  LBM_CASE(19, 0)         \
-  LBM_CASE(5, 1)          \
-  LBM_CASE(9, 1)          \
-  LBM_CASE(13, 1)         \
-  LBM_CASE(19, 1)         \
-  LBM_CASE(2, 2)          \
-  LBM_CASE(5, 2)          \
-  LBM_CASE(7, 2)          \
-  LBM_CASE(11, 2)         \
-  LBM_CASE(2, 3)          \
+#define LBM_POLY_CASES \
+  LBM_CASE(5, 0)       \
+  LBM_CASE(7, 0)       \
+  LBM_CASE(9, 0)       \
+  LBM_CASE(13, 0)      \
+  LBM_CASE(19, 0)      \
+  LBM_CASE(5, 1)       \
+  LBM_CASE(9, 1)       \
+  LBM_CASE(13, 1)      \
+  LBM_CASE(19, 1)
+#define LBM_POWER_CASES \
+  LBM_CASE(2, 2)        \
+  LBM_CASE(5, 2)        \
+  LBM_CASE(7, 2)        \
+  LBM_CASE(11, 2)       \
+  LBM_CASE(2, 3)        \
   LBM_CASE(5, 3)
+#define LBM_VARIANT_CASES LBM_POLY_CASES LBM_POWER_CASES
 
 // dense degrees available to the initialisation kernel
 #define LBM_INIT_CASES \
@@ -94,6 +96,32 @@ const void* stream_kernel(int q, int code, int prec);
 hipError_t launch_resident(int q, int prec, int code, const DevJob* jobs, const DevJobInst* jinst, int njobs,
                            int nchunks, int* counter, int* slots, int* done, const DevCoef* coefs, int* status,
                            long long wait_ticks, int stall_item, int grid, int block, size_t lds, hipStream_t s);
+// Register-resident kernels (polynomial variants, parity < 2): nodes per lane.
+// The narrow kernels fit 128 registers (four waves per SIMD), the wide ones 256
+// (two); the i-th width of either, 0 past the last.  (Multiples of four on D1Q4
+// and D1Q5 cost the narrow kernels a register move for every sixth operation;
+// large tables, which few problems use, are built for fewer widths.)
+constexpr int kRegWidths = 6;
+constexpr int reg_width(int q, int elem, int degree, int parity, bool wide, int i) {
+  constexpr int w[8][2][kRegWidths] = {{{2, 3, 5, 6}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP64
+                                       {{2, 3, 4}, {3, 4, 6, 8}},                // D1Q6 / D1Q7, FP64
+                                       {{2, 3, 5, 8}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP32 storage
+                                       {{2, 3, 6}, {3, 6, 8, 10, 12}},           // D1Q6 / D1Q7, FP32 storage
+                                       {{3, 6}, {6, 10, 17}},                    // the same, large tables
+                                       {{2, 4}, {4, 8}},
+                                       {{3, 6}, {6, 10, 17}},
+                                       {{2, 4}, {4, 8, 12}}};
+  const bool large = parity == 0 ? degree >= 9 : degree >= 13;
+  return w[(large ? 4 : 0) + (elem == 8 ? 0 : 2) + (q >= 6 ? 1 : 0)][wide ? 1 : 0][i];
+}
+constexpr int reg_waves(bool wide) { return wide ? 8 : 16; }   // most waves of a workgroup: a CU's
+inline bool reg_variant(int code) { return ((code >> 8) & 0xff) < 2; }
+// persistent launch over `nitems` parts of jobs of ring segments; done[job] and
+// the counter start at 0; waits and stall_item as launch_resident
+hipError_t launch_reg(int q, int prec, int code, bool wide, const DevItem* items, int nitems, const DevJob* jobs,
+                      const DevSeg* segs, int* counter, int* done, const DevCoef* coefs, int* status,
+                      long long wait_ticks, int stall_item, int grid, int block, size_t lds, hipStream_t s);
+hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu);
 // VGPRs per thread of the resident kernel of variant `code`
 int resident_vgprs(int q, int prec, int code);
 // static LDS bytes of the resident kernel (0 by construction)

@@ -3,6 +3,7 @@
 // launchers as the table q_kernels_<q>.  `prec` selects (storage, arithmetic):
 // 0 (double, double), 1 (float, double), 2 (float, float).
 #include "kernels_body.hpp"
+#include "reg_body.hpp"
 #include "kernels_table.hpp"
 
 #ifndef LBM_Q
@@ -61,7 +62,7 @@ const void* resident_fn(int code) {
 #define LBM_CASE(DD, PP) \
   case DD | (PP << 8):   \
     return (const void*)k_resident<Q, DD, PP, T, A, false>;
-    LBM_VARIANT_CASES
+    LBM_POWER_CASES
 #undef LBM_CASE
 #define LBM_CASE(DD, PP)            \
   case DD | (PP << 8) | (1 << 16): \
@@ -77,6 +78,24 @@ const void* resident_prec(int prec, int code) {
   if (prec == 0) return resident_fn<Q, double, double>(code);
   if (prec == 1) return resident_fn<Q, float, double>(code);
   return resident_fn<Q, float, float>(code);
+}
+
+template <int Q, typename T, typename A>
+const void* reg_fn(int code, bool wide) {
+  switch (code) {
+#define LBM_CASE(DD, PP) \
+  case DD | (PP << 8):   \
+    return wide ? (const void*)k_reg<Q, DD, PP, T, A, true> : (const void*)k_reg<Q, DD, PP, T, A, false>;
+    LBM_POLY_CASES
+#undef LBM_CASE
+  }
+  return nullptr;
+}
+template <int Q>
+const void* reg_prec(int prec, int code, bool wide) {
+  if (prec == 0) return reg_fn<Q, double, double>(code, wide);
+  if (prec == 1) return reg_fn<Q, float, double>(code, wide);
+  return reg_fn<Q, float, float>(code, wide);
 }
 
 template <int Q>
@@ -152,7 +171,7 @@ const void* slab_prec(int prec, int code) {
 
 QKernels LBM_CAT(q_kernels_, LBM_Q) = {
     &launch_init_p<LBM_Q>, &launch_bound_p<LBM_Q>, &launch_stream_p<LBM_Q>, &stream_prec<LBM_Q>,
-    &resident_prec<LBM_Q>, &tile_prec<LBM_Q>,      &slab_prec<LBM_Q>,
+    &resident_prec<LBM_Q>, &reg_prec<LBM_Q>, &tile_prec<LBM_Q>, &slab_prec<LBM_Q>,
 };
 
 }  // namespace lbm

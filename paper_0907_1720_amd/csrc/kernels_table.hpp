@@ -15,6 +15,7 @@ struct QKernels {
                        hipStream_t s);
   const void* (*stream_fn)(int prec, int code);
   const void* (*resident_fn)(int prec, int code);
+  const void* (*reg_fn)(int prec, int code, bool wide);
   const void* (*tile_fn)(int prec);
   const void* (*slab_fn)(int prec, int code);
 };

@@ -1,0 +1,458 @@
+// Register-resident time steps for gfx950: a wave holds 64 R consecutive nodes
+// of a periodic instance in vector registers, lane l the nodes l R .. l R + R-1
+// (all q populations), and advances `s_per` steps between exchanges.
+//
+// Streaming is the alternating (AA) pattern of the LDS kernels with registers
+// for slots: an even step relaxes each node and swaps opposite populations in
+// place; an odd step gathers from the neighbouring nodes' slots and scatters
+// back to them.  Within a lane both are a renaming of registers; the sum_j
+// |e_j| values that cross a lane edge move with wave-shift DPP moves, twice per
+// odd step.  What crosses a wave edge is not moved at all: a wave carries
+// `halo` = s_per max|e_j| extra nodes on each side, the exact region shrinks by
+// max|e_j| nodes per step, and after s_per steps the waves of an instance
+// publish the outer `halo` nodes of their cores in LDS, meet at one workgroup
+// barrier and refill their halos (two strip buffers alternate, so one barrier
+// suffices).  The per-node arithmetic is the Relaxer's, in its order: results
+// are bitwise those of every other kernel.
+//
+// Bound: VALU issue.  Per KdV node update in FP64 the step loop issues 34
+// arithmetic operations and 0.7 to 4 lane-edge moves (17 to 3 nodes per lane);
+// the LDS-resident loop before it issued 37.7 and, with one 160 KB instance set
+// per CU, kept VALU busy 0.54 of the time (LDS latency, one barrier per step).
+// On one MI355X the loop alone reaches 1.0e12 node updates/s in FP64 (issue
+// peak at 2.4 GHz: 1.1e12) and 8.5e11 in FP32 storage, whose ten conversions
+// per node stay; with halos and exchanges 9.3e11 and 8.2e11 (8 to 17 nodes per
+// lane).  Batches, LDS-resident before -> now: 4096 KdV/mKdV grids of 256..4096
+// nodes 5.4e11 -> 8.3e11 (FP64) and 6.0e11 -> 6.8e11 (FP32 storage) node
+// updates/s; 512 Kuramoto-Sivashinsky grids of 1024 nodes 8.1 -> 5.8 ms per 8000
+// steps; one KdV grid of 800 nodes 0.53 -> 0.35 us per step.
+#pragma once
+
+#include <utility>
+
+#include "kernels.hpp"
+
+namespace lbm {
+
+// Relaxation of R nodes held in registers, in place, with opposite populations
+// swapped: f[r][opp(j)] = f*_j(r).  Same operations in the same order per node
+// as Relaxer<Q, D, P, T, A>; nodes advance together a population pair at a
+// time, so that a coefficient is read once for all of them.
+template <int Q, int D, int P, typename T, typename A>
+struct RegRelaxer {
+  static_assert(P < 2, "polynomial equilibria");
+  static constexpr int K = P == 0 ? D + 1 : (D + 1) / 2;   // coefficients per population
+  static constexpr bool kRest = (sizeof(T) == 4 && sizeof(A) == 8);
+  // coefficients below the leading one: held in scalar registers for the whole
+  // launch when they fit, else read from the constant cache at every step
+  static constexpr bool kPin = Q * (K - 1) * (int)sizeof(A) / 4 <= 52;
+  using CT = const __attribute__((address_space(4))) A*;
+  CT c;
+  A top[Q];
+  A low[kPin ? Q : 1][kPin ? K - 1 : 1];
+  A add[kRest && P == 1 ? Q : 1];
+  A w0;
+  double s0;
+
+  __device__ __forceinline__ void init(const DevCoef* __restrict__ cf) {
+    c = (CT)Relax<T, A>::coef(cf);
+    const CT coef = c;
+    w0 = *(CT)Relax<T, A>::w0p(cf);
+    s0 = *(const __attribute__((address_space(4))) double*)&cf->s0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      top[j] = coef[j * kRow + K - 1];
+      asm volatile("" : "+v"(top[j]));
+    }
+    if constexpr (kPin) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j)
+#pragma unroll
+        for (int d = 0; d < K - 1; ++d) {
+          low[j][d] = coef[j * kRow + d];
+#if defined(__HIP_DEVICE_COMPILE__)
+          asm volatile("" : "+s"(low[j][d]));
+#endif
+        }
+    }
+    if constexpr (kRest && P == 1) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        add[j] = (A) * (const __attribute__((address_space(4))) double*)&cf->cst[j];
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+s"(add[j]));
+#endif
+      }
+    }
+  }
+  __device__ __forceinline__ A finish(int j, A acc, A p, A f) const {
+    if constexpr (P == 1) {
+      if constexpr (kRest)
+        acc = fma_a(acc, p, add[j]);
+      else
+        acc = fma_a(acc, p, (A)0);
+    }
+    return fma_a(w0, f, acc);
+  }
+
+  // the nodes R0 .. R0 + B - 1 of the R
+  template <int R, int R0, int B>
+  __device__ __forceinline__ void relax_nodes(T (&f)[R][Q]) const {
+    A p[R], u[R];
+#pragma unroll
+    for (int r = R0; r < R0 + B; ++r) {
+      double s = (double)f[r][0];
+      if constexpr (kRest && P == 1) s = s0 + s;
+#pragma unroll
+      for (int j = 1; j < Q; ++j) s += (double)f[r][j];
+      p[r] = (A)s;
+      u[r] = P == 0 ? p[r] : p[r] * p[r];
+    }
+    // tables outside registers: a group of kGroup coefficients is loaded while
+    // the one before is evaluated, and no earlier (two pointers the compiler
+    // must treat as new after every other group), so that at most two are held
+    CT pt[2] = {c, c};
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (!kPin) asm volatile("" : "+s"(pt[0]), "+s"(pt[1]) : "v"(p[R0 + B - 1]));
+#endif
+    int used = 0;
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+      const int o = opposite<Q>(j);
+      if (o < j) continue;
+      A a[R], b[R];
+      horner<R, R0, B>(j, a, u, pt, used);
+      if (o != j) horner<R, R0, B>(o, b, u, pt, used);
+#pragma unroll
+      for (int r = R0; r < R0 + B; ++r) {
+        const T x = (T)finish(j, a[r], p[r], (A)f[r][j]);
+        if (o != j) {
+          const T y = (T)finish(o, b[r], p[r], (A)f[r][o]);
+          f[r][j] = y;
+        }
+        f[r][o] = x;
+      }
+    }
+  }
+  static constexpr int kGroup = 32 / (int)sizeof(A) * 2;
+  template <int R, int R0, int B>
+  __device__ __forceinline__ void horner(int j, A (&a)[R], const A (&u)[R], CT (&pt)[2], int& used) const {
+#pragma unroll
+    for (int r = R0; r < R0 + B; ++r) a[r] = top[j];
+#pragma unroll
+    for (int d = K - 2; d >= 0; --d, ++used) {
+      const A cd = kPin ? low[kPin ? j : 0][kPin ? d : 0] : pt[(used / kGroup) & 1][j * kRow + d];
+#pragma unroll
+      for (int r = R0; r < R0 + B; ++r) a[r] = fma_a(a[r], u[r], cd);
+#if defined(__HIP_DEVICE_COMPILE__)
+      if constexpr (!kPin)
+        if (used % kGroup == kGroup - 1) asm volatile("" : "+s"(pt[(used / kGroup) & 1]) : "v"(a[R0]));
+#endif
+    }
+  }
+  // all R nodes, B at a time
+  template <int B, int R, int R0 = 0>
+  __device__ __forceinline__ void relax_swap(T (&f)[R][Q]) const {
+    constexpr int N = B < R - R0 ? B : R - R0;
+    relax_nodes<R, R0, N>(f);
+    if constexpr (R0 + N < R) {
+      __builtin_amdgcn_sched_barrier(0);
+      relax_swap<B, R, R0 + N>(f);
+    }
+  }
+};
+
+// value of lane l - 1 (up) or l + 1 (down), `By` lanes away; lanes beyond the
+// wave read zero (their nodes are outside the exact region)
+template <int Ctrl>
+__device__ __forceinline__ int dpp_move(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, Ctrl, 0xf, 0xf, true);
+}
+template <int By>
+__device__ __forceinline__ int lane_shift(int v) {
+  if constexpr (By > 0)
+    return lane_shift<By - 1>(dpp_move<0x138>(v));   // wave_shr:1
+  else if constexpr (By < 0)
+    return lane_shift<By + 1>(dpp_move<0x130>(v));   // wave_shl:1
+  else
+    return v;
+}
+template <int By>
+__device__ __forceinline__ float lane_shift(float v) {
+  return __int_as_float(lane_shift<By>(__float_as_int(v)));
+}
+template <int By>
+__device__ __forceinline__ double lane_shift(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = lane_shift<By>((int)(unsigned)(b & 0xffffffffll));
+  const int hi = lane_shift<By>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+constexpr int floor_div(int a, int b) { return a >= 0 ? a / b : -((b - 1 - a) / b); }
+
+// n[r][j] = the value at node (lane R + r) - e_j, population opp(j): what node r
+// reads in an odd step
+template <int Q, int R, typename T>
+__device__ __forceinline__ void reg_gather(const T (&f)[R][Q], T (&n)[R][Q]) {
+  auto each = [&]<int r, int j>() {
+    constexpr int at = r - velocity<Q>(j);
+    constexpr int off = floor_div(at, R);   // lane offset of the source
+    n[r][j] = lane_shift<-off>(f[at - off * R][opposite<Q>(j)]);
+  };
+  [&]<int... i>(std::integer_sequence<int, i...>) { (each.template operator()<i / Q, i % Q>(), ...); }
+  (std::make_integer_sequence<int, R * Q>{});
+}
+// the inverse: n[r][j] goes to node (lane R + r) - e_j, population opp(j)
+template <int Q, int R, typename T>
+__device__ __forceinline__ void reg_scatter(const T (&n)[R][Q], T (&f)[R][Q]) {
+  auto each = [&]<int r, int j>() {
+    constexpr int at = r - velocity<Q>(j);
+    constexpr int off = floor_div(at, R);
+    f[at - off * R][opposite<Q>(j)] = lane_shift<off>(n[r][j]);
+  };
+  [&]<int... i>(std::integer_sequence<int, i...>) { (each.template operator()<i / Q, i % Q>(), ...); }
+  (std::make_integer_sequence<int, R * Q>{});
+}
+
+template <int Q, int R, int B, typename T, typename X>
+__device__ __forceinline__ void reg_even(T (&f)[R][Q], X& relax) {
+  relax.template relax_swap<B>(f);
+}
+template <int Q, int R, int B, typename T, typename X>
+__device__ __forceinline__ void reg_odd(T (&f)[R][Q], X& relax) {
+  T n[R][Q];
+  reg_gather<Q, R>(f, n);
+  relax.template relax_swap<B>(n);
+  reg_scatter<Q, R>(n, f);
+}
+
+
+// all of this wave's loads have returned (waited for here, and not at their
+// first uses inside the step loop)
+__device__ __forceinline__ void wait_loads() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) expcnt(7) lgkmcnt(15)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// the sign-free word that holds the exponent: not below infinity's for NaN and Inf
+__device__ __forceinline__ unsigned exponent_word(float v) { return (unsigned)__float_as_int(v) & 0x7fffffffu; }
+__device__ __forceinline__ unsigned exponent_word(double v) { return (unsigned)__double2hiint(v) & 0x7fffffffu; }
+
+// Advance of one segment by the waves that hold it.  `sg` is the segment, `w`
+// this wave's number in it; waves without a segment (act false) only meet the
+// barriers.  The outer halos of a ring segment's first and last waves are each
+// other's.
+template <int Q, int R, int B, int D, int P, typename T, typename A>
+__device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w, bool act,
+                                            const DevCoef* __restrict__ cf, int* __restrict__ status) {
+  constexpr int H = Q / 2;
+  using GT = __attribute__((address_space(1))) T;   // global memory
+  const int lane = threadIdx.x & 63;
+  const int hl = (s_per * H + R - 1) / R;   // halo lanes at each end of a wave
+  if (!act) {
+    __syncthreads();
+    for (int done = s_per; done < steps; done += s_per) __syncthreads();
+    return;
+  }
+  RegRelaxer<Q, D, P, T, A> relax;
+  relax.init(cf);
+  const int W = sg.waves, n = sg.n;
+  // lanes of nodes advanced by this wave, among the segment's `lanes`
+  const int b0 = (int)((int64_t)w * sg.lanes / W), b1 = (int)((int64_t)(w + 1) * sg.lanes / W);
+  const int cl = b1 - b0;
+  const int ring = sg.kind == 0;
+  // strips: [wave][buffer][side][(hl + 1) R nodes][Q]
+  const int strip = (hl + 1) * R * Q;
+  int pub = -1, ref = -1;
+  {
+    const int i = lane - hl;
+    if (i >= 0 && i <= hl)
+      pub = w * 4 * strip + i * R * Q;
+    else if (i < cl && i >= cl - 1 - hl)
+      pub = (w * 4 + 1) * strip + (i - (cl - 1 - hl)) * R * Q;
+    if (lane < hl) {
+      if (w > 0)
+        ref = ((w - 1) * 4 + 1) * strip + (lane + 1) * R * Q;
+      else if (ring)
+        ref = ((W - 1) * 4 + 1) * strip + ((lane + 1) * R - sg.over) * Q;
+    } else if (i >= cl && i < cl + hl) {
+      if (w < W - 1)
+        ref = (w + 1) * 4 * strip + (i - cl) * R * Q;
+      else if (ring)
+        ref = ((i - cl) * R + sg.over) * Q;
+    }
+  }
+  T* S = L + sg.lds_off;
+  T f[R][Q];
+  const int lane_x = (b0 - hl + lane - sg.extra) * R;   // first node of the lane, relative to x0
+  {
+    const GT* g = (const GT*)(uintptr_t)sg.in;
+    int base = (sg.x0 + lane_x) % n;
+    base += base < 0 ? n : 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      int x = base + r;
+      x -= x >= n ? n : 0;
+      x -= x >= n ? n : 0;
+#pragma unroll
+      for (int j = 0; j < Q; ++j) f[r][j] = g[(int64_t)j * sg.stride + x];
+    }
+  }
+  // in == out for rings: every wave has loaded before the first one stores
+  // (calls of at most s_per steps meet no other barrier)
+  wait_loads();
+  __syncthreads();
+  int pairs = steps >> 1, k = s_per >> 1, buf = 0;
+  if (pairs > 0) do {
+      reg_even<Q, R, B>(f, relax);
+      reg_odd<Q, R, B>(f, relax);
+      if (--k == 0 && (pairs > 1 || (steps & 1))) {   // more steps to come: exchange
+        k = s_per >> 1;
+        if (pub >= 0) {
+          T* p = S + pub + buf;
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < Q; ++j) p[r * Q + j] = f[r][j];
+        }
+        __syncthreads();
+        if (ref >= 0) {
+          const T* p = S + ref + buf;
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < Q; ++j) f[r][j] = p[r * Q + j];
+        }
+        buf = 2 * strip - buf;
+      }
+    } while (--pairs > 0);
+  if (steps & 1) {   // the last step: relax, then stream to the natural layout
+    T t[R][Q];
+    reg_even<Q, R, B>(f, relax);
+    reg_gather<Q, R>(f, t);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int j = 0; j < Q; ++j) f[r][j] = t[r][j];
+  }
+  GT* out = (GT*)(uintptr_t)sg.out;
+  // the largest exponent written by the lane, as an unsigned word (a lane mask
+  // of the test itself, carried through these branches, cost scalar registers)
+  unsigned top = 0;
+  const int i = lane - hl;
+  if (i >= 0 && i < cl) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (lane_x + r >= 0 && lane_x + r < sg.len) {
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+          const unsigned e = exponent_word(f[r][j]);
+          top = top > e ? top : e;
+          out[(int64_t)j * sg.stride + sg.x0 + lane_x + r] = f[r][j];
+        }
+      }
+    }
+  }
+  if (top >= exponent_word((T)__builtin_inf())) atomicOr(status + sg.inst, 1);
+}
+
+// Nodes relaxed together: all of a lane's where each coefficient is loaded once
+// for them; else few, since more would only hold more temporaries.
+constexpr int reg_together(bool pin, int R) { return !pin ? R : R <= 3 ? R : R == 5 ? 3 : 2; }
+
+// the width of this job
+template <int Q, int D, int P, typename T, typename A, bool Wide, int I>
+__device__ __forceinline__ void reg_widths(int nodes, T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w,
+                                           bool act, const DevCoef* __restrict__ cf, int* __restrict__ status) {
+  constexpr int R = reg_width(Q, (int)sizeof(T), D, P, Wide, I);
+  if constexpr (R > 0) {
+    if (nodes == R)
+      reg_segment<Q, R, reg_together(RegRelaxer<Q, D, P, T, A>::kPin, R), D, P, T, A>(L, steps, s_per, sg, w, act, cf,
+                                                                                  status);
+    else if constexpr (I + 1 < kRegWidths)
+      reg_widths<Q, D, P, T, A, Wide, I + 1>(nodes, L, steps, s_per, sg, w, act, cf, status);
+  }
+}
+
+// Persistent kernel over the parts of jobs (a job: ring segments of one variant
+// and one width, all the waves of a workgroup).  A workgroup takes the next item
+// of the list until it is empty; the list holds part p of a job before part
+// p + 1, so a part that waits for its predecessor (done[job]) waits for a
+// workgroup that is running.  The wait is bounded: after `wait_ticks` ticks of
+// the constant-rate wall clock the part marks its instances (status bit 4), is
+// skipped and published, so that a scheduling fault ends the kernel.
+// `stall_item` (-1 normally) names an item that is taken but never run nor
+// published -- a test hook that makes the next part's wait give up.
+template <int Q, int D, int P, typename T, typename A, bool Wide>
+__global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_per_eu(Wide ? 2 : 4))) void k_reg(
+    const DevItem* __restrict__ items, int nitems, const DevJob* __restrict__ jobs, const DevSeg* __restrict__ segs,
+    int* __restrict__ counter, int* __restrict__ done, const DevCoef* __restrict__ coefs, int* __restrict__ status,
+    long long wait_ticks, int stall_item) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* L = reinterpret_cast<T*>(smem_raw);
+  __shared__ int slot;   // the queue item, then whether a wait gave up
+  const int tid = threadIdx.x;
+  int pub_job = -1, pub_val = 0;
+  for (;;) {
+    if (tid == 0) {
+      if (pub_job >= 0) __hip_atomic_store(done + pub_job, pub_val, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      slot = atomicAdd(counter, 1);
+    }
+    __syncthreads();
+    const int item = __builtin_amdgcn_readfirstlane(slot);
+    __syncthreads();
+    if (item >= nitems) break;
+    pub_job = -1;
+    if (item == stall_item) continue;
+    const DevItem it = items[item];
+    const DevJob jb = jobs[it.job];
+    if (it.steps > 0) {
+      if (it.part > 0) {
+        if (tid == 0) {
+          const long long t0 = wall_clock64();
+          int seen;
+          while ((seen = __hip_atomic_load(done + it.job, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < it.part &&
+                 wall_clock64() - t0 < wait_ticks)
+            __builtin_amdgcn_s_sleep(8);
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+          slot = seen < it.part ? 1 : 0;
+        }
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const int gave_up = __builtin_amdgcn_readfirstlane(slot);
+        if (gave_up) {
+          if (tid < jb.count) atomicOr(status + segs[jb.first + tid].inst, 4);
+          __syncthreads();
+          if (it.more) {
+            pub_job = it.job;
+            pub_val = it.part + 1;
+          }
+          continue;
+        }
+      }
+      // the segment of this wave
+      const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      int mine = -1;
+      for (int k = 0; k < jb.count; ++k)
+        if (wave >= segs[jb.first + k].w0 && wave < segs[jb.first + k].w0 + segs[jb.first + k].waves) mine = k;
+      mine = __builtin_amdgcn_readfirstlane(mine);
+      const bool act = mine >= 0;
+      DevSeg sg{};
+      if (act) sg = segs[jb.first + mine];
+      const DevCoef* cf = coefs + (act ? sg.inst : 0);
+      const int w = wave - sg.w0;
+      reg_widths<Q, D, P, T, A, Wide, 0>(jb.nodes, L, it.steps, jb.s_per, sg, w, act, cf, status);
+      __syncthreads();   // strips are read before the next item's are written
+      if (it.more) {
+        __threadfence();   // this thread's write-back is visible to every CU
+        __syncthreads();
+        pub_job = it.job;
+        pub_val = it.part + 1;
+      }
+    }
+  }
+}
+
+}  // namespace lbm

@@ -35,7 +35,8 @@ constexpr int kBlock = 256;
 constexpr int kMaxSlabs = 2048;       // workgroups of one slab launch
 constexpr int kSplitNodes = 1024;     // smallest grid split into slabs when the GPU is mostly idle
 constexpr int kMaxResidentGrid = 256 * 8;
-constexpr int kMaxLaunches = 64;      // resident launches per advance pass (one per lattice, precision, variant)
+constexpr int kMaxLaunches = 512;     // queue launches per advance pass (one per lattice, precision, variant, kernel)
+constexpr int kMaxResident = 64;      // those of the LDS-resident kernels
 constexpr int kAuxStreams = 16;       // concurrent lanes (resident launches, tiled groups, slab launches)
 constexpr uint64_t kMagic = 0x4c424d4850444531ull;   // "LBMHPDE1"
 
@@ -119,6 +120,11 @@ struct lbm_batch_s {
   DevJob* jobs = nullptr;             // two slots of items_cap jobs
   int* done = nullptr;                // per job: chunks published (two slots of items_cap)
   DevJob* jobs_host = nullptr;
+  DevSeg* segs = nullptr;             // register-resident segments: two slots of items_cap records
+  DevSeg* segs_host = nullptr;
+  DevItem* parts = nullptr;           // queue items of the register launches: two slots of parts_cap
+  DevItem* parts_host = nullptr;
+  int parts_cap = 0;
   hipEvent_t items_done[2] = {nullptr, nullptr};
   int items_cap = 0;
   int slot = 0;
@@ -268,6 +274,10 @@ void destroy_batch(lbm_batch_s* b) {
   for (StepGraph& g : b->step_graphs) release_graph(&g);
   hipFree(b->bound);
   if (b->jobs_host) hipHostFree(b->jobs_host);
+  hipFree(b->segs);
+  if (b->segs_host) hipHostFree(b->segs_host);
+  hipFree(b->parts);
+  if (b->parts_host) hipHostFree(b->parts_host);
   for (int k = 0; k < 2; ++k)
     if (b->items_done[k]) hipEventDestroy(b->items_done[k]);
   hipFree(b->scratch);
@@ -372,7 +382,7 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn) {
   b->counters_cap = 2 * kMaxLaunches;   // 2 item slots x up to kMaxLaunches launches
   if (hipMalloc(&b->counter, sizeof(int) * b->counters_cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   // one queue slot per workgroup of each resident launch
-  if (hipMalloc(&b->slots, sizeof(int) * kMaxResidentGrid * 2 * kMaxLaunches) != hipSuccess)
+  if (hipMalloc(&b->slots, sizeof(int) * kMaxResidentGrid * 2 * kMaxResident) != hipSuccess)
     return LBM_ERR_OUT_OF_MEMORY;
   for (int k = 0; k < kAuxStreams; ++k) {
     LBM_HIP(hipStreamCreateWithFlags(&b->aux[k], hipStreamNonBlocking));
@@ -390,6 +400,9 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn) {
   if (hipMalloc(&b->jobs, sizeof(DevJob) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&b->done, sizeof(int) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   if (hipHostMalloc((void**)&b->jobs_host, sizeof(DevJob) * 2 * count, hipHostMallocDefault) != hipSuccess)
+    return LBM_ERR_OUT_OF_MEMORY;
+  if (hipMalloc(&b->segs, sizeof(DevSeg) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+  if (hipHostMalloc((void**)&b->segs_host, sizeof(DevSeg) * 2 * count, hipHostMallocDefault) != hipSuccess)
     return LBM_ERR_OUT_OF_MEMORY;
   for (int k = 0; k < 2; ++k) LBM_HIP(hipEventCreateWithFlags(&b->items_done[k], hipEventDisableTiming));
   b->scratch_elems = maxn + 64;
@@ -576,12 +589,74 @@ int hw_lanes() {
   return lanes;
 }
 
+// Register-resident path: how an instance of n nodes lies in waves of R nodes
+// per lane.  A wave's 64 lanes hold its core and `halo` lanes at each end
+// (s max|e| nodes for s steps between exchanges).  A grid shorter than a wave's
+// smallest core is held as several periods of itself.
+struct RegFit {
+  int R = 0;       // nodes per lane
+  int s = 0;       // steps between wave exchanges
+  bool wide = false;
+  int lanes = 0;   // lanes of owned nodes (all periods)
+  int over = 0;    // nodes by which they exceed the periods
+  int waves = 0;
+  double cost = 0.0;   // of one wave and step, in VALU operations
+};
+int reg_halo(int q, int R, int s) { return (s * (q / 2) + R - 1) / R; }
+// elements of one wave's exchange strips in LDS
+int reg_strip(int q, int R, int s) { return 4 * (reg_halo(q, R, s) + 1) * R * q; }
+void reg_place(int q, int n, RegFit* f) {
+  const int hl = reg_halo(q, f->R, f->s), least = 2 * (hl + 1), cap = 64 - 2 * hl;
+  const int periods = std::max(1, (least * f->R + n - 1) / n);
+  f->lanes = (periods * n + f->R - 1) / f->R;
+  f->over = f->lanes * f->R - periods * n;
+  f->waves = (f->lanes + cap - 1) / cap;
+}
+// The widths of a variant's kernels, ascending, each with its steps between
+// exchanges: those with the least cost per core node.  Cost of a wave's step:
+// the nodes' operations, the lane-edge moves (2 sum|e| per two steps, two
+// registers each in FP64), and 1/s of an exchange, which took about 5 R q
+// (FP64) or 2 R q (FP32) operations' time.
+int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
+  const bool f32 = prec != 0;
+  const int D = code & 0xff, K = (code >> 8) == 0 ? D + 1 : (D + 1) / 2 + 1;
+  const int conv = f32 ? (prec == 2 ? q + 2 : 2 * q) : 0;
+  const int cross = (q <= 5 ? 6 : 12) * (f32 ? 1 : 2);
+  int count = 0;
+  for (int k = 0; k < kRegWidths; ++k) {
+    const int R = reg_width(q, f32 ? 4 : 8, D, code >> 8, wide, k);
+    if (R == 0) break;
+    RegFit best;
+    double least = 0.0;
+    for (int s = 4; s <= 16; s += 2) {
+      const int hl = reg_halo(q, R, s), cap = 64 - 2 * hl;
+      if (cap < 4 * (hl + 1)) break;   // the strips of a wave's two ends stay apart
+      const double c = R * (q * (K + 1) + q - 1.0 + conv) + cross + ((f32 ? 2.0 : 5.0) * R * q + 40.0) / s;
+      if (least == 0.0 || c / cap < least) {
+        least = c / cap;
+        best.R = R;
+        best.s = s;
+        best.wide = wide;
+        best.cost = c;
+      }
+    }
+    if (best.R) out[count++] = best;
+  }
+  if (wide) {   // the largest grids of one LDS need the widest kernel at its least halo
+    out[count] = out[count - 1];
+    out[count].s = 4;
+    out[count].cost *= 1.1;
+    ++count;
+  }
+  return count;
+}
 // One pass: every instance advances by steps[i] <= kMaxStepsPerLaunch.
 lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const int count = (int)b->inst.size();
   // resident groups by (q, precision, variant); the rest streams through HBM
   // (q, prec, variant code, bounded)
   std::map<std::tuple<int, int, int, int>, std::vector<int>> res;
+  std::map<std::tuple<int, int, int>, std::vector<int>> reg;   // register-resident, by (q, prec, variant)
   std::vector<int> str;          // one launch per step (the plain path)
   std::vector<int> til[8][3];    // temporal blocking, by (q, prec)
   // slabs, by (q, prec, variant, workgroups per CU)
@@ -606,6 +681,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     if (steps[i] == 0) continue;
     const HostInst& h = b->inst[i];
     const bool fits = fits_resident(b, h);
+    const bool in_reg = reg_variant(h.D) && h.desc.bc == LBM_BC_PERIODIC;
     if (h.desc.bc != LBM_BC_PERIODIC) {
       // bounded instances advance only in a bounded call, on the resident path
       if (!b->bnd_active) return LBM_ERR_INVALID_ARG;
@@ -622,6 +698,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       slb[std::make_tuple(h.q, h.prec, h.D, slab_wgs)].push_back(i);
     else if (latency && h.n >= kSplitNodes)
       slb[std::make_tuple(h.q, h.prec, h.D, 8)].push_back(i);
+    else if (in_reg)
+      reg[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else
       res[std::make_tuple(h.q, h.prec, h.D, 0)].push_back(i);
   }
@@ -632,10 +710,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   LBM_HIP(hipEventSynchronize(b->items_done[k]));
   DevJobInst* hitems = b->items_host + (size_t)k * b->items_cap;
   DevJob* hjobs = b->jobs_host + (size_t)k * b->items_cap;
+  DevSeg* hsegs = b->segs_host + (size_t)k * b->items_cap;
   // est_max / est_sum: the longest job's and all jobs' duration estimates
-  struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; };
+  struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; bool reg, wide; int grid, part0, parts; int64_t partsteps; };
   std::vector<Launch> launches;
-  int used = 0, njobs = 0;
+  int used = 0, njobs = 0, nsegs = 0;
   constexpr int kMaxJobInstances = 16;   // instances per job (one wave each at least)
   for (const auto& group : res) {
     {
@@ -719,7 +798,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       const int slots = jobs_per_cu * b->lim.cus;
       if (!latency && (int)bins.size() < slots && (int)g.size() > (int)bins.size())
         pack(std::max(1, ((int)g.size() + slots - 1) / slots));
-      Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0};
+      Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, false, false, 0, 0, 0, 0};
       struct Planned { const Bin* bin; std::vector<int> waves; double est; };
       std::vector<Planned> plan;
       for (const Bin& bn : bins) {
@@ -790,9 +869,239 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         L.block = std::max(L.block, t0);
       }
       L.count = njobs - L.first;
-      if ((int)launches.size() >= kMaxLaunches) return LBM_ERR_UNSUPPORTED;
+      if ((int)launches.size() >= kMaxResident) return LBM_ERR_UNSUPPORTED;
       launches.push_back(L);
     }
+  }
+  // register-resident jobs: ring segments of one variant, step count and width,
+  // bin-packed by waves
+  double reg_work = 0.0;   // node updates x operations of all groups
+  std::vector<double> group_work;
+  for (const auto& group : reg) {
+    double w = 0.0;
+    for (int i : group.second) w += (double)steps[i] * b->inst[i].n;
+    const int D = std::get<2>(group.first) & 0xff;
+    group_work.push_back(w * (std::get<0>(group.first) * (D + 3)));
+    reg_work += group_work.back();
+  }
+  std::vector<double> reg_job_est;
+  double reg_est = 0.0;    // estimated CU time of all register launches
+  int64_t reg_jobs = 0;
+  size_t gi = 0;
+  for (const auto& group : reg) {
+    const int q = std::get<0>(group.first), pr = std::get<1>(group.first), code = std::get<2>(group.first);
+    const std::vector<int>& g = group.second;
+    const int es = pr != 0 ? 4 : 8;
+    // the CUs that are this group's by its share of the pass's work
+    const double cus = std::max(1.0, b->lim.cus * group_work[gi++] / std::max(1.0, reg_work));
+    // Nodes per lane: few spend more on halos and lane edges, many leave more of
+    // an instance's last lanes empty and give fewer waves to share the SIMDs.
+    // Each instance takes the width with the least wave time among one kernel's
+    // (narrow or wide: one launch per group, since a pass's launches run side by
+    // side only while there are hardware queues) up to a bound, and kernel and
+    // bound are those for which the group -- its waves over its CUs, or one job
+    // of the longest waves -- is estimated to end first.  One wave per
+    // SIMD takes about 1.25 times, two about 1.05 times the time per wave that
+    // three or four do.
+    std::vector<RegFit> fit(g.size()), trial(g.size());
+    double best = 0.0;
+    int job_waves = 4;
+    bool wide = false;
+    for (int cls = 0; cls < 2; ++cls) {
+      RegFit menu[kRegWidths + 1];
+      const int widths = reg_menu(q, pr, code, cls != 0, menu), full = reg_waves(cls != 0);
+      for (int most = widths - 1; most >= 0; --most) {
+        double sum = 0.0, longest = 0.0;
+        int64_t waves = 0;
+        int top = 1;
+        bool ok = true;
+        for (size_t u = 0; u < g.size() && ok; ++u) {
+          double least = 0.0;
+          for (int w = 0; w <= most; ++w) {
+            RegFit f = menu[w];
+            reg_place(q, b->inst[g[u]].n, &f);
+            if (f.waves > full) continue;
+            if (least == 0.0 || f.waves * f.cost < least) {
+              trial[u] = f;
+              least = f.waves * f.cost;
+            }
+          }
+          ok = least > 0.0;
+          if (!ok) break;
+          sum += least;
+          waves += trial[u].waves;
+          top = std::max(top, trial[u].waves);
+          longest = std::max(longest, trial[u].cost);
+        }
+        if (!ok) break;
+        // waves of a job: all a CU holds, or as many as the waves make for each CU
+        const int share = std::max(top, (int)std::min<double>(full, std::ceil(waves / cus)));
+        const int per_simd = (share + 3) / 4;
+        const double slow = per_simd == 1 ? 1.25 : per_simd == 2 ? 1.05 : 1.0;
+        const double est = slow * std::max(per_simd * longest, sum / (4.0 * cus));
+        if (best == 0.0 || est < best) {
+          best = est;
+          fit = trial;
+          job_waves = share;
+          wide = cls != 0;
+        }
+      }
+    }
+    if (best == 0.0) return LBM_ERR_UNSUPPORTED;
+    std::vector<int> order(g.size());
+    for (size_t u = 0; u < g.size(); ++u) order[u] = (int)u;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
+      if (steps[g[a]] != steps[g[c]]) return steps[g[a]] > steps[g[c]];
+      if (fit[a].R != fit[c].R) return fit[a].R > fit[c].R;
+      if (fit[a].s != fit[c].s) return fit[a].s > fit[c].s;
+      return fit[a].waves > fit[c].waves;
+    });
+    // first fit, decreasing; `open` holds the first bin of this width with room
+    // for a given number of waves
+    struct Bin { int waves; std::vector<int> members; };
+    std::vector<Bin> bins;
+    size_t open[17] = {};
+    for (size_t o = 0; o < order.size(); ++o) {
+      const int u = order[o], w = fit[u].waves;
+      if (o == 0 || steps[g[u]] != steps[g[order[o - 1]]] || fit[u].R != fit[order[o - 1]].R ||
+          fit[u].s != fit[order[o - 1]].s)
+        for (size_t& v : open) v = bins.size();
+      size_t& v = open[w];
+      while (v < bins.size() && bins[v].waves + w > job_waves) ++v;
+      if (v == bins.size()) bins.push_back(Bin{0, {}});
+      bins[v].waves += w;
+      bins[v].members.push_back(u);
+    }
+    auto job_est = [&](const Bin& bn) {
+      return (double)steps[g[bn.members[0]]] * ((bn.waves + 3) / 4) * fit[bn.members[0]].cost;
+    };
+    std::stable_sort(bins.begin(), bins.end(), [&](const Bin& a, const Bin& c) { return job_est(a) > job_est(c); });
+    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, wide, 0, 0, 0, 0};
+    for (const Bin& bn : bins) {
+      const RegFit& f0 = fit[bn.members[0]];
+      const int64_t st = steps[g[bn.members[0]]];
+      const double est = job_est(bn);
+      L.maxsteps = std::max<int64_t>(L.maxsteps, st);
+      L.est_max = std::max(L.est_max, est);
+      L.est_sum += est;
+      DevJob& jb = hjobs[njobs++];
+      jb = DevJob{};
+      jb.first = nsegs;
+      jb.count = (int)bn.members.size();
+      jb.steps = (int)st;
+      jb.degree = code;
+      jb.nodes = f0.R;
+      jb.s_per = f0.s;
+      int w0 = 0, off = 0;
+      for (int u : bn.members) {
+        const int i = g[u];
+        const HostInst& h = b->inst[i];
+        DevSeg& sg = hsegs[nsegs++];
+        sg = DevSeg{};
+        sg.in = sg.out = (uint64_t)(uintptr_t)state_cur(b, h);
+        sg.n = sg.len = h.n;
+        sg.stride = h.stride;
+        sg.inst = i;
+        sg.lanes = fit[u].lanes;
+        sg.over = fit[u].over;
+        sg.w0 = w0;
+        sg.waves = fit[u].waves;
+        sg.lds_off = off;
+        w0 += fit[u].waves;
+        off += fit[u].waves * reg_strip(q, f0.R, f0.s);
+      }
+      L.lds = std::max(L.lds, (size_t)off * es);
+      L.block = std::max(L.block, 64 * w0);
+    }
+    L.count = njobs - L.first;
+    reg_est += L.est_sum;
+    reg_jobs += L.count;
+    if ((int)launches.size() >= kMaxLaunches) return LBM_ERR_UNSUPPORTED;
+    launches.push_back(L);
+    for (const Bin& bn : bins) reg_job_est.push_back(job_est(bn));
+  }
+  // Queue items of the register launches.  Where the jobs of all launches
+  // outnumber the CUs, a launch takes the share of the workgroups that is its
+  // share of the work, and its jobs are laid end to end over them: each
+  // workgroup gets the same time, and the job that crosses from one to the next
+  // is split -- its first steps open the next workgroup's time, its last close
+  // the previous one's, so that the second part has the first one's result
+  // before it starts (preemptive scheduling on identical machines, McNaughton
+  // 1959; fixed step chunks, with a queue barely longer than the workgroups,
+  // spent a third of the time waiting for the chunk before).  Items are taken
+  // in the order of their planned start.
+  std::vector<DevItem> parts;
+  size_t job0 = 0;
+  for (Launch& L : launches) {
+    if (!L.reg) continue;
+    const double* est = &reg_job_est[job0];
+    job0 += L.count;
+    int per_cu = 0;
+    LBM_HIP(reg_occupancy(L.q, L.prec, L.code, L.wide, L.block, L.lds, &per_cu));
+    if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
+    L.grid = std::min<int>(L.count, per_cu * b->lim.cus);
+    if (reg_jobs > b->lim.cus)
+      L.grid = std::max(1, std::min(L.grid, (int)std::lround(per_cu * b->lim.cus * L.est_sum / reg_est)));
+    if (b->res_grid > 0) L.grid = std::min(L.grid, b->res_grid);
+    L.part0 = (int)parts.size();
+    const DevJob* jobs = hjobs + L.first;
+    if (b->res_chunks > 0) {   // chunks as asked, chunk by chunk
+      for (int c = 0; c < b->res_chunks; ++c)
+        for (int k = 0; k < L.count; ++k) {
+          const int base = jobs[k].steps / b->res_chunks, rem = jobs[k].steps % b->res_chunks;
+          const int st = base + (c < rem ? 1 : 0);
+          if (st == 0 && c > 0) continue;
+          const int next = base + (c + 1 < rem ? 1 : 0);
+          parts.push_back(DevItem{k, c, st, c + 1 < b->res_chunks && next > 0 ? 1 : 0});
+        }
+    } else if (L.grid >= L.count) {
+      for (int k = 0; k < L.count; ++k) parts.push_back(DevItem{k, 0, jobs[k].steps, 0});
+    } else {
+      const double span = std::max(L.est_sum / L.grid, L.est_max);
+      struct Planned { double start; DevItem item; };
+      std::vector<Planned> plan;
+      double t = 0.0;   // end of the current workgroup's last item
+      int used_wgs = 1;
+      for (int k = 0; k < L.count; ++k) {
+        const int st = jobs[k].steps;
+        int second = 0;   // steps that stay with this workgroup, at its end
+        if (t + est[k] > span * (1.0 + 1e-9) && used_wgs < L.grid) {
+          second = (int)(st * ((span - t) / est[k]));
+          if (second < st / 32 || second < 8) second = 0;
+          if (st - second < st / 32 || st - second < 8) second = st;
+        } else {
+          second = st;
+        }
+        const int first = st - second;
+        if (second > 0) plan.push_back({t, DevItem{k, first > 0 ? 1 : 0, second, 0}});
+        if (first > 0) {
+          plan.push_back({0.0, DevItem{k, 0, first, second > 0 ? 1 : 0}});
+          t = est[k] * first / st;
+          ++used_wgs;
+        } else {
+          t += est[k];
+        }
+      }
+      std::stable_sort(plan.begin(), plan.end(), [](const Planned& x, const Planned& y) {
+        return x.start != y.start ? x.start < y.start : x.item.part < y.item.part;
+      });
+      for (const Planned& pl : plan) parts.push_back(pl.item);
+    }
+    L.parts = (int)parts.size() - L.part0;
+    for (int k = L.part0; k < (int)parts.size(); ++k) L.partsteps = std::max<int64_t>(L.partsteps, parts[k].steps);
+  }
+  if ((int)parts.size() > b->parts_cap) {
+    LBM_HIP(hipStreamSynchronize(b->stream));   // earlier passes must be done with them
+    hipFree(b->parts);
+    if (b->parts_host) hipHostFree(b->parts_host);
+    b->parts = nullptr;
+    b->parts_host = nullptr;
+    b->parts_cap = 0;
+    const int cap = (int)parts.size() * 2;
+    if (hipMalloc(&b->parts, sizeof(DevItem) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+    if (hipHostMalloc((void**)&b->parts_host, sizeof(DevItem) * 2 * cap, hipHostMallocDefault) != hipSuccess)
+      return LBM_ERR_OUT_OF_MEMORY;
+    b->parts_cap = cap;
   }
   // temporal blocking plan per (q, prec) group
   struct TileGroup { int q; int prec; int first, ntiles, tfirst, tcount, s, halo, launches, block; size_t lds; double est; };
@@ -1125,8 +1434,16 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   DevJobInst* ditems = b->items + (size_t)k * b->items_cap;
   DevJob* djobs = b->jobs + (size_t)k * b->items_cap;
   int* counters = b->counter + k * kMaxLaunches;
-  if (used) {
-    LBM_HIP(hipMemcpyAsync(ditems, hitems, sizeof(DevJobInst) * used, hipMemcpyHostToDevice, b->stream));
+  if (used) LBM_HIP(hipMemcpyAsync(ditems, hitems, sizeof(DevJobInst) * used, hipMemcpyHostToDevice, b->stream));
+  DevSeg* dsegs = b->segs + (size_t)k * b->items_cap;
+  DevItem* dparts = b->parts + (size_t)k * b->parts_cap;
+  if (nsegs) {
+    DevItem* hparts = b->parts_host + (size_t)k * b->parts_cap;
+    std::memcpy(hparts, parts.data(), sizeof(DevItem) * parts.size());
+    LBM_HIP(hipMemcpyAsync(dparts, hparts, sizeof(DevItem) * parts.size(), hipMemcpyHostToDevice, b->stream));
+    LBM_HIP(hipMemcpyAsync(dsegs, hsegs, sizeof(DevSeg) * nsegs, hipMemcpyHostToDevice, b->stream));
+  }
+  if (njobs) {
     LBM_HIP(hipMemcpyAsync(djobs, hjobs, sizeof(DevJob) * njobs, hipMemcpyHostToDevice, b->stream));
     LBM_HIP(hipMemsetAsync(counters, 0, sizeof(int) * kMaxLaunches, b->stream));
     LBM_HIP(hipMemsetAsync(b->done + (size_t)k * b->items_cap, 0, sizeof(int) * njobs, b->stream));
@@ -1197,6 +1514,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     if (it.kind == 0) {
       const int l = it.idx;
       const Launch& L = launches[l];
+      int* done = b->done + (size_t)k * b->items_cap + L.first;
+      if (L.reg) {
+        const int stall = (b->test_stall == 1 && l == 0 && L.parts > L.count) ? 0 : -1;
+        LBM_HIP(launch_reg(L.q, L.prec, L.code, L.wide, dparts + L.part0, L.parts, djobs + L.first, dsegs, counters + l,
+                           done, b->coefs, b->status, wait_ticks(b, L.partsteps), stall, L.grid, L.block, L.lds, st));
+        continue;
+      }
       int per_cu = 0;
       LBM_HIP(resident_occupancy(L.q, L.prec, L.code, L.block, L.lds, &per_cu));
       if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
@@ -1212,12 +1536,12 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         nchunks = std::max(1, std::min(nchunks, kMaxChunks));
       }
       if (b->res_chunks > 0) nchunks = b->res_chunks;
-      int* slots = b->slots + (size_t)(k * kMaxLaunches + l) * kMaxResidentGrid;
-      int* done = b->done + (size_t)k * b->items_cap + L.first;
+      // (the LDS-resident launches come first in the list)
+      int* slots = b->slots + (size_t)(k * kMaxResident + l) * kMaxResidentGrid;
       const long long ticks = wait_ticks(b, L.maxsteps / nchunks + 1);
       const int stall = (b->test_stall == 1 && l == 0 && nchunks > 1) ? 0 : -1;
-      LBM_HIP(launch_resident(L.q, L.prec, L.code, djobs + L.first, ditems, L.count, nchunks, counters + l, slots,
-                              done, b->coefs, b->status, ticks, stall, grid, L.block, L.lds, st));
+      LBM_HIP(launch_resident(L.q, L.prec, L.code, djobs + L.first, ditems, L.count, nchunks, counters + l, slots, done,
+                              b->coefs, b->status, ticks, stall, grid, L.block, L.lds, st));
     } else if (it.kind == 1) {
       const TileGroup& G = tgroups[it.idx];
       DevTile* dt = b->tiles + (size_t)k * b->tiles_cap + G.first;
@@ -1602,7 +1926,9 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
   unsigned char* bytes = (unsigned char*)base;
   DevCoef* dcoef = (DevCoef*)bytes;
   DevJob* djob = (DevJob*)(bytes + 12288);
-  DevJobInst* dji = (DevJobInst*)(bytes + 12288 + 256);
+  DevJobInst* dji = (DevJobInst*)(bytes + 12288 + 256);   // or the register path's segment
+  DevItem* ditem = (DevItem*)(bytes + 12288 + 128);
+  static_assert(sizeof(DevJob) <= 128 && sizeof(DevItem) <= 128 && sizeof(DevSeg) <= 256 && sizeof(DevJobInst) <= 256, "job record outgrew its scratch region");
   int* ints = (int*)(bytes + 12288 + 512);   // queue counter, slot, done, status, non-finite flag
   void* f = bytes + kNoAllocTableBytes;
   // phi0 on the host: the checks of lbm_load_phi and the rest state (mean of phi0)
@@ -1617,9 +1943,36 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
   if (h.f32) set_rest_state(&h.mdl, (double)(sum / h.n));
   DevCoef cf;
   fill_devcoef(h, &cf);
-  // one job of one instance: a wave per 64 nodes, at most 16
+  // one job of one instance.  Register-resident (polynomial equilibria): the
+  // fewest nodes per lane whose waves fit one workgroup; else a wave per 64
+  // nodes, at most 16
+  const bool in_reg = reg_variant(h.D);
+  RegFit fit;
+  if (in_reg) {
+    fit.waves = 1 << 30;
+    for (int cls = 0; cls < 2 && fit.waves > reg_waves(fit.wide); ++cls) {
+      RegFit menu[kRegWidths + 1];
+      const int widths = reg_menu(h.q, h.prec, h.D, cls != 0, menu);
+      for (int k = 0; k < widths && fit.waves > reg_waves(fit.wide); ++k) {
+        fit = menu[k];
+        reg_place(h.q, h.n, &fit);
+      }
+    }
+    if (fit.waves > reg_waves(fit.wide)) return LBM_ERR_INVALID_ARG;
+  }
+  DevSeg sg{};
+  sg.in = sg.out = (uint64_t)(uintptr_t)f;
+  sg.n = sg.len = h.n;
+  sg.stride = h.stride;
+  sg.lanes = fit.lanes;
+  sg.over = fit.over;
+  sg.waves = fit.waves;
   const int waves = std::max(1, std::min(16, (h.n + 63) / 64));
-  DevJob jb{0, 1, 0, h.D, 0, 0};
+  DevJob jb{};
+  jb.count = 1;
+  jb.degree = h.D;
+  jb.nodes = fit.R;
+  jb.s_per = fit.s;
   DevJobInst ji{};
   ji.addr = (uint64_t)(uintptr_t)f;
   ji.n = h.n;
@@ -1627,18 +1980,27 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
   ji.degree = h.D;
   ji.nt = 64 * waves;
   LBM_HIP(hipMemcpyAsync(dcoef, &cf, sizeof(cf), hipMemcpyHostToDevice, st));
-  LBM_HIP(hipMemcpyAsync(dji, &ji, sizeof(ji), hipMemcpyHostToDevice, st));
+  if (in_reg)
+    LBM_HIP(hipMemcpyAsync(dji, &sg, sizeof(sg), hipMemcpyHostToDevice, st));
+  else
+    LBM_HIP(hipMemcpyAsync(dji, &ji, sizeof(ji), hipMemcpyHostToDevice, st));
   LBM_HIP(launch_zero_ints(ints, 5, st));
   LBM_HIP(launch_init(h.q, h.Dinit, h.prec, phi0, f, h.n, h.stride, dcoef, st));
   for (int64_t left = steps; left > 0;) {
     const int64_t now = std::min(left, kMaxStepsPerLaunch);
     left -= now;
     jb.steps = (int)now;
+    const DevItem item{0, 0, (int)now, 0};
     LBM_HIP(hipMemcpyAsync(djob, &jb, sizeof(jb), hipMemcpyHostToDevice, st));
-    LBM_HIP(hipStreamSynchronize(st));   // jb is reused by the next launch
+    LBM_HIP(hipMemcpyAsync(ditem, &item, sizeof(item), hipMemcpyHostToDevice, st));
+    LBM_HIP(hipStreamSynchronize(st));   // jb and item are reused by the next launch
     LBM_HIP(launch_zero_ints(ints, 3, st));
-    LBM_HIP(launch_resident(h.q, h.prec, h.D, djob, dji, 1, 1, ints, ints + 1, ints + 2, dcoef, ints + 3, 0, -1, 1,
-                            ji.nt, lds, st));
+    if (in_reg)
+      LBM_HIP(launch_reg(h.q, h.prec, h.D, fit.wide, ditem, 1, djob, (const DevSeg*)dji, ints, ints + 2, dcoef, ints + 3,
+                         0, -1, 1, 64 * fit.waves, (size_t)fit.waves * reg_strip(h.q, fit.R, fit.s) * es, st));
+    else
+      LBM_HIP(launch_resident(h.q, h.prec, h.D, djob, dji, 1, 1, ints, ints + 1, ints + 2, dcoef, ints + 3, 0, -1, 1,
+                              ji.nt, lds, st));
   }
   LBM_HIP(launch_phi(h.prec, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 4, st));
   int flags[2] = {0, 0};
