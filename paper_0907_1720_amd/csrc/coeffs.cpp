@@ -192,6 +192,16 @@ long long binom(int n, int k) {
   return r;
 }
 
+// C(k, p) up to the largest degree (a rest state needs every one of them for
+// every population, on every load of FP32 storage)
+struct BinomTable {
+  qf v[kMaxDeg + 1][kMaxDeg + 1];
+  BinomTable() {
+    for (int k = 0; k <= kMaxDeg; ++k)
+      for (int p = 0; p <= kMaxDeg; ++p) v[k][p] = p <= k ? (qf)binom(k, p) : 0;
+  }
+};
+
 // M[k][j] = e_j^k, inverted by Gauss-Jordan with partial pivoting
 bool invert_moment_matrix(int q, qf inv[kMaxQ][kMaxQ]) {
   qf a[kMaxQ][2 * kMaxQ];
@@ -536,6 +546,7 @@ lbm_status build_model(const lbm_desc& d, Model* out) {
 void set_rest_state(Model* mdl, double phi_rest) {
   const qf r = phi_rest;
   const qf omega = 1 / (qf)mdl->tau;
+  static const BinomTable C;
   mdl->phi_rest = phi_rest;
   if (mdl->gF > 0) {   // power sums: f_rest only (the relaxation stays in phi)
     for (int j = 0; j < mdl->q; ++j) {
@@ -545,15 +556,15 @@ void set_rest_state(Model* mdl, double phi_rest) {
     }
     return;
   }
+  qf rp[kMaxDeg + 1];   // r^k
+  rp[0] = 1;
+  for (int k = 1; k <= mdl->D; ++k) rp[k] = rp[k - 1] * r;
   for (int j = 0; j < mdl->q; ++j) {
     // Taylor shift: f_eq_j(r + delta) = sum_p H[j][p] delta^p, H[j][p] = sum_k C(k,p) G[j][k] r^{k-p}
     for (int p = 0; p <= mdl->D; ++p) {
       qf h = 0;
-      qf rp = 1;
-      for (int k = p; k <= mdl->D; ++k) {
-        h += (qf)binom(k, p) * mdl->Gq[j][k] * rp;
-        rp *= r;
-      }
+      for (int k = p; k <= mdl->D; ++k)
+        if (mdl->Gq[j][k] != 0) h += C.v[k][p] * mdl->Gq[j][k] * rp[k - p];
       if (p == 0) {
         mdl->f_rest[j] = (double)h;
         mdl->wfrest[j] = (double)(omega * h);

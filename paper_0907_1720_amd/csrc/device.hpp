@@ -70,6 +70,18 @@ struct DevJobInst {
   int32_t pad_;
 };
 
+// Initialisation: a run of nodes of one instance, f := f_eq(phi).
+struct DevInit {
+  uint64_t src;              // device address of phi (doubles; device or pinned host memory)
+  uint64_t dst;              // device address of population 0 of the run's first node
+  int32_t len;               // nodes
+  int32_t stride;            // row stride in elements
+  int32_t inst;              // index into coefficients / status
+  int32_t q;
+  int32_t degree;            // of the initialisation polynomials
+  int32_t first;             // 1: the run starts the instance (clears its status)
+};
+
 // Register-resident path: queue items.  A job's steps are split into parts (one
 // for most jobs), taken in the order of the list; part p waits for part p - 1.
 struct DevItem {
@@ -206,6 +218,20 @@ __device__ __forceinline__ double frac_pow(double nu, double phi, double lg, boo
     return nu == 0.25 ? r4 : r * r4;
   }
   return exp2(nu * lg);
+}
+
+// stored equilibrium of a power-sum model: f_eq_j(phi) - f_rest_j (f_rest = 0
+// for FP64 storage); phi >= 0
+__device__ __forceinline__ double general_stored_eq(const DevCoef* __restrict__ cf, int j, double phi) {
+  const bool roots = cf->groots != 0;
+  const double lg = roots ? 0.0 : log2(phi);
+  double acc = 0.0;
+  for (int c = 0; c < cf->gF; ++c) {
+    double a = cf->ginit[c][j][kGRow - 1];
+    for (int d = kGRow - 2; d >= 0; --d) a = __builtin_fma(a, phi, cf->ginit[c][j][d]);
+    acc = __builtin_fma(c == 0 ? 1.0 : frac_pow(cf->gnu[c], phi, lg, roots), a, acc);
+  }
+  return acc - cf->grest[j];
 }
 
 // x^k for a small wave-uniform k >= 0 (k - 1 products; x^0 = 1)

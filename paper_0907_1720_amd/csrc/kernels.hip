@@ -2,7 +2,8 @@
 // itself is in kernels_body.hpp, instantiated per lattice size by
 // kernels_q.hip (tables q_kernels_4 .. q_kernels_7).
 //
-//  k_phi       phi = sum_j f_j  (FP64)
+//  k_read      phi = sum_j f_j  (FP64)
+//  k_init_*    f := f_eq(phi)   (initial distribution)
 //  k_sum       FP64 sum of phi over a grid, deterministic two-pass
 #include <mutex>
 #include <unordered_map>
@@ -15,17 +16,73 @@ namespace lbm {
 // ---------------------------------------------------------------------------
 // read-outs
 // ---------------------------------------------------------------------------
+// phi may lie in pinned host memory: the values cross to the host as they are
+// summed, instead of a read-out buffer and three copies (55 -> 14 us per call
+// of 1400 nodes)
 template <typename T>
-__global__ __launch_bounds__(256) void k_phi(const T* __restrict__ f, double* __restrict__ phi, int n,
-                                             int stride, int q, double phi_rest,
-                                             int* __restrict__ nonfinite) {
+__global__ __launch_bounds__(256) void k_read(const T* __restrict__ f, double* __restrict__ phi, int n, int stride,
+                                              int q, double phi_rest, const int* __restrict__ status,
+                                              int* __restrict__ words) {
   const int x = blockIdx.x * 256 + threadIdx.x;
+  if (x == 0) words[0] = *status;
   if (x >= n) return;
   double s = (double)f[x];
   for (int j = 1; j < q; ++j) s += (double)f[(int64_t)j * stride + x];
   s += phi_rest;
   phi[x] = s;
-  if (!__builtin_isfinite(s)) atomicOr(nonfinite, 1);
+  if (!__builtin_isfinite(s)) words[1] = 1;   // (every writer stores the same word)
+}
+
+// ---------------------------------------------------------------------------
+// f := f_eq(phi) and the check of a phi that is already on the device
+// ---------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ void init_run(const DevInit& r, int x, const DevCoef* __restrict__ coefs,
+                                         int* __restrict__ status) {
+  if (x == 0 && r.first) status[r.inst] = 0;
+  if (x >= r.len) return;
+  const DevCoef* __restrict__ cf = coefs + r.inst;
+  T* f = reinterpret_cast<T*>(r.dst);
+  const double phi = reinterpret_cast<const double*>(r.src)[x];
+  if (cf->gF > 0) {
+    for (int j = 0; j < r.q; ++j) f[(int64_t)j * r.stride + x] = (T)general_stored_eq(cf, j, phi);
+    return;
+  }
+  const double p = phi - cf->phi_rest;   // phi_rest = 0 for FP64 storage
+  for (int j = 0; j < r.q; ++j) {
+    const double* __restrict__ c = cf->init[j];
+    double acc = c[r.degree];
+    for (int d = r.degree - 1; d >= 0; --d) acc = __builtin_fma(acc, p, c[d]);
+    f[(int64_t)j * r.stride + x] = (T)acc;
+  }
+}
+
+// one launch for all instances of a batch, phi read from pinned host memory
+// (one copy, one clear and one launch per instance before: 27 -> 3 us each)
+template <typename T>
+__global__ __launch_bounds__(256) void k_init_many(const DevInit* __restrict__ recs, const DevCoef* __restrict__ coefs,
+                                                   int* __restrict__ status) {
+  const DevInit r = recs[blockIdx.y];
+  const int x0 = blockIdx.x * 256;
+  if (x0 >= r.len) return;
+  init_run<T>(r, x0 + threadIdx.x, coefs, status);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_init_one(DevInit r, const DevCoef* __restrict__ coefs,
+                                                  int* __restrict__ status) {
+  init_run<T>(r, blockIdx.x * 256 + threadIdx.x, coefs, status);
+}
+
+__global__ __launch_bounds__(256) void k_check_phi(const double* __restrict__ phi, int n, int* __restrict__ words) {
+  bool bad = false, neg = false;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const double v = phi[i];
+    bad |= !__builtin_isfinite(v);
+    neg |= v < 0;
+  }
+  // (plain stores: every writer of a word stores the same value)
+  if (bad) words[0] = 1;
+  if (neg) words[1] = 1;
 }
 
 __global__ __launch_bounds__(256) void k_sum_partial(const double* __restrict__ v, int n,
@@ -77,10 +134,31 @@ const void* slab_kernel(int q, int prec, int code) {
 }
 }  // namespace
 
-hipError_t launch_init(int q, int D, int prec, const double* phi, void* f, int n, int stride,
-                       const DevCoef* cf, hipStream_t s) {
-  const QKernels* t = table(q);
-  return t ? t->init(D, prec, phi, f, n, stride, cf, s) : hipErrorInvalidValue;
+hipError_t launch_init_many(bool f32, const DevInit* recs, int count, int longest, const DevCoef* coefs, int* status,
+                            hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  if (count > 65535) return hipErrorInvalidValue;
+  const dim3 grid((longest + 255) / 256, count);
+  if (f32)
+    k_init_many<float><<<grid, 256, 0, s>>>(recs, coefs, status);
+  else
+    k_init_many<double><<<grid, 256, 0, s>>>(recs, coefs, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, hipStream_t s) {
+  const dim3 grid((rec.len + 255) / 256);
+  if (f32)
+    k_init_one<float><<<grid, 256, 0, s>>>(rec, coefs, status);
+  else
+    k_init_one<double><<<grid, 256, 0, s>>>(rec, coefs, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_check_phi(const double* phi, int n, int* words, hipStream_t s) {
+  const int blocks = (n + 255) / 256;
+  k_check_phi<<<blocks < 1024 ? blocks : 1024, 256, 0, s>>>(phi, n, words);
+  return hipGetLastError();
 }
 
 hipError_t launch_bound(int q, int D, int prec, void* f, int n, int stride, int layers, int kind,
@@ -207,12 +285,12 @@ hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, 
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, block, lds);
 }
 
-hipError_t launch_phi(int prec, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                      int* nonfinite, hipStream_t s) {
-  if (prec == 0)
-    k_phi<double><<<(n + 255) / 256, 256, 0, s>>>((const double*)f, phi, n, stride, q, phi_rest, nonfinite);
+hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
+                       const int* status, int* words, hipStream_t s) {
+  if (f32)
+    k_read<float><<<(n + 255) / 256, 256, 0, s>>>((const float*)f, phi, n, stride, q, phi_rest, status, words);
   else
-    k_phi<float><<<(n + 255) / 256, 256, 0, s>>>((const float*)f, phi, n, stride, q, phi_rest, nonfinite);
+    k_read<double><<<(n + 255) / 256, 256, 0, s>>>((const double*)f, phi, n, stride, q, phi_rest, status, words);
   return hipGetLastError();
 }
 

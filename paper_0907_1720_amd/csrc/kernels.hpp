@@ -30,7 +30,7 @@
   LBM_CASE(5, 3)
 #define LBM_VARIANT_CASES LBM_POLY_CASES LBM_POWER_CASES
 
-// dense degrees available to the initialisation kernel
+// dense degrees available to the boundary kernel
 #define LBM_INIT_CASES \
   LBM_CASE(5)          \
   LBM_CASE(7)          \
@@ -66,8 +66,15 @@ inline int variant_code(int D, int parity) { return D | (parity << 8); }
 
 // prec: 0 = FP64 storage and arithmetic; 1 = FP32 deviation storage, FP64
 // relaxation; 2 = FP32 deviation storage, FP32 relaxation.
-hipError_t launch_init(int q, int D, int prec, const double* phi, void* f, int n, int stride,
-                       const DevCoef* cf, hipStream_t s);
+// f := f_eq(phi) for `count` runs of nodes (records in device or pinned host
+// memory, all of one storage), the longest of `longest` nodes; or for one run,
+// by value
+hipError_t launch_init_many(bool f32, const DevInit* recs, int count, int longest, const DevCoef* coefs, int* status,
+                            hipStream_t s);
+hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, hipStream_t s);
+// words[0] |= 1 if any phi is not finite, |= 2 if any is negative (device or
+// pinned host memory)
+hipError_t launch_check_phi(const double* phi, int n, int* words, hipStream_t s);
 // slabs: one launch no larger than the GPU holds at once, one workgroup per
 // slab; flags[0 .. nslabs) start at 0; xbuf holds 4 Q halo values per slab;
 // a halo wait gives up after wait_ticks ticks of the wall clock (status bit
@@ -126,8 +133,10 @@ hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t
 int resident_vgprs(int q, int prec, int code);
 // static LDS bytes of the resident kernel (0 by construction)
 size_t resident_static_lds(int q, int prec, int code);
-hipError_t launch_phi(int prec, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                      int* nonfinite, hipStream_t s);
+// phi = sum_j f_j into device or pinned host memory; words[0] := *status,
+// words[1] := 1 if any value is not finite (left alone otherwise)
+hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
+                       const int* status, int* words, hipStream_t s);
 hipError_t launch_sum(const double* v, int n, double* part, int nparts, hipStream_t s);
 hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, int* blocks_per_cu);
 // lbm_advance_noalloc: the fixed per-device scratch (tables at offset 0, the

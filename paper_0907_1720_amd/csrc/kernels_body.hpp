@@ -4,7 +4,6 @@
 // them once per lattice (one translation unit each, compiled in parallel);
 // kernels.hip holds the read-outs and the host launchers.
 //
-//  k_init      f := f_eq(phi)                        (initial distribution)
 //  k_bound     exact-solution boundary layers of a bounded domain
 //  k_stream    one fused collide+stream step, state in HBM, SoA rows,
 //              coalesced loads, shifted stores with periodic wrap
@@ -23,44 +22,12 @@
 namespace lbm {
 
 // ---------------------------------------------------------------------------
-// f := f_eq(phi)
-// ---------------------------------------------------------------------------
-// stored equilibrium of a power-sum model: f_eq_j(phi) - f_rest_j (f_rest = 0
-// for FP64 storage); phi >= 0
-__device__ __forceinline__ double general_stored_eq(const DevCoef* __restrict__ cf, int j, double phi) {
-  const bool roots = cf->groots != 0;
-  const double lg = roots ? 0.0 : log2(phi);
-  double acc = 0.0;
-  for (int c = 0; c < cf->gF; ++c) {
-    double a = cf->ginit[c][j][kGRow - 1];
-    for (int d = kGRow - 2; d >= 0; --d) a = __builtin_fma(a, phi, cf->ginit[c][j][d]);
-    acc = __builtin_fma(c == 0 ? 1.0 : frac_pow(cf->gnu[c], phi, lg, roots), a, acc);
-  }
-  return acc - cf->grest[j];
-}
-
-template <int Q, int D, typename T>
-__global__ __launch_bounds__(256) void k_init(const double* __restrict__ phi, T* __restrict__ f,
-                                              int n, int stride, const DevCoef* __restrict__ cf) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= n) return;
-  if (cf->gF > 0) {
-#pragma unroll
-    for (int j = 0; j < Q; ++j) f[(int64_t)j * stride + x] = (T)general_stored_eq(cf, j, phi[x]);
-    return;
-  }
-  const double p = phi[x] - cf->phi_rest;   // phi_rest = 0 for FP64 storage
-#pragma unroll
-  for (int j = 0; j < Q; ++j) f[(int64_t)j * stride + x] = (T)poly_eval<D, 0, double>(cf->init[j], p);
-}
-
-// ---------------------------------------------------------------------------
 // Bounded domains (exact-solution boundaries of Sec. IV): after a step the
 // `layers` outer nodes at each end are reset from the exact solution phi* at
 // the new time -- kind 1: f = f_eq(phi*); kind 2 (non-equilibrium
 // extrapolation): f = f_eq(phi*) + (f - f_eq(phi)) taken at the first interior
 // node.  One thread per boundary node; phib = {left layers, right layers}.
-// The stored value is the one k_init stores: f (FP64) or f - f_rest (FP32).
+// The stored value is the one the initialisation stores: f (FP64) or f - f_rest (FP32).
 // ---------------------------------------------------------------------------
 template <int Q, int D, typename T>
 __global__ __launch_bounds__(64) void k_bound(T* __restrict__ f, int n, int stride, int layers, int kind,

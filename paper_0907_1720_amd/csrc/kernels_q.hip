@@ -14,21 +14,6 @@
 
 namespace lbm {
 namespace {
-template <int Q, typename T>
-hipError_t launch_init_q(int D, const double* phi, T* f, int n, int stride, const DevCoef* cf,
-                         hipStream_t s) {
-  dim3 grid((n + 255) / 256);
-  switch (D) {
-#define LBM_CASE(DD) \
-  case DD:           \
-    k_init<Q, DD, T><<<grid, 256, 0, s>>>(phi, f, n, stride, cf); \
-    return hipGetLastError();
-    LBM_INIT_CASES
-#undef LBM_CASE
-  }
-  return hipErrorInvalidValue;
-}
-
 template <int Q, typename T, typename A>
 hipError_t launch_stream_q(int code, const T* fin, T* fout, int n, int stride, const DevCoef* cf,
                            hipStream_t s) {
@@ -98,13 +83,6 @@ const void* reg_prec(int prec, int code, bool wide) {
   return reg_fn<Q, float, float>(code, wide);
 }
 
-template <int Q>
-hipError_t launch_init_p(int D, int prec, const double* phi, void* f, int n, int stride, const DevCoef* cf,
-                         hipStream_t s) {
-  if (prec == 0) return launch_init_q<Q, double>(D, phi, (double*)f, n, stride, cf, s);
-  return launch_init_q<Q, float>(D, phi, (float*)f, n, stride, cf, s);
-}
-
 template <int Q, typename T>
 hipError_t launch_bound_q(int D, T* f, int n, int stride, int layers, int kind, const double* phib,
                           const DevCoef* cf, hipStream_t s) {
@@ -170,8 +148,8 @@ const void* slab_prec(int prec, int code) {
 }  // namespace
 
 QKernels LBM_CAT(q_kernels_, LBM_Q) = {
-    &launch_init_p<LBM_Q>, &launch_bound_p<LBM_Q>, &launch_stream_p<LBM_Q>, &stream_prec<LBM_Q>,
-    &resident_prec<LBM_Q>, &reg_prec<LBM_Q>, &tile_prec<LBM_Q>, &slab_prec<LBM_Q>,
+    &launch_bound_p<LBM_Q>, &launch_stream_p<LBM_Q>, &stream_prec<LBM_Q>, &resident_prec<LBM_Q>,
+    &reg_prec<LBM_Q>,       &tile_prec<LBM_Q>,       &slab_prec<LBM_Q>,
 };
 
 }  // namespace lbm

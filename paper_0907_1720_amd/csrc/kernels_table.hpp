@@ -7,8 +7,6 @@
 namespace lbm {
 
 struct QKernels {
-  hipError_t (*init)(int D, int prec, const double* phi, void* f, int n, int stride, const DevCoef* cf,
-                     hipStream_t s);
   hipError_t (*bound)(int D, int prec, void* f, int n, int stride, int layers, int kind, const double* phib,
                       const DevCoef* cf, hipStream_t s);
   hipError_t (*stream)(int code, int prec, const void* fin, void* fout, int n, int stride, const DevCoef* cf,

@@ -128,9 +128,13 @@ struct lbm_batch_s {
   hipEvent_t items_done[2] = {nullptr, nullptr};
   int items_cap = 0;
   int slot = 0;
-  double* scratch = nullptr;          // phi read-out (max n) + partial sums
+  double* scratch = nullptr;          // phi read-out of grids beyond the stage; partial sums
   size_t scratch_elems = 0;
-  int* flag = nullptr;                // non-finite flag for read-outs
+  // Pinned host memory that kernels read phi0 from and write phi to: kStageHead
+  // bytes of status words, then data.  Every call that uses it synchronises the
+  // stream before it returns.
+  unsigned char* stage = nullptr;
+  size_t stage_bytes = 0;             // data bytes
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // temporal blocking tables (two slots like the items)
   DevTile* tiles = nullptr;
@@ -155,7 +159,6 @@ struct lbm_batch_s {
   hipEvent_t fork = nullptr;
   hipEvent_t join[kAuxStreams] = {};
   float last_ms = 0.0f;
-  std::vector<DevCoef> hcoef;
   std::vector<StepGraph> step_graphs;   // per instance and current-buffer parity
   double* bound = nullptr;              // boundary values of bounded problems (device)
   size_t bound_cap = 0;                 // doubles
@@ -241,12 +244,6 @@ void fill_devcoef(const HostInst& h, DevCoef* c) {
   }
 }
 
-lbm_status upload_coef(lbm_batch_s* b, int i) {
-  fill_devcoef(b->inst[i], &b->hcoef[i]);
-  LBM_HIP(hipMemcpyAsync(b->coefs + i, &b->hcoef[i], sizeof(DevCoef), hipMemcpyHostToDevice, b->stream));
-  return LBM_OK;
-}
-
 size_t elem_size(const HostInst& h) { return h.f32 ? sizeof(float) : sizeof(double); }
 
 void destroy_batch(lbm_batch_s* b) {
@@ -281,7 +278,7 @@ void destroy_batch(lbm_batch_s* b) {
   for (int k = 0; k < 2; ++k)
     if (b->items_done[k]) hipEventDestroy(b->items_done[k]);
   hipFree(b->scratch);
-  hipFree(b->flag);
+  if (b->stage) hipHostFree(b->stage);
   hipFree(b->tiles);
   hipFree(b->tinsts);
   if (b->tiles_host) hipHostFree(b->tiles_host);
@@ -342,11 +339,18 @@ lbm_status prepare_instances(const lbm_desc* descs, int count, std::vector<HostI
   return LBM_OK;
 }
 
-lbm_status alloc_tables(lbm_batch_s* b, size_t maxn);
+constexpr size_t kStageHead = 256, kStageLeast = size_t(16) << 10, kStageMost = size_t(8) << 20;
+// stage bytes of `len` nodes of an instance (phi, its record, its coefficients)
+size_t stage_need(int64_t len, bool coefs) {
+  return (size_t)len * sizeof(double) + sizeof(DevInit) + (coefs ? sizeof(DevCoef) : 0) + 64;
+}
+
+lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want);
 
 lbm_status alloc_batch(lbm_batch_s* b, void* dev_buf, size_t buf_bytes) {
-  size_t n64 = 0, n32 = 0, maxn = 0;
+  size_t n64 = 0, n32 = 0, maxn = 0, stage = 0;
   for (HostInst& h : b->inst) {
+    stage += stage_need(h.n, h.f32);
     size_t e = (size_t)h.q * h.stride;
     if (h.f32) {
       h.off = (int64_t)n32;
@@ -370,12 +374,12 @@ lbm_status alloc_batch(lbm_batch_s* b, void* dev_buf, size_t buf_bytes) {
     if (n64 && hipMalloc(&b->f64[0], n64 * sizeof(double)) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
     if (n32 && hipMalloc(&b->f32[0], n32 * sizeof(float)) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   }
-  return alloc_tables(b, maxn);
+  return alloc_tables(b, maxn, stage);
 }
 
 // Per-instance tables, queues, streams and events for `b->inst.size()` slots;
-// read-out scratch for grids of up to maxn nodes.
-lbm_status alloc_tables(lbm_batch_s* b, size_t maxn) {
+// read-out scratch for grids of up to maxn nodes, a stage of up to stage_want bytes.
+lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want) {
   const int count = (int)b->inst.size();
   if (hipMalloc(&b->coefs, sizeof(DevCoef) * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&b->status, sizeof(int) * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
@@ -407,11 +411,25 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn) {
   for (int k = 0; k < 2; ++k) LBM_HIP(hipEventCreateWithFlags(&b->items_done[k], hipEventDisableTiming));
   b->scratch_elems = maxn + 64;
   if (hipMalloc(&b->scratch, sizeof(double) * b->scratch_elems) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipMalloc(&b->flag, sizeof(int)) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+  b->stage_bytes = std::min(kStageMost, std::max(kStageLeast, stage_want));
+  if (hipHostMalloc((void**)&b->stage, kStageHead + b->stage_bytes, hipHostMallocDefault) != hipSuccess)
+    return LBM_ERR_OUT_OF_MEMORY;
   LBM_HIP(hipMemsetAsync(b->status, 0, sizeof(int) * count, b->stream));
   LBM_HIP(hipEventCreate(&b->ev0));
   LBM_HIP(hipEventCreate(&b->ev1));
-  b->hcoef.resize(count);
+  return LBM_OK;
+}
+
+// every instance's coefficients, through the stage
+lbm_status upload_coefs(lbm_batch_s* b) {
+  DevCoef* hc = reinterpret_cast<DevCoef*>(b->stage + kStageHead);
+  const int most = (int)(b->stage_bytes / sizeof(DevCoef)), count = (int)b->inst.size();
+  for (int i = 0; i < count; i += most) {
+    const int n = std::min(most, count - i);
+    for (int k = 0; k < n; ++k) fill_devcoef(b->inst[i + k], hc + k);
+    LBM_HIP(hipMemcpyAsync(b->coefs + i, hc, sizeof(DevCoef) * (size_t)n, hipMemcpyHostToDevice, b->stream));
+    LBM_HIP(hipStreamSynchronize(b->stream));
+  }
   return LBM_OK;
 }
 
@@ -431,7 +449,7 @@ lbm_status create_batch(const lbm_desc* descs, int count, void* stream, void* de
     return LBM_ERR_DEVICE;
   }
   s = alloc_batch(b, dev_buf, buf_bytes);
-  for (int i = 0; i < count && s == LBM_OK; ++i) s = upload_coef(b, i);
+  if (s == LBM_OK) s = upload_coefs(b);
   if (s != LBM_OK) {
     destroy_batch(b);
     return s;
@@ -460,36 +478,132 @@ lbm_status ensure_second_buffer(lbm_batch_s* b, bool f32) {
   return LBM_OK;
 }
 
-lbm_status load_phi_one(lbm_batch_s* b, int i, const double* phi, int on_device) {
+// The checks of an initial state and, for FP32 storage, its rest state (the mean
+// of phi0, conserved on a periodic grid).
+lbm_status check_phi(const HostInst& h, const double* phi) {
+  bool bad = false, neg = false;
+  for (int x = 0; x < h.n; ++x) {
+    bad |= !std::isfinite(phi[x]);
+    neg |= phi[x] < 0;
+  }
+  // real (non-integer) powers of phi need phi >= 0
+  return bad || (neg && h.mdl.gF > 1) ? LBM_ERR_INVALID_ARG : LBM_OK;
+}
+void rest_from(HostInst* h, const double* phi) {
+  long double s = 0;
+  for (int x = 0; x < h->n; ++x) s += phi[x];
+  set_rest_state(&h->mdl, (double)(s / h->n));
+}
+
+// f := f_eq(phi) of instances idx[k] from host arrays phi[k], already checked.
+// phi0 and the records go through the pinned stage, as many instances at a time
+// as it holds (or a piece of one that is larger), and one launch per storage
+// reads them there; coefficients are copied where they changed (FP32 storage:
+// the rest state; `fresh`: new models).  Synchronises the stream.
+lbm_status load_many(lbm_batch_s* b, const int* idx, const double* const* phi, int count, bool fresh) {
+  unsigned char* base = b->stage + kStageHead;
+  struct Piece { int inst; const double* phi; int64_t x0, len; };
+  int64_t x0 = 0;   // nodes of instance k already sent
+  for (int k = 0; k < count;) {
+    std::vector<Piece> pieces;
+    size_t need = 0;
+    while (k < count) {
+      const HostInst& h = b->inst[idx[k]];
+      const bool coefs = x0 == 0 && (h.f32 || fresh);
+      if (need + stage_need(h.n - x0, coefs) > b->stage_bytes) break;
+      need += stage_need(h.n - x0, coefs);
+      pieces.push_back({idx[k], phi[k] + x0, x0, h.n - x0});
+      x0 = 0;
+      ++k;
+    }
+    if (pieces.empty()) {   // larger than the stage
+      const HostInst& h = b->inst[idx[k]];
+      const int64_t len = (int64_t)(b->stage_bytes - stage_need(0, x0 == 0)) / (int64_t)sizeof(double);
+      pieces.push_back({idx[k], phi[k] + x0, x0, std::min<int64_t>(len, h.n - x0)});
+      x0 += pieces[0].len;
+    }
+    // coefficients, in runs of consecutive instances
+    DevCoef* hc = reinterpret_cast<DevCoef*>(base);
+    int nc = 0;
+    std::vector<int> coef_inst;
+    for (const Piece& pc : pieces) {
+      HostInst& h = b->inst[pc.inst];
+      if (pc.x0 != 0) continue;
+      h.cur = 0;
+      h.steps_done = 0;
+      if (h.f32) rest_from(&h, pc.phi);
+      if (!h.f32 && !fresh) continue;
+      fill_devcoef(h, hc + nc++);
+      coef_inst.push_back(pc.inst);
+    }
+    for (int c = 0; c < nc;) {
+      int e = c + 1;
+      while (e < nc && coef_inst[e] == coef_inst[e - 1] + 1) ++e;
+      LBM_HIP(hipMemcpyAsync(b->coefs + coef_inst[c], hc + c, sizeof(DevCoef) * (size_t)(e - c), hipMemcpyHostToDevice,
+                             b->stream));
+      c = e;
+    }
+    // records (FP64 storage, then FP32) and phi0
+    DevInit* rec = reinterpret_cast<DevInit*>(base + sizeof(DevCoef) * (size_t)nc);
+    double* data = reinterpret_cast<double*>(rec + pieces.size());
+    int at = 0;
+    for (int f32 = 0; f32 < 2; ++f32) {
+      const int first = at;
+      int64_t longest = 0;
+      for (const Piece& pc : pieces) {
+        const HostInst& h = b->inst[pc.inst];
+        if (h.f32 != (f32 != 0)) continue;
+        std::memcpy(data, pc.phi, sizeof(double) * (size_t)pc.len);
+        DevInit r{};
+        r.src = (uint64_t)(uintptr_t)data;
+        r.dst = (uint64_t)(uintptr_t)state_cur(b, h) + (uint64_t)pc.x0 * elem_size(h);
+        r.len = (int32_t)pc.len;
+        r.stride = h.stride;
+        r.inst = pc.inst;
+        r.q = h.q;
+        r.degree = h.Dinit;
+        r.first = pc.x0 == 0;
+        rec[at++] = r;
+        data += pc.len;
+        longest = std::max(longest, pc.len);
+      }
+      for (int c = first; c < at; c += 65535)
+        LBM_HIP(launch_init_many(f32 != 0, rec + c, std::min(at - c, 65535), (int)longest, b->coefs, b->status, b->stream));
+    }
+    LBM_HIP(hipStreamSynchronize(b->stream));   // the stage is free again
+  }
+  return LBM_OK;
+}
+
+// f := f_eq(phi) of instance i from device memory
+lbm_status load_device(lbm_batch_s* b, int i, const double* phi) {
   HostInst& h = b->inst[i];
-  std::vector<double> host;
-  if (on_device) {
-    host.resize(h.n);
+  if (h.f32) {   // the rest state is summed on the host
+    std::vector<double> host(h.n);
     LBM_HIP(hipMemcpyAsync(host.data(), phi, sizeof(double) * h.n, hipMemcpyDeviceToHost, b->stream));
     LBM_HIP(hipStreamSynchronize(b->stream));
-  } else {
-    host.assign(phi, phi + h.n);
+    lbm_status s = check_phi(h, host.data());
+    const double* from = host.data();
+    return s == LBM_OK ? load_many(b, &i, &from, 1, false) : s;
   }
-  for (double v : host)
-    if (!std::isfinite(v)) return LBM_ERR_INVALID_ARG;
-  if (h.mdl.gF > 1)   // real (non-integer) powers of phi need phi >= 0
-    for (double v : host)
-      if (v < 0) return LBM_ERR_INVALID_ARG;
-  if (h.f32) {
-    // rest state: the mean of phi0 (conserved on a periodic grid)
-    long double s = 0;
-    for (double v : host) s += v;
-    set_rest_state(&h.mdl, (double)(s / h.n));
-  }
-  lbm_status st = upload_coef(b, i);
-  if (st != LBM_OK) return st;
-  LBM_HIP(hipMemcpyAsync(b->scratch, host.data(), sizeof(double) * h.n, hipMemcpyHostToDevice, b->stream));
+  volatile int* words = reinterpret_cast<volatile int*>(b->stage);
+  words[0] = words[1] = 0;
+  LBM_HIP(launch_check_phi(phi, h.n, reinterpret_cast<int*>(b->stage), b->stream));
+  LBM_HIP(hipStreamSynchronize(b->stream));
+  if (words[0] || (words[1] && h.mdl.gF > 1)) return LBM_ERR_INVALID_ARG;
   h.cur = 0;
   h.steps_done = 0;
-  LBM_HIP(hipMemsetAsync(b->status + i, 0, sizeof(int), b->stream));
-  LBM_HIP(launch_init(h.q, h.Dinit, h.prec, b->scratch, state_cur(b, h), h.n, h.stride, b->coefs + i, b->stream));
-  // the scratch buffer is reused by the next call on this stream; keep order
-  LBM_HIP(hipStreamSynchronize(b->stream));
+  DevInit r{};
+  r.src = (uint64_t)(uintptr_t)phi;
+  r.dst = (uint64_t)(uintptr_t)state_cur(b, h);
+  r.len = h.n;
+  r.stride = h.stride;
+  r.inst = i;
+  r.q = h.q;
+  r.degree = h.Dinit;
+  r.first = 1;
+  LBM_HIP(launch_init_one(false, r, b->coefs, b->status, b->stream));
+  LBM_HIP(hipStreamSynchronize(b->stream));   // phi may be reused by the caller
   return LBM_OK;
 }
 
@@ -1620,28 +1734,25 @@ lbm_status advance(lbm_batch_s* b, const int64_t* steps) {
   }
 }
 
-// phi of instance i into the device scratch buffer; raises b->flag on NaN/Inf
-lbm_status phi_to_scratch(lbm_batch_s* b, int i) {
-  HostInst& h = b->inst[i];
-  LBM_HIP(hipMemsetAsync(b->flag, 0, sizeof(int), b->stream));
-  LBM_HIP(launch_phi(h.prec, state_cur(b, h), b->scratch, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0,
-                     b->flag, b->stream));
-  return LBM_OK;
-}
-
+// phi of instance i, and its status.  Grids up to the stage are summed straight
+// into it (or into device memory); larger ones go by the scratch buffer.
 lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_status* inst_status) {
   HostInst& h = b->inst[i];
-  lbm_status s0 = phi_to_scratch(b, i);
-  if (s0 != LBM_OK) return s0;
-  LBM_HIP(hipMemcpyAsync(out, b->scratch, sizeof(double) * h.n,
-                         on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, b->stream));
-  int flags[2] = {0, 0};
-  LBM_HIP(hipMemcpyAsync(&flags[0], b->flag, sizeof(int), hipMemcpyDeviceToHost, b->stream));
-  LBM_HIP(hipMemcpyAsync(&flags[1], b->status + i, sizeof(int), hipMemcpyDeviceToHost, b->stream));
+  const double rest = h.f32 ? h.mdl.phi_rest : 0.0;
+  int* words = reinterpret_cast<int*>(b->stage);
+  volatile int* seen = words;
+  seen[0] = seen[1] = 0;
+  const bool staged = !on_device && sizeof(double) * (size_t)h.n <= b->stage_bytes;
+  double* to = on_device ? out : staged ? reinterpret_cast<double*>(b->stage + kStageHead) : b->scratch;
+  LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, b->stream));
+  if (!on_device && !staged)
+    LBM_HIP(hipMemcpyAsync(out, to, sizeof(double) * h.n, hipMemcpyDeviceToHost, b->stream));
   LBM_HIP(hipStreamSynchronize(b->stream));
+  if (staged) std::memcpy(out, to, sizeof(double) * h.n);
   // status bit 1: a non-finite value; bits 2 and 4: a device wait for a
   // cooperating workgroup gave up, so the state was not advanced as asked
-  lbm_status s = (flags[1] & 6) ? LBM_ERR_TIMEOUT : (flags[0] || flags[1]) ? LBM_ERR_NONFINITE : LBM_OK;
+  const int flags = seen[0], bad = seen[1];
+  lbm_status s = (flags & 6) ? LBM_ERR_TIMEOUT : (bad || flags) ? LBM_ERR_NONFINITE : LBM_OK;
   if (inst_status) *inst_status = s;
   return s;
 }
@@ -1680,7 +1791,6 @@ lbm_status clone_for_tuning(lbm_batch_s* b, lbm_batch_s** out) {
   for (int i = 0; i < count && s == LBM_OK; ++i) {
     c->inst[i].mdl = b->inst[i].mdl;
     c->inst[i].cur = b->inst[i].cur;
-    c->hcoef[i] = b->hcoef[i];
   }
   auto copy = [&](void* dst, const void* src, size_t bytes) -> lbm_status {
     if (!bytes) return LBM_OK;
@@ -1893,7 +2003,11 @@ lbm_status lbm_create(const lbm_desc* d, void* stream, void* dev_buf, size_t buf
 
 lbm_status lbm_load_phi(lbm_problem h, const double* phi, int phi_on_device) {
   if (!h || !phi) return LBM_ERR_INVALID_ARG;
-  return load_phi_one(h->b, 0, phi, phi_on_device);
+  if (phi_on_device) return load_device(h->b, 0, phi);
+  const lbm_status s = check_phi(h->b->inst[0], phi);
+  if (s != LBM_OK) return s;
+  const int i = 0;
+  return load_many(h->b, &i, &phi, 1, false);
 }
 
 lbm_status lbm_advance(lbm_problem h, int64_t steps) {
@@ -1929,7 +2043,7 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
   DevJobInst* dji = (DevJobInst*)(bytes + 12288 + 256);   // or the register path's segment
   DevItem* ditem = (DevItem*)(bytes + 12288 + 128);
   static_assert(sizeof(DevJob) <= 128 && sizeof(DevItem) <= 128 && sizeof(DevSeg) <= 256 && sizeof(DevJobInst) <= 256, "job record outgrew its scratch region");
-  int* ints = (int*)(bytes + 12288 + 512);   // queue counter, slot, done, status, non-finite flag
+  int* ints = (int*)(bytes + 12288 + 512);   // queue counter, slot, done, status, read-out words
   void* f = bytes + kNoAllocTableBytes;
   // phi0 on the host: the checks of lbm_load_phi and the rest state (mean of phi0)
   double host[kNoAllocMaxNodes];
@@ -1984,8 +2098,16 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
     LBM_HIP(hipMemcpyAsync(dji, &sg, sizeof(sg), hipMemcpyHostToDevice, st));
   else
     LBM_HIP(hipMemcpyAsync(dji, &ji, sizeof(ji), hipMemcpyHostToDevice, st));
-  LBM_HIP(launch_zero_ints(ints, 5, st));
-  LBM_HIP(launch_init(h.q, h.Dinit, h.prec, phi0, f, h.n, h.stride, dcoef, st));
+  LBM_HIP(launch_zero_ints(ints, 6, st));
+  DevInit init{};
+  init.src = (uint64_t)(uintptr_t)phi0;
+  init.dst = (uint64_t)(uintptr_t)f;
+  init.len = h.n;
+  init.stride = h.stride;
+  init.q = h.q;
+  init.degree = h.Dinit;
+  init.first = 1;
+  LBM_HIP(launch_init_one(h.f32, init, dcoef, ints + 3, st));
   for (int64_t left = steps; left > 0;) {
     const int64_t now = std::min(left, kMaxStepsPerLaunch);
     left -= now;
@@ -2002,9 +2124,9 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
       LBM_HIP(launch_resident(h.q, h.prec, h.D, djob, dji, 1, 1, ints, ints + 1, ints + 2, dcoef, ints + 3, 0, -1, 1,
                               ji.nt, lds, st));
   }
-  LBM_HIP(launch_phi(h.prec, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 4, st));
+  LBM_HIP(launch_read(h.f32, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 3, ints + 4, st));
   int flags[2] = {0, 0};
-  LBM_HIP(hipMemcpyAsync(flags, ints + 3, sizeof(flags), hipMemcpyDeviceToHost, st));
+  LBM_HIP(hipMemcpyAsync(flags, ints + 4, sizeof(flags), hipMemcpyDeviceToHost, st));
   LBM_HIP(hipStreamSynchronize(st));
   if (flags[0] & 6) return LBM_ERR_TIMEOUT;
   return (flags[0] || flags[1]) ? LBM_ERR_NONFINITE : LBM_OK;
@@ -2209,8 +2331,9 @@ lbm_status lbm_sum_phi(lbm_problem h, double* total) {
   if (!h || !total) return LBM_ERR_INVALID_ARG;
   lbm_batch_s* b = h->b;
   HostInst& hi = b->inst[0];
-  lbm_status s = phi_to_scratch(b, 0);
-  if (s != LBM_OK) return s;
+  int* words = reinterpret_cast<int*>(b->stage);
+  LBM_HIP(launch_read(hi.f32, state_cur(b, hi), b->scratch, hi.n, hi.stride, hi.q, hi.f32 ? hi.mdl.phi_rest : 0.0,
+                      b->status, words, b->stream));
   // deterministic FP64 reduction: fixed partition on the device, fixed order on the host
   const int parts = 64;
   double* part = b->scratch + hi.n;
@@ -2301,11 +2424,13 @@ lbm_status lbm_batch_load_phi(lbm_batch b, const double* const* phi0) {
   if (!b || !phi0) return LBM_ERR_INVALID_ARG;
   for (size_t i = 0; i < b->inst.size(); ++i)
     if (!phi0[i]) return LBM_ERR_INVALID_ARG;
+  std::vector<int> idx(b->inst.size());
   for (size_t i = 0; i < b->inst.size(); ++i) {
-    lbm_status s = load_phi_one(b, (int)i, phi0[i], 0);
+    lbm_status s = check_phi(b->inst[i], phi0[i]);
     if (s != LBM_OK) return s;
+    idx[i] = (int)i;
   }
-  return LBM_OK;
+  return load_many(b, idx.data(), phi0, (int)idx.size(), false);
 }
 
 lbm_status lbm_batch_advance(lbm_batch b, const int64_t* steps) {
@@ -2510,7 +2635,7 @@ lbm_status lbm_server_create(void* stream, size_t budget_bytes, int32_t max_slot
     b->f32[1] = (float*)b->arena[1];
     b->n64 = sv->arena.size / sizeof(double);
     b->n32 = sv->arena.size / sizeof(float);
-    s = alloc_tables(b, (size_t)max_n);
+    s = alloc_tables(b, (size_t)max_n, (size_t)2 << 20);
   }
   if (s != LBM_OK) {
     destroy_batch(b);
@@ -2553,10 +2678,24 @@ lbm_status lbm_server_submit(lbm_server sv, const lbm_desc* d, const double* phi
 
 namespace {
 
+// retires the request in `slot`, which could not be started, with status s
+void server_drop(lbm_server_s* sv, int slot, lbm_status s) {
+  Slot& sl = sv->slots[slot];
+  Result& res = sv->results[sl.id - 1];
+  sv->arena.release(sl.off, sl.bytes);
+  sv->b->inst[slot] = HostInst();
+  res.status = s;
+  res.t_admit = res.t_retire = now_s();
+  sv->done[sl.id - 1] = 1;
+  sl = Slot();
+}
+
 // Admission: queued requests in arrival order while a slot and arena space
 // are free (f := f_eq(phi0) on the stream, which it synchronises).
 void server_admit(lbm_server_s* sv) {
   lbm_batch_s* b = sv->b;
+  std::vector<int> idx;
+  std::vector<const double*> phi;
   size_t qi = 0;
   for (; qi < sv->queue.size(); ++qi) {
     Request& r = sv->queue[qi];
@@ -2571,29 +2710,29 @@ void server_admit(lbm_server_s* sv) {
     size_t off = 0;
     if (!sv->arena.alloc(bytes, &off)) break;   // FIFO: wait for space
     HostInst& h = b->inst[slot];
-    lbm_status s = prepare_one(r.desc, &h);
-    if (s == LBM_OK) {
-      h.off = (int64_t)(off / (h.f32 ? sizeof(float) : sizeof(double)));
-      s = load_phi_one(b, slot, r.phi0.data(), 0);
-    }
-    Result& res = sv->results[r.id - 1];
-    res.t_admit = now_s();
-    if (s != LBM_OK) {
-      // submission ran the same checks, so this is a device error: the request
-      // retires with it (no phi) and the queue moves on
-      sv->arena.release(off, bytes);
-      h = HostInst();
-      res.status = s;
-      res.t_retire = res.t_admit;
-      sv->done[r.id - 1] = 1;
-      continue;
-    }
+    const lbm_status s = prepare_one(r.desc, &h);
     Slot& sl = sv->slots[slot];
     sl.active = true;
     sl.id = r.id;
     sl.remaining = r.steps;
     sl.off = off;
     sl.bytes = bytes;
+    if (s == LBM_OK) {
+      h.off = (int64_t)(off / (h.f32 ? sizeof(float) : sizeof(double)));
+      idx.push_back(slot);
+      phi.push_back(r.phi0.data());
+    } else {
+      server_drop(sv, slot, s);
+    }
+  }
+  // one load for all; submission ran the same checks, so a failure is a device
+  // error: its requests retire with it (no phi) and the queue moves on
+  if (!idx.empty()) {
+    const lbm_status s = load_many(b, idx.data(), phi.data(), (int)idx.size(), true);
+    for (int slot : idx) {
+      sv->results[sv->slots[slot].id - 1].t_admit = now_s();
+      if (s != LBM_OK) server_drop(sv, slot, s);
+    }
   }
   sv->queue.erase(sv->queue.begin(), sv->queue.begin() + qi);
 }
