@@ -46,8 +46,8 @@ LATTICES = (4, 5, 6, 7)
 
 def build(verbose: bool = False) -> str:
     """Compiles the host sources, the read-out/launcher unit, the boundary-wave
-    unit and one kernel unit per lattice size (kernels_q.hip with LBM_Q = 4..7)
-    in parallel, then links."""
+    unit, one kernel unit per lattice size (kernels_q.hip with LBM_Q = 4..7) and
+    one per lattice size and precision (kernels_reg.hip) in parallel, then links."""
     os.makedirs(BUILD, exist_ok=True)
     inc = [f"-I{INCLUDE}", f"-I{CSRC}"]
     steps = []
@@ -61,8 +61,12 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(BUILD, f"kernels_q{q}.hip.o")
         steps.append((obj, [HIPCC] + DEVICE_FLAGS + inc + [f"-DLBM_Q={q}", "-c",
                                                             os.path.join(CSRC, "kernels_q.hip"), "-o", obj]))
-    # the D1Q7 and D1Q5 units take longest: start them first
-    steps.sort(key=lambda st: ("q7" not in st[0], "q5" not in st[0]))
+        for prec in range(3):
+            obj = os.path.join(BUILD, f"kernels_reg{q}_{prec}.hip.o")
+            steps.append((obj, [HIPCC] + DEVICE_FLAGS + inc + [f"-DLBM_Q={q}", f"-DLBM_PREC={prec}", "-c",
+                                                                os.path.join(CSRC, "kernels_reg.hip"), "-o", obj]))
+    # the largest lattices' units take longest: start them first
+    steps.sort(key=lambda st: next((-q for q in LATTICES if f"q{q}." in st[0] or f"reg{q}_" in st[0]), 0))
     jobs = max(1, min(len(steps), os.cpu_count() or 1, 8))
     with ThreadPoolExecutor(jobs) as pool:
         list(pool.map(lambda st: _run(st[1]), steps))

@@ -93,21 +93,25 @@ struct DevItem {
 
 // Register-resident path: a segment is a run of consecutive nodes of an
 // instance advanced by `waves` waves of one workgroup, R nodes per lane.
+enum { kSegRing = 0, kSegSlab = 1 };
 struct DevSeg {
   uint64_t in;               // device address of row 0 of the state read ...
   uint64_t out;              // ... and written
   int32_t n;                 // nodes of the instance
   int32_t stride;            // row stride in elements
   int32_t inst;              // index into coefficients / status
-  int32_t kind;              // 0 ring: the whole instance, its ends joined
   int32_t x0;                // first node owned
   int32_t len;               // nodes owned (written back)
   int32_t lanes;             // lanes advanced: the owned nodes' and `extra` at each end
-  int32_t extra;
-  int32_t over;              // nodes by which the owned lanes exceed the ring (< R)
+  int32_t extra;             // slab, tile: outer halo lanes beside a wave's own
+  int32_t over;              // nodes by which the owned lanes exceed the ring's end (< R), else 0
+  int32_t over_left;         // slab: the left neighbour's `over`
   int32_t w0;                // first wave of the workgroup
   int32_t waves;
   int32_t lds_off;           // element offset of the segment's strips in LDS
+  int32_t steps;             // slab, tile: steps of the advance
+  int32_t left, right;       // slab: ring neighbours (segments of the launch)
+  int32_t pad_;
 };
 
 // Slab path: an instance split over several co-resident workgroups (one slab

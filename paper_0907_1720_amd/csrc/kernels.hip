@@ -118,9 +118,17 @@ const void* resident_kernel(int q, int prec, int code) {
   return t ? t->resident_fn(prec, code) : nullptr;
 }
 
-const void* reg_kernel(int q, int prec, int code, bool wide) {
-  const QKernels* t = table(q);
-  return t ? t->reg_fn(prec, code, wide) : nullptr;
+template <int Q>
+const void* reg_or_seg(bool seg, int prec, int code, bool wide) {
+  if (prec == 0) return seg ? seg_kernel<Q, 0>(code, wide) : reg_kernel<Q, 0>(code, wide);
+  if (prec == 1) return seg ? seg_kernel<Q, 1>(code, wide) : reg_kernel<Q, 1>(code, wide);
+  return seg ? seg_kernel<Q, 2>(code, wide) : reg_kernel<Q, 2>(code, wide);
+}
+const void* reg_or_seg(bool seg, int q, int prec, int code, bool wide) {
+  if (q == 4) return reg_or_seg<4>(seg, prec, code, wide);
+  if (q == 5) return reg_or_seg<5>(seg, prec, code, wide);
+  if (q == 6) return reg_or_seg<6>(seg, prec, code, wide);
+  return q == 7 ? reg_or_seg<7>(seg, prec, code, wide) : nullptr;
 }
 
 const void* tile_kernel(int q, int prec) {
@@ -195,7 +203,7 @@ hipError_t launch_resident(int q, int prec, int code, const DevJob* jobs, const 
 hipError_t launch_reg(int q, int prec, int code, bool wide, const DevItem* items, int nitems, const DevJob* jobs,
                       const DevSeg* segs, int* counter, int* done, const DevCoef* coefs, int* status,
                       long long wait_ticks, int stall_item, int grid, int block, size_t lds, hipStream_t s) {
-  const void* fn = reg_kernel(q, prec, code, wide);
+  const void* fn = reg_or_seg(false, q, prec, code, wide);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -205,7 +213,28 @@ hipError_t launch_reg(int q, int prec, int code, bool wide, const DevItem* items
 }
 
 hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu) {
-  const void* fn = reg_kernel(q, prec, code, wide);
+  const void* fn = reg_or_seg(false, q, prec, code, wide);
+  if (!fn) return hipErrorInvalidValue;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, fn, block, lds);
+}
+
+hipError_t launch_seg(int q, int prec, int code, bool wide, const DevSeg* segs, int nsegs, int nodes, int s_per, int sx,
+                      bool tile, int launch, void* xbuf, int* flags, const DevCoef* coefs, int* status,
+                      long long wait_ticks, int mute_seg, int block, size_t lds, hipStream_t s) {
+  const void* fn = reg_or_seg(true, q, prec, code, wide);
+  if (!fn) return hipErrorInvalidValue;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  int as_tile = tile ? 1 : 0;
+  void* args[] = {(void*)&segs, (void*)&nodes, (void*)&s_per, (void*)&sx,     (void*)&as_tile,    (void*)&launch,
+                  (void*)&xbuf, (void*)&flags, (void*)&coefs, (void*)&status, (void*)&wait_ticks, (void*)&mute_seg};
+  return hipLaunchKernel(fn, dim3(nsegs), dim3(block), args, lds, s);
+}
+
+hipError_t seg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu) {
+  const void* fn = reg_or_seg(true, q, prec, code, wide);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

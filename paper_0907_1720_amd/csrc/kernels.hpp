@@ -129,6 +129,13 @@ hipError_t launch_reg(int q, int prec, int code, bool wide, const DevItem* items
                       const DevSeg* segs, int* counter, int* done, const DevCoef* coefs, int* status,
                       long long wait_ticks, int stall_item, int grid, int block, size_t lds, hipStream_t s);
 hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu);
+// one segment per workgroup (polynomial variants): slabs of one launch, or tiles
+// (`launch`-th block of sx steps); flags[2 nsegs] start at 0; xbuf holds 4 (hg +
+// 1) R q values per segment; segment mute_seg (-1: none) never raises its flags
+hipError_t launch_seg(int q, int prec, int code, bool wide, const DevSeg* segs, int nsegs, int nodes, int s_per, int sx,
+                      bool tile, int launch, void* xbuf, int* flags, const DevCoef* coefs, int* status,
+                      long long wait_ticks, int mute_seg, int block, size_t lds, hipStream_t s);
+hipError_t seg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu);
 // VGPRs per thread of the resident kernel of variant `code`
 int resident_vgprs(int q, int prec, int code);
 // static LDS bytes of the resident kernel (0 by construction)

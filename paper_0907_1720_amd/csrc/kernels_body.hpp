@@ -11,13 +11,16 @@
 //              into a workgroup's LDS, threads split in proportion to their
 //              nodes); f stays in LDS for all steps of the launch; streaming in
 //              place with the alternating (AA) access pattern, one barrier per
-//              step
+//              step (bounded grids and power sums)
 //  k_tile      temporal blocking for grids larger than one workgroup's LDS
 //  k_slab      grids larger than one workgroup's LDS split over co-resident
-//              workgroups that exchange halo strips
+//              workgroups that exchange halo strips (both for power sums)
+// Periodic grids with polynomial equilibria advance in registers instead
+// (reg_body.hpp).
 #pragma once
 
 #include "kernels.hpp"
+#include "reg_body.hpp"
 
 namespace lbm {
 
@@ -553,7 +556,7 @@ __global__ __launch_bounds__(1024) void k_tile(const DevTile* __restrict__ tiles
   case DD | (PP << 8):                                                                                     \
     tile_instance<Q, DD, PP, T, A>(S, gin, gout, ti.n, ti.stride, tl.x0, tl.core, halo, st, cf, status + ti.inst); \
     break;
-    LBM_VARIANT_CASES
+    LBM_POWER_CASES
 #undef LBM_CASE
     default:
       break;
@@ -583,21 +586,6 @@ __global__ __launch_bounds__(1024) void k_tile(const DevTile* __restrict__ tiles
 // (vmcnt 0) before the workgroup barrier that precedes the flag store, and the
 // strips are loaded only after the flag load has returned.
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void store_agent(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ T load_agent(const T* p) {
-  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// wait until this wave's vector memory operations have completed
-__device__ __forceinline__ void wait_vm() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) expcnt(7) lgkmcnt(15)
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 template <int Q, int D, int P, typename T, typename A>
 __device__ void slab_instance(T* __restrict__ S, int* __restrict__ bail, const DevSlab& sl, const DevTileInst& ti,
                               const T* __restrict__ gin, T* __restrict__ gout, int s_per, int halo,
@@ -645,7 +633,7 @@ __device__ void slab_instance(T* __restrict__ S, int* __restrict__ bail, const D
       const int x = side == 0 ? halo + h : W - 2 * halo + h;
       store_agent(mine + idx, S[x * lds_stride(Q) + j]);
     }
-    wait_vm();
+    wait_vector_memory();
     __syncthreads();
     if (t == 0) {
       if (!mute) store_agent(flags + me, blk + 1);

@@ -3,7 +3,6 @@
 // launchers as the table q_kernels_<q>.  `prec` selects (storage, arithmetic):
 // 0 (double, double), 1 (float, double), 2 (float, float).
 #include "kernels_body.hpp"
-#include "reg_body.hpp"
 #include "kernels_table.hpp"
 
 #ifndef LBM_Q
@@ -65,24 +64,6 @@ const void* resident_prec(int prec, int code) {
   return resident_fn<Q, float, float>(code);
 }
 
-template <int Q, typename T, typename A>
-const void* reg_fn(int code, bool wide) {
-  switch (code) {
-#define LBM_CASE(DD, PP) \
-  case DD | (PP << 8):   \
-    return wide ? (const void*)k_reg<Q, DD, PP, T, A, true> : (const void*)k_reg<Q, DD, PP, T, A, false>;
-    LBM_POLY_CASES
-#undef LBM_CASE
-  }
-  return nullptr;
-}
-template <int Q>
-const void* reg_prec(int prec, int code, bool wide) {
-  if (prec == 0) return reg_fn<Q, double, double>(code, wide);
-  if (prec == 1) return reg_fn<Q, float, double>(code, wide);
-  return reg_fn<Q, float, float>(code, wide);
-}
-
 template <int Q, typename T>
 hipError_t launch_bound_q(int D, T* f, int n, int stride, int layers, int kind, const double* phib,
                           const DevCoef* cf, hipStream_t s) {
@@ -134,7 +115,7 @@ const void* slab_fn(int code) {
 #define LBM_CASE(DD, PP) \
   case DD | (PP << 8):   \
     return (const void*)k_slab<Q, DD, PP, T, A>;
-    LBM_VARIANT_CASES
+    LBM_POWER_CASES
 #undef LBM_CASE
   }
   return nullptr;
@@ -149,7 +130,7 @@ const void* slab_prec(int prec, int code) {
 
 QKernels LBM_CAT(q_kernels_, LBM_Q) = {
     &launch_bound_p<LBM_Q>, &launch_stream_p<LBM_Q>, &stream_prec<LBM_Q>, &resident_prec<LBM_Q>,
-    &reg_prec<LBM_Q>,       &tile_prec<LBM_Q>,       &slab_prec<LBM_Q>,
+    &tile_prec<LBM_Q>,      &slab_prec<LBM_Q>,
 };
 
 }  // namespace lbm

@@ -228,25 +228,76 @@ __device__ __forceinline__ void reg_odd(T (&f)[R][Q], X& relax) {
 }
 
 
-// all of this wave's loads have returned (waited for here, and not at their
-// first uses inside the step loop)
-__device__ __forceinline__ void wait_loads() {
+// all of this wave's vector memory operations have completed
+__device__ __forceinline__ void wait_vector_memory() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) expcnt(7) lgkmcnt(15)
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+template <typename T>
+__device__ __forceinline__ void store_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) {
+  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // the sign-free word that holds the exponent: not below infinity's for NaN and Inf
 __device__ __forceinline__ unsigned exponent_word(float v) { return (unsigned)__float_as_int(v) & 0x7fffffffu; }
 __device__ __forceinline__ unsigned exponent_word(double v) { return (unsigned)__double2hiint(v) & 0x7fffffffu; }
 
+// What the segments of a slab launch share.
+struct SegLinks {
+  int sx;                    // steps between exchanges with the neighbours (a multiple of s_per)
+  void* xbuf;                // strips: [segment][buffer][side][(hg + 1) R nodes][Q]
+  int* flags;                // [segment][side]: blocks published
+  int me;                    // this segment
+  bool mute;                 // never raises its flags (test hook)
+  long long wait_ticks;
+};
+
+// LDS elements of one wave: its exchange strips, or one row of its nodes on the
+// way between memory order and lane order
+constexpr int reg_lds(int q, int R, int hl) {
+  const int strips = 4 * (hl + 1) * R * q;
+  return strips > 64 * R ? strips : 64 * R;
+}
+
 // Advance of one segment by the waves that hold it.  `sg` is the segment, `w`
 // this wave's number in it; waves without a segment (act false) only meet the
-// barriers.  The outer halos of a ring segment's first and last waves are each
-// other's.
-template <int Q, int R, int B, int D, int P, typename T, typename A>
+// barriers.
+//  Ring: the whole instance; the outer halos of the first and last waves are
+//   each other's.
+//  Slab: part of an instance, one workgroup each, all of a launch resident
+//   together.  A segment carries `extra` lanes more at each end, so that its
+//   ends stay exact for `sx` steps; then its first and last waves publish the
+//   outer owned lanes in global memory, raise a flag each, wait for the
+//   neighbour's and refill their outer halos.  Strips and flags move with
+//   device-scope relaxed atomics (coherent across the XCDs' L2 caches without
+//   whole-cache write-back): a wave waits for its strip stores to complete
+//   before it stores its flag, and loads strips only after the flag load has
+//   returned.  Strips alternate between two buffers by block; a wave overwrites
+//   one only after the neighbour has raised the next block's flag, i.e. after it
+//   has read it.  A wait that outlasts `wait_ticks` ticks of the constant-rate
+//   wall clock marks the instance (status bit 2) and is the wave's last: it runs
+//   on without waiting, so that every kernel ends.
+//  (A tile is a slab of at most `sx` steps, which meets no exchange with
+//   neighbours.)
+// State moves between memory order and lane order through a row of LDS per wave,
+// so that both sides are coalesced.
+// Bounded by VALU issue where the waves fill the SIMDs, by the exchange (2.1 us:
+// stores to the other XCD's reach, flag, poll, strip) where one instance is
+// spread thin.  Against the LDS-resident slabs and tiles (two to four workgroup
+// barriers and Q LDS accesses per node and step): one 4096-node FP32 KS solve
+// 4.03 -> 1.52 ms per 4000 steps, 128 x 8192 KS FP64 x 2000 4.46 -> 3.36 ms, 96
+// Kawahara FP64 of 2048..16384 nodes x 2000 10.8 -> 4.64 ms, a 3,000,017-node
+// KdV grid x 64 0.65 -> 0.34 ms.
+template <int Q, int R, int B, int Kind, int D, int P, typename T, typename A>
 __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w, bool act,
-                                            const DevCoef* __restrict__ cf, int* __restrict__ status) {
+                                            const DevCoef* __restrict__ cf, int* __restrict__ status,
+                                            const SegLinks& lk) {
   constexpr int H = Q / 2;
   using GT = __attribute__((address_space(1))) T;   // global memory
   const int lane = threadIdx.x & 63;
@@ -254,6 +305,7 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
   if (!act) {
     __syncthreads();
     for (int done = s_per; done < steps; done += s_per) __syncthreads();
+    __syncthreads();
     return;
   }
   RegRelaxer<Q, D, P, T, A> relax;
@@ -262,48 +314,80 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
   // lanes of nodes advanced by this wave, among the segment's `lanes`
   const int b0 = (int)((int64_t)w * sg.lanes / W), b1 = (int)((int64_t)(w + 1) * sg.lanes / W);
   const int cl = b1 - b0;
-  const int ring = sg.kind == 0;
-  // strips: [wave][buffer][side][(hl + 1) R nodes][Q]
-  const int strip = (hl + 1) * R * Q;
+  constexpr bool ring = Kind == kSegRing;
+  // strips: [buffer][side][(hl + 1) R nodes][Q] of each wave
+  const int strip = (hl + 1) * R * Q, per_wave = reg_lds(Q, R, hl);
   int pub = -1, ref = -1;
   {
     const int i = lane - hl;
     if (i >= 0 && i <= hl)
-      pub = w * 4 * strip + i * R * Q;
+      pub = w * per_wave + i * R * Q;
     else if (i < cl && i >= cl - 1 - hl)
-      pub = (w * 4 + 1) * strip + (i - (cl - 1 - hl)) * R * Q;
+      pub = w * per_wave + strip + (i - (cl - 1 - hl)) * R * Q;
     if (lane < hl) {
       if (w > 0)
-        ref = ((w - 1) * 4 + 1) * strip + (lane + 1) * R * Q;
+        ref = (w - 1) * per_wave + strip + (lane + 1) * R * Q;
       else if (ring)
-        ref = ((W - 1) * 4 + 1) * strip + ((lane + 1) * R - sg.over) * Q;
+        ref = (W - 1) * per_wave + strip + ((lane + 1) * R - sg.over) * Q;
     } else if (i >= cl && i < cl + hl) {
       if (w < W - 1)
-        ref = (w + 1) * 4 * strip + (i - cl) * R * Q;
+        ref = (w + 1) * per_wave + (i - cl) * R * Q;
       else if (ring)
         ref = ((i - cl) * R + sg.over) * Q;
     }
   }
   T* S = L + sg.lds_off;
+  T* row = S + w * per_wave;   // this wave's, for one row of its nodes
   T f[R][Q];
-  const int lane_x = (b0 - hl + lane - sg.extra) * R;   // first node of the lane, relative to x0
+  const int first = (b0 - hl - sg.extra) * R;   // the wave's first node, relative to x0
   {
     const GT* g = (const GT*)(uintptr_t)sg.in;
-    int base = (sg.x0 + lane_x) % n;
+    int base = (sg.x0 + first) % n;
     base += base < 0 ? n : 0;
+    const bool once = n >= 64 * R;   // the wave's nodes pass the ring's end once at most
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      int x = base + r;
-      x -= x >= n ? n : 0;
-      x -= x >= n ? n : 0;
+    for (int j = 0; j < Q; ++j) {
+      T v[R];
 #pragma unroll
-      for (int j = 0; j < Q; ++j) f[r][j] = g[(int64_t)j * sg.stride + x];
+      for (int r = 0; r < R; ++r) {
+        int x = base + r * 64 + lane;
+        x = once ? x - (x >= n ? n : 0) : x % n;
+        v[r] = g[(int64_t)j * sg.stride + x];
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) row[r * 64 + lane] = v[r];
+      __builtin_amdgcn_wave_barrier();   // (a wave's LDS operations complete in order)
+#pragma unroll
+      for (int r = 0; r < R; ++r) f[r][j] = row[lane * R + r];
+      __builtin_amdgcn_wave_barrier();
     }
   }
   // in == out for rings: every wave has loaded before the first one stores
-  // (calls of at most s_per steps meet no other barrier)
-  wait_loads();
+  // (calls of at most s_per steps meet no other barrier); and no wave publishes
+  // into another's row
+  wait_vector_memory();
   __syncthreads();
+  // slab: this lane's part in the exchange with the neighbours (element offsets, -1 none)
+  int gpub = -1, gref = -1, kx = 0, blk = 0;
+  bool left_end = false, right_end = false, waits = true;
+  [[maybe_unused]] int gstrip = 0;
+  if constexpr (Kind == kSegSlab) {
+    const int hg = hl + sg.extra, owned = sg.lanes - 2 * sg.extra;
+    const int o = b0 - hl + lane - sg.extra;   // among the owned lanes
+    gstrip = (hg + 1) * R * Q;
+    left_end = w == 0;
+    right_end = w == W - 1;
+    kx = lk.sx;
+    const bool core = lane >= hl && lane < hl + cl;
+    if (left_end && core && o >= 0 && o <= hg)
+      gpub = o * R * Q;
+    else if (right_end && core && o < owned && o >= owned - 1 - hg)
+      gpub = gstrip + (o - (owned - 1 - hg)) * R * Q;
+    if (left_end && o >= -hg && o < 0)
+      gref = sg.left * 4 * gstrip + gstrip + ((o + hg + 1) * R - sg.over_left) * Q;
+    else if (right_end && o >= owned && o < owned + hg)
+      gref = sg.right * 4 * gstrip + ((o - owned) * R + sg.over) * Q;
+  }
   int pairs = steps >> 1, k = s_per >> 1, buf = 0;
   if (pairs > 0) do {
       reg_even<Q, R, B>(f, relax);
@@ -317,6 +401,28 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
 #pragma unroll
             for (int j = 0; j < Q; ++j) p[r * Q + j] = f[r][j];
         }
+        bool across = false;   // this exchange is with the neighbours too
+        if constexpr (Kind == kSegSlab) {
+          kx -= s_per;
+          across = kx == 0;
+          if (across && (left_end || right_end)) {
+            kx = lk.sx;
+            if (gpub >= 0) {
+              T* p = (T*)lk.xbuf + (int64_t)lk.me * 4 * gstrip + (blk & 1) * 2 * gstrip + gpub;
+#pragma unroll
+              for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int j = 0; j < Q; ++j) store_agent(p + r * Q + j, f[r][j]);
+            }
+            wait_vector_memory();
+            if (lane == 0 && !lk.mute) {
+              if (left_end) store_agent(lk.flags + 2 * lk.me, blk + 1);
+              if (right_end) store_agent(lk.flags + 2 * lk.me + 1, blk + 1);
+            }
+          } else if (across) {
+            kx = lk.sx;
+          }
+        }
         __syncthreads();
         if (ref >= 0) {
           const T* p = S + ref + buf;
@@ -326,6 +432,32 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
             for (int j = 0; j < Q; ++j) f[r][j] = p[r * Q + j];
         }
         buf = 2 * strip - buf;
+        if constexpr (Kind == kSegSlab) {
+          if (across) {
+            if (left_end || right_end) {
+              if (waits) {
+                const long long t0 = wall_clock64();
+                bool ready;
+                while (!(ready = (!left_end || load_agent(lk.flags + 2 * sg.left + 1) > blk) &&
+                                 (!right_end || load_agent(lk.flags + 2 * sg.right) > blk)) &&
+                       wall_clock64() - t0 < lk.wait_ticks)
+                  __builtin_amdgcn_s_sleep(1);
+                if (!ready) {
+                  waits = false;
+                  if (lane == 0) atomicOr(status + sg.inst, 2);
+                }
+              }
+              if (gref >= 0) {
+                const T* p = (const T*)lk.xbuf + (int64_t)(blk & 1) * 2 * gstrip + gref;
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                  for (int j = 0; j < Q; ++j) f[r][j] = load_agent(p + r * Q + j);
+              }
+            }
+            ++blk;
+          }
+        }
       }
     } while (--pairs > 0);
   if (steps & 1) {   // the last step: relax, then stream to the natural layout
@@ -338,24 +470,36 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
       for (int j = 0; j < Q; ++j) f[r][j] = t[r][j];
   }
   GT* out = (GT*)(uintptr_t)sg.out;
-  // the largest exponent written by the lane, as an unsigned word (a lane mask
-  // of the test itself, carried through these branches, cost scalar registers)
+  // the largest exponent of the lane's owned nodes, as an unsigned word
   unsigned top = 0;
-  const int i = lane - hl;
-  if (i >= 0 && i < cl) {
+  const bool core = lane >= hl && lane < hl + cl;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (lane_x + r >= 0 && lane_x + r < sg.len) {
+  for (int r = 0; r < R; ++r) {
+    const int x = first + lane * R + r;
+    const bool own = core && x >= 0 && x < sg.len;
 #pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          const unsigned e = exponent_word(f[r][j]);
-          top = top > e ? top : e;
-          out[(int64_t)j * sg.stride + sg.x0 + lane_x + r] = f[r][j];
-        }
-      }
+    for (int j = 0; j < Q; ++j) {
+      const unsigned e = own ? exponent_word(f[r][j]) : 0u;
+      top = top > e ? top : e;
     }
   }
   if (top >= exponent_word((T)__builtin_inf())) atomicOr(status + sg.inst, 1);
+  __syncthreads();   // the strips have been read: rows may go over them
+  const int lo = hl * R > -first ? hl * R : -first;   // owned nodes of the wave, in memory order
+  const int hi = (hl + cl) * R < sg.len - first ? (hl + cl) * R : sg.len - first;
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) row[lane * R + r] = f[r][j];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int x = r * 64 + lane;
+      const T v = row[x];
+      if (x >= lo && x < hi) out[(int64_t)j * sg.stride + sg.x0 + first + x] = v;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // Nodes relaxed together: all of a lane's where each coefficient is loaded once
@@ -363,17 +507,46 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
 constexpr int reg_together(bool pin, int R) { return !pin ? R : R <= 3 ? R : R == 5 ? 3 : 2; }
 
 // the width of this job
-template <int Q, int D, int P, typename T, typename A, bool Wide, int I>
+template <int Q, int Kind, int D, int P, typename T, typename A, bool Wide, int I>
 __device__ __forceinline__ void reg_widths(int nodes, T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w,
-                                           bool act, const DevCoef* __restrict__ cf, int* __restrict__ status) {
+                                           bool act, const DevCoef* __restrict__ cf, int* __restrict__ status,
+                                           const SegLinks& lk) {
   constexpr int R = reg_width(Q, (int)sizeof(T), D, P, Wide, I);
   if constexpr (R > 0) {
     if (nodes == R)
-      reg_segment<Q, R, reg_together(RegRelaxer<Q, D, P, T, A>::kPin, R), D, P, T, A>(L, steps, s_per, sg, w, act, cf,
-                                                                                  status);
+      reg_segment<Q, R, reg_together(RegRelaxer<Q, D, P, T, A>::kPin, R), Kind, D, P, T, A>(L, steps, s_per, sg, w, act,
+                                                                                       cf, status, lk);
     else if constexpr (I + 1 < kRegWidths)
-      reg_widths<Q, D, P, T, A, Wide, I + 1>(nodes, L, steps, s_per, sg, w, act, cf, status);
+      reg_widths<Q, Kind, D, P, T, A, Wide, I + 1>(nodes, L, steps, s_per, sg, w, act, cf, status, lk);
   }
+}
+
+// One segment per workgroup: the slabs of co-resident workgroups (a launch no
+// larger than the GPU holds at once), or, with `tile`, tiles: launch `launch` of
+// an advance reads one state buffer and writes the other, `sx` steps each.
+template <int Q, int D, int P, typename T, typename A, bool Wide>
+__global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_per_eu(Wide ? 2 : 4))) void k_seg(
+    const DevSeg* __restrict__ segs, int nodes, int s_per, int sx, int tile, int launch, void* __restrict__ xbuf,
+    int* __restrict__ flags, const DevCoef* __restrict__ coefs, int* __restrict__ status, long long wait_ticks,
+    int mute_seg) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int me = blockIdx.x;
+  DevSeg sg = segs[me];
+  int steps = sg.steps;
+  if (tile) {
+    steps -= launch * sx;
+    if (steps <= 0) return;
+    if (steps > sx) steps = sx;
+    if (launch & 1) {
+      const uint64_t t = sg.in;
+      sg.in = sg.out;
+      sg.out = t;
+    }
+  }
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const SegLinks lk{sx, xbuf, flags, me, me == mute_seg, wait_ticks};
+  reg_widths<Q, kSegSlab, D, P, T, A, Wide, 0>(nodes, reinterpret_cast<T*>(smem_raw), steps, s_per, sg, w, w < sg.waves,
+                                               coefs + sg.inst, status, lk);
 }
 
 // Persistent kernel over the parts of jobs (a job: ring segments of one variant
@@ -443,7 +616,7 @@ __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_p
       if (act) sg = segs[jb.first + mine];
       const DevCoef* cf = coefs + (act ? sg.inst : 0);
       const int w = wave - sg.w0;
-      reg_widths<Q, D, P, T, A, Wide, 0>(jb.nodes, L, it.steps, jb.s_per, sg, w, act, cf, status);
+      reg_widths<Q, kSegRing, D, P, T, A, Wide, 0>(jb.nodes, L, it.steps, jb.s_per, sg, w, act, cf, status, SegLinks{});
       __syncthreads();   // strips are read before the next item's are written
       if (it.more) {
         __threadfence();   // this thread's write-back is visible to every CU

@@ -122,6 +122,9 @@ struct lbm_batch_s {
   DevJob* jobs_host = nullptr;
   DevSeg* segs = nullptr;             // register-resident segments: two slots of items_cap records
   DevSeg* segs_host = nullptr;
+  DevSeg* xsegs = nullptr;            // slabs and tiles of the register path: two slots of xsegs_cap
+  DevSeg* xsegs_host = nullptr;
+  int xsegs_cap = 0;
   DevItem* parts = nullptr;           // queue items of the register launches: two slots of parts_cap
   DevItem* parts_host = nullptr;
   int parts_cap = 0;
@@ -275,6 +278,8 @@ void destroy_batch(lbm_batch_s* b) {
   if (b->segs_host) hipHostFree(b->segs_host);
   hipFree(b->parts);
   if (b->parts_host) hipHostFree(b->parts_host);
+  hipFree(b->xsegs);
+  if (b->xsegs_host) hipHostFree(b->xsegs_host);
   for (int k = 0; k < 2; ++k)
     if (b->items_done[k]) hipEventDestroy(b->items_done[k]);
   hipFree(b->scratch);
@@ -462,6 +467,9 @@ double* f64_cur(lbm_batch_s* b, const HostInst& h) { return b->f64[h.cur] + h.of
 float* f32_cur(lbm_batch_s* b, const HostInst& h) { return b->f32[h.cur] + h.off; }
 void* state_cur(lbm_batch_s* b, const HostInst& h) {
   return h.f32 ? (void*)f32_cur(b, h) : (void*)f64_cur(b, h);
+}
+void* state_at(lbm_batch_s* b, const HostInst& h, int buf) {
+  return h.f32 ? (void*)(b->f32[buf] + h.off) : (void*)(b->f64[buf] + h.off);
 }
 void* state_other(lbm_batch_s* b, const HostInst& h) {
   return h.f32 ? (void*)(b->f32[1 - h.cur] + h.off) : (void*)(b->f64[1 - h.cur] + h.off);
@@ -717,8 +725,8 @@ struct RegFit {
   double cost = 0.0;   // of one wave and step, in VALU operations
 };
 int reg_halo(int q, int R, int s) { return (s * (q / 2) + R - 1) / R; }
-// elements of one wave's exchange strips in LDS
-int reg_strip(int q, int R, int s) { return 4 * (reg_halo(q, R, s) + 1) * R * q; }
+// LDS elements of one wave: its exchange strips, or a row of its nodes
+int reg_strip(int q, int R, int s) { return std::max(4 * (reg_halo(q, R, s) + 1) * R * q, 64 * R); }
 void reg_place(int q, int n, RegFit* f) {
   const int hl = reg_halo(q, f->R, f->s), least = 2 * (hl + 1), cap = 64 - 2 * hl;
   const int periods = std::max(1, (least * f->R + n - 1) / n);
@@ -764,13 +772,108 @@ int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
   }
   return count;
 }
+
+// Slabs and tiles of the register path: an instance cut into segments of about
+// equal lanes, one workgroup each, whose ends stay exact for sx steps.
+struct SegPlan {
+  RegFit f;
+  int sx = 0;          // steps between exchanges with the neighbours, or of a tile's launch
+  int extra = 0;       // outer halo lanes beside a wave's own
+  int most = 0;        // owned lanes of a segment, at most
+  int waves = 0;       // of the largest segment
+  int per_cu = 1;      // workgroups a CU is meant to hold
+  double est = 0.0;    // of a step of the whole group, in VALU operations of a wave
+};
+// An exchange between workgroups, in VALU operations of a wave (about 1.67 ns):
+// 2.5 us, and 2.2 us more for each further workgroup that shares the CU
+// (2000-step batches of 128 KS and 96 Kawahara grids, 1 to 6 a CU).
+constexpr double kLinkCost = 1500.0, kLinkShare = 1300.0;
+// Segments of an instance of n nodes; 0: they cannot be cut as planned.  A
+// slab's outer owned lanes, which its neighbour reads, lie in its first and
+// last wave, and a wave's strips apart; a tile only needs the latter.
+int seg_count(const SegPlan& p, int q, int n, bool tile) {
+  const int hl = reg_halo(q, p.f.R, p.f.s), cap = 64 - 2 * hl, hg = hl + p.extra;
+  const int all = (n + p.f.R - 1) / p.f.R, k = (all + p.most - 1) / p.most;
+  const int lanes = all / k + 2 * p.extra, waves = (lanes + cap - 1) / cap;   // of the smallest
+  if (waves > 1 && lanes / waves < 2 * (hl + 1)) return 0;
+  if (tile) return k;
+  if (waves == 1 ? all / k < 2 * (hg + 1) : lanes / waves < p.extra + hg + 1) return 0;
+  // the largest may take a wave more
+  const int top = (all + k - 1) / k + 2 * p.extra, more = (top + cap - 1) / cap;
+  return top / more < p.extra + hg + 1 || top / more < 2 * (hl + 1) ? 0 : k;
+}
+// The cheapest plan of a group (sizes: node count, instances of it) on `cus`
+// CUs.  A step costs the waves that share a SIMD their operations (1.25 and 1.05
+// times for one and two waves, as for whole instances), and 1/sx of an exchange
+// or of a tile's way from and to HBM.
+// `want`: steps asked for (0: free); `wgs`: workgroups per CU asked for (0: free).
+bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cus, int want, int wgs, bool tile,
+              SegPlan* out) {
+  const int H = q / 2;
+  int64_t nodes = 0;
+  for (const auto& [n, times] : sizes) nodes += (int64_t)n * times;
+  bool found = false;
+  for (int cls = 0; cls < 2; ++cls) {
+    RegFit menu[kRegWidths + 1];
+    const int widths = reg_menu(q, prec, code, cls != 0, menu), full = reg_waves(cls != 0);
+    for (int k = 0; k < widths; ++k)
+      for (int pick = 0; pick < 4; ++pick) {
+        SegPlan p;
+        p.f = menu[k];
+        if (want > 0) {
+          if (pick > 0) break;
+          while (p.f.s > 2 && want % p.f.s != 0) p.f.s -= 2;
+          p.sx = want;
+        } else {
+          p.sx = ((8 << pick) + p.f.s - 1) / p.f.s * p.f.s;
+        }
+        const int hl = reg_halo(q, p.f.R, p.f.s), cap = 64 - 2 * hl;
+        p.extra = std::max(0, (p.sx * H + p.f.R - 1) / p.f.R - hl);
+        for (int w = 1; w <= (wgs > 0 ? std::max(1, full / wgs) : full); w = w < 4 ? w + 1 : w + 2) {
+          p.waves = w;
+          p.most = w * cap - 2 * p.extra;
+          if (p.most < 1) continue;
+          const int hold = full / w;   // workgroups a CU holds
+          auto price = [&](int64_t total) {
+            p.per_cu = (int)std::min<int64_t>(hold, (total + cus - 1) / cus);
+            const int per_simd = (p.per_cu * w + 3) / 4;
+            const double slow = per_simd == 1 ? 1.25 : per_simd == 2 ? 1.05 : 1.0;
+            const double rounds = std::max(1.0, (double)total / ((double)p.per_cu * cus));
+            const double link = tile ? 3000.0 + 0.4 * (p.per_cu * p.most * p.f.R) * q
+                                     : kLinkCost + kLinkShare * (p.per_cu - 1) + (prec != 0 ? 2.0 : 5.0) * p.f.R * q;
+            p.est = (tile ? std::ceil(rounds) : rounds > 1.0 ? 1.05 * rounds : 1.0) *
+                    (slow * per_simd * p.f.cost + link / p.sx);
+          };
+          price(std::max<int64_t>(1, nodes / ((int64_t)p.most * p.f.R)));   // as few segments as there can be
+          if (found && p.est >= out->est) continue;
+          int64_t total = 0;
+          bool ok = true;
+          for (const auto& [n, times] : sizes) {
+            const int c = seg_count(p, q, n, tile);
+            ok = c > 0 && (tile || c <= cus);
+            if (!ok) break;
+            total += (int64_t)c * times;
+          }
+          if (!ok) continue;
+          price(total);
+          if (!found || p.est < out->est) {
+            *out = p;
+            found = true;
+          }
+        }
+      }
+  }
+  return found;
+}
+
 // One pass: every instance advances by steps[i] <= kMaxStepsPerLaunch.
 lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const int count = (int)b->inst.size();
   // resident groups by (q, precision, variant); the rest streams through HBM
   // (q, prec, variant code, bounded)
   std::map<std::tuple<int, int, int, int>, std::vector<int>> res;
-  std::map<std::tuple<int, int, int>, std::vector<int>> reg;   // register-resident, by (q, prec, variant)
+  // register-resident, by (q, prec, variant): whole instances, slabs, tiles
+  std::map<std::tuple<int, int, int>, std::vector<int>> reg, spread, rtile;
   std::vector<int> str;          // one launch per step (the plain path)
   std::vector<int> til[8][3];    // temporal blocking, by (q, prec)
   // slabs, by (q, prec, variant, workgroups per CU)
@@ -806,11 +909,15 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     if (b->path == 2 && !fits) return LBM_ERR_UNSUPPORTED;
     if (b->path == 1)
       str.push_back(i);
+    else if (b->path == 3 && in_reg)
+      rtile[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else if (b->path == 3)
       til[h.q][h.prec].push_back(i);
+    else if (in_reg && (b->path == 4 || !fits || (latency && h.n >= kSplitNodes)))
+      spread[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else if (b->path == 4 || !fits)
       slb[std::make_tuple(h.q, h.prec, h.D, slab_wgs)].push_back(i);
-    else if (latency && h.n >= kSplitNodes)
+    else if (!in_reg && latency && h.n >= kSplitNodes)
       slb[std::make_tuple(h.q, h.prec, h.D, 8)].push_back(i);
     else if (in_reg)
       reg[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
@@ -998,6 +1105,191 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     group_work.push_back(w * (std::get<0>(group.first) * (D + 3)));
     reg_work += group_work.back();
   }
+  // Slabs and tiles.  Every group takes its share of the CUs, so that the
+  // launches run side by side; where one needs more workgroups than that at
+  // once, the launches run one after another, each over the whole GPU.  What
+  // cannot be cut into that many slabs is advanced tile by tile.
+  struct SegLaunch { int q; int prec; int code; SegPlan p; bool tile; int first, count, launches; size_t lds, xoff; int foff; double est; };
+  std::vector<SegLaunch> segs;
+  std::vector<DevSeg> xsv;
+  std::vector<std::pair<int, int>> flips;   // (instance, buffer exchanges)
+  size_t xbuf_need = 0;
+  int flags_need = 0;
+  int slab_cus = 0;        // workgroups of all slab launches
+  double spread_work = 0.0;
+  auto work_of = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g) {
+    double w = 0.0;
+    for (int i : g) w += (double)steps[i] * b->inst[i].n;
+    return w * (std::get<0>(key) * ((std::get<2>(key) & 0xff) + 3));
+  };
+  for (const auto& group : spread) spread_work += work_of(group.first, group.second);
+  const double spread_all = std::max(1.0, reg_work + spread_work);
+  // one group's launches: rounds of slabs (at most `cus` workgroups' places each), or tiles
+  auto add_segs = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g, const SegPlan& p, int cus,
+                      bool tile) -> lbm_status {
+    const int q = std::get<0>(key), pr = std::get<1>(key), code = std::get<2>(key), R = p.f.R;
+    const size_t es = pr != 0 ? 4 : 8;
+    const int hg = reg_halo(q, R, p.f.s) + p.extra;
+    SegLaunch L{q, pr, code, p, tile, (int)xsv.size(), 0, 1, (size_t)p.waves * reg_strip(q, R, p.f.s) * es, 0, 0, 0.0};
+    int per_cu = 0;
+    LBM_HIP(seg_occupancy(q, pr, code, p.f.wide, 64 * p.waves, L.lds, &per_cu));
+    if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
+    const int64_t capacity = (int64_t)std::min(per_cu, p.per_cu) * cus;
+    int64_t total = 0, maxsteps = 0;
+    for (int i : g) {
+      total += seg_count(p, q, b->inst[i].n, tile);
+      maxsteps = std::max<int64_t>(maxsteps, steps[i]);
+    }
+    // More slabs than a launch holds: the steps are cut into chunks, whose
+    // (instance, chunk) items fill the launches evenly in chunk order; an
+    // instance's chunk c + 1 always lies in a later launch than its chunk c.
+    // c chunks cost (launches of c chunks) / c: the fewest within 3% of the
+    // cheapest, each of kMinSlabChunk steps or more.
+    int nch = 1;
+    int64_t share = capacity;
+    if (!tile && total > capacity) {
+      auto launches_for = [&](int c) { return (total * c + capacity - 1) / capacity; };
+      double least = 1e30;
+      for (int c = 1; c <= 8 && (c == 1 || maxsteps / c >= kMinSlabChunk); ++c) {
+        const double cost = (double)launches_for(c) / c;
+        if (cost < 0.97 * least) {
+          least = cost;
+          nch = c;
+        }
+      }
+      share = (total * nch + launches_for(nch) - 1) / launches_for(nch);
+    }
+    auto close = [&] {
+      if (L.count == 0) return;
+      if (!tile) {
+        L.xoff = xbuf_need;
+        L.foff = flags_need;
+        xbuf_need += ((size_t)L.count * 4 * (hg + 1) * R * q * es + 255) / 256 * 256;
+        flags_need += 2 * L.count;
+        slab_cus += L.count;
+      }
+      segs.push_back(L);
+      L.first = (int)xsv.size();
+      L.count = 0;
+      L.est = 0.0;
+    };
+    const int wave_nodes = (p.per_cu * p.waves + 3) / 4;
+    for (int c = 0; c < nch; ++c)
+      for (int i : g) {
+        const HostInst& h = b->inst[i];
+        const int64_t st = steps[i] / nch + (c < steps[i] % nch ? 1 : 0);
+        if (st == 0) continue;
+        const int ks = seg_count(p, q, h.n, tile), all = (h.n + R - 1) / R;
+        if (!tile && (L.count + ks > capacity || L.count >= share)) close();
+        L.est = std::max(L.est, (double)st * wave_nodes * p.f.cost);
+        const int from = h.cur ^ (c & 1);   // each earlier chunk flipped the buffer once
+        for (int m = 0; m < ks; ++m) {
+          const int l0 = (int)((int64_t)all * m / ks), l1 = (int)((int64_t)all * (m + 1) / ks);
+          DevSeg sg{};
+          sg.in = (uint64_t)(uintptr_t)state_at(b, h, from);
+          sg.out = (uint64_t)(uintptr_t)state_at(b, h, 1 - from);
+          sg.n = h.n;
+          sg.stride = h.stride;
+          sg.inst = i;
+          sg.x0 = l0 * R;
+          sg.len = std::min(l1 * R, h.n) - sg.x0;
+          sg.lanes = l1 - l0 + 2 * p.extra;
+          sg.extra = p.extra;
+          sg.over = m + 1 == ks ? all * R - h.n : 0;
+          sg.over_left = m == 0 ? all * R - h.n : 0;
+          const int cap = 64 - 2 * reg_halo(q, R, p.f.s);
+          sg.waves = (sg.lanes + cap - 1) / cap;
+          sg.steps = (int)st;
+          sg.left = L.count + (m + ks - 1) % ks;
+          sg.right = L.count + (m + 1) % ks;
+          xsv.push_back(sg);
+        }
+        L.count += ks;
+        const int turns = tile ? (int)((st + p.sx - 1) / p.sx) : 1;
+        L.launches = std::max(L.launches, turns);
+        flips.push_back({i, turns});
+      }
+    close();
+    return LBM_OK;
+  };
+  if (!spread.empty() || !rtile.empty()) {
+    const int slab_steps = b->tile_steps > 0 ? (b->tile_steps + 1) / 2 * 2 : 0;   // even: strips in natural layout
+    auto sizes_of = [&](const std::vector<int>& g) {
+      std::map<int, int> sizes;
+      for (int i : g) ++sizes[b->inst[i].n];
+      return sizes;
+    };
+    auto plan = [&](const std::tuple<int, int, int>& key, const std::map<int, int>& sizes, int cus, int want, bool tile,
+                    SegPlan* p) {
+      return seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile, p);
+    };
+    // what no slab plan takes goes by tiles
+    std::vector<SegPlan> plans;     // over the whole GPU, then those taken
+    std::vector<int> places;
+    for (auto it = spread.begin(); it != spread.end();) {
+      const auto& key = it->first;
+      std::vector<int>& g = it->second;
+      SegPlan p;
+      if (!plan(key, sizes_of(g), b->lim.cus, slab_steps, false, &p)) {
+        std::map<int, bool> cuts;
+        for (int i : g) {
+          const int n = b->inst[i].n;
+          if (!cuts.count(n)) cuts[n] = plan(key, {{n, 1}}, b->lim.cus, slab_steps, false, &p);
+        }
+        std::vector<int> keep;
+        for (int i : g) {
+          if (cuts[b->inst[i].n])
+            keep.push_back(i);
+          else
+            rtile[key].push_back(i);
+        }
+        g.swap(keep);
+        if (!g.empty() && !plan(key, sizes_of(g), b->lim.cus, slab_steps, false, &p)) {
+          for (int i : g) rtile[key].push_back(i);
+          g.clear();
+        }
+      }
+      if (!g.empty()) plans.push_back(p);
+      places.push_back(b->lim.cus);
+      it = g.empty() ? spread.erase(it) : std::next(it);
+    }
+    places.resize(plans.size());
+    for (const auto* part : {&spread, &rtile})
+      for (const auto& group : *part) {
+        lbm_status st = ensure_second_buffer(b, std::get<1>(group.first) != 0);
+        if (st != LBM_OK) return st;
+      }
+    if (spread.size() > 1) {   // by share, if each fits its share at once
+      std::vector<SegPlan> shared;
+      std::vector<int> cus;
+      bool once = true;
+      for (const auto& [key, g] : spread) {
+        SegPlan p;
+        cus.push_back(std::max(1, (int)(b->lim.cus * work_of(key, g) / spread_all)));
+        once = once && plan(key, sizes_of(g), cus.back(), slab_steps, false, &p);
+        int64_t total = 0;
+        for (size_t u = 0; u < g.size() && once; ++u) total += seg_count(p, std::get<0>(key), b->inst[g[u]].n, false);
+        once = once && total <= cus.back();
+        shared.push_back(p);
+      }
+      if (once) {
+        plans.swap(shared);
+        places.swap(cus);
+      }
+    }
+    size_t at = 0;
+    for (const auto& [key, g] : spread) {
+      lbm_status st = add_segs(key, g, plans[at], places[at], false);
+      if (st != LBM_OK) return st;
+      ++at;
+    }
+    for (const auto& [key, g] : rtile) {
+      SegPlan p;
+      if (!plan(key, sizes_of(g), b->lim.cus, b->tile_steps, true, &p)) return LBM_ERR_UNSUPPORTED;
+      lbm_status st = add_segs(key, g, p, b->lim.cus, true);
+      if (st != LBM_OK) return st;
+    }
+  }
   std::vector<double> reg_job_est;
   double reg_est = 0.0;    // estimated CU time of all register launches
   int64_t reg_jobs = 0;
@@ -1007,7 +1299,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     const std::vector<int>& g = group.second;
     const int es = pr != 0 ? 4 : 8;
     // the CUs that are this group's by its share of the pass's work
-    const double cus = std::max(1.0, b->lim.cus * group_work[gi++] / std::max(1.0, reg_work));
+    const double cus = std::max(1.0, b->lim.cus * group_work[gi++] / spread_all);
     // Nodes per lane: few spend more on halos and lane edges, many leave more of
     // an instance's last lanes empty and give fewer waves to share the SIMDs.
     // Each instance takes the width with the least wave time among one kernel's
@@ -1238,10 +1530,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   struct SlabLaunch { int q; int prec; int code; int first, count, cap, s, halo, block; size_t lds; size_t xoff; int foff; double est; };
   std::vector<SlabLaunch> slaunch;
   std::vector<DevSlab> svec;
-  size_t xbuf_need = 0;
-  int flags_need = 0;
   int min_per_cu = 1 << 30;
   const int tin_slab0 = tin_used;
+  const size_t xbuf_segs = xbuf_need;
+  const int flags_segs = flags_need;
   std::vector<int> slab_insts;
   for (const auto& group : slb) {
     {
@@ -1382,7 +1674,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     total_slabs += S.count;
     total_cap += S.cap;
   }
-  bool slab_side_by_side = slaunch.size() > 1 && 2 * total_slabs <= (int64_t)min_per_cu * b->lim.cus;
+  bool slab_side_by_side =
+      segs.empty() && slaunch.size() > 1 && 2 * total_slabs <= (int64_t)min_per_cu * b->lim.cus;
   // A small pass (a serving round) whose slab launches would run one after
   // another, each less than half full on average, is bound by that sequence of
   // mostly idle launches; temporal blocking has no co-residency condition, so
@@ -1394,14 +1687,27 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     htin.resize(tin_slab0);
     svec.clear();
     slaunch.clear();
-    xbuf_need = 0;
-    flags_need = 0;
+    xbuf_need = xbuf_segs;
+    flags_need = flags_segs;
     slab_side_by_side = false;
   }
-  if (!svec.empty()) {
-    if ((int)svec.size() > b->slabs_cap || xbuf_need > b->xbuf_bytes || flags_need > b->sflags_cap) {
+  if (!svec.empty() || !xsv.empty()) {
+    if ((int)svec.size() > b->slabs_cap || xbuf_need > b->xbuf_bytes || flags_need > b->sflags_cap ||
+        (int)xsv.size() > b->xsegs_cap) {
       // grow the slab tables and exchange buffers; earlier passes must be done with them
       LBM_HIP(hipStreamSynchronize(b->stream));
+      if ((int)xsv.size() > b->xsegs_cap) {
+        hipFree(b->xsegs);
+        if (b->xsegs_host) hipHostFree(b->xsegs_host);
+        b->xsegs = nullptr;
+        b->xsegs_host = nullptr;
+        b->xsegs_cap = 0;
+        const int cap = (int)xsv.size() * 2;
+        if (hipMalloc(&b->xsegs, sizeof(DevSeg) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+        if (hipHostMalloc((void**)&b->xsegs_host, sizeof(DevSeg) * 2 * cap, hipHostMallocDefault) != hipSuccess)
+          return LBM_ERR_OUT_OF_MEMORY;
+        b->xsegs_cap = cap;
+      }
       if ((int)svec.size() > b->slabs_cap) {
         hipFree(b->slabs);
         if (b->slabs_host) hipHostFree(b->slabs_host);
@@ -1429,7 +1735,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         b->sflags_cap = flags_need;
       }
     }
-    std::memcpy(b->slabs_host + (size_t)k * b->slabs_cap, svec.data(), sizeof(DevSlab) * svec.size());
+    if (!xsv.empty())
+      std::memcpy(b->xsegs_host + (size_t)k * b->xsegs_cap, xsv.data(), sizeof(DevSeg) * xsv.size());
+    if (!svec.empty())
+      std::memcpy(b->slabs_host + (size_t)k * b->slabs_cap, svec.data(), sizeof(DevSlab) * svec.size());
     for (const auto& group : slb) {
       lbm_status st = ensure_second_buffer(b, std::get<1>(group.first) != 0);
       if (st != LBM_OK) return st;
@@ -1520,6 +1829,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     LBM_HIP(hipMemcpyAsync(dt, b->tiles_host + (size_t)k * b->tiles_cap, sizeof(DevTile) * tvec.size(),
                            hipMemcpyHostToDevice, b->stream));
   }
+  DevSeg* dxsegs = b->xsegs + (size_t)k * b->xsegs_cap;
+  if (!xsv.empty())
+    LBM_HIP(hipMemcpyAsync(dxsegs, b->xsegs_host + (size_t)k * b->xsegs_cap, sizeof(DevSeg) * xsv.size(),
+                           hipMemcpyHostToDevice, b->stream));
   if (!svec.empty()) {
     DevSlab* ds = b->slabs + (size_t)k * b->slabs_cap;
     LBM_HIP(hipMemcpyAsync(ds, b->slabs_host + (size_t)k * b->slabs_cap, sizeof(DevSlab) * svec.size(),
@@ -1576,8 +1889,23 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // workgroups all get CUs once those kernels retire; two slab launches side
   // by side could each hold CUs the other waits for, so they share a lane, in
   // order, unless all of them fit the GPU twice over
-  struct LaneItem { int kind; int idx; double est; };   // kind 0 resident, 1 tiled, 2 slab (-1: the chain)
+  // (register slabs plan a place for every workgroup: side by side as long as
+  // there is a CU for each of all their workgroups -- one that waits for a place
+  // then has an empty CU, or a CU whose kernel waits for no slab)
+  // kind 0 resident, 1 tiled, 2 slab (-1: the chain), 3 register slab or tile
+  struct LaneItem { int kind; int idx; double est; };
   std::vector<LaneItem> items;
+  const bool segs_side_by_side = slaunch.empty() && slab_cus <= b->lim.cus;
+  double chain_est = 0.0;
+  bool chain = false;
+  for (size_t l = 0; l < segs.size(); ++l) {
+    if (segs[l].tile || segs_side_by_side) {
+      items.push_back({3, (int)l, segs[l].est});
+    } else {
+      chain_est += segs[l].est;
+      chain = true;
+    }
+  }
   for (size_t l = 0; l < launches.size(); ++l) {
     const Launch& L = launches[l];
     items.push_back({0, (int)l, std::max(L.est_max, L.est_sum / b->lim.cus)});
@@ -1586,16 +1914,17 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   if (slab_side_by_side) {
     for (size_t l = 0; l < slaunch.size(); ++l) items.push_back({2, (int)l, slaunch[l].est});
   } else if (!slaunch.empty()) {
-    double est = 0.0;
-    for (const SlabLaunch& S : slaunch) est += S.est;
-    items.push_back({2, -1, est});
+    for (const SlabLaunch& S : slaunch) chain_est += S.est;
+    chain = true;
   }
+  if (chain) items.push_back({2, -1, chain_est});
   const bool fork = items.size() > 1;
   const int nlanes = std::min<int>((int)items.size(), b->lanes > 0 ? b->lanes : hw_lanes());
   if ((int)items.size() > nlanes)
     std::stable_sort(items.begin(), items.end(), [](const LaneItem& x, const LaneItem& y) { return x.est > y.est; });
   std::vector<double> lane_load(nlanes, 0.0);
   std::vector<char> lane_forked(nlanes, 0);
+  if (!segs.empty() && flags_need > 0) LBM_HIP(hipMemsetAsync(b->sflags, 0, sizeof(int) * flags_need, b->stream));
   if (fork) LBM_HIP(hipEventRecord(b->fork, b->stream));
   const DevSlab* ds = b->slabs + (size_t)k * b->slabs_cap;
   const DevTileInst* dti_all = b->tinsts + (size_t)k * b->tinsts_cap;
@@ -1609,6 +1938,17 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     LBM_HIP(launch_slab(L.q, L.prec, L.code, ds + L.first, L.count, dti_all, b0, b1, L.s, L.halo,
                         (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.s), mute,
                         L.block, L.lds, st));
+    return LBM_OK;
+  };
+  auto issue_seg = [&](size_t l, hipStream_t st) -> lbm_status {
+    const SegLaunch& L = segs[l];
+    int* flags = b->sflags + L.foff;
+    // (the flags of all a pass's slab launches are cleared before the fork)
+    const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
+    for (int r = 0; r < L.launches; ++r)
+      LBM_HIP(launch_seg(L.q, L.prec, L.code, L.p.f.wide, dxsegs + L.first, L.count, L.p.f.R, L.p.f.s, L.p.sx, L.tile, r,
+                         (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.p.sx), mute,
+                         64 * L.p.waves, L.lds, st));
     return LBM_OK;
   };
   for (size_t ii = 0; ii < items.size(); ++ii) {
@@ -1670,16 +2010,25 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         const int L = (int)((htin[t].steps + G.s - 1) / G.s);
         h.cur = htin[t].cur0 ^ (L & 1);
       }
+    } else if (it.kind == 3) {
+      lbm_status s = issue_seg((size_t)it.idx, st);
+      if (s != LBM_OK) return s;
     } else if (it.idx >= 0) {
       lbm_status s = issue_slab((size_t)it.idx, st);
       if (s != LBM_OK) return s;
     } else {
+      for (size_t l = 0; l < segs.size(); ++l) {
+        if (segs[l].tile || segs_side_by_side) continue;
+        lbm_status s = issue_seg(l, st);
+        if (s != LBM_OK) return s;
+      }
       for (size_t l = 0; l < slaunch.size(); ++l) {
         lbm_status s = issue_slab(l, st);
         if (s != LBM_OK) return s;
       }
     }
   }
+  for (const auto& [i, turns] : flips) b->inst[i].cur ^= turns & 1;
   if (!slaunch.empty())
     for (const DevSlab& sl : svec)
       if (sl.x0 == 0) b->inst[htin[sl.ti].inst].cur ^= 1;   // one flip per instance: output in the other buffer

@@ -94,3 +94,46 @@ def test_split_jobs_equal_solo(prec, lo, hi, count):
             want = _run(ps[k], phis[k], (steps[k], steps[k] // 2), lbm.PATH_STREAM)
             assert np.array_equal(got, want), (k, ns[k])
     b.close()
+
+
+# Slabs (one per workgroup) and tiles of instances beyond one workgroup, at the planner's own choice and
+# with it forced narrow and wide: 1031..9973: node counts that leave a part of the last lane; steps: fewer
+# than an exchange, odd, several exchanges (an odd number of tile launches), a call that ends on one.
+@pytest.mark.parametrize("n", [1031, 4099, 9973])
+@pytest.mark.parametrize("kind", ["kdv", "mkdv", "d1q4", "d1q6", "kawahara", "m6"])
+@pytest.mark.parametrize("prec", [W.F64, W.F32_DEV, W.F32_DEV_ARITH32])
+def test_slabs_and_tiles_equal_stream(kind, n, prec):
+    p, phi0 = _problem(kind, n, prec)
+    steps = (1, 2, 83, 64)
+    say("case segments", kind, n, prec)
+    want = _run(p, phi0, steps, lbm.PATH_STREAM)
+    for path in (lbm.PATH_SLAB, lbm.PATH_TILED):
+        for tiling in ((0, 0), (6, 1), (24, 8), (3, 2)):
+            s = lbm.Solver(p)
+            s.set_path(path)
+            s.set_tiling(*tiling)
+            s.load_phi(phi0)
+            for k in steps:
+                s.advance(k)
+            got = s.read_phi()
+            s.close()
+            assert np.array_equal(got, want), (path, tiling)
+
+
+def test_mixed_batch_of_slabs_tiles_and_rings_equals_solo():
+    """Groups of several variants and precisions that need more workgroups than
+    the GPU has CUs: their slab launches run one after another, in step chunks."""
+    kinds = [("kdv", 20011, W.F64), ("mkdv", 9001, W.F32_DEV), ("kawahara", 12007, W.F64), ("kdv", 301, W.F64)]
+    ps, phis = zip(*[_problem(*kinds[i % 4][:2], kinds[i % 4][2]) for i in range(240)])
+    steps = [600 + i % 3 for i in range(240)]
+    say("case mixed segments")
+    b = lbm.Batch(list(ps))
+    b.load_phi(list(phis))
+    b.advance(steps)
+    b.advance([37] * 240)
+    for k in range(240):
+        got, st = b.read_phi(k)
+        assert st == lbm.OK, k
+        if k < 12 or k > 235:
+            assert np.array_equal(got, _run(ps[k], phis[k], (steps[k], 37), lbm.PATH_STREAM)), k
+    b.close()
