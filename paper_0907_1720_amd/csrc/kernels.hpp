@@ -141,9 +141,11 @@ int resident_vgprs(int q, int prec, int code);
 // static LDS bytes of the resident kernel (0 by construction)
 size_t resident_static_lds(int q, int prec, int code);
 // phi = sum_j f_j into device or pinned host memory; words[0] := *status,
-// words[1] := 1 if any value is not finite (left alone otherwise)
+// words[1] := 1 if any value is not finite (left alone otherwise).  With
+// `arrived` (0, and 0 again after) words[2] := seq at system scope once all of it
+// is there.
 hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                       const int* status, int* words, hipStream_t s);
+                       const int* status, int* words, int* arrived, int seq, hipStream_t s);
 hipError_t launch_sum(const double* v, int n, double* part, int nparts, hipStream_t s);
 hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, int* blocks_per_cu);
 // lbm_advance_noalloc: the fixed per-device scratch (tables at offset 0, the
