@@ -233,7 +233,7 @@ hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t
 }
 
 hipError_t launch_seg(int q, int prec, int code, bool wide, const DevSeg* segs, int nsegs, int nodes, int s_per, int sx,
-                      bool tile, int launch, void* xbuf, int* flags, const DevCoef* coefs, int* status,
+                      bool tile, int launch, void* xbuf, unsigned tag, const DevCoef* coefs, int* status,
                       long long wait_ticks, int mute_seg, int block, size_t lds, hipStream_t s) {
   const void* fn = reg_or_seg(true, q, prec, code, wide);
   if (!fn) return hipErrorInvalidValue;
@@ -241,7 +241,7 @@ hipError_t launch_seg(int q, int prec, int code, bool wide, const DevSeg* segs, 
   if (e != hipSuccess) return e;
   int as_tile = tile ? 1 : 0;
   void* args[] = {(void*)&segs, (void*)&nodes, (void*)&s_per, (void*)&sx,     (void*)&as_tile,    (void*)&launch,
-                  (void*)&xbuf, (void*)&flags, (void*)&coefs, (void*)&status, (void*)&wait_ticks, (void*)&mute_seg};
+                  (void*)&xbuf, (void*)&tag,   (void*)&coefs, (void*)&status, (void*)&wait_ticks, (void*)&mute_seg};
   return hipLaunchKernel(fn, dim3(nsegs), dim3(block), args, lds, s);
 }
 

@@ -110,16 +110,26 @@ hipError_t launch_resident(int q, int prec, int code, const DevJob* jobs, const 
 // large tables, which few problems use, are built for fewer widths.)
 constexpr int kRegWidths = 6;
 constexpr int reg_width(int q, int elem, int degree, int parity, bool wide, int i) {
-  constexpr int w[8][2][kRegWidths] = {{{2, 3, 5, 6}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP64
-                                       {{2, 3, 4}, {3, 4, 6, 8}},                // D1Q6 / D1Q7, FP64
-                                       {{2, 3, 5, 8}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP32 storage
-                                       {{2, 3, 6}, {3, 6, 8, 10, 12}},           // D1Q6 / D1Q7, FP32 storage
-                                       {{3, 6}, {6, 10, 17}},                    // the same, large tables
-                                       {{2, 4}, {4, 8}},
-                                       {{3, 6}, {6, 10, 17}},
-                                       {{2, 4}, {4, 8, 12}}};
+  constexpr int w[8][2][kRegWidths] = {{{1, 2, 3, 5, 6}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP64
+                                       {{2, 3, 4}, {1, 2, 3, 4, 6, 8}},             // D1Q6 / D1Q7, FP64
+                                       {{1, 2, 3, 5, 8}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP32 storage
+                                       {{2, 3, 6}, {1, 3, 6, 8, 10, 12}},           // D1Q6 / D1Q7, FP32 storage
+                                       {{3, 6}, {1, 6, 10, 17}},                    // the same, large tables
+                                       {{2, 4}, {1, 4, 8}},
+                                       {{3, 6}, {1, 6, 10, 17}},
+                                       {{2, 4}, {1, 4, 8, 12}}};
   const bool large = parity == 0 ? degree >= 9 : degree >= 13;
   return w[(large ? 4 : 0) + (elem == 8 ? 0 : 2) + (q >= 6 ? 1 : 0)][wide ? 1 : 0][i];
+}
+// coefficients per population; whether those below the leading one fit the scalar
+// registers; or else, with few nodes per lane, the vector registers of a wide kernel
+constexpr int reg_coefs(int degree, int parity) { return parity == 0 ? degree + 1 : (degree + 1) / 2; }
+constexpr bool reg_pinned(int q, int degree, int parity, int arith) {
+  return q * (reg_coefs(degree, parity) - 1) * arith / 4 <= 52;
+}
+constexpr bool reg_held(int q, int degree, int parity, int elem, int arith, bool wide, int R) {
+  return wide && R <= 2 && !reg_pinned(q, degree, parity, arith) &&
+         q * (reg_coefs(degree, parity) * arith + R * (elem + arith)) / 4 <= 224;
 }
 constexpr int reg_waves(bool wide) { return wide ? 8 : 16; }   // most waves of a workgroup: a CU's
 inline bool reg_variant(int code) { return ((code >> 8) & 0xff) < 2; }
@@ -130,10 +140,11 @@ hipError_t launch_reg(int q, int prec, int code, bool wide, const DevItem* items
                       long long wait_ticks, int stall_item, int grid, int block, size_t lds, hipStream_t s);
 hipError_t reg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu);
 // one segment per workgroup (polynomial variants): slabs of one launch, or tiles
-// (`launch`-th block of sx steps); flags[2 nsegs] start at 0; xbuf holds 4 (hg +
-// 1) R q values per segment; segment mute_seg (-1: none) never raises its flags
+// (`launch`-th block of sx steps); xbuf holds 4 (hg + 1) R q words per
+// segment for each 32 bits of a value, none of them tagged `tag` or above;
+// segment mute_seg (-1: none) never publishes
 hipError_t launch_seg(int q, int prec, int code, bool wide, const DevSeg* segs, int nsegs, int nodes, int s_per, int sx,
-                      bool tile, int launch, void* xbuf, int* flags, const DevCoef* coefs, int* status,
+                      bool tile, int launch, void* xbuf, unsigned tag, const DevCoef* coefs, int* status,
                       long long wait_ticks, int mute_seg, int block, size_t lds, hipStream_t s);
 hipError_t seg_occupancy(int q, int prec, int code, bool wide, int block, size_t lds, int* blocks_per_cu);
 // VGPRs per thread of the resident kernel of variant `code`

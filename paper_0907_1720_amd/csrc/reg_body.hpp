@@ -25,7 +25,7 @@
 // lane).  Batches, LDS-resident before -> now: 4096 KdV/mKdV grids of 256..4096
 // nodes 5.4e11 -> 8.3e11 (FP64) and 6.0e11 -> 6.8e11 (FP32 storage) node
 // updates/s; 512 Kuramoto-Sivashinsky grids of 1024 nodes 8.1 -> 5.8 ms per 8000
-// steps; one KdV grid of 800 nodes 0.53 -> 0.35 us per step.
+// steps; one KdV grid of 800 nodes 0.53 -> 0.34 us per step.
 #pragma once
 
 #include <utility>
@@ -38,14 +38,18 @@ namespace lbm {
 // swapped: f[r][opp(j)] = f*_j(r).  Same operations in the same order per node
 // as Relaxer<Q, D, P, T, A>; nodes advance together a population pair at a
 // time, so that a coefficient is read once for all of them.
-template <int Q, int D, int P, typename T, typename A>
+template <int Q, int D, int P, typename T, typename A, bool Held>
 struct RegRelaxer {
   static_assert(P < 2, "polynomial equilibria");
-  static constexpr int K = P == 0 ? D + 1 : (D + 1) / 2;   // coefficients per population
+  static constexpr int K = reg_coefs(D, P);   // coefficients per population
   static constexpr bool kRest = (sizeof(T) == 4 && sizeof(A) == 8);
   // coefficients below the leading one: held in scalar registers for the whole
-  // launch when they fit, else read from the constant cache at every step
-  static constexpr bool kPin = Q * (K - 1) * (int)sizeof(A) / 4 <= 52;
+  // launch when they fit, in vector registers (Held) where a lane has few nodes,
+  // else read from the constant cache at every step.  That read takes about 150
+  // cycles per group of eight FP64 coefficients whatever the nodes, so that a
+  // lone wave of one node per lane spent 2500 cycles on a degree-13 D1Q7 step of
+  // 450 issue cycles.
+  static constexpr bool kPin = reg_pinned(Q, D, P, (int)sizeof(A)) || Held;
   using CT = const __attribute__((address_space(4))) A*;
   CT c;
   A top[Q];
@@ -71,7 +75,10 @@ struct RegRelaxer {
         for (int d = 0; d < K - 1; ++d) {
           low[j][d] = coef[j * kRow + d];
 #if defined(__HIP_DEVICE_COMPILE__)
-          asm volatile("" : "+s"(low[j][d]));
+          if constexpr (Held)
+            asm volatile("" : "+v"(low[j][d]));
+          else
+            asm volatile("" : "+s"(low[j][d]));
 #endif
         }
     }
@@ -251,12 +258,24 @@ __device__ __forceinline__ unsigned exponent_word(double v) { return (unsigned)_
 // What the segments of a slab launch share.
 struct SegLinks {
   int sx;                    // steps between exchanges with the neighbours (a multiple of s_per)
-  void* xbuf;                // strips: [segment][buffer][side][(hg + 1) R nodes][Q]
-  int* flags;                // [segment][side]: blocks published
+  uint64_t* xbuf;            // strips: [segment][buffer][side][node of a lane][population][half][hg + 1 lanes]
+  unsigned tag;              // block b's words carry tag + b
   int me;                    // this segment
-  bool mute;                 // never raises its flags (test hook)
+  bool mute;                 // never publishes (test hook)
   long long wait_ticks;
 };
+
+// 32 bits of a value with the tag of their block, moved as one word: a strip word
+// tells by itself whether it has arrived, so an exchange is one store on its way
+// and one load that finds it -- no wait for stores before a flag, no flag before
+// the loads (2.1 -> 1.2 us per exchange).
+__device__ __forceinline__ uint64_t tagged(unsigned tag, unsigned bits) { return ((uint64_t)tag << 32) | bits; }
+__device__ __forceinline__ unsigned value_bits(float v, int) { return (unsigned)__float_as_int(v); }
+__device__ __forceinline__ unsigned value_bits(double v, int half) {
+  return (unsigned)(half ? __double2hiint(v) : __double2loint(v));
+}
+__device__ __forceinline__ void value_of(float* v, const unsigned (&b)[1]) { *v = __int_as_float((int)b[0]); }
+__device__ __forceinline__ void value_of(double* v, const unsigned (&b)[2]) { *v = __hiloint2double((int)b[1], (int)b[0]); }
 
 // LDS elements of one wave: its exchange strips, or one row of its nodes on the
 // way between memory order and lane order
@@ -273,28 +292,27 @@ constexpr int reg_lds(int q, int R, int hl) {
 //  Slab: part of an instance, one workgroup each, all of a launch resident
 //   together.  A segment carries `extra` lanes more at each end, so that its
 //   ends stay exact for `sx` steps; then its first and last waves publish the
-//   outer owned lanes in global memory, raise a flag each, wait for the
-//   neighbour's and refill their outer halos.  Strips and flags move with
-//   device-scope relaxed atomics (coherent across the XCDs' L2 caches without
-//   whole-cache write-back): a wave waits for its strip stores to complete
-//   before it stores its flag, and loads strips only after the flag load has
-//   returned.  Strips alternate between two buffers by block; a wave overwrites
-//   one only after the neighbour has raised the next block's flag, i.e. after it
-//   has read it.  A wait that outlasts `wait_ticks` ticks of the constant-rate
+//   outer owned lanes in global memory and refill their outer halos from their
+//   neighbours', reading until every word carries the block's tag.  Words move
+//   with device-scope relaxed atomics (coherent across the XCDs' L2 caches
+//   without whole-cache write-back).  Strips alternate between two buffers by
+//   block; a wave overwrites one only after it has the neighbour's next block,
+//   which the neighbour publishes after it has read this one.  Tags grow from
+//   launch to launch, so that nothing is cleared in between.  A wait that outlasts `wait_ticks` ticks of the constant-rate
 //   wall clock marks the instance (status bit 2) and is the wave's last: it runs
 //   on without waiting, so that every kernel ends.
 //  (A tile is a slab of at most `sx` steps, which meets no exchange with
 //   neighbours.)
 // State moves between memory order and lane order through a row of LDS per wave,
 // so that both sides are coalesced.
-// Bounded by VALU issue where the waves fill the SIMDs, by the exchange (2.1 us:
-// stores to the other XCD's reach, flag, poll, strip) where one instance is
-// spread thin.  Against the LDS-resident slabs and tiles (two to four workgroup
-// barriers and Q LDS accesses per node and step): one 4096-node FP32 KS solve
-// 4.03 -> 1.52 ms per 4000 steps, 128 x 8192 KS FP64 x 2000 4.46 -> 3.36 ms, 96
-// Kawahara FP64 of 2048..16384 nodes x 2000 10.8 -> 4.64 ms, a 3,000,017-node
-// KdV grid x 64 0.65 -> 0.34 ms.
-template <int Q, int R, int B, int Kind, int D, int P, typename T, typename A>
+// Bounded by VALU issue where the waves fill the SIMDs, by the exchange (1.2 us)
+// and the latency of a lone wave's step where one instance is spread thin.
+// Against the LDS-resident slabs and tiles (two to four workgroup barriers and Q
+// LDS accesses per node and step): one 4096-node FP32 KS solve 4.03 -> 0.93 ms
+// per 4000 steps, 128 x 8192 KS FP64 x 2000 4.46 -> 3.2 ms, 96 Kawahara FP64 of
+// 2048..16384 nodes x 2000 10.8 -> 4.6 ms, a 3,000,017-node KdV grid x 64 0.65 ->
+// 0.34 ms; one 800-node KdV grid, one workgroup before, 0.34 -> 0.25 us per step.
+template <int Q, int R, int B, int Kind, int D, int P, typename T, typename A, bool Held>
 __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w, bool act,
                                             const DevCoef* __restrict__ cf, int* __restrict__ status,
                                             const SegLinks& lk) {
@@ -308,7 +326,7 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
     __syncthreads();
     return;
   }
-  RegRelaxer<Q, D, P, T, A> relax;
+  RegRelaxer<Q, D, P, T, A, Held> relax;
   relax.init(cf);
   const int W = sg.waves, n = sg.n;
   // lanes of nodes advanced by this wave, among the segment's `lanes`
@@ -368,25 +386,33 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
   wait_vector_memory();
   __syncthreads();
   // slab: this lane's part in the exchange with the neighbours (element offsets, -1 none)
-  int gpub = -1, gref = -1, kx = 0, blk = 0;
-  bool left_end = false, right_end = false, waits = true;
-  [[maybe_unused]] int gstrip = 0;
+  int gpub = -1, gref = -1, gshift = 0, kx = 0;
+  bool ends = false, waits = true;
+  [[maybe_unused]] int gstrip = 0, glanes = 0;
+  [[maybe_unused]] unsigned tag = lk.tag, gbuf = 0;
+  constexpr int Halves = (int)sizeof(T) / 4;
   if constexpr (Kind == kSegSlab) {
     const int hg = hl + sg.extra, owned = sg.lanes - 2 * sg.extra;
     const int o = b0 - hl + lane - sg.extra;   // among the owned lanes
-    gstrip = (hg + 1) * R * Q;
-    left_end = w == 0;
-    right_end = w == W - 1;
+    glanes = hg + 1;
+    gstrip = glanes * R * Q * Halves;
+    const bool left_end = w == 0, right_end = w == W - 1;
+    ends = left_end || right_end;
     kx = lk.sx;
     const bool core = lane >= hl && lane < hl + cl;
     if (left_end && core && o >= 0 && o <= hg)
-      gpub = o * R * Q;
+      gpub = lk.me * 4 * gstrip + o;
     else if (right_end && core && o < owned && o >= owned - 1 - hg)
-      gpub = gstrip + (o - (owned - 1 - hg)) * R * Q;
-    if (left_end && o >= -hg && o < 0)
-      gref = sg.left * 4 * gstrip + gstrip + ((o + hg + 1) * R - sg.over_left) * Q;
-    else if (right_end && o >= owned && o < owned + hg)
-      gref = sg.right * 4 * gstrip + ((o - owned) * R + sg.over) * Q;
+      gpub = lk.me * 4 * gstrip + gstrip + o - (owned - 1 - hg);
+    // the ring's end may lie inside a lane: the neighbour's nodes are `gshift` off
+    if (left_end && o >= -hg && o < 0) {
+      gshift = sg.over_left ? R - sg.over_left : 0;
+      gref = sg.left * 4 * gstrip + gstrip + o + hg + 1 - (sg.over_left ? 1 : 0);
+    } else if (right_end && o >= owned && o < owned + hg) {
+      gshift = sg.over;
+      gref = sg.right * 4 * gstrip + o - owned;
+    }
+    if (lk.mute) gpub = -1;
   }
   int pairs = steps >> 1, k = s_per >> 1, buf = 0;
   if (pairs > 0) do {
@@ -394,34 +420,30 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
       reg_odd<Q, R, B>(f, relax);
       if (--k == 0 && (pairs > 1 || (steps & 1))) {   // more steps to come: exchange
         k = s_per >> 1;
+        bool across = false;   // this exchange is with the neighbours too
+        if constexpr (Kind == kSegSlab) {
+          kx -= s_per;
+          across = kx == 0;
+          if (across) {
+            kx = lk.sx;
+            if (gpub >= 0) {
+              uint64_t* p = lk.xbuf + gbuf + gpub;
+#pragma unroll
+              for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int j = 0; j < Q; ++j)
+#pragma unroll
+                  for (int h = 0; h < Halves; ++h)
+                    store_agent(p + ((r * Q + j) * Halves + h) * glanes, tagged(tag, value_bits(f[r][j], h)));
+            }
+          }
+        }
         if (pub >= 0) {
           T* p = S + pub + buf;
 #pragma unroll
           for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int j = 0; j < Q; ++j) p[r * Q + j] = f[r][j];
-        }
-        bool across = false;   // this exchange is with the neighbours too
-        if constexpr (Kind == kSegSlab) {
-          kx -= s_per;
-          across = kx == 0;
-          if (across && (left_end || right_end)) {
-            kx = lk.sx;
-            if (gpub >= 0) {
-              T* p = (T*)lk.xbuf + (int64_t)lk.me * 4 * gstrip + (blk & 1) * 2 * gstrip + gpub;
-#pragma unroll
-              for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int j = 0; j < Q; ++j) store_agent(p + r * Q + j, f[r][j]);
-            }
-            wait_vector_memory();
-            if (lane == 0 && !lk.mute) {
-              if (left_end) store_agent(lk.flags + 2 * lk.me, blk + 1);
-              if (right_end) store_agent(lk.flags + 2 * lk.me + 1, blk + 1);
-            }
-          } else if (across) {
-            kx = lk.sx;
-          }
         }
         __syncthreads();
         if (ref >= 0) {
@@ -434,28 +456,44 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
         buf = 2 * strip - buf;
         if constexpr (Kind == kSegSlab) {
           if (across) {
-            if (left_end || right_end) {
-              if (waits) {
-                const long long t0 = wall_clock64();
-                bool ready;
-                while (!(ready = (!left_end || load_agent(lk.flags + 2 * sg.left + 1) > blk) &&
-                                 (!right_end || load_agent(lk.flags + 2 * sg.right) > blk)) &&
-                       wall_clock64() - t0 < lk.wait_ticks)
-                  __builtin_amdgcn_s_sleep(1);
-                if (!ready) {
-                  waits = false;
-                  if (lane == 0) atomicOr(status + sg.inst, 2);
-                }
-              }
-              if (gref >= 0) {
-                const T* p = (const T*)lk.xbuf + (int64_t)(blk & 1) * 2 * gstrip + gref;
+            if (ends) {
+              // a few nodes of a lane at a time: twice their registers are in flight
+              constexpr int C = sizeof(T) == 4 ? (R < 4 ? R : 4) : (R < 2 ? R : 2);
+              const uint64_t* p = lk.xbuf + gbuf + gref;
+              const long long t0 = wall_clock64();
 #pragma unroll
-                for (int r = 0; r < R; ++r)
+              for (int c = 0; c < R; c += C) {
+                bool here;
+                do {
+                  here = true;
+                  if (gref >= 0) {
 #pragma unroll
-                  for (int j = 0; j < Q; ++j) f[r][j] = load_agent(p + r * Q + j);
+                    for (int r = c; r < c + C && r < R; ++r) {
+                      const int at = r + gshift >= R ? (r + gshift - R) * Q * Halves * glanes + 1
+                                                     : (r + gshift) * Q * Halves * glanes;
+#pragma unroll
+                      for (int j = 0; j < Q; ++j) {
+                        unsigned b[Halves];
+#pragma unroll
+                        for (int h = 0; h < Halves; ++h) {
+                          const uint64_t v = load_agent(p + at + (j * Halves + h) * glanes);
+                          here &= (unsigned)(v >> 32) == tag;
+                          b[h] = (unsigned)v;
+                        }
+                        value_of(&f[r][j], b);
+                      }
+                    }
+                  }
+                  here = __all(here);
+                  if (!here && waits && wall_clock64() - t0 >= lk.wait_ticks) {
+                    waits = false;
+                    if (lane == 0) atomicOr(status + sg.inst, 2);
+                  }
+                } while (!here && waits);
               }
             }
-            ++blk;
+            ++tag;
+            gbuf = 2 * gstrip - gbuf;
           }
         }
       }
@@ -513,9 +551,10 @@ __device__ __forceinline__ void reg_widths(int nodes, T* __restrict__ L, int ste
                                            const SegLinks& lk) {
   constexpr int R = reg_width(Q, (int)sizeof(T), D, P, Wide, I);
   if constexpr (R > 0) {
+    constexpr bool held = reg_held(Q, D, P, (int)sizeof(T), (int)sizeof(A), Wide, R);
+    constexpr int B = reg_together(held || reg_pinned(Q, D, P, (int)sizeof(A)), R);
     if (nodes == R)
-      reg_segment<Q, R, reg_together(RegRelaxer<Q, D, P, T, A>::kPin, R), Kind, D, P, T, A>(L, steps, s_per, sg, w, act,
-                                                                                       cf, status, lk);
+      reg_segment<Q, R, B, Kind, D, P, T, A, held>(L, steps, s_per, sg, w, act, cf, status, lk);
     else if constexpr (I + 1 < kRegWidths)
       reg_widths<Q, Kind, D, P, T, A, Wide, I + 1>(nodes, L, steps, s_per, sg, w, act, cf, status, lk);
   }
@@ -526,8 +565,8 @@ __device__ __forceinline__ void reg_widths(int nodes, T* __restrict__ L, int ste
 // an advance reads one state buffer and writes the other, `sx` steps each.
 template <int Q, int D, int P, typename T, typename A, bool Wide>
 __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_per_eu(Wide ? 2 : 4))) void k_seg(
-    const DevSeg* __restrict__ segs, int nodes, int s_per, int sx, int tile, int launch, void* __restrict__ xbuf,
-    int* __restrict__ flags, const DevCoef* __restrict__ coefs, int* __restrict__ status, long long wait_ticks,
+    const DevSeg* __restrict__ segs, int nodes, int s_per, int sx, int tile, int launch, uint64_t* xbuf,
+    unsigned tag, const DevCoef* __restrict__ coefs, int* __restrict__ status, long long wait_ticks,
     int mute_seg) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int me = blockIdx.x;
@@ -544,7 +583,7 @@ __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_p
     }
   }
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const SegLinks lk{sx, xbuf, flags, me, me == mute_seg, wait_ticks};
+  const SegLinks lk{sx, xbuf, tag, me, me == mute_seg, wait_ticks};
   reg_widths<Q, kSegSlab, D, P, T, A, Wide, 0>(nodes, reinterpret_cast<T*>(smem_raw), steps, s_per, sg, w, w < sg.waves,
                                                coefs + sg.inst, status, lk);
 }

@@ -33,7 +33,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kMaxSlabs = 2048;       // workgroups of one slab launch
-constexpr int kSplitNodes = 1024;     // smallest grid split into slabs when the GPU is mostly idle
+constexpr int kSplitNodes = 1024;     // smallest power-sum grid split into slabs when the GPU is mostly idle
 constexpr int kMaxResidentGrid = 256 * 8;
 constexpr int kMaxLaunches = 512;     // queue launches per advance pass (one per lattice, precision, variant, kernel)
 constexpr int kMaxResident = 64;      // those of the LDS-resident kernels
@@ -122,6 +122,8 @@ struct lbm_batch_s {
   DevJob* jobs_host = nullptr;
   DevSeg* segs = nullptr;             // register-resident segments: two slots of items_cap records
   DevSeg* segs_host = nullptr;
+  // whether a (q, prec, variant, nodes) instance on so many CUs advances sooner in slabs
+  std::map<std::tuple<int, int, int, int, int>, bool> sooner;
   DevSeg* xsegs = nullptr;            // slabs and tiles of the register path: two slots of xsegs_cap
   DevSeg* xsegs_host = nullptr;
   int xsegs_cap = 0;
@@ -150,6 +152,10 @@ struct lbm_batch_s {
   DevSlab* slabs = nullptr;           // two slots of slabs_cap records
   DevSlab* slabs_host = nullptr;
   int slabs_cap = 0;
+  // halo strips of register slabs: words tagged below strip_tag (0: never written)
+  uint64_t* strips = nullptr;
+  size_t strips_cap = 0;
+  uint32_t strip_tag = 1;
   void* xbuf = nullptr;               // halo strips of the slab path
   size_t xbuf_bytes = 0;
   int* sflags = nullptr;              // per-slab block flags
@@ -292,6 +298,7 @@ void destroy_batch(lbm_batch_s* b) {
   if (b->tinsts_host) hipHostFree(b->tinsts_host);
   hipFree(b->slabs);
   if (b->slabs_host) hipHostFree(b->slabs_host);
+  hipFree(b->strips);
   hipFree(b->xbuf);
   hipFree(b->sflags);
   if (b->ev0) hipEventDestroy(b->ev0);
@@ -727,7 +734,15 @@ struct RegFit {
   int over = 0;    // nodes by which they exceed the periods
   int waves = 0;
   double cost = 0.0;   // of one wave and step, in VALU operations
+  double lag = 0.0;    // what a lone wave waits for its coefficients beside
 };
+// A step of `waves` waves that share a SIMD: one takes about 1.25 times, two
+// about 1.05 times its operations' time each, unless the wait for coefficients is
+// longer.
+double reg_step(const RegFit& f, int waves) {
+  const double slow = waves == 1 ? 1.25 : waves == 2 ? 1.05 : 1.0;
+  return std::max(slow * waves * f.cost, 1.25 * f.cost + f.lag);
+}
 int reg_halo(int q, int R, int s) { return (s * (q / 2) + R - 1) / R; }
 // LDS elements of one wave: its exchange strips, or a row of its nodes
 int reg_strip(int q, int R, int s) { return std::max(4 * (reg_halo(q, R, s) + 1) * R * q, 64 * R); }
@@ -746,15 +761,16 @@ void reg_place(int q, int n, RegFit* f) {
 int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
   const bool f32 = prec != 0;
   const int D = code & 0xff, K = (code >> 8) == 0 ? D + 1 : (D + 1) / 2 + 1;
+  const int elem = f32 ? 4 : 8, arith = prec == 2 ? 4 : 8;
   const int conv = f32 ? (prec == 2 ? q + 2 : 2 * q) : 0;
   const int cross = (q <= 5 ? 6 : 12) * (f32 ? 1 : 2);
   int count = 0;
   for (int k = 0; k < kRegWidths; ++k) {
-    const int R = reg_width(q, f32 ? 4 : 8, D, code >> 8, wide, k);
+    const int R = reg_width(q, elem, D, code >> 8, wide, k);
     if (R == 0) break;
     RegFit best;
     double least = 0.0;
-    for (int s = 4; s <= 16; s += 2) {
+    for (int s = 2; s <= 16; s += 2) {
       const int hl = reg_halo(q, R, s), cap = 64 - 2 * hl;
       if (cap < 4 * (hl + 1)) break;   // the strips of a wave's two ends stay apart
       const double c = R * (q * (K + 1) + q - 1.0 + conv) + cross + ((f32 ? 2.0 : 5.0) * R * q + 40.0) / s;
@@ -764,6 +780,9 @@ int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
         best.s = s;
         best.wide = wide;
         best.cost = c;
+        best.lag = reg_pinned(q, D, code >> 8, arith) || reg_held(q, D, code >> 8, elem, arith, wide, R)
+                       ? 0.0
+                       : 37.0 * q * (K - 1) * arith / 64;
       }
     }
     if (best.R) out[count++] = best;
@@ -789,9 +808,9 @@ struct SegPlan {
   double est = 0.0;    // of a step of the whole group, in VALU operations of a wave
 };
 // An exchange between workgroups, in VALU operations of a wave (about 1.67 ns):
-// 2.5 us, and 2.2 us more for each further workgroup that shares the CU
+// 1.2 us, and 2.2 us more for each further workgroup that shares the CU
 // (2000-step batches of 128 KS and 96 Kawahara grids, 1 to 6 a CU).
-constexpr double kLinkCost = 1500.0, kLinkShare = 1300.0;
+constexpr double kLinkCost = 700.0, kLinkShare = 1300.0;
 // Segments of an instance of n nodes; 0: they cannot be cut as planned.  A
 // slab's outer owned lanes, which its neighbour reads, lie in its first and
 // last wave, and a wave's strips apart; a tile only needs the latter.
@@ -807,9 +826,8 @@ int seg_count(const SegPlan& p, int q, int n, bool tile) {
   return top / more < p.extra + hg + 1 || top / more < 2 * (hl + 1) ? 0 : k;
 }
 // The cheapest plan of a group (sizes: node count, instances of it) on `cus`
-// CUs.  A step costs the waves that share a SIMD their operations (1.25 and 1.05
-// times for one and two waves, as for whole instances), and 1/sx of an exchange
-// or of a tile's way from and to HBM.
+// CUs: a step of the waves that share a SIMD, and 1/sx of an exchange or of a
+// tile's way from and to HBM.
 // `want`: steps asked for (0: free); `wgs`: workgroups per CU asked for (0: free).
 bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cus, int want, int wgs, bool tile,
               SegPlan* out) {
@@ -817,11 +835,17 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
   int64_t nodes = 0;
   for (const auto& [n, times] : sizes) nodes += (int64_t)n * times;
   bool found = false;
-  for (int cls = 0; cls < 2; ++cls) {
+  // (what is likely good first: the rest is then passed over by its bounds)
+  const bool much = nodes > (int64_t)cus * 1024;
+  for (int c = 0; c < 2; ++c) {
+    const int cls = much ? 1 - c : c;
     RegFit menu[kRegWidths + 1];
     const int widths = reg_menu(q, prec, code, cls != 0, menu), full = reg_waves(cls != 0);
-    for (int k = 0; k < widths; ++k)
-      for (int pick = 0; pick < 4; ++pick) {
+    for (int m = 0; m < widths; ++m) {
+      const int k = much ? widths - 1 - m : m;
+      const double least = std::max(reg_step(menu[k], 1), nodes / (256.0 * menu[k].R * cus) * menu[k].cost);
+      if (found && least >= out->est) continue;
+      for (int pick = 0; pick < 7; ++pick) {
         SegPlan p;
         p.f = menu[k];
         if (want > 0) {
@@ -829,10 +853,11 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
           while (p.f.s > 2 && want % p.f.s != 0) p.f.s -= 2;
           p.sx = want;
         } else {
-          p.sx = ((8 << pick) + p.f.s - 1) / p.f.s * p.f.s;
+          p.sx = (((pick & 1 ? 12 : 8) << pick / 2) + p.f.s - 1) / p.f.s * p.f.s;
         }
         const int hl = reg_halo(q, p.f.R, p.f.s), cap = 64 - 2 * hl;
         p.extra = std::max(0, (p.sx * H + p.f.R - 1) / p.f.R - hl);
+        if (found && !tile && least + kLinkCost / p.sx >= out->est) continue;
         for (int w = 1; w <= (wgs > 0 ? std::max(1, full / wgs) : full); w = w < 4 ? w + 1 : w + 2) {
           p.waves = w;
           p.most = w * cap - 2 * p.extra;
@@ -841,12 +866,12 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
           auto price = [&](int64_t total) {
             p.per_cu = (int)std::min<int64_t>(hold, (total + cus - 1) / cus);
             const int per_simd = (p.per_cu * w + 3) / 4;
-            const double slow = per_simd == 1 ? 1.25 : per_simd == 2 ? 1.05 : 1.0;
             const double rounds = std::max(1.0, (double)total / ((double)p.per_cu * cus));
             const double link = tile ? 3000.0 + 0.4 * (p.per_cu * p.most * p.f.R) * q
                                      : kLinkCost + kLinkShare * (p.per_cu - 1) + (prec != 0 ? 2.0 : 5.0) * p.f.R * q;
-            p.est = (tile ? std::ceil(rounds) : rounds > 1.0 ? 1.05 * rounds : 1.0) *
-                    (slow * per_simd * p.f.cost + link / p.sx);
+            // (slabs over more than one launch go in up to eight chunks of steps)
+            p.est = (tile ? std::ceil(rounds) : rounds > 1.0 ? 1.02 * std::ceil(8.0 * rounds) / 8.0 : 1.0) *
+                    (reg_step(p.f, per_simd) + link / p.sx);
           };
           price(std::max<int64_t>(1, nodes / ((int64_t)p.most * p.f.R)));   // as few segments as there can be
           if (found && p.est >= out->est) continue;
@@ -866,8 +891,24 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
           }
         }
       }
+    }
   }
   return found;
+}
+
+// A step of one instance alone on a CU, in VALU operations of a wave.
+double ring_step(int q, int prec, int code, int n) {
+  double least = 1e30;
+  for (int cls = 0; cls < 2; ++cls) {
+    RegFit menu[kRegWidths + 1];
+    const int widths = reg_menu(q, prec, code, cls != 0, menu);
+    for (int k = 0; k < widths; ++k) {
+      reg_place(q, n, &menu[k]);
+      if (menu[k].waves > reg_waves(cls != 0)) continue;
+      least = std::min(least, reg_step(menu[k], (menu[k].waves + 3) / 4));
+    }
+  }
+  return least;
 }
 
 // One pass: every instance advances by steps[i] <= kMaxStepsPerLaunch.
@@ -897,6 +938,21 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   }
   const size_t lds_all = (size_t)b->lim.cus * b->lim.lds_max;
   const bool latency = b->path == 0 && b->res_grid == 0 && 4 * res_bytes < lds_all;
+  // Polynomial instances there go by estimate: over their share of the CUs, or
+  // whole on one, whichever ends a step sooner.
+  int sharing = 0;
+  for (int i = 0; i < count; ++i) sharing += latency && steps[i] > 0;
+  auto spread_sooner = [&](const HostInst& h) {
+    const int cus = b->lim.cus / std::max(1, sharing);
+    const auto key = std::make_tuple(h.q, h.prec, h.D, h.n, cus);
+    const auto it = b->sooner.find(key);
+    if (it != b->sooner.end()) return it->second;
+    if (b->sooner.size() >= 4096) b->sooner.clear();
+    SegPlan p;
+    const bool yes = cus > 1 && seg_plan(h.q, h.prec, h.D, {{h.n, 1}}, cus, 0, 0, false, &p) &&
+                     p.est < 0.95 * ring_step(h.q, h.prec, h.D, h.n);
+    return b->sooner[key] = yes;
+  };
   const int slab_wgs = b->tile_wgs > 0 ? b->tile_wgs : latency && 4 * all_bytes < lds_all ? 8 : 2;
   for (int i = 0; i < count; ++i) {
     if (steps[i] == 0) continue;
@@ -917,7 +973,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       rtile[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else if (b->path == 3)
       til[h.q][h.prec].push_back(i);
-    else if (in_reg && (b->path == 4 || !fits || (latency && h.n >= kSplitNodes)))
+    else if (in_reg && (b->path == 4 || !fits || (latency && spread_sooner(h))))
       spread[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else if (b->path == 4 || !fits)
       slb[std::make_tuple(h.q, h.prec, h.D, slab_wgs)].push_back(i);
@@ -1113,12 +1169,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // launches run side by side; where one needs more workgroups than that at
   // once, the launches run one after another, each over the whole GPU.  What
   // cannot be cut into that many slabs is advanced tile by tile.
-  struct SegLaunch { int q; int prec; int code; SegPlan p; bool tile; int first, count, launches; size_t lds, xoff; int foff; double est; };
+  struct SegLaunch { int q; int prec; int code; SegPlan p; bool tile; int first, count, launches; size_t lds, at; int64_t blocks; double est; };
   std::vector<SegLaunch> segs;
   std::vector<DevSeg> xsv;
   std::vector<std::pair<int, int>> flips;   // (instance, buffer exchanges)
-  size_t xbuf_need = 0;
-  int flags_need = 0;
+  size_t strips_need = 0;  // words
   int slab_cus = 0;        // workgroups of all slab launches
   double spread_work = 0.0;
   auto work_of = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g) {
@@ -1166,15 +1221,14 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     auto close = [&] {
       if (L.count == 0) return;
       if (!tile) {
-        L.xoff = xbuf_need;
-        L.foff = flags_need;
-        xbuf_need += ((size_t)L.count * 4 * (hg + 1) * R * q * es + 255) / 256 * 256;
-        flags_need += 2 * L.count;
+        L.at = strips_need;
+        strips_need += (size_t)L.count * 4 * (hg + 1) * R * q * (es / 4);
         slab_cus += L.count;
       }
       segs.push_back(L);
       L.first = (int)xsv.size();
       L.count = 0;
+      L.blocks = 0;
       L.est = 0.0;
     };
     const int wave_nodes = (p.per_cu * p.waves + 3) / 4;
@@ -1186,6 +1240,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         const int ks = seg_count(p, q, h.n, tile), all = (h.n + R - 1) / R;
         if (!tile && (L.count + ks > capacity || L.count >= share)) close();
         L.est = std::max(L.est, (double)st * wave_nodes * p.f.cost);
+        L.blocks = std::max<int64_t>(L.blocks, (st + p.sx - 1) / p.sx);
         const int from = h.cur ^ (c & 1);   // each earlier chunk flipped the buffer once
         for (int m = 0; m < ks; ++m) {
           const int l0 = (int)((int64_t)all * m / ks), l1 = (int)((int64_t)all * (m + 1) / ks);
@@ -1263,20 +1318,28 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         lbm_status st = ensure_second_buffer(b, std::get<1>(group.first) != 0);
         if (st != LBM_OK) return st;
       }
-    if (spread.size() > 1) {   // by share, if each fits its share at once
+    // Several groups: each by its plan for the whole GPU if all their
+    // workgroups find a CU there, else by its share, else one after another.
+    auto places_of = [&](const std::vector<SegPlan>& ps) {
+      int64_t total = 0;
+      size_t at = 0;
+      for (const auto& [key, g] : spread) {
+        for (int i : g) total += seg_count(ps[at], std::get<0>(key), b->inst[i].n, false);
+        ++at;
+      }
+      return total;
+    };
+    if (spread.size() > 1 && places_of(plans) > b->lim.cus) {
       std::vector<SegPlan> shared;
       std::vector<int> cus;
-      bool once = true;
+      bool ok = true;
       for (const auto& [key, g] : spread) {
         SegPlan p;
-        cus.push_back(std::max(1, (int)(b->lim.cus * work_of(key, g) / spread_all)));
-        once = once && plan(key, sizes_of(g), cus.back(), slab_steps, false, &p);
-        int64_t total = 0;
-        for (size_t u = 0; u < g.size() && once; ++u) total += seg_count(p, std::get<0>(key), b->inst[g[u]].n, false);
-        once = once && total <= cus.back();
+        cus.push_back(std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / spread_all)));
+        ok = ok && plan(key, sizes_of(g), cus.back(), slab_steps, false, &p);
         shared.push_back(p);
       }
-      if (once) {
+      if (ok && places_of(shared) <= b->lim.cus) {
         plans.swap(shared);
         places.swap(cus);
       }
@@ -1310,9 +1373,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     // (narrow or wide: one launch per group, since a pass's launches run side by
     // side only while there are hardware queues) up to a bound, and kernel and
     // bound are those for which the group -- its waves over its CUs, or one job
-    // of the longest waves -- is estimated to end first.  One wave per
-    // SIMD takes about 1.25 times, two about 1.05 times the time per wave that
-    // three or four do.
+    // of the longest waves -- is estimated to end first.
     std::vector<RegFit> fit(g.size()), trial(g.size());
     double best = 0.0;
     int job_waves = 4;
@@ -1321,7 +1382,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       RegFit menu[kRegWidths + 1];
       const int widths = reg_menu(q, pr, code, cls != 0, menu), full = reg_waves(cls != 0);
       for (int most = widths - 1; most >= 0; --most) {
-        double sum = 0.0, longest = 0.0;
+        double sum = 0.0, longest = 0.0, lag = 0.0;
         int64_t waves = 0;
         int top = 1;
         bool ok = true;
@@ -1342,13 +1403,14 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
           waves += trial[u].waves;
           top = std::max(top, trial[u].waves);
           longest = std::max(longest, trial[u].cost);
+          lag = std::max(lag, trial[u].lag);
         }
         if (!ok) break;
         // waves of a job: all a CU holds, or as many as the waves make for each CU
         const int share = std::max(top, (int)std::min<double>(full, std::ceil(waves / cus)));
         const int per_simd = (share + 3) / 4;
         const double slow = per_simd == 1 ? 1.25 : per_simd == 2 ? 1.05 : 1.0;
-        const double est = slow * std::max(per_simd * longest, sum / (4.0 * cus));
+        const double est = std::max({slow * per_simd * longest, slow * sum / (4.0 * cus), 1.25 * longest + lag});
         if (best == 0.0 || est < best) {
           best = est;
           fit = trial;
@@ -1534,10 +1596,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   struct SlabLaunch { int q; int prec; int code; int first, count, cap, s, halo, block; size_t lds; size_t xoff; int foff; double est; };
   std::vector<SlabLaunch> slaunch;
   std::vector<DevSlab> svec;
+  size_t xbuf_need = 0;
+  int flags_need = 0;
   int min_per_cu = 1 << 30;
   const int tin_slab0 = tin_used;
-  const size_t xbuf_segs = xbuf_need;
-  const int flags_segs = flags_need;
   std::vector<int> slab_insts;
   for (const auto& group : slb) {
     {
@@ -1691,15 +1753,23 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     htin.resize(tin_slab0);
     svec.clear();
     slaunch.clear();
-    xbuf_need = xbuf_segs;
-    flags_need = flags_segs;
+    xbuf_need = 0;
+    flags_need = 0;
     slab_side_by_side = false;
   }
   if (!svec.empty() || !xsv.empty()) {
     if ((int)svec.size() > b->slabs_cap || xbuf_need > b->xbuf_bytes || flags_need > b->sflags_cap ||
-        (int)xsv.size() > b->xsegs_cap) {
+        (int)xsv.size() > b->xsegs_cap || strips_need > b->strips_cap) {
       // grow the slab tables and exchange buffers; earlier passes must be done with them
       LBM_HIP(hipStreamSynchronize(b->stream));
+      if (strips_need > b->strips_cap) {
+        hipFree(b->strips);
+        b->strips = nullptr;
+        b->strips_cap = 0;
+        if (hipMalloc(&b->strips, sizeof(uint64_t) * strips_need) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+        b->strips_cap = strips_need;
+        b->strip_tag = UINT32_MAX;   // to be cleared
+      }
       if ((int)xsv.size() > b->xsegs_cap) {
         hipFree(b->xsegs);
         if (b->xsegs_host) hipHostFree(b->xsegs_host);
@@ -1928,7 +1998,12 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     std::stable_sort(items.begin(), items.end(), [](const LaneItem& x, const LaneItem& y) { return x.est > y.est; });
   std::vector<double> lane_load(nlanes, 0.0);
   std::vector<char> lane_forked(nlanes, 0);
-  if (!segs.empty() && flags_need > 0) LBM_HIP(hipMemsetAsync(b->sflags, 0, sizeof(int) * flags_need, b->stream));
+  int64_t strip_tags = 0;   // of this pass
+  for (const SegLaunch& L : segs) strip_tags += L.blocks;
+  if (strips_need > 0 && b->strip_tag + strip_tags >= UINT32_MAX) {
+    LBM_HIP(hipMemsetAsync(b->strips, 0, sizeof(uint64_t) * b->strips_cap, b->stream));
+    b->strip_tag = 1;
+  }
   if (fork) LBM_HIP(hipEventRecord(b->fork, b->stream));
   const DevSlab* ds = b->slabs + (size_t)k * b->slabs_cap;
   const DevTileInst* dti_all = b->tinsts + (size_t)k * b->tinsts_cap;
@@ -1946,13 +2021,12 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   };
   auto issue_seg = [&](size_t l, hipStream_t st) -> lbm_status {
     const SegLaunch& L = segs[l];
-    int* flags = b->sflags + L.foff;
-    // (the flags of all a pass's slab launches are cleared before the fork)
+    const uint32_t tag = b->strip_tag;
+    if (!L.tile) b->strip_tag += (uint32_t)L.blocks;
     const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
     for (int r = 0; r < L.launches; ++r)
       LBM_HIP(launch_seg(L.q, L.prec, L.code, L.p.f.wide, dxsegs + L.first, L.count, L.p.f.R, L.p.f.s, L.p.sx, L.tile, r,
-                         (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.p.sx), mute,
-                         64 * L.p.waves, L.lds, st));
+                         b->strips + L.at, tag, b->coefs, b->status, wait_ticks(b, L.p.sx), mute, 64 * L.p.waves, L.lds, st));
     return LBM_OK;
   };
   for (size_t ii = 0; ii < items.size(); ++ii) {
