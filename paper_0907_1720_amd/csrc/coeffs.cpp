@@ -203,7 +203,7 @@ struct BinomTable {
 };
 
 // M[k][j] = e_j^k, inverted by Gauss-Jordan with partial pivoting
-bool invert_moment_matrix(int q, qf inv[kMaxQ][kMaxQ]) {
+bool invert_moments(int q, qf inv[kMaxQ][kMaxQ]) {
   qf a[kMaxQ][2 * kMaxQ];
   for (int k = 0; k < q; ++k) {
     for (int j = 0; j < q; ++j) {
@@ -234,6 +234,21 @@ bool invert_moment_matrix(int q, qf inv[kMaxQ][kMaxQ]) {
   }
   for (int r = 0; r < q; ++r)
     for (int j = 0; j < q; ++j) inv[r][j] = a[r][q + j];
+  return true;
+}
+
+// the inverse depends on q alone
+struct MomentInverse {
+  bool ok[kMaxQ + 1] = {};
+  qf v[kMaxQ + 1][kMaxQ][kMaxQ];
+  MomentInverse() {
+    for (int q = 4; q <= kMaxQ; ++q) ok[q] = invert_moments(q, v[q]);
+  }
+};
+bool invert_moment_matrix(int q, qf inv[kMaxQ][kMaxQ]) {
+  static const MomentInverse all;
+  if (q < 4 || q > kMaxQ || !all.ok[q]) return false;
+  std::memcpy(inv, all.v[q], sizeof(all.v[q]));
   return true;
 }
 
@@ -562,9 +577,10 @@ void set_rest_state(Model* mdl, double phi_rest) {
   for (int j = 0; j < mdl->q; ++j) {
     // Taylor shift: f_eq_j(r + delta) = sum_p H[j][p] delta^p, H[j][p] = sum_k C(k,p) G[j][k] r^{k-p}
     for (int p = 0; p <= mdl->D; ++p) {
-      qf h = 0;
-      for (int k = p; k <= mdl->D; ++k)
-        if (mdl->Gq[j][k] != 0) h += C.v[k][p] * mdl->Gq[j][k] * rp[k - p];
+      // (factors of 1 left out, and at r = 0 every term but the first)
+      qf h = mdl->Gq[j][p];
+      for (int k = p + 1; k <= mdl->D && phi_rest != 0; ++k)
+        if (mdl->Gq[j][k] != 0) h += (p > 0 ? C.v[k][p] * mdl->Gq[j][k] : mdl->Gq[j][k]) * rp[k - p];
       if (p == 0) {
         mdl->f_rest[j] = (double)h;
         mdl->wfrest[j] = (double)(omega * h);

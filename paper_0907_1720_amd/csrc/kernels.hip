@@ -26,8 +26,10 @@ namespace lbm {
 template <typename T>
 __global__ __launch_bounds__(256) void k_read(const T* __restrict__ f, double* __restrict__ phi, int n, int stride,
                                               int q, double phi_rest, const int* __restrict__ status,
-                                              int* __restrict__ words, int* __restrict__ arrived, int seq) {
+                                              int* __restrict__ words, int* __restrict__ arrived, int seq,
+                                              const int* __restrict__ bad) {
   const int x = blockIdx.x * 256 + threadIdx.x;
+  if (bad && *bad) return;   // phi0 was refused: phi stays as it was
   if (x == 0) words[0] = *status;
   if (x < n) {
     double s = (double)f[x];
@@ -79,10 +81,13 @@ __global__ __launch_bounds__(256) void k_init_many(const DevInit* __restrict__ r
   if (x0 >= r.len) return;
   init_run<T>(r, x0 + threadIdx.x, coefs, status);
 }
+// `bad` (if given) is set where phi is not finite
 template <typename T>
 __global__ __launch_bounds__(256) void k_init_one(DevInit r, const DevCoef* __restrict__ coefs,
-                                                  int* __restrict__ status) {
-  init_run<T>(r, blockIdx.x * 256 + threadIdx.x, coefs, status);
+                                                  int* __restrict__ status, int* __restrict__ bad) {
+  const int x = blockIdx.x * 256 + threadIdx.x;
+  if (bad && x < r.len && !__builtin_isfinite(reinterpret_cast<const double*>(r.src)[x])) *bad = 1;
+  init_run<T>(r, x, coefs, status);
 }
 
 __global__ __launch_bounds__(256) void k_check_phi(const double* __restrict__ phi, int n, int* __restrict__ words) {
@@ -166,12 +171,12 @@ hipError_t launch_init_many(bool f32, const DevInit* recs, int count, int longes
   return hipGetLastError();
 }
 
-hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, hipStream_t s) {
+hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, int* bad, hipStream_t s) {
   const dim3 grid((rec.len + 255) / 256);
   if (f32)
-    k_init_one<float><<<grid, 256, 0, s>>>(rec, coefs, status);
+    k_init_one<float><<<grid, 256, 0, s>>>(rec, coefs, status, bad);
   else
-    k_init_one<double><<<grid, 256, 0, s>>>(rec, coefs, status);
+    k_init_one<double><<<grid, 256, 0, s>>>(rec, coefs, status, bad);
   return hipGetLastError();
 }
 
@@ -327,12 +332,12 @@ hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, 
 }
 
 hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                       const int* status, int* words, int* arrived, int seq, hipStream_t s) {
+                       const int* status, int* words, int* arrived, int seq, const int* bad, hipStream_t s) {
   const dim3 grid((n + 255) / 256);
   if (f32)
-    k_read<float><<<grid, 256, 0, s>>>((const float*)f, phi, n, stride, q, phi_rest, status, words, arrived, seq);
+    k_read<float><<<grid, 256, 0, s>>>((const float*)f, phi, n, stride, q, phi_rest, status, words, arrived, seq, bad);
   else
-    k_read<double><<<grid, 256, 0, s>>>((const double*)f, phi, n, stride, q, phi_rest, status, words, arrived, seq);
+    k_read<double><<<grid, 256, 0, s>>>((const double*)f, phi, n, stride, q, phi_rest, status, words, arrived, seq, bad);
   return hipGetLastError();
 }
 

@@ -3,6 +3,8 @@
 // take device pointers.
 #pragma once
 
+#include <cstddef>
+
 #include "device.hpp"
 
 // Kernel variants of the relaxation polynomial: (padded degree D, parity P).
@@ -71,7 +73,7 @@ inline int variant_code(int D, int parity) { return D | (parity << 8); }
 // by value
 hipError_t launch_init_many(bool f32, const DevInit* recs, int count, int longest, const DevCoef* coefs, int* status,
                             hipStream_t s);
-hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, hipStream_t s);
+hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, int* bad, hipStream_t s);
 // words[0] |= 1 if any phi is not finite, |= 2 if any is negative (device or
 // pinned host memory)
 hipError_t launch_check_phi(const double* phi, int n, int* words, hipStream_t s);
@@ -154,9 +156,9 @@ size_t resident_static_lds(int q, int prec, int code);
 // phi = sum_j f_j into device or pinned host memory; words[0] := *status,
 // words[1] := 1 if any value is not finite (left alone otherwise).  With
 // `arrived` (0, and 0 again after) words[2] := seq at system scope once all of it
-// is there.
+// is there.  Nothing is written where *bad (if given) is set.
 hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                       const int* status, int* words, int* arrived, int seq, hipStream_t s);
+                       const int* status, int* words, int* arrived, int seq, const int* bad, hipStream_t s);
 hipError_t launch_sum(const double* v, int n, double* part, int nparts, hipStream_t s);
 hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, int* blocks_per_cu);
 // lbm_advance_noalloc: the fixed per-device scratch (tables at offset 0, the
@@ -167,6 +169,20 @@ constexpr size_t kNoAllocStateBytes = size_t(256) << 10;
 constexpr size_t kNoAllocScratchBytes = kNoAllocTableBytes + kNoAllocStateBytes;
 hipError_t noalloc_scratch(void** out);
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
+// The tables of a register-resident call, carried to the scratch `base` by the
+// kernel's own arguments: the polynomial part of DevCoef, one job of one segment,
+// and words that start at zero.  `later`: the next launch of the same call (job,
+// item and the first three words only).
+constexpr size_t kNoAllocCoefBytes = (offsetof(DevCoef, groots) + 15) / 16 * 16;
+constexpr size_t kNoAllocJobAt = 12288, kNoAllocItemAt = kNoAllocJobAt + 128, kNoAllocSegAt = kNoAllocJobAt + 256,
+                 kNoAllocIntsAt = kNoAllocJobAt + 512;
+struct alignas(16) NoAllocTables {
+  unsigned char coef[kNoAllocCoefBytes];
+  DevJob job;
+  DevItem item;
+  DevSeg seg;
+};
+hipError_t launch_tables(const NoAllocTables& t, unsigned char* base, bool later, hipStream_t s);
 // temporal blocking: launch `launch` of an advance, s_per steps per launch
 hipError_t launch_tile(int q, int prec, const DevTile* tiles, int ntiles, const DevTileInst* tinsts, void* buf0,
                        void* buf1, int launch, int s_per, int halo, const DevCoef* coefs, int* status, int block,

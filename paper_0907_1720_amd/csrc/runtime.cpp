@@ -621,7 +621,7 @@ lbm_status load_device(lbm_batch_s* b, int i, const double* phi) {
   r.q = h.q;
   r.degree = h.Dinit;
   r.first = 1;
-  LBM_HIP(launch_init_one(false, r, b->coefs, b->status, b->stream));
+  LBM_HIP(launch_init_one(false, r, b->coefs, b->status, nullptr, b->stream));
   LBM_HIP(hipStreamSynchronize(b->stream));   // phi may be reused by the caller
   return LBM_OK;
 }
@@ -2177,7 +2177,7 @@ lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_statu
     const int seq = b->read_seq = (b->read_seq + 1) & 0x7fffffff;
     seen[2] = seq ^ 1;
     LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, b->arrived, seq,
-                        b->stream));
+                        nullptr, b->stream));
     const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(kReadWatchUs);
     bool there = false;
     do {
@@ -2185,7 +2185,7 @@ lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_statu
     } while (!there && std::chrono::steady_clock::now() < until);
     if (!there) LBM_HIP(hipStreamSynchronize(b->stream));
   } else {
-    LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, nullptr, 0, b->stream));
+    LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, nullptr, 0, nullptr, b->stream));
     if (!on_device && !staged)
       LBM_HIP(hipMemcpyAsync(out, to, sizeof(double) * h.n, hipMemcpyDeviceToHost, b->stream));
     LBM_HIP(hipStreamSynchronize(b->stream));
@@ -2462,6 +2462,10 @@ lbm_status lbm_advance(lbm_problem h, int64_t steps) {
 // the fixed per-device scratch (noalloc.hip): the same kernels (k_init, one
 // resident launch per 2^30 steps, k_phi), so the result is bitwise that of the
 // handle path.  Host-side buffers live on this call's stack.
+//
+// Short calls are bound by their launches, copies and waits: 257 nodes and 101
+// steps took 118 us, of which the steps are 25.  A polynomial FP64 call is four
+// launches, one copy (the flags) and one wait; phi0 is checked where it is.
 lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t steps, double* phi, void* stream) {
   if (!d || !phi0 || !phi || steps < 0 || d->n < 1 || d->n > kNoAllocMaxNodes) return LBM_ERR_INVALID_ARG;
   if (d->bc != LBM_BC_PERIODIC) return LBM_ERR_INVALID_ARG;
@@ -2478,69 +2482,68 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
   void* base = nullptr;
   LBM_HIP(noalloc_scratch(&base));
   // tables at the start of the scratch, the state after them
-  static_assert(sizeof(DevCoef) <= 12288, "coefficient table outgrew its scratch region");
+  static_assert(sizeof(DevCoef) <= kNoAllocJobAt, "coefficient table outgrew its scratch region");
+  static_assert(sizeof(DevJob) <= 128 && sizeof(DevItem) <= 128 && sizeof(DevSeg) <= 256 && sizeof(DevJobInst) <= 256,
+                "job record outgrew its scratch region");
   unsigned char* bytes = (unsigned char*)base;
   DevCoef* dcoef = (DevCoef*)bytes;
-  DevJob* djob = (DevJob*)(bytes + 12288);
-  DevJobInst* dji = (DevJobInst*)(bytes + 12288 + 256);   // or the register path's segment
-  DevItem* ditem = (DevItem*)(bytes + 12288 + 128);
-  static_assert(sizeof(DevJob) <= 128 && sizeof(DevItem) <= 128 && sizeof(DevSeg) <= 256 && sizeof(DevJobInst) <= 256, "job record outgrew its scratch region");
-  int* ints = (int*)(bytes + 12288 + 512);   // queue counter, slot, done, status, read-out words
+  DevJob* djob = (DevJob*)(bytes + kNoAllocJobAt);
+  DevItem* ditem = (DevItem*)(bytes + kNoAllocItemAt);
+  DevSeg* dseg = (DevSeg*)(bytes + kNoAllocSegAt);
+  DevJobInst* dji = (DevJobInst*)(bytes + kNoAllocSegAt);   // the LDS path's record, in its place
+  int* ints = (int*)(bytes + kNoAllocIntsAt);   // queue counter, slot, done, status, read-out words, phi0 refused
   void* f = bytes + kNoAllocTableBytes;
-  // phi0 on the host: the checks of lbm_load_phi and the rest state (mean of phi0)
-  double host[kNoAllocMaxNodes];
-  LBM_HIP(hipMemcpyAsync(host, phi0, sizeof(double) * h.n, hipMemcpyDeviceToHost, st));
-  LBM_HIP(hipStreamSynchronize(st));
-  long double sum = 0;
-  for (int i = 0; i < h.n; ++i) {
-    if (!std::isfinite(host[i]) || (h.mdl.gF > 1 && host[i] < 0)) return LBM_ERR_INVALID_ARG;
-    sum += host[i];
+  const bool in_reg = reg_variant(h.D);
+  if (h.f32 || !in_reg) {
+    // phi0 on the host: the checks of lbm_load_phi and the rest state (mean of phi0)
+    double host[kNoAllocMaxNodes];
+    LBM_HIP(hipMemcpyAsync(host, phi0, sizeof(double) * h.n, hipMemcpyDeviceToHost, st));
+    LBM_HIP(hipStreamSynchronize(st));
+    if (check_phi(h, host) != LBM_OK) return LBM_ERR_INVALID_ARG;
+    if (h.f32) rest_from(&h, host);
   }
-  if (h.f32) set_rest_state(&h.mdl, (double)(sum / h.n));
   DevCoef cf;
   fill_devcoef(h, &cf);
-  // one job of one instance.  Register-resident (polynomial equilibria): the
-  // fewest nodes per lane whose waves fit one workgroup; else a wave per 64
-  // nodes, at most 16
-  const bool in_reg = reg_variant(h.D);
+  // one job of one instance: in registers the way its step is shortest, else a
+  // wave per 64 nodes, at most 16
+  NoAllocTables tables{};
   RegFit fit;
-  if (in_reg) {
-    fit.waves = 1 << 30;
-    for (int cls = 0; cls < 2 && fit.waves > reg_waves(fit.wide); ++cls) {
-      RegFit menu[kRegWidths + 1];
-      const int widths = reg_menu(h.q, h.prec, h.D, cls != 0, menu);
-      for (int k = 0; k < widths && fit.waves > reg_waves(fit.wide); ++k) {
-        fit = menu[k];
-        reg_place(h.q, h.n, &fit);
-      }
-    }
-    if (fit.waves > reg_waves(fit.wide)) return LBM_ERR_INVALID_ARG;
-  }
-  DevSeg sg{};
-  sg.in = sg.out = (uint64_t)(uintptr_t)f;
-  sg.n = sg.len = h.n;
-  sg.stride = h.stride;
-  sg.lanes = fit.lanes;
-  sg.over = fit.over;
-  sg.waves = fit.waves;
-  const int waves = std::max(1, std::min(16, (h.n + 63) / 64));
-  DevJob jb{};
+  DevJob& jb = tables.job;
   jb.count = 1;
   jb.degree = h.D;
-  jb.nodes = fit.R;
-  jb.s_per = fit.s;
   DevJobInst ji{};
-  ji.addr = (uint64_t)(uintptr_t)f;
-  ji.n = h.n;
-  ji.stride = h.stride;
-  ji.degree = h.D;
-  ji.nt = 64 * waves;
-  LBM_HIP(hipMemcpyAsync(dcoef, &cf, sizeof(cf), hipMemcpyHostToDevice, st));
-  if (in_reg)
-    LBM_HIP(hipMemcpyAsync(dji, &sg, sizeof(sg), hipMemcpyHostToDevice, st));
-  else
+  if (in_reg) {
+    for (int cls = 0; cls < 2; ++cls) {
+      RegFit menu[kRegWidths + 1];
+      const int widths = reg_menu(h.q, h.prec, h.D, cls != 0, menu);
+      for (int k = 0; k < widths; ++k) {
+        reg_place(h.q, h.n, &menu[k]);
+        if (menu[k].waves <= reg_waves(cls != 0) &&
+            (fit.waves == 0 || reg_step(menu[k], (menu[k].waves + 3) / 4) < reg_step(fit, (fit.waves + 3) / 4)))
+          fit = menu[k];
+      }
+    }
+    if (fit.waves == 0) return LBM_ERR_INVALID_ARG;
+    jb.nodes = fit.R;
+    jb.s_per = fit.s;
+    DevSeg& sg = tables.seg;
+    sg.in = sg.out = (uint64_t)(uintptr_t)f;
+    sg.n = sg.len = h.n;
+    sg.stride = h.stride;
+    sg.lanes = fit.lanes;
+    sg.over = fit.over;
+    sg.waves = fit.waves;
+    std::memcpy(tables.coef, &cf, kNoAllocCoefBytes);
+  } else {
+    ji.addr = (uint64_t)(uintptr_t)f;
+    ji.n = h.n;
+    ji.stride = h.stride;
+    ji.degree = h.D;
+    ji.nt = 64 * std::max(1, std::min(16, (h.n + 63) / 64));
+    LBM_HIP(hipMemcpyAsync(dcoef, &cf, sizeof(cf), hipMemcpyHostToDevice, st));
     LBM_HIP(hipMemcpyAsync(dji, &ji, sizeof(ji), hipMemcpyHostToDevice, st));
-  LBM_HIP(launch_zero_ints(ints, 6, st));
+    LBM_HIP(launch_zero_ints(ints, 8, st));
+  }
   DevInit init{};
   init.src = (uint64_t)(uintptr_t)phi0;
   init.dst = (uint64_t)(uintptr_t)f;
@@ -2549,27 +2552,33 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
   init.q = h.q;
   init.degree = h.Dinit;
   init.first = 1;
-  LBM_HIP(launch_init_one(h.f32, init, dcoef, ints + 3, st));
-  for (int64_t left = steps; left > 0;) {
+  bool first = true;
+  for (int64_t left = steps; left > 0 || first;) {
     const int64_t now = std::min(left, kMaxStepsPerLaunch);
     left -= now;
     jb.steps = (int)now;
-    const DevItem item{0, 0, (int)now, 0};
-    LBM_HIP(hipMemcpyAsync(djob, &jb, sizeof(jb), hipMemcpyHostToDevice, st));
-    LBM_HIP(hipMemcpyAsync(ditem, &item, sizeof(item), hipMemcpyHostToDevice, st));
-    LBM_HIP(hipStreamSynchronize(st));   // jb and item are reused by the next launch
-    LBM_HIP(launch_zero_ints(ints, 3, st));
-    if (in_reg)
-      LBM_HIP(launch_reg(h.q, h.prec, h.D, fit.wide, ditem, 1, djob, (const DevSeg*)dji, ints, ints + 2, dcoef, ints + 3,
-                         0, -1, 1, 64 * fit.waves, (size_t)fit.waves * reg_strip(h.q, fit.R, fit.s) * es, st));
-    else
+    tables.item = DevItem{0, 0, (int)now, 0};
+    if (in_reg) LBM_HIP(launch_tables(tables, bytes, !first, st));
+    if (first) LBM_HIP(launch_init_one(h.f32, init, dcoef, ints + 3, in_reg ? ints + 6 : nullptr, st));
+    first = false;
+    if (now == 0) break;
+    if (in_reg) {
+      LBM_HIP(launch_reg(h.q, h.prec, h.D, fit.wide, ditem, 1, djob, dseg, ints, ints + 2, dcoef, ints + 3, 0, -1, 1,
+                         64 * fit.waves, (size_t)fit.waves * reg_strip(h.q, fit.R, fit.s) * es, st));
+    } else {
+      LBM_HIP(hipMemcpyAsync(djob, &jb, sizeof(jb), hipMemcpyHostToDevice, st));
+      LBM_HIP(hipStreamSynchronize(st));   // jb is reused by the next launch
+      LBM_HIP(launch_zero_ints(ints, 3, st));
       LBM_HIP(launch_resident(h.q, h.prec, h.D, djob, dji, 1, 1, ints, ints + 1, ints + 2, dcoef, ints + 3, 0, -1, 1,
                               ji.nt, lds, st));
+    }
   }
-  LBM_HIP(launch_read(h.f32, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 3, ints + 4, nullptr, 0, st));
-  int flags[2] = {0, 0};
+  LBM_HIP(launch_read(h.f32, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 3, ints + 4, nullptr, 0,
+                      ints + 6, st));
+  int flags[3] = {0, 0, 0};
   LBM_HIP(hipMemcpyAsync(flags, ints + 4, sizeof(flags), hipMemcpyDeviceToHost, st));
   LBM_HIP(hipStreamSynchronize(st));
+  if (flags[2]) return LBM_ERR_INVALID_ARG;
   if (flags[0] & 6) return LBM_ERR_TIMEOUT;
   return (flags[0] || flags[1]) ? LBM_ERR_NONFINITE : LBM_OK;
 }
@@ -2775,7 +2784,7 @@ lbm_status lbm_sum_phi(lbm_problem h, double* total) {
   HostInst& hi = b->inst[0];
   int* words = reinterpret_cast<int*>(b->stage);
   LBM_HIP(launch_read(hi.f32, state_cur(b, hi), b->scratch, hi.n, hi.stride, hi.q, hi.f32 ? hi.mdl.phi_rest : 0.0,
-                      b->status, words, nullptr, 0, b->stream));
+                      b->status, words, nullptr, 0, nullptr, b->stream));
   // deterministic FP64 reduction: fixed partition on the device, fixed order on the host
   const int parts = 64;
   double* part = b->scratch + hi.n;

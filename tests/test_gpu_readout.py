@@ -43,3 +43,18 @@ def test_read_phi_at_workgroup_edges_and_behind_an_advance(prec):
         for n, (a, sa), (c, sc) in zip(ns, behind, idle):
             assert sa == sc == lbm.OK and np.array_equal(a, c), (n, steps)
     b.close()
+
+
+@pytest.mark.parametrize("n", [64, 257, 3000])
+def test_noalloc_refuses_a_non_finite_state_and_leaves_phi(n):
+    import torch
+
+    print("case noalloc refusal", n, flush=True)
+    p = W.kdv(0.5, n, 0.1, 1e-4, 2.0, 0.0)
+    phi0 = torch.full((n,), 0.25, dtype=torch.float64, device="cuda")
+    phi0[n - 1] = float("inf")
+    out = torch.full_like(phi0, 7.0)
+    with pytest.raises(lbm.LBMError) as e:
+        lbm.advance_noalloc(p, phi0, 5, out)
+    assert e.value.status == lbm.INVALID_ARG
+    assert bool((out == 7.0).all())
