@@ -18,15 +18,15 @@ namespace lbm {
 // ---------------------------------------------------------------------------
 // phi may lie in pinned host memory: the values cross to the host as they are
 // summed, instead of a read-out buffer and three copies (55 -> 16 us per call
-// of 1400 nodes).  With `arrived` (a count of workgroups, 0 between launches) the
-// last workgroup to finish stores words[2] = seq at system scope, and the host
-// watches that word: the stream's completion signal and its handling took longer
-// than the kernel.  One workgroup would need no count, but alone it writes only
-// 4 GB/s across the link (8192 nodes: 18 us).
+// of 1400 nodes).  With seq > 0 each workgroup that has finished stores words[2 +
+// blockIdx] = seq at system scope, and the host watches those words: the stream's
+// completion signal and its handling took longer than the kernel (a word that the
+// last of counted workgroups stores cost another 0.9 of 10.5 us).  One workgroup alone writes
+// only 4 GB/s across the link (8192 nodes: 18 us).
 template <typename T>
 __global__ __launch_bounds__(256) void k_read(const T* __restrict__ f, double* __restrict__ phi, int n, int stride,
                                               int q, double phi_rest, const int* __restrict__ status,
-                                              int* __restrict__ words, int* __restrict__ arrived, int seq,
+                                              int* __restrict__ words, int seq,
                                               const int* __restrict__ bad) {
   const int x = blockIdx.x * 256 + threadIdx.x;
   if (bad && *bad) return;   // phi0 was refused: phi stays as it was
@@ -38,13 +38,10 @@ __global__ __launch_bounds__(256) void k_read(const T* __restrict__ f, double* _
     phi[x] = s;
     if (!__builtin_isfinite(s)) words[1] = 1;   // (every writer stores the same word)
   }
-  if (!arrived) return;
-  __threadfence_system();
+  if (seq == 0) return;
   __syncthreads();
-  if (threadIdx.x == 0 && atomicAdd(arrived, 1) == (int)gridDim.x - 1) {
-    __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(words + 2, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
+  if (threadIdx.x == 0)
+    __hip_atomic_store(words + 2 + blockIdx.x, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------
@@ -332,12 +329,12 @@ hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, 
 }
 
 hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                       const int* status, int* words, int* arrived, int seq, const int* bad, hipStream_t s) {
+                       const int* status, int* words, int seq, const int* bad, hipStream_t s) {
   const dim3 grid((n + 255) / 256);
   if (f32)
-    k_read<float><<<grid, 256, 0, s>>>((const float*)f, phi, n, stride, q, phi_rest, status, words, arrived, seq, bad);
+    k_read<float><<<grid, 256, 0, s>>>((const float*)f, phi, n, stride, q, phi_rest, status, words, seq, bad);
   else
-    k_read<double><<<grid, 256, 0, s>>>((const double*)f, phi, n, stride, q, phi_rest, status, words, arrived, seq, bad);
+    k_read<double><<<grid, 256, 0, s>>>((const double*)f, phi, n, stride, q, phi_rest, status, words, seq, bad);
   return hipGetLastError();
 }
 

@@ -155,10 +155,11 @@ int resident_vgprs(int q, int prec, int code);
 size_t resident_static_lds(int q, int prec, int code);
 // phi = sum_j f_j into device or pinned host memory; words[0] := *status,
 // words[1] := 1 if any value is not finite (left alone otherwise).  With
-// `arrived` (0, and 0 again after) words[2] := seq at system scope once all of it
-// is there.  Nothing is written where *bad (if given) is set.
+// seq > 0, at most 256 kReadWords nodes: words[2 + k] := seq at system scope once
+// the k-th 256 values are there.  Nothing is written where *bad (if given) is set.
+constexpr int kReadWords = 60;
 hipError_t launch_read(bool f32, const void* f, double* phi, int n, int stride, int q, double phi_rest,
-                       const int* status, int* words, int* arrived, int seq, const int* bad, hipStream_t s);
+                       const int* status, int* words, int seq, const int* bad, hipStream_t s);
 hipError_t launch_sum(const double* v, int n, double* part, int nparts, hipStream_t s);
 hipError_t resident_occupancy(int q, int prec, int code, int block, size_t lds, int* blocks_per_cu);
 // lbm_advance_noalloc: the fixed per-device scratch (tables at offset 0, the

@@ -139,7 +139,6 @@ struct lbm_batch_s {
   // bytes of status words, then data.  Every call that uses it synchronises the
   // stream before it returns.
   unsigned char* stage = nullptr;
-  int* arrived = nullptr;             // the read-out's count of workgroups (behind status)
   int read_seq = 0;                   // read-outs watched so far
   size_t stage_bytes = 0;             // data bytes
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -397,8 +396,7 @@ lbm_status alloc_batch(lbm_batch_s* b, void* dev_buf, size_t buf_bytes) {
 lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want) {
   const int count = (int)b->inst.size();
   if (hipMalloc(&b->coefs, sizeof(DevCoef) * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipMalloc(&b->status, sizeof(int) * (count + 1)) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  b->arrived = b->status + count;
+  if (hipMalloc(&b->status, sizeof(int) * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   b->counters_cap = 2 * kMaxLaunches;   // 2 item slots x up to kMaxLaunches launches
   if (hipMalloc(&b->counter, sizeof(int) * b->counters_cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   // one queue slot per workgroup of each resident launch
@@ -430,7 +428,7 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want) {
   b->stage_bytes = std::min(kStageMost, std::max(kStageLeast, stage_want));
   if (hipHostMalloc((void**)&b->stage, kStageHead + b->stage_bytes, hipHostMallocDefault) != hipSuccess)
     return LBM_ERR_OUT_OF_MEMORY;
-  LBM_HIP(hipMemsetAsync(b->status, 0, sizeof(int) * (count + 1), b->stream));
+  LBM_HIP(hipMemsetAsync(b->status, 0, sizeof(int) * count, b->stream));
   LBM_HIP(hipEventCreate(&b->ev0));
   LBM_HIP(hipEventCreate(&b->ev1));
   return LBM_OK;
@@ -2171,21 +2169,25 @@ lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_statu
   seen[0] = seen[1] = 0;
   const bool staged = !on_device && sizeof(double) * (size_t)h.n <= b->stage_bytes;
   double* to = on_device ? out : staged ? reinterpret_cast<double*>(b->stage + kStageHead) : b->scratch;
-  if (staged) {
+  if (staged && h.n <= 256 * kReadWords) {
     // watched for as long as an idle stream takes; behind an advance that is
     // still running (and on errors) the stream is waited for
-    const int seq = b->read_seq = (b->read_seq + 1) & 0x7fffffff;
-    seen[2] = seq ^ 1;
-    LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, b->arrived, seq,
-                        nullptr, b->stream));
+    static_assert(sizeof(int) * (2 + kReadWords) <= kStageHead, "the stage's words");
+    const int blocks = (h.n + 255) / 256;
+    const int seq = b->read_seq = b->read_seq % 0x7fffffff + 1;
+    for (int k = 0; k < blocks; ++k) seen[2 + k] = 0;
+    LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, seq, nullptr,
+                        b->stream));
     const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(kReadWatchUs);
-    bool there = false;
+    int here = 0;
     do {
-      for (int k = 0; k < 64 && !there; ++k) there = __atomic_load_n(words + 2, __ATOMIC_ACQUIRE) == seq;
-    } while (!there && std::chrono::steady_clock::now() < until);
+      for (int k = 0; k < 64 && here < blocks; ++k)
+        while (here < blocks && __atomic_load_n(words + 2 + here, __ATOMIC_ACQUIRE) == seq) ++here;
+    } while (here < blocks && std::chrono::steady_clock::now() < until);
+    const bool there = here == blocks;
     if (!there) LBM_HIP(hipStreamSynchronize(b->stream));
   } else {
-    LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, nullptr, 0, nullptr, b->stream));
+    LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, 0, nullptr, b->stream));
     if (!on_device && !staged)
       LBM_HIP(hipMemcpyAsync(out, to, sizeof(double) * h.n, hipMemcpyDeviceToHost, b->stream));
     LBM_HIP(hipStreamSynchronize(b->stream));
@@ -2573,8 +2575,8 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
                               ji.nt, lds, st));
     }
   }
-  LBM_HIP(launch_read(h.f32, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 3, ints + 4, nullptr, 0,
-                      ints + 6, st));
+  LBM_HIP(launch_read(h.f32, f, phi, h.n, h.stride, h.q, h.f32 ? h.mdl.phi_rest : 0.0, ints + 3, ints + 4, 0, ints + 6,
+                      st));
   int flags[3] = {0, 0, 0};
   LBM_HIP(hipMemcpyAsync(flags, ints + 4, sizeof(flags), hipMemcpyDeviceToHost, st));
   LBM_HIP(hipStreamSynchronize(st));
@@ -2784,7 +2786,7 @@ lbm_status lbm_sum_phi(lbm_problem h, double* total) {
   HostInst& hi = b->inst[0];
   int* words = reinterpret_cast<int*>(b->stage);
   LBM_HIP(launch_read(hi.f32, state_cur(b, hi), b->scratch, hi.n, hi.stride, hi.q, hi.f32 ? hi.mdl.phi_rest : 0.0,
-                      b->status, words, nullptr, 0, nullptr, b->stream));
+                      b->status, words, 0, nullptr, b->stream));
   // deterministic FP64 reduction: fixed partition on the device, fixed order on the host
   const int parts = 64;
   double* part = b->scratch + hi.n;
