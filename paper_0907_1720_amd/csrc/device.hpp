@@ -88,12 +88,13 @@ struct DevItem {
   int32_t job;               // index into the launch's jobs
   int32_t part;
   int32_t steps;
+  int32_t from;              // steps of the job before this part
   int32_t more;              // 1: the job has a further part
 };
 
 // Register-resident path: a segment is a run of consecutive nodes of an
 // instance advanced by `waves` waves of one workgroup, R nodes per lane.
-enum { kSegRing = 0, kSegSlab = 1 };
+enum { kSegRing = 0, kSegSlab = 1, kSegBound = 2 };
 struct DevSeg {
   uint64_t in;               // device address of row 0 of the state read ...
   uint64_t out;              // ... and written
@@ -111,7 +112,8 @@ struct DevSeg {
   int32_t lds_off;           // element offset of the segment's strips in LDS
   int32_t steps;             // slab, tile: steps of the advance
   int32_t left, right;       // slab: ring neighbours (segments of the launch)
-  int32_t pad_;
+  int32_t layers, kind;      // bounded: boundary layers at each end, 1 equilibrium or 2 extrapolation
+  uint64_t rows;             // bounded: phi* rows [step][2 layers] (FP64, device address)
 };
 
 // Slab path: an instance split over several co-resident workgroups (one slab

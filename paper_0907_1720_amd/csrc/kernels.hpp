@@ -133,6 +133,16 @@ constexpr bool reg_held(int q, int degree, int parity, int elem, int arith, bool
   return wide && R <= 2 && !reg_pinned(q, degree, parity, arith) &&
          q * (reg_coefs(degree, parity) * arith + R * (elem + arith)) / 4 <= 224;
 }
+// Bounded instances: two nodes per lane and four steps between exchanges, with
+// tables in scalar registers; the lanes that compute the layers are one wave's.
+constexpr int kBoundWidth = 2, kBoundSteps = 4;
+constexpr int kBoundValues = 32;                     // layers x populations of an end, at most
+// LDS elements of a wave besides its strips (slots outside the layers read up to
+// seven places beyond the last)
+constexpr int bound_lds(int elem) { return (4 * kBoundValues + 64) * 8 / elem; }
+constexpr bool bound_variant(int q, int degree, int parity, int arith) {
+  return q <= 5 && parity < 2 && reg_pinned(q, degree, parity, arith);
+}
 constexpr int reg_waves(bool wide) { return wide ? 8 : 16; }   // most waves of a workgroup: a CU's
 inline bool reg_variant(int code) { return ((code >> 8) & 0xff) < 2; }
 // persistent launch over `nitems` parts of jobs of ring segments; done[job] and

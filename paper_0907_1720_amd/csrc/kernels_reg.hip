@@ -18,12 +18,29 @@
 
 namespace lbm {
 
+namespace {
+// the kernel of bounded instances, where there is one
+template <int D, int P, typename T, typename A>
+const void* bound_fn() {
+  if constexpr (bound_variant(LBM_Q, D, P, (int)sizeof(A)))
+    return (const void*)k_reg<LBM_Q, kSegBound, D, P, T, A, false>;
+  else
+    return nullptr;
+}
+}  // namespace
+
 template <>
 const void* reg_kernel<LBM_Q, LBM_PREC>(int code, bool wide) {
   switch (code) {
 #define LBM_CASE(DD, PP) \
   case DD | (PP << 8):   \
-    return wide ? (const void*)k_reg<LBM_Q, DD, PP, LBM_TA, true> : (const void*)k_reg<LBM_Q, DD, PP, LBM_TA, false>;
+    return wide ? (const void*)k_reg<LBM_Q, kSegRing, DD, PP, LBM_TA, true>  \
+                : (const void*)k_reg<LBM_Q, kSegRing, DD, PP, LBM_TA, false>;
+    LBM_POLY_CASES
+#undef LBM_CASE
+#define LBM_CASE(DD, PP)           \
+  case DD | (PP << 8) | (1 << 16): \
+    return bound_fn<DD, PP, LBM_TA>();
     LBM_POLY_CASES
 #undef LBM_CASE
   }

@@ -284,6 +284,99 @@ constexpr int reg_lds(int q, int R, int hl) {
   return strips > 64 * R ? strips : 64 * R;
 }
 
+// The value of lane l, the same in all lanes.
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// The reset of a bounded instance's outer layers after a step, by the wave that
+// holds them (the first wave the left ones, the last the right ones), with the
+// arithmetic of k_bound: f_j := f_eq_j(phi*), for kind 2 plus the
+// non-equilibrium part of the first interior node.  The equilibria of four steps
+// are computed ahead, lane c population c % Q of layer c / Q, and wait in LDS.
+// The interior node's populations are read from their lanes, lane j evaluates
+// its population's polynomial, and the differences are read back.  Odd: an odd
+// number of steps is done, so f_j(x) lies at node x - e_j, population opp(j).
+// The boundary waves' steps bound the instance, by latency: 0.60 us per step of
+// 801 nodes with equilibrium layers, 0.69 with extrapolation, 0.40 without any;
+// with the interior node's part exchanged through LDS it was 0.82, and 1.14 with
+// the state in LDS.
+template <int Q, int D, typename T>
+struct RegBound {
+  double* eq;            // [4 steps][layers][Q]
+  double row[D + 1];     // of population lane % Q
+  double rest;
+  int layers, kind;
+  bool comp;             // this lane computes
+  bool near;             // this lane holds slots of the layers
+  int inner;             // the first interior node, counted from the wave's first (uniform)
+  int at;                // this lane's first node, relative to the first layer
+
+  // the interior node's populations; its place in a lane is M
+  template <bool Odd, int R, int M>
+  __device__ __forceinline__ void populations(const T (&f)[R][Q], T (&g)[Q]) const {
+    auto one = [&]<int j>() {
+      constexpr int y = M - (Odd ? velocity<Q>(j) : 0);
+      constexpr int off = floor_div(y, R);
+      g[j] = lane_value(f[y - off * R][Odd ? opposite<Q>(j) : j], inner / R + off);
+    };
+    [&]<int... j>(std::integer_sequence<int, j...>) { (one.template operator()<j>(), ...); }
+    (std::make_integer_sequence<int, Q>{});
+  }
+  template <bool Odd, int R, int U>
+  __device__ __forceinline__ void reset(T (&f)[R][Q]) const {
+    static_assert(R == 2, "a place for each parity");
+    // (what decides for each slot is computed anew: held, it spilled registers;
+    // slots outside the layers read whatever lies there)
+    int b0 = at;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(b0));
+#endif
+    const double* p = eq + (near ? (U * layers + b0) * Q : 0);
+    double v[R][Q];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        const int j = Odd ? opposite<Q>(k) : k;
+        const int b = r + (Odd ? velocity<Q>(j) : 0);
+        v[r][k] = p[b * Q + j];
+      }
+    double neq[Q] = {};
+    if (kind == 2) {
+      T g[Q];
+      if (inner & 1)
+        populations<Odd, R, 1>(f, g);
+      else
+        populations<Odd, R, 0>(f, g);
+      double s = 0.0;
+#pragma unroll
+      for (int k = 0; k < Q; ++k) s += (double)g[k];
+      const double h = horner(s);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) neq[k] = (double)g[k] - lane_value(h, k);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        const int j = Odd ? opposite<Q>(k) : k;
+        const int b = b0 + r + (Odd ? velocity<Q>(j) : 0);
+        const T x = (T)(v[r][k] + neq[j]);
+        f[r][k] = (unsigned)b < (unsigned)layers ? x : f[r][k];
+      }
+  }
+  __device__ __forceinline__ double horner(double p) const {
+    double acc = row[D];
+#pragma unroll
+    for (int d = D - 1; d >= 0; --d) acc = __builtin_fma(acc, p, row[d]);
+    return acc;
+  }
+};
+
 // Advance of one segment by the waves that hold it.  `sg` is the segment, `w`
 // this wave's number in it; waves without a segment (act false) only meet the
 // barriers.
@@ -301,6 +394,8 @@ constexpr int reg_lds(int q, int R, int hl) {
 //   launch to launch, so that nothing is cleared in between.  A wait that outlasts `wait_ticks` ticks of the constant-rate
 //   wall clock marks the instance (status bit 2) and is the wave's last: it runs
 //   on without waiting, so that every kernel ends.
+//  Bounded: the whole instance, no ring; after every step the outer layers are
+//   reset from the exact solution (reg_reset).
 //  (A tile is a slab of at most `sx` steps, which meets no exchange with
 //   neighbours.)
 // State moves between memory order and lane order through a row of LDS per wave,
@@ -315,7 +410,7 @@ constexpr int reg_lds(int q, int R, int hl) {
 template <int Q, int R, int B, int Kind, int D, int P, typename T, typename A, bool Held>
 __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w, bool act,
                                             const DevCoef* __restrict__ cf, int* __restrict__ status,
-                                            const SegLinks& lk) {
+                                            const SegLinks& lk, [[maybe_unused]] int from) {
   constexpr int H = Q / 2;
   using GT = __attribute__((address_space(1))) T;   // global memory
   const int lane = threadIdx.x & 63;
@@ -334,7 +429,7 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
   const int cl = b1 - b0;
   constexpr bool ring = Kind == kSegRing;
   // strips: [buffer][side][(hl + 1) R nodes][Q] of each wave
-  const int strip = (hl + 1) * R * Q, per_wave = reg_lds(Q, R, hl);
+  const int strip = (hl + 1) * R * Q, per_wave = reg_lds(Q, R, hl) + (Kind == kSegBound ? bound_lds((int)sizeof(T)) : 0);
   int pub = -1, ref = -1;
   {
     const int i = lane - hl;
@@ -414,7 +509,73 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
     }
     if (lk.mute) gpub = -1;
   }
-  int pairs = steps >> 1, k = s_per >> 1, buf = 0;
+  if constexpr (Kind == kSegBound) {
+    // exchanges every four steps; the exact solution is loaded four steps ahead
+    const bool right = w == W - 1, edge = w == 0 || right;   // (two waves or more)
+    const int nl = sg.layers;
+    RegBound<Q, D, T> bound;
+    bound.eq = reinterpret_cast<double*>(S + w * per_wave + reg_lds(Q, R, hl));
+    bound.rest = cf->phi_rest;
+    bound.layers = nl;
+    bound.kind = sg.kind;
+    bound.comp = edge && lane < nl * Q;
+    bound.inner = (right ? n - 1 - nl : nl) - first;
+    bound.at = first + lane * R - (right ? n - nl : 0);
+    bound.near = edge && bound.at + R - 1 + H >= 0 && bound.at - H < nl;
+    const double* rows = (const double*)(uintptr_t)sg.rows + (right ? nl : 0) + (edge ? lane / Q : 0);
+#pragma unroll
+    for (int d = 0; d <= D; ++d) bound.row[d] = edge ? cf->init[lane % Q][d] : 0.0;
+    double next[4] = {};
+    if (bound.comp) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) next[u] = u < steps ? rows[(int64_t)(from + u) * 2 * nl] : 0.0;
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the row has arrived: no step waits for it, and with it for the loads ahead
+#pragma unroll
+    for (int d = 0; d <= D; ++d) asm volatile("" : "+v"(bound.row[d]));
+#endif
+    int buf = 0;
+    for (int left = steps, at = from + 4;; left -= 4, at += 4) {
+      if (bound.comp) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) bound.eq[u * nl * Q + lane] = bound.horner(next[u] - bound.rest);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) next[u] = 4 + u < left ? rows[(int64_t)(at + u) * 2 * nl] : 0.0;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      reg_even<Q, R, B>(f, relax);
+      if (edge) bound.template reset<true, R, 0>(f);
+      if (left == 1) break;
+      reg_odd<Q, R, B>(f, relax);
+      if (edge) bound.template reset<false, R, 1>(f);
+      if (left == 2) break;
+      reg_even<Q, R, B>(f, relax);
+      if (edge) bound.template reset<true, R, 2>(f);
+      if (left == 3) break;
+      reg_odd<Q, R, B>(f, relax);
+      if (edge) bound.template reset<false, R, 3>(f);
+      if (left <= 4) break;
+      if (pub >= 0) {
+        T* p = S + pub + buf;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int j = 0; j < Q; ++j) p[r * Q + j] = f[r][j];
+      }
+      __syncthreads();
+      if (ref >= 0) {
+        const T* p = S + ref + buf;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int j = 0; j < Q; ++j) f[r][j] = p[r * Q + j];
+      }
+      buf = 2 * strip - buf;
+    }
+  }
+  int pairs = Kind == kSegBound ? 0 : steps >> 1, k = s_per >> 1, buf = 0;
   if (pairs > 0) do {
       reg_even<Q, R, B>(f, relax);
       reg_odd<Q, R, B>(f, relax);
@@ -500,7 +661,7 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
     } while (--pairs > 0);
   if (steps & 1) {   // the last step: relax, then stream to the natural layout
     T t[R][Q];
-    reg_even<Q, R, B>(f, relax);
+    if constexpr (Kind != kSegBound) reg_even<Q, R, B>(f, relax);
     reg_gather<Q, R>(f, t);
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -548,15 +709,15 @@ constexpr int reg_together(bool pin, int R) { return !pin ? R : R <= 3 ? R : R =
 template <int Q, int Kind, int D, int P, typename T, typename A, bool Wide, int I>
 __device__ __forceinline__ void reg_widths(int nodes, T* __restrict__ L, int steps, int s_per, const DevSeg& sg, int w,
                                            bool act, const DevCoef* __restrict__ cf, int* __restrict__ status,
-                                           const SegLinks& lk) {
-  constexpr int R = reg_width(Q, (int)sizeof(T), D, P, Wide, I);
+                                           const SegLinks& lk, int from) {
+  constexpr int R = Kind == kSegBound ? (I == 0 ? kBoundWidth : 0) : reg_width(Q, (int)sizeof(T), D, P, Wide, I);
   if constexpr (R > 0) {
     constexpr bool held = reg_held(Q, D, P, (int)sizeof(T), (int)sizeof(A), Wide, R);
     constexpr int B = reg_together(held || reg_pinned(Q, D, P, (int)sizeof(A)), R);
     if (nodes == R)
-      reg_segment<Q, R, B, Kind, D, P, T, A, held>(L, steps, s_per, sg, w, act, cf, status, lk);
+      reg_segment<Q, R, B, Kind, D, P, T, A, held>(L, steps, s_per, sg, w, act, cf, status, lk, from);
     else if constexpr (I + 1 < kRegWidths)
-      reg_widths<Q, Kind, D, P, T, A, Wide, I + 1>(nodes, L, steps, s_per, sg, w, act, cf, status, lk);
+      reg_widths<Q, Kind, D, P, T, A, Wide, I + 1>(nodes, L, steps, s_per, sg, w, act, cf, status, lk, from);
   }
 }
 
@@ -585,7 +746,7 @@ __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_p
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const SegLinks lk{sx, xbuf, tag, me, me == mute_seg, wait_ticks};
   reg_widths<Q, kSegSlab, D, P, T, A, Wide, 0>(nodes, reinterpret_cast<T*>(smem_raw), steps, s_per, sg, w, w < sg.waves,
-                                               coefs + sg.inst, status, lk);
+                                               coefs + sg.inst, status, lk, 0);
 }
 
 // Persistent kernel over the parts of jobs (a job: ring segments of one variant
@@ -597,7 +758,7 @@ __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_p
 // skipped and published, so that a scheduling fault ends the kernel.
 // `stall_item` (-1 normally) names an item that is taken but never run nor
 // published -- a test hook that makes the next part's wait give up.
-template <int Q, int D, int P, typename T, typename A, bool Wide>
+template <int Q, int Kind, int D, int P, typename T, typename A, bool Wide>
 __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_per_eu(Wide ? 2 : 4))) void k_reg(
     const DevItem* __restrict__ items, int nitems, const DevJob* __restrict__ jobs, const DevSeg* __restrict__ segs,
     int* __restrict__ counter, int* __restrict__ done, const DevCoef* __restrict__ coefs, int* __restrict__ status,
@@ -655,7 +816,8 @@ __global__ __launch_bounds__(64 * reg_waves(Wide)) __attribute__((amdgpu_waves_p
       if (act) sg = segs[jb.first + mine];
       const DevCoef* cf = coefs + (act ? sg.inst : 0);
       const int w = wave - sg.w0;
-      reg_widths<Q, kSegRing, D, P, T, A, Wide, 0>(jb.nodes, L, it.steps, jb.s_per, sg, w, act, cf, status, SegLinks{});
+      reg_widths<Q, Kind, D, P, T, A, Wide, 0>(jb.nodes, L, it.steps, jb.s_per, sg, w, act, cf, status, SegLinks{},
+                                               it.from);
       __syncthreads();   // strips are read before the next item's are written
       if (it.more) {
         __threadfence();   // this thread's write-back is visible to every CU

@@ -794,6 +794,15 @@ int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
   return count;
 }
 
+// bounded instances: one width
+RegFit bound_fit() {
+  RegFit f;
+  f.R = kBoundWidth;
+  f.s = kBoundSteps;
+  f.cost = 250.0;   // of the waves with layers
+  return f;
+}
+
 // Slabs and tiles of the register path: an instance cut into segments of about
 // equal lanes, one workgroup each, whose ends stay exact for sx steps.
 struct SegPlan {
@@ -916,6 +925,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // (q, prec, variant code, bounded)
   std::map<std::tuple<int, int, int, int>, std::vector<int>> res;
   // register-resident, by (q, prec, variant): whole instances, slabs, tiles
+  // (bounded instances among the first: variant | 1 << 16)
   std::map<std::tuple<int, int, int>, std::vector<int>> reg, spread, rtile;
   std::vector<int> str;          // one launch per step (the plain path)
   std::vector<int> til[8][3];    // temporal blocking, by (q, prec)
@@ -961,7 +971,16 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       // bounded instances advance only in a bounded call, on the resident path
       if (!b->bnd_active) return LBM_ERR_INVALID_ARG;
       if (!fits || (b->path != 0 && b->path != 2)) return LBM_ERR_UNSUPPORTED;
-      res[std::make_tuple(h.q, h.prec, h.D, 1)].push_back(i);
+      // two nodes per lane on the register path where two waves or more, of one
+      // CU, hold them and a wave's lanes the layers' values (801 nodes: 1.14 -> 0.69 us
+      // per step); in LDS otherwise
+      RegFit f = bound_fit();
+      reg_place(h.q, h.n, &f);
+      if (bound_variant(h.q, h.D & 0xff, (h.D >> 8) & 0xff, h.prec == 2 ? 4 : 8) && f.waves >= 2 &&
+          f.waves <= reg_waves(false) && b->bnd_layers * h.q <= kBoundValues)
+        reg[std::make_tuple(h.q, h.prec, h.D | (1 << 16))].push_back(i);
+      else
+        res[std::make_tuple(h.q, h.prec, h.D, 1)].push_back(i);
       continue;
     }
     if (b->path == 2 && !fits) return LBM_ERR_UNSUPPORTED;
@@ -1363,6 +1382,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     const int q = std::get<0>(group.first), pr = std::get<1>(group.first), code = std::get<2>(group.first);
     const std::vector<int>& g = group.second;
     const int es = pr != 0 ? 4 : 8;
+    const bool bounded = (code >> 16) != 0;
     // the CUs that are this group's by its share of the pass's work
     const double cus = std::max(1.0, b->lim.cus * group_work[gi++] / spread_all);
     // Nodes per lane: few spend more on halos and lane edges, many leave more of
@@ -1378,7 +1398,14 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     bool wide = false;
     for (int cls = 0; cls < 2; ++cls) {
       RegFit menu[kRegWidths + 1];
-      const int widths = reg_menu(q, pr, code, cls != 0, menu), full = reg_waves(cls != 0);
+      const int full = reg_waves(cls != 0);
+      int widths = 0;
+      if (!bounded) {
+        widths = reg_menu(q, pr, code, cls != 0, menu);
+      } else if (cls == 0) {
+        menu[0] = bound_fit();
+        widths = 1;
+      }
       for (int most = widths - 1; most >= 0; --most) {
         double sum = 0.0, longest = 0.0, lag = 0.0;
         int64_t waves = 0;
@@ -1477,8 +1504,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         sg.w0 = w0;
         sg.waves = fit[u].waves;
         sg.lds_off = off;
+        if (bounded) {
+          sg.layers = b->bnd_layers;
+          sg.kind = h.desc.bc == LBM_BC_DIRICHLET_EQ ? 1 : 2;
+          sg.rows = b->bnd_ptr[i];
+        }
         w0 += fit[u].waves;
-        off += fit[u].waves * reg_strip(q, f0.R, f0.s);
+        off += fit[u].waves * (reg_strip(q, f0.R, f0.s) + (bounded ? bound_lds(es) : 0));
       }
       L.lds = std::max(L.lds, (size_t)off * es);
       L.block = std::max(L.block, 64 * w0);
@@ -1522,10 +1554,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
           const int st = base + (c < rem ? 1 : 0);
           if (st == 0 && c > 0) continue;
           const int next = base + (c + 1 < rem ? 1 : 0);
-          parts.push_back(DevItem{k, c, st, c + 1 < b->res_chunks && next > 0 ? 1 : 0});
+          parts.push_back(DevItem{k, c, st, c * base + std::min(c, rem), c + 1 < b->res_chunks && next > 0 ? 1 : 0});
         }
     } else if (L.grid >= L.count) {
-      for (int k = 0; k < L.count; ++k) parts.push_back(DevItem{k, 0, jobs[k].steps, 0});
+      for (int k = 0; k < L.count; ++k) parts.push_back(DevItem{k, 0, jobs[k].steps, 0, 0});
     } else {
       const double span = std::max(L.est_sum / L.grid, L.est_max);
       struct Planned { double start; DevItem item; };
@@ -1543,9 +1575,9 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
           second = st;
         }
         const int first = st - second;
-        if (second > 0) plan.push_back({t, DevItem{k, first > 0 ? 1 : 0, second, 0}});
+        if (second > 0) plan.push_back({t, DevItem{k, first > 0 ? 1 : 0, second, first, 0}});
         if (first > 0) {
-          plan.push_back({0.0, DevItem{k, 0, first, second > 0 ? 1 : 0}});
+          plan.push_back({0.0, DevItem{k, 0, first, 0, second > 0 ? 1 : 0}});
           t = est[k] * first / st;
           ++used_wgs;
         } else {
@@ -2559,7 +2591,7 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
     const int64_t now = std::min(left, kMaxStepsPerLaunch);
     left -= now;
     jb.steps = (int)now;
-    tables.item = DevItem{0, 0, (int)now, 0};
+    tables.item = DevItem{0, 0, (int)now, 0, 0};
     if (in_reg) LBM_HIP(launch_tables(tables, bytes, !first, st));
     if (first) LBM_HIP(launch_init_one(h.f32, init, dcoef, ints + 3, in_reg ? ints + 6 : nullptr, st));
     first = false;
@@ -2607,18 +2639,6 @@ bool valid_wave(const lbm_wave* w) {
   return true;
 }
 
-// rows [steps][2 layers] of instance i into device memory dst (on b->stream)
-lbm_status fill_rows(lbm_batch_s* b, int i, const RowSource& src, double* dst, int64_t steps, int layers) {
-  const HostInst& h = b->inst[i];
-  const size_t rows = (size_t)steps * 2 * layers;
-  if (src.host) {
-    LBM_HIP(hipMemcpy(dst, src.host[i], sizeof(double) * rows, hipMemcpyHostToDevice));
-  } else {
-    LBM_HIP(launch_wave_rows(dst, steps, layers, h.n, h.desc.dx, h.desc.dt, src.waves[i], b->stream));
-  }
-  return LBM_OK;
-}
-
 // Bounded instances of a batch advance `steps` (<= kMaxStepsPerLaunch) steps on
 // the resident path, their boundary layers reset in LDS after every step;
 // rows [steps][2 layers] of bounded instance i from `src`.
@@ -2638,13 +2658,18 @@ lbm_status advance_bounded_resident(lbm_batch_s* b, int64_t steps, const RowSour
     b->bound_cap = need;
   }
   b->bnd_ptr.assign(count, 0);
+  std::vector<WaveRows> waves;
   for (int i = 0, k = 0; i < count; ++i) {
-    if (b->inst[i].desc.bc == LBM_BC_PERIODIC) continue;
+    const HostInst& h = b->inst[i];
+    if (h.desc.bc == LBM_BC_PERIODIC) continue;
     double* dst = b->bound + (size_t)k++ * rows;
-    lbm_status s = fill_rows(b, i, src, dst, steps, layers);
-    if (s != LBM_OK) return s;
+    if (src.host)
+      LBM_HIP(hipMemcpy(dst, src.host[i], sizeof(double) * rows, hipMemcpyHostToDevice));
+    else
+      waves.push_back(wave_rows(dst, h.n, h.desc.dx, h.desc.dt, src.waves[i]));
     b->bnd_ptr[i] = (uint64_t)(uintptr_t)dst;
   }
+  LBM_HIP(launch_wave_rows(waves.data(), (int)waves.size(), steps, layers, b->stream));
   b->bnd_active = true;
   b->bnd_layers = layers;
   std::vector<int64_t> st(count, steps);
@@ -2707,8 +2732,12 @@ lbm_status advance_bounded_one(lbm_batch_s* b, int64_t steps, const RowSource& s
   const size_t need = (size_t)steps * 2 * layers;
   s = bound_rows_buffer(b, need);
   if (s != LBM_OK) return s;
-  s = fill_rows(b, 0, src, b->bound, steps, layers);
-  if (s != LBM_OK) return s;
+  if (src.host) {
+    LBM_HIP(hipMemcpy(b->bound, src.host[0], sizeof(double) * need, hipMemcpyHostToDevice));
+  } else {
+    const WaveRows wr = wave_rows(b->bound, in.n, in.desc.dx, in.desc.dt, src.waves[0]);
+    LBM_HIP(launch_wave_rows(&wr, 1, steps, layers, b->stream));
+  }
   const int kind = in.desc.bc == LBM_BC_DIRICHLET_EQ ? 1 : 2;
   LBM_HIP(hipEventRecord(b->ev0, b->stream));
   for (int64_t t = 0; t < steps; ++t) {
@@ -2766,10 +2795,9 @@ lbm_status lbm_wave_rows(lbm_problem h, int64_t steps, const lbm_wave* w, int32_
   const size_t need = (size_t)steps * 2 * layers;
   s = bound_rows_buffer(b, need);
   if (s != LBM_OK) return s;
-  RowSource src;
-  src.waves = w;
-  s = fill_rows(b, 0, src, b->bound, steps, layers);
-  if (s != LBM_OK) return s;
+  const HostInst& in = b->inst[0];
+  const WaveRows wr = wave_rows(b->bound, in.n, in.desc.dx, in.desc.dt, *w);
+  LBM_HIP(launch_wave_rows(&wr, 1, steps, layers, b->stream));
   LBM_HIP(hipStreamSynchronize(b->stream));
   LBM_HIP(hipMemcpy(out, b->bound, sizeof(double) * need, hipMemcpyDeviceToHost));
   return LBM_OK;

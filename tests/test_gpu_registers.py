@@ -137,3 +137,26 @@ def test_mixed_batch_of_slabs_tiles_and_rings_equals_solo():
         if k < 12 or k > 235:
             assert np.array_equal(got, _run(ps[k], phis[k], (steps[k], 37), lbm.PATH_STREAM)), k
     b.close()
+
+
+# bounded instances: one wave (in LDS) and the fewest nodes of two, odd and even places of the interior
+# node, the most nodes of 16 waves and one more (in LDS again); 6 layers are the most computed on D1Q5
+@pytest.mark.parametrize("n", [63, 112, 113, 114, 801, 1791, 1792, 1793])
+@pytest.mark.parametrize("kind", ["kdv", "mkdv", "d1q4"])
+@pytest.mark.parametrize("prec", [W.F64, W.F32_DEV, W.F32_DEV_ARITH32])
+def test_bounded_resident_equals_stream_at_wave_edges(kind, n, prec):
+    p, phi0 = _problem(kind, n, prec)
+    for bc, layers in ((1, p.lattice() // 2), (2, p.lattice() // 2), (2, 6), (2, 7)):
+        p = dataclasses.replace(p, bc=bc)
+        say("case bounded registers", kind, n, prec, bc, layers)
+        outs = []
+        for path in (lbm.PATH_STREAM, lbm.PATH_RESIDENT):
+            s = lbm.Solver(p)
+            s.set_path(path)
+            s.load_phi(phi0)
+            for steps in (1, 2, 3, 4, 5, 34):
+                rows = np.random.default_rng(steps).uniform(0.35, 0.45, (steps, 2 * layers))
+                s.advance_bounded(rows)
+            outs.append(s.read_phi())
+            s.close()
+        assert np.array_equal(outs[0], outs[1]), (bc, layers)
