@@ -903,9 +903,10 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
   return found;
 }
 
-// A step of one instance alone on a CU, in VALU operations of a wave.
-double ring_step(int q, int prec, int code, int n) {
-  double least = 1e30;
+// A step of one instance alone on a CU, in VALU operations of a wave; `share`: of
+// the CU's time in a full GPU, at least.
+double ring_step(int q, int prec, int code, int n, double* share = nullptr) {
+  double least = 1e30, part = 1e30;
   for (int cls = 0; cls < 2; ++cls) {
     RegFit menu[kRegWidths + 1];
     const int widths = reg_menu(q, prec, code, cls != 0, menu);
@@ -913,8 +914,12 @@ double ring_step(int q, int prec, int code, int n) {
       reg_place(q, n, &menu[k]);
       if (menu[k].waves > reg_waves(cls != 0)) continue;
       least = std::min(least, reg_step(menu[k], (menu[k].waves + 3) / 4));
+      // (as many whole instances as a CU's waves hold)
+      const int hold = reg_waves(cls != 0) / menu[k].waves;
+      part = std::min(part, reg_step(menu[k], (hold * menu[k].waves + 3) / 4) / hold);
     }
   }
+  if (share) *share = part;
   return least;
 }
 
@@ -1173,15 +1178,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   }
   // register-resident jobs: ring segments of one variant, step count and width,
   // bin-packed by waves
-  double reg_work = 0.0;   // node updates x operations of all groups
-  std::vector<double> group_work;
-  for (const auto& group : reg) {
-    double w = 0.0;
-    for (int i : group.second) w += (double)steps[i] * b->inst[i].n;
-    const int D = std::get<2>(group.first) & 0xff;
-    group_work.push_back(w * (std::get<0>(group.first) * (D + 3)));
-    reg_work += group_work.back();
-  }
   // Slabs and tiles.  Every group takes its share of the CUs, so that the
   // launches run side by side; where one needs more workgroups than that at
   // once, the launches run one after another, each over the whole GPU.  What
@@ -1192,14 +1188,14 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   std::vector<std::pair<int, int>> flips;   // (instance, buffer exchanges)
   size_t strips_need = 0;  // words
   int slab_cus = 0;        // workgroups of all slab launches
-  double spread_work = 0.0;
+  double all_work = 1.0;   // node updates x operations of all register groups
   auto work_of = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g) {
     double w = 0.0;
     for (int i : g) w += (double)steps[i] * b->inst[i].n;
     return w * (std::get<0>(key) * ((std::get<2>(key) & 0xff) + 3));
   };
-  for (const auto& group : spread) spread_work += work_of(group.first, group.second);
-  const double spread_all = std::max(1.0, reg_work + spread_work);
+  for (const auto* part : {&reg, &spread})
+    for (const auto& group : *part) all_work += work_of(group.first, group.second);
   // one group's launches: rounds of slabs (at most `cus` workgroups' places each), or tiles
   auto add_segs = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g, const SegPlan& p, int cus,
                       bool tile) -> lbm_status {
@@ -1297,8 +1293,36 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     };
     auto plan = [&](const std::tuple<int, int, int>& key, const std::map<int, int>& sizes, int cus, int want, bool tile,
                     SegPlan* p) {
-      return seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile, p);
+      // (steps asked for that no segment's halos hold are halved)
+      while (!seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile, p)) {
+        if (want <= (tile ? 1 : 2)) return false;
+        want = tile ? want / 2 : want / 4 * 2;
+      }
+      return true;
     };
+    // Whole instances instead where enough of them fill the GPU: the group's
+    // waves over the CUs, no exchange between workgroups and no rounds of
+    // launches.
+    for (auto it = spread.begin(); it != spread.end();) {
+      const auto& key = it->first;
+      const int q = std::get<0>(key), pr = std::get<1>(key), code = std::get<2>(key);
+      double longest = 0.0, sum = 0.0;
+      for (int i : it->second) {
+        double step = 0.0;
+        const double one = ring_step(q, pr, code, b->inst[i].n, &step);
+        longest = std::max(longest, one);
+        sum += step / b->lim.cus;
+      }
+      SegPlan p;
+      const bool whole = b->path == 0 && longest < 1e29 && b->tile_steps == 0 && b->tile_wgs == 0 &&
+                         (!plan(key, sizes_of(it->second), b->lim.cus, slab_steps, false, &p) ||
+                          std::max(longest, sum) < p.est);
+      if (whole) {
+        std::vector<int>& to = reg[key];
+        to.insert(to.end(), it->second.begin(), it->second.end());
+      }
+      it = whole ? spread.erase(it) : std::next(it);
+    }
     // what no slab plan takes goes by tiles
     std::vector<SegPlan> plans;     // over the whole GPU, then those taken
     std::vector<int> places;
@@ -1352,7 +1376,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       bool ok = true;
       for (const auto& [key, g] : spread) {
         SegPlan p;
-        cus.push_back(std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / spread_all)));
+        cus.push_back(std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / all_work)));
         ok = ok && plan(key, sizes_of(g), cus.back(), slab_steps, false, &p);
         shared.push_back(p);
       }
@@ -1377,14 +1401,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   std::vector<double> reg_job_est;
   double reg_est = 0.0;    // estimated CU time of all register launches
   int64_t reg_jobs = 0;
-  size_t gi = 0;
   for (const auto& group : reg) {
     const int q = std::get<0>(group.first), pr = std::get<1>(group.first), code = std::get<2>(group.first);
     const std::vector<int>& g = group.second;
     const int es = pr != 0 ? 4 : 8;
     const bool bounded = (code >> 16) != 0;
     // the CUs that are this group's by its share of the pass's work
-    const double cus = std::max(1.0, b->lim.cus * group_work[gi++] / spread_all);
+    const double cus = std::max(1.0, b->lim.cus * work_of(group.first, group.second) / all_work);
     // Nodes per lane: few spend more on halos and lane edges, many leave more of
     // an instance's last lanes empty and give fewer waves to share the SIMDs.
     // Each instance takes the width with the least wave time among one kernel's

@@ -108,7 +108,7 @@ def test_slabs_and_tiles_equal_stream(kind, n, prec):
     say("case segments", kind, n, prec)
     want = _run(p, phi0, steps, lbm.PATH_STREAM)
     for path in (lbm.PATH_SLAB, lbm.PATH_TILED):
-        for tiling in ((0, 0), (6, 1), (24, 8), (3, 2)):
+        for tiling in ((0, 0), (6, 1), (24, 8), (3, 2), (4096, 8)):
             s = lbm.Solver(p)
             s.set_path(path)
             s.set_tiling(*tiling)
