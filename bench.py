@@ -70,7 +70,7 @@ PEAK_VALU_TFLOPS = 78.6      # 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz x 2 flop/FM
 PEAK_VALU_TOPS = 39.3        # the same issue rate counted in operations (FMA = 1): 3.93e13 lane ops/s
 GOLDEN = os.path.join(ROOT, "tests", "golden", "long_horizon.npz")
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "hbm_counters_kdv_mkdv_batch4096.md")
-KERNEL_SOURCES = ("kernels_body.hpp", "kernels_q.hip", "kernels.hip", "device.hpp", "kernels.hpp", "runtime.cpp")
+KERNEL_SOURCES = ("kernels_body.hpp", "kernels_q.hip", "reg_body.hpp", "kernels_reg.hip", "kernels.hip", "device.hpp", "kernels.hpp", "runtime.cpp")
 
 
 def kernel_source_digest() -> str:
@@ -652,7 +652,7 @@ def main():
     traffic = measured_traffic() if default_plan else None
     achieved_ops = r32["ops_pass"] / (k_ms * 1e-3) / 1e12
     achieved = r32["flops_pass"] / (k_ms * 1e-3) / 1e12
-    kernel = "k_resident<5, D, P, float, double>: KdV (D 5) and mKdV (D 9, odd) launches of one pass"
+    kernel = "k_reg<5, ring, D, P, float, double>: KdV (D 5) and mKdV (D 9, odd) launches of one pass"
     roofline = {"bound": "alu", "achieved": achieved_ops, "peak": PEAK_VALU_TOPS, "unit": "Tops/s",
                 "frac": achieved_ops / PEAK_VALU_TOPS, "traffic": traffic, "traffic_unit": "HBM bytes per pass",
                 "accounting": "VALU lane operations of one node update (FMA = 1): 39 per KdV, 40 per mKdV node "

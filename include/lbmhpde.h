@@ -174,7 +174,7 @@ lbm_status lbm_advance(lbm_problem h, int64_t steps);
    harnesses that forbid hipMalloc): lbm_create + lbm_load_phi + lbm_advance +
    lbm_read_phi of one periodic problem in one call that allocates nothing.
    phi0 and phi are caller-owned device arrays of d->n doubles (they may be the
-   same array); f := f_eq(phi0), `steps` steps on the LDS-resident path, phi :=
+   same array); f := f_eq(phi0), `steps` steps on the resident path, phi :=
    sum_j f_j -- the kernels of lbm_advance, so the result is bitwise the one of
    the handle calls.  Every device buffer besides phi0 and phi (coefficient and
    job tables, queue words, status flags, the state) lies in one fixed array of
@@ -197,7 +197,7 @@ lbm_status lbm_advance_noalloc(const lbm_desc* d, const double* phi0, int64_t st
    steps already taken.  phib is a host array of steps * 2 * layers doubles,
    copied before the call returns.  layers = 0 means q/2; layers must lie in
    [q/2, 32] and n >= 2 layers + 2.  A state that fits one workgroup's LDS
-   advances on the resident path (the layers reset in LDS after every step;
+   advances on the resident path (the layers reset on chip after every step;
    steps <= 2^30), otherwise -- or with lbm_set_path(LBM path 1) -- each step
    is one fused collide+stream launch through HBM plus one boundary launch;
    both give bitwise equal results.  INVALID_ARG for a periodic problem or bad
@@ -251,20 +251,23 @@ lbm_status lbm_save_f(lbm_problem h, void* host_buf, size_t bytes);
 lbm_status lbm_load_f(lbm_problem h, const void* host_buf, size_t bytes);
 
 /* Kernel path for lbm_advance: 0 = automatic (resident when the state fits one
-   workgroup's LDS, else temporal blocking), 1 = HBM streaming (one fused
+   workgroup's LDS and slabs would not end sooner, else slabs), 1 = HBM streaming (one fused
    collide+stream launch per step), 2 = on-chip resident (all steps of a call
    in one launch; UNSUPPORTED if the state does not fit), 3 = temporal blocking
-   (tiles of the grid with halos advance several steps per launch in LDS),
+   (tiles of the grid with halos advance several steps per launch on chip),
    4 = slabs (the grid split over workgroups that are resident together for
    all steps of the call and exchange halos every few steps; the automatic
    choice for grids larger than one workgroup's LDS, with temporal blocking
-   as the fallback when the slabs do not fit one launch). */
+   as the fallback when the slabs do not fit one launch).  On paths 2, 3 and 4
+   the state of a polynomial equilibrium stays in registers during the steps,
+   that of a power sum in LDS; the limits are the same. */
 lbm_status lbm_set_path(lbm_problem h, int32_t path);
 
 /* Temporal blocking and slab parameters: steps per launch, or per halo
    exchange of the slab path (rounded up to even there) (0 = automatic, <= 4096),
-   and the number of workgroups per CU the 160 KiB LDS is split for
-   (0 = automatic, <= 8), which sets the tile and slab width. */
+   and the number of workgroups per CU that a CU's LDS (or waves) are split
+   for (0 = automatic, <= 8), which sets the tile and slab width.  Steps that
+   no tile's or slab's halos can hold are lowered. */
 lbm_status lbm_set_tiling(lbm_problem h, int32_t steps_per_launch, int32_t wgs_per_cu);
 
 /* Device time of the kernels of the last lbm_advance, in ms (HIP events). */
