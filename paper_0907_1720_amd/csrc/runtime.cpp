@@ -33,6 +33,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kMaxSlabs = 2048;       // workgroups of one slab launch
+constexpr int kUnevenNodes = 256;     // smallest power-sum grid split where its group is uneven
 constexpr int kSplitNodes = 1024;     // smallest power-sum grid split into slabs when the GPU is mostly idle
 constexpr int kMaxResidentGrid = 256 * 8;
 constexpr int kMaxLaunches = 512;     // queue launches per advance pass (one per lattice, precision, variant, kernel)
@@ -966,6 +967,23 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
                      p.est < 0.95 * ring_step(h.q, h.prec, h.D, h.n);
     return b->sooner[key] = yes;
   };
+  // Power sums in LDS: an instance is one CU's work, so that a group ends with its
+  // largest one.  Where that takes more than one and a half times the even share
+  // of the CUs, the group goes in slabs of a quarter of an LDS (256 grids of 256
+  // to 4096 nodes, 2.9 times: 4.80 -> 2.49 ms per 1000 steps; half-LDS slabs
+  // 4.11, an eighth 2.62; 1024 such grids, 0.7 times, stay whole).
+  std::map<std::tuple<int, int, int>, std::pair<int64_t, int64_t>> loads;   // steps x nodes: all, largest
+  for (int i = 0; i < count; ++i) {
+    const HostInst& h = b->inst[i];
+    if (reg_variant(h.D) || h.desc.bc != LBM_BC_PERIODIC || steps[i] == 0) continue;
+    auto& l = loads[std::make_tuple(h.q, h.prec, h.D)];
+    l.first += steps[i] * h.n;
+    l.second = std::max<int64_t>(l.second, steps[i] * h.n);
+  }
+  auto uneven = [&](const HostInst& h) {
+    const auto& l = loads[std::make_tuple(h.q, h.prec, h.D)];
+    return b->path == 0 && b->res_grid == 0 && b->res_chunks == 0 && b->tile_wgs == 0 && 2.0 * b->lim.cus * l.second > 3.0 * l.first;
+  };
   const int slab_wgs = b->tile_wgs > 0 ? b->tile_wgs : latency && 4 * all_bytes < lds_all ? 8 : 2;
   for (int i = 0; i < count; ++i) {
     if (steps[i] == 0) continue;
@@ -1001,6 +1019,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       slb[std::make_tuple(h.q, h.prec, h.D, slab_wgs)].push_back(i);
     else if (!in_reg && latency && h.n >= kSplitNodes)
       slb[std::make_tuple(h.q, h.prec, h.D, 8)].push_back(i);
+    else if (!in_reg && !latency && h.n >= kUnevenNodes && uneven(h))
+      slb[std::make_tuple(h.q, h.prec, h.D, 4)].push_back(i);
     else if (in_reg)
       reg[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else
