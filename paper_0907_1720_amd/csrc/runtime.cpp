@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <new>
 #include <vector>
@@ -922,6 +923,49 @@ double ring_step(int q, int prec, int code, int n, double* share = nullptr) {
   }
   if (share) *share = part;
   return least;
+}
+
+// Slab workgroups of all batches of this process on one GPU.  A slab launch ends
+// only if all its workgroups get a place; two launches that each hold places the
+// other waits for would not.  So the launches in flight together never count more
+// workgroups than the GPU has CUs: a workgroup that waits for a place then has an
+// empty CU, or one whose kernel waits for no slab.  A launch that would exceed
+// that waits, on the device, for the ones issued before it.
+struct SlabGate {
+  std::mutex mu;
+  std::vector<std::pair<hipEvent_t, int>> flight;   // (done, workgroups), in the order of issue
+};
+SlabGate& slab_gate() {
+  static SlabGate gates[64];
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  return gates[dev & 63];
+}
+// waits of `stream` before a launch of `need` workgroups (gate held)
+lbm_status pass_gate(SlabGate& gate, int need, int cus, hipStream_t stream) {
+  auto& fl = gate.flight;
+  int sum = 0;
+  for (size_t k = 0; k < fl.size();) {
+    if (hipEventQuery(fl[k].first) == hipSuccess) {
+      LBM_HIP(hipEventDestroy(fl[k].first));
+      fl.erase(fl.begin() + k);
+    } else {
+      sum += fl[k++].second;
+    }
+  }
+  (void)hipGetLastError();   // (an event that is not ready is no error)
+  for (size_t k = 0; k < fl.size() && sum + need > cus; ++k) {
+    LBM_HIP(hipStreamWaitEvent(stream, fl[k].first, 0));
+    sum -= fl[k].second;
+  }
+  return LBM_OK;
+}
+lbm_status enter_gate(SlabGate& gate, int need, hipStream_t stream) {
+  hipEvent_t done;
+  LBM_HIP(hipEventCreateWithFlags(&done, hipEventDisableTiming));
+  LBM_HIP(hipEventRecord(done, stream));
+  gate.flight.push_back({done, need});
+  return LBM_OK;
 }
 
 // One pass: every instance advances by steps[i] <= kMaxStepsPerLaunch.
@@ -2071,6 +2115,18 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     std::stable_sort(items.begin(), items.end(), [](const LaneItem& x, const LaneItem& y) { return x.est > y.est; });
   std::vector<double> lane_load(nlanes, 0.0);
   std::vector<char> lane_forked(nlanes, 0);
+  SlabGate& gate = slab_gate();
+  std::unique_lock<std::mutex> gate_lock;
+  int gate_need = 0;
+  for (const SegLaunch& L : segs)
+    if (!L.tile) gate_need = segs_side_by_side ? slab_cus : std::max(gate_need, L.count);
+  for (const SlabLaunch& L : slaunch) gate_need += L.count;
+  gate_need = std::min(gate_need, b->lim.cus);
+  if (gate_need > 0) {
+    gate_lock = std::unique_lock<std::mutex>(gate.mu);
+    lbm_status gs = pass_gate(gate, gate_need, b->lim.cus, b->stream);
+    if (gs != LBM_OK) return gs;
+  }
   int64_t strip_tags = 0;   // of this pass
   for (const SegLaunch& L : segs) strip_tags += L.blocks;
   if (strips_need > 0 && b->strip_tag + strip_tags >= UINT32_MAX) {
@@ -2191,6 +2247,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     }
   }
   LBM_HIP(hipEventRecord(b->items_done[k], b->stream));
+  if (gate_need > 0) {
+    lbm_status gs = enter_gate(gate, gate_need, b->stream);
+    if (gs != LBM_OK) return gs;
+    gate_lock.unlock();
+  }
   // streaming instances: one fused collide+stream launch per step, whole
   // blocks of kStepBlock steps replayed from a graph
   for (int i : str) {
