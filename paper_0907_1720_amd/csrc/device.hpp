@@ -159,6 +159,15 @@ __host__ __device__ constexpr int opposite(int j) {
   else return j ^ 1;
 }
 
+// all of this wave's vector memory operations have completed
+__device__ __forceinline__ void wait_vector_memory() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) expcnt(7) lgkmcnt(15)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#endif
+}
+
 // ---- a1 + a2 + a3 + a4: phi = sum_j f_j, f_eq_j(phi) by Horner, BGK ----
 //
 // Storage type T, arithmetic type A; the zeroth moment is always summed in

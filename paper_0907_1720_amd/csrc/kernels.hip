@@ -19,10 +19,20 @@ namespace lbm {
 // phi may lie in pinned host memory: the values cross to the host as they are
 // summed, instead of a read-out buffer and three copies (55 -> 16 us per call
 // of 1400 nodes).  With seq > 0 each workgroup that has finished stores words[2 +
-// blockIdx] = seq at system scope, and the host watches those words: the stream's
-// completion signal and its handling took longer than the kernel (a word that the
-// last of counted workgroups stores cost another 0.9 of 10.5 us).  One workgroup alone writes
-// only 4 GB/s across the link (8192 nodes: 18 us).
+// blockIdx] = seq, and the host watches those words: the stream's completion
+// signal and its handling took longer than the kernel (a word that the last of
+// counted workgroups stores cost another 0.9 of 10.5 us).  The barrier does not
+// wait for other waves' stores that are still on their way, so there every value
+// goes past the caches (a system-scope store), and every wave waits for its own
+// before the barrier that the word's store follows (10.2 us per read of 1400
+// nodes; 10.5 with a write-back of the whole cache before the word).  One
+// workgroup alone writes only 4 GB/s across the link (8192 nodes: 18 us).
+__device__ __forceinline__ void put_word(int* p, int v, bool watched) {
+  if (watched)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  else
+    *p = v;
+}
 template <typename T>
 __global__ __launch_bounds__(256) void k_read(const T* __restrict__ f, double* __restrict__ phi, int n, int stride,
                                               int q, double phi_rest, const int* __restrict__ status,
@@ -30,18 +40,22 @@ __global__ __launch_bounds__(256) void k_read(const T* __restrict__ f, double* _
                                               const int* __restrict__ bad) {
   const int x = blockIdx.x * 256 + threadIdx.x;
   if (bad && *bad) return;   // phi0 was refused: phi stays as it was
-  if (x == 0) words[0] = *status;
+  const bool watched = seq > 0;
+  if (x == 0) put_word(words, *status, watched);
   if (x < n) {
     double s = (double)f[x];
     for (int j = 1; j < q; ++j) s += (double)f[(int64_t)j * stride + x];
     s += phi_rest;
-    phi[x] = s;
-    if (!__builtin_isfinite(s)) words[1] = 1;   // (every writer stores the same word)
+    if (watched)
+      __hip_atomic_store(phi + x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    else
+      phi[x] = s;
+    if (!__builtin_isfinite(s)) put_word(words + 1, 1, watched);   // (every writer stores the same word)
   }
-  if (seq == 0) return;
+  if (!watched) return;
+  wait_vector_memory();
   __syncthreads();
-  if (threadIdx.x == 0)
-    __hip_atomic_store(words + 2 + blockIdx.x, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) put_word(words + 2 + blockIdx.x, seq, true);
 }
 
 // ---------------------------------------------------------------------------

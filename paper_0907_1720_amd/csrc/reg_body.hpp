@@ -234,14 +234,6 @@ __device__ __forceinline__ void reg_odd(T (&f)[R][Q], X& relax) {
   reg_scatter<Q, R>(n, f);
 }
 
-
-// all of this wave's vector memory operations have completed
-__device__ __forceinline__ void wait_vector_memory() {
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) expcnt(7) lgkmcnt(15)
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
 template <typename T>
 __device__ __forceinline__ void store_agent(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
