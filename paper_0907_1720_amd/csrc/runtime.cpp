@@ -1260,8 +1260,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   };
   for (const auto* part : {&reg, &spread})
     for (const auto& group : *part) all_work += work_of(group.first, group.second);
-  // one group's launches: rounds of slabs (at most `cus` workgroups' places each), or tiles
-  auto add_segs = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g, const SegPlan& p, int cus,
+  // One group's launches: slabs, or tiles.  `together`: the workgroups of all slab
+  // groups find a CU at once, so that the group is one launch beside the others;
+  // else it has the GPU to itself, in as many launches as that takes.
+  bool in_chunks = false;   // a group's steps are cut into chunks: its launches must keep their order
+  auto add_segs = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g, const SegPlan& p, bool together,
                       bool tile) -> lbm_status {
     const int q = std::get<0>(key), pr = std::get<1>(key), code = std::get<2>(key), R = p.f.R;
     const size_t es = pr != 0 ? 4 : 8;
@@ -1270,7 +1273,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     int per_cu = 0;
     LBM_HIP(seg_occupancy(q, pr, code, p.f.wide, 64 * p.waves, L.lds, &per_cu));
     if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
-    const int64_t capacity = (int64_t)std::min(per_cu, p.per_cu) * cus;
+    const int64_t capacity = together ? b->lim.cus : (int64_t)std::min(per_cu, p.per_cu) * b->lim.cus;
     int64_t total = 0, maxsteps = 0;
     for (int i : g) {
       total += seg_count(p, q, b->inst[i].n, tile);
@@ -1294,6 +1297,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         }
       }
       share = (total * nch + launches_for(nch) - 1) / launches_for(nch);
+      in_chunks |= nch > 1;
     }
     auto close = [&] {
       if (L.count == 0) return;
@@ -1389,7 +1393,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     }
     // what no slab plan takes goes by tiles
     std::vector<SegPlan> plans;     // over the whole GPU, then those taken
-    std::vector<int> places;
     for (auto it = spread.begin(); it != spread.end();) {
       const auto& key = it->first;
       std::vector<int>& g = it->second;
@@ -1414,10 +1417,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         }
       }
       if (!g.empty()) plans.push_back(p);
-      places.push_back(b->lim.cus);
       it = g.empty() ? spread.erase(it) : std::next(it);
     }
-    places.resize(plans.size());
     for (const auto* part : {&spread, &rtile})
       for (const auto& group : *part) {
         lbm_status st = ensure_second_buffer(b, std::get<1>(group.first) != 0);
@@ -1434,31 +1435,31 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       }
       return total;
     };
-    if (spread.size() > 1 && places_of(plans) > b->lim.cus) {
+    bool together = places_of(plans) <= b->lim.cus;
+    if (spread.size() > 1 && !together) {
       std::vector<SegPlan> shared;
-      std::vector<int> cus;
       bool ok = true;
       for (const auto& [key, g] : spread) {
         SegPlan p;
-        cus.push_back(std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / all_work)));
-        ok = ok && plan(key, sizes_of(g), cus.back(), slab_steps, false, &p);
+        const int cus = std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / all_work));
+        ok = ok && plan(key, sizes_of(g), cus, slab_steps, false, &p);
         shared.push_back(p);
       }
       if (ok && places_of(shared) <= b->lim.cus) {
         plans.swap(shared);
-        places.swap(cus);
+        together = true;
       }
     }
     size_t at = 0;
     for (const auto& [key, g] : spread) {
-      lbm_status st = add_segs(key, g, plans[at], places[at], false);
+      lbm_status st = add_segs(key, g, plans[at], together, false);
       if (st != LBM_OK) return st;
       ++at;
     }
     for (const auto& [key, g] : rtile) {
       SegPlan p;
       if (!plan(key, sizes_of(g), b->lim.cus, b->tile_steps, true, &p)) return LBM_ERR_UNSUPPORTED;
-      lbm_status st = add_segs(key, g, p, b->lim.cus, true);
+      lbm_status st = add_segs(key, g, p, false, true);
       if (st != LBM_OK) return st;
     }
   }
@@ -2082,11 +2083,12 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // order, unless all of them fit the GPU twice over
   // (register slabs plan a place for every workgroup: side by side as long as
   // there is a CU for each of all their workgroups -- one that waits for a place
-  // then has an empty CU, or a CU whose kernel waits for no slab)
+  // then has an empty CU, or a CU whose kernel waits for no slab -- and no group
+  // is cut into step chunks, which read what the chunk before them wrote)
   // kind 0 resident, 1 tiled, 2 slab (-1: the chain), 3 register slab or tile
   struct LaneItem { int kind; int idx; double est; };
   std::vector<LaneItem> items;
-  const bool segs_side_by_side = slaunch.empty() && slab_cus <= b->lim.cus;
+  const bool segs_side_by_side = slaunch.empty() && !in_chunks && slab_cus <= b->lim.cus;
   double chain_est = 0.0;
   bool chain = false;
   for (size_t l = 0; l < segs.size(); ++l) {
