@@ -1280,8 +1280,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       maxsteps = std::max<int64_t>(maxsteps, steps[i]);
     }
     // More slabs than a launch holds: the steps are cut into chunks, whose
-    // (instance, chunk) items fill the launches evenly in chunk order; an
-    // instance's chunk c + 1 always lies in a later launch than its chunk c.
+    // (instance, chunk) items fill the launches evenly in chunk order.  Instances
+    // of fewer steps than chunks drop out of the later ones, so that a launch may
+    // take items of several chunks; it is closed before a second one of an
+    // instance, whose chunk c + 1 must follow its chunk c.
     // c chunks cost (launches of c chunks) / c: the fewest within 3% of the
     // cheapest, each of kMinSlabChunk steps or more.
     int nch = 1;
@@ -1313,13 +1315,15 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       L.est = 0.0;
     };
     const int wave_nodes = (p.per_cu * p.waves + 3) / 4;
+    std::vector<size_t> in_launch(b->inst.size(), SIZE_MAX);   // the launch of an instance's last item
     for (int c = 0; c < nch; ++c)
       for (int i : g) {
         const HostInst& h = b->inst[i];
         const int64_t st = steps[i] / nch + (c < steps[i] % nch ? 1 : 0);
         if (st == 0) continue;
         const int ks = seg_count(p, q, h.n, tile), all = (h.n + R - 1) / R;
-        if (!tile && (L.count + ks > capacity || L.count >= share)) close();
+        if (!tile && (L.count + ks > capacity || L.count >= share || in_launch[i] == segs.size())) close();
+        in_launch[i] = segs.size();
         L.est = std::max(L.est, (double)st * wave_nodes * p.f.cost);
         L.blocks = std::max<int64_t>(L.blocks, (st + p.sx - 1) / p.sx);
         const int from = h.cur ^ (c & 1);   // each earlier chunk flipped the buffer once
@@ -1708,9 +1712,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // group's instances need several launches, their steps are split into
   // chunks and the (instance, chunk) items fill the launches in chunk-major
   // order, an even share each (without chunks, a last launch with a few
-  // instances costs a whole launch's time).  An instance's chunk c + 1 always
-  // lies in a later launch than its chunk c (a launch holds less than one
-  // chunk's items plus one instance), which the lane's order serialises.
+  // instances costs a whole launch's time).  A launch is closed before a second
+  // item of an instance (one of fewer steps than chunks leaves the later chunks
+  // smaller), so that an instance's chunk c + 1 lies in a later launch than its
+  // chunk c, which the lane's order serialises.
   struct SlabLaunch { int q; int prec; int code; int first, count, cap, s, halo, block; size_t lds; size_t xoff; int foff; double est; };
   std::vector<SlabLaunch> slaunch;
   std::vector<DevSlab> svec;
@@ -1801,6 +1806,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       // its steps faster but still about as long as a full one
       const int64_t share = total * nch > capacity ? (total * nch + launches_for(nch) - 1) / launches_for(nch)
                                                    : capacity;
+      std::vector<size_t> in_launch(b->inst.size(), SIZE_MAX);   // the launch of an instance's last item
       for (int c = 0; c < nch; ++c) {
         for (const auto& [i, ks] : mem) {
           const HostInst& h = b->inst[i];
@@ -1808,12 +1814,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
           const int64_t st = base + (c < rem ? 1 : 0);
           if (st == 0) continue;
           const int core = (h.n + ks - 1) / ks;
-          if (L.count + ks > capacity || L.count >= share) {
+          if (L.count + ks > capacity || L.count >= share || in_launch[i] == slaunch.size()) {
             slaunch.push_back(L);
             L.first = (int)svec.size();
             L.count = 0;
             L.est = 0.0;
           }
+          in_launch[i] = slaunch.size();
           // duration estimate, in the unit of the resident jobs' (steps x nodes
           // of the busiest thread x arithmetic per node)
           L.est = std::max(L.est, (double)st * ((core + 2 * halo + block - 1) / block) * (q * ((h.D & 0xff) + 3)));

@@ -52,3 +52,9 @@ def _check(name, problems, steps, sample):
 def test_groups_on_their_shares_of_the_gpu_equal_stream():
     ps = [_problem("kdv", 4324, W.F32_DEV)] * 3 + [_problem("mkdv", 41530, W.F32_DEV)] * 20
     _check("shares", ps, [4000, 600, 600] + [1000] * 20, range(23))
+
+
+@pytest.mark.parametrize("kind,n,few,many,steps", [("power", 4096, 511, 1, 5000), ("kdv", 20000, 30, 30, 4000)])
+def test_instances_of_fewer_steps_than_chunks_equal_stream(kind, n, few, many, steps):
+    ps = [_problem(kind, n, W.F64)] * (few + many)
+    _check(f"few steps {kind}", ps, [1] * few + [steps] * many, [0, few - 1] + list(range(few, few + many)))

@@ -49,3 +49,29 @@ def test_step_chunks_of_a_group_on_its_share_of_the_gpu_stay_in_order(host):
     P = problem
     advance(host, [P("kdv", 4324, W.F32_DEV)] * 3 + [P("mkdv", 41530, W.F32_DEV)] * 20, [4000, 600, 600] + [1000] * 20)
     advance(host, [P("kdv", 229000)] * 2 + [P("kdv", 20000, W.F32_DEV)] * 4 + [P("kdv", 1024)] * 2650, [4000] * 2656)
+
+
+@pytest.mark.parametrize("kind,prec,n,few,many", [("power", W.F64, 4096, [1] * 511, [5000]),
+                                                  ("kdv", W.F64, 20000, [1] * 30, [4000] * 30),
+                                                  ("kdv", W.F64, 50000, [1] * 20, [4000] * 20)])
+def test_a_launch_holds_one_step_chunk_of_an_instance(host, kind, prec, n, few, many):
+    """Instances of fewer steps than chunks drop out of the later chunks."""
+    steps = few + many
+    launches = advance(host, [problem(kind, n, prec)] * len(steps), steps)
+    assert sum(r[0] in (H.SLABS, H.LDS_SLABS) for r in launches) > 1
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_random_mixed_batches_do_every_step_in_order(host, seed):
+    rng = np.random.default_rng([20261205, seed])
+    count = int(np.exp(rng.uniform(np.log(4), np.log(300))))
+    top = rng.choice([4000, 16384, 60000])
+    kinds = ["kdv", "mkdv", "kawahara", "power"][: int(rng.integers(1, 5))]
+    ps, steps = [], []
+    for _ in range(count):
+        n = int(np.exp(rng.uniform(np.log(128), np.log(top))))
+        kind = kinds[int(rng.integers(len(kinds)))]
+        ps.append(problem(kind, n, int(rng.integers(2))))
+        steps.append(int(np.exp(rng.uniform(0, np.log(8000)))) if seed % 2 else [1000, 4000, 1][int(rng.integers(3))])
+    for path in (0, 3, 4):
+        advance(host, ps, steps, path)
