@@ -706,6 +706,7 @@ long long wait_ticks(const lbm_batch_s* b, int64_t steps) {
 constexpr int kChunkItems = 16;        // queue items per workgroup when jobs outnumber workgroups
 constexpr int64_t kMinChunkSteps = 256;
 constexpr int kMaxChunks = 64;
+constexpr int64_t kSlabLaunchSteps = 16;
 constexpr int64_t kMinSlabChunk = 256;   // steps of one chunk of a slab launch
 
 // Lanes a pass spreads its launches over.  HIP runs a process's streams on
@@ -923,6 +924,79 @@ double ring_step(int q, int prec, int code, int n, double* share = nullptr) {
   }
   if (share) *share = part;
   return least;
+}
+
+// Step chunks of a slab group that needs more workgroups than a launch holds.
+// The (instance, chunk) items fill the launches in chunk order, whole instances
+// at a time; a launch is closed before an item that exceeds `fill` workgroups and
+// before a second item of an instance (one of fewer steps than chunks leaves the
+// later chunks smaller), so that an instance's chunk c + 1 always lies in a later
+// launch than its chunk c.
+struct SlabChunks {
+  int chunks = 1;
+  int64_t fill = 0;   // workgroups a launch is filled to
+};
+int64_t chunk_steps(int64_t steps, int chunks, int c) { return steps / chunks + (c < steps % chunks ? 1 : 0); }
+// Launches of `chunks` chunks filled to `fill`; `time`: their longest items' steps,
+// added up (a launch lasts about its longest item's steps, whatever its fill).
+// mem: (workgroups, steps) of each instance.
+int slab_launches(const std::vector<std::pair<int, int64_t>>& mem, int chunks, int64_t fill, int64_t* time) {
+  int launches = 0, at = 0;
+  int64_t count = 0, longest = 0;
+  std::vector<int> in(mem.size(), 0);   // the launch of an instance's last item
+  *time = 0;
+  for (int c = 0; c < chunks; ++c)
+    for (size_t m = 0; m < mem.size(); ++m) {
+      const int64_t st = chunk_steps(mem[m].second, chunks, c);
+      if (st == 0) continue;
+      if (at == 0 || count + mem[m].first > fill || in[m] == at) {
+        at = ++launches;
+        *time += longest;
+        count = longest = 0;
+      }
+      in[m] = at;
+      count += mem[m].first;
+      longest = std::max(longest, st);
+    }
+  *time += longest;
+  return launches;
+}
+// The chunks, each of kMinSlabChunk steps or more, with the least time (a launch
+// of its own takes about as long as kSlabLaunchSteps steps: its states' way in and
+// out); and the least fill that needs no more launches, so that none is a short
+// tail that costs a whole launch's time (512 Kawahara and K(2,2) grids, FP32
+// storage, counted in workgroups instead of whole instances: 255, 255, 255 and 3,
+// 65.9 ms; counted as they are filled 58.5 ms).
+SlabChunks slab_chunks(const std::vector<std::pair<int, int64_t>>& mem, int64_t capacity) {
+  SlabChunks out;
+  out.fill = capacity;
+  int64_t total = 0, longest = 0, most = 0;
+  for (const auto& [slabs, steps] : mem) {
+    total += slabs;
+    longest = std::max(longest, steps);
+    most = std::max<int64_t>(most, slabs);
+  }
+  if (total <= capacity) return out;
+  int64_t time = 0, least = INT64_MAX;
+  int launches = 0;
+  for (int c = 1; c <= 8 && (c == 1 || longest / c >= kMinSlabChunk); ++c) {
+    int64_t t;
+    const int l = slab_launches(mem, c, capacity, &t);
+    if (t + l * kSlabLaunchSteps >= least) continue;
+    least = t + l * kSlabLaunchSteps;
+    out.chunks = c;
+    launches = l;
+    time = t;
+  }
+  for (int64_t lo = most, hi = capacity; lo < hi;) {
+    const int64_t mid = (lo + hi) / 2;
+    int64_t t;
+    if (slab_launches(mem, out.chunks, mid, &t) <= launches && t <= time)
+      out.fill = hi = mid;
+    else
+      lo = mid + 1;
+  }
+  return out;
 }
 
 // Slab workgroups of all batches of this process on one GPU.  A slab launch ends
@@ -1274,32 +1348,12 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     LBM_HIP(seg_occupancy(q, pr, code, p.f.wide, 64 * p.waves, L.lds, &per_cu));
     if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
     const int64_t capacity = together ? b->lim.cus : (int64_t)std::min(per_cu, p.per_cu) * b->lim.cus;
-    int64_t total = 0, maxsteps = 0;
-    for (int i : g) {
-      total += seg_count(p, q, b->inst[i].n, tile);
-      maxsteps = std::max<int64_t>(maxsteps, steps[i]);
-    }
-    // More slabs than a launch holds: the steps are cut into chunks, whose
-    // (instance, chunk) items fill the launches evenly in chunk order.  Instances
-    // of fewer steps than chunks drop out of the later ones, so that a launch may
-    // take items of several chunks; it is closed before a second one of an
-    // instance, whose chunk c + 1 must follow its chunk c.
-    // c chunks cost (launches of c chunks) / c: the fewest within 3% of the
-    // cheapest, each of kMinSlabChunk steps or more.
-    int nch = 1;
-    int64_t share = capacity;
-    if (!tile && total > capacity) {
-      auto launches_for = [&](int c) { return (total * c + capacity - 1) / capacity; };
-      double least = 1e30;
-      for (int c = 1; c <= 8 && (c == 1 || maxsteps / c >= kMinSlabChunk); ++c) {
-        const double cost = (double)launches_for(c) / c;
-        if (cost < 0.97 * least) {
-          least = cost;
-          nch = c;
-        }
-      }
-      share = (total * nch + launches_for(nch) - 1) / launches_for(nch);
-      in_chunks |= nch > 1;
+    SlabChunks cut;
+    if (!tile) {
+      std::vector<std::pair<int, int64_t>> mem;
+      for (int i : g) mem.push_back({seg_count(p, q, b->inst[i].n, false), steps[i]});
+      cut = slab_chunks(mem, capacity);
+      in_chunks |= cut.chunks > 1;
     }
     auto close = [&] {
       if (L.count == 0) return;
@@ -1316,13 +1370,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     };
     const int wave_nodes = (p.per_cu * p.waves + 3) / 4;
     std::vector<size_t> in_launch(b->inst.size(), SIZE_MAX);   // the launch of an instance's last item
-    for (int c = 0; c < nch; ++c)
+    for (int c = 0; c < cut.chunks; ++c)
       for (int i : g) {
         const HostInst& h = b->inst[i];
-        const int64_t st = steps[i] / nch + (c < steps[i] % nch ? 1 : 0);
+        const int64_t st = chunk_steps(steps[i], cut.chunks, c);
         if (st == 0) continue;
         const int ks = seg_count(p, q, h.n, tile), all = (h.n + R - 1) / R;
-        if (!tile && (L.count + ks > capacity || L.count >= share || in_launch[i] == segs.size())) close();
+        if (!tile && (L.count + ks > cut.fill || in_launch[i] == segs.size())) close();
         in_launch[i] = segs.size();
         L.est = std::max(L.est, (double)st * wave_nodes * p.f.cost);
         L.blocks = std::max<int64_t>(L.blocks, (st + p.sx - 1) / p.sx);
@@ -1708,14 +1762,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // slab plan per (q, prec): cooperative launches of at most `capacity` slabs
   // (every workgroup of a launch resident at once), run one after another on
   // one lane; an instance whose slabs exceed one launch, or whose slabs would
-  // be narrower than a halo, goes to temporal blocking instead.  When a
-  // group's instances need several launches, their steps are split into
-  // chunks and the (instance, chunk) items fill the launches in chunk-major
-  // order, an even share each (without chunks, a last launch with a few
-  // instances costs a whole launch's time).  A launch is closed before a second
-  // item of an instance (one of fewer steps than chunks leaves the later chunks
-  // smaller), so that an instance's chunk c + 1 lies in a later launch than its
-  // chunk c, which the lane's order serialises.
+  // be narrower than a halo, goes to temporal blocking instead.  What needs
+  // several launches goes in step chunks (slab_chunks).
   struct SlabLaunch { int q; int prec; int code; int first, count, cap, s, halo, block; size_t lds; size_t xoff; int foff; double est; };
   std::vector<SlabLaunch> slaunch;
   std::vector<DevSlab> svec;
@@ -1757,7 +1805,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       SlabLaunch L{q, pr, code, (int)svec.size(), 0, capacity, sp, halo, block, lds, 0, 0, 0.0};
       // the instances that take slabs, their slab counts and core widths
       std::vector<std::pair<int, int>> mem;   // (instance, slabs)
-      int64_t total = 0, maxsteps = 0;
       for (int i : g) {
         const HostInst& h = b->inst[i];
         const int ks = cmax > 0 ? (h.n + cmax - 1) / cmax : 0;
@@ -1767,54 +1814,18 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
           continue;
         }
         mem.push_back({i, ks});
-        total += ks;
-        maxsteps = std::max<int64_t>(maxsteps, steps[i]);
       }
-      // step chunks: a launch lasts about its chunk's steps whatever its fill,
-      // so c chunks cost (launches needed for c chunks) / c; take the fewest
-      // chunks (at most 8, each >= kMinSlabChunk steps) within 3% of the
-      // cheapest, counting launches by packing whole instances as below
-      auto launches_for = [&](int c) {
-        int nl = 1, fill = 0;
-        for (int r = 0; r < c; ++r)
-          for (const auto& m : mem) {
-            if (fill + m.second > capacity) {
-              ++nl;
-              fill = 0;
-            }
-            fill += m.second;
-          }
-        return nl;
-      };
-      int nch = 1;
-      if (total > capacity && maxsteps >= 2 * kMinSlabChunk) {
-        double best = 1e30;
-        std::vector<double> cost(9, 1e30);
-        for (int c = 1; c <= 8 && maxsteps / c >= kMinSlabChunk; ++c) {
-          cost[c] = (double)launches_for(c) / c;
-          best = std::min(best, cost[c]);
-        }
-        for (int c = 1; c <= 8; ++c)
-          if (cost[c] <= 1.03 * best) {
-            nch = c;
-            break;
-          }
-      }
-      // the items spread evenly over that many launches (a launch is closed
-      // once it holds its share), so that no launch is a short tail: the
-      // packing above would fill all but the last, which, lightly loaded, runs
-      // its steps faster but still about as long as a full one
-      const int64_t share = total * nch > capacity ? (total * nch + launches_for(nch) - 1) / launches_for(nch)
-                                                   : capacity;
+      std::vector<std::pair<int, int64_t>> cost;
+      for (const auto& [i, ks] : mem) cost.push_back({ks, steps[i]});
+      const SlabChunks cut = slab_chunks(cost, capacity);
       std::vector<size_t> in_launch(b->inst.size(), SIZE_MAX);   // the launch of an instance's last item
-      for (int c = 0; c < nch; ++c) {
+      for (int c = 0; c < cut.chunks; ++c) {
         for (const auto& [i, ks] : mem) {
           const HostInst& h = b->inst[i];
-          const int64_t base = steps[i] / nch, rem = steps[i] % nch;
-          const int64_t st = base + (c < rem ? 1 : 0);
+          const int64_t st = chunk_steps(steps[i], cut.chunks, c);
           if (st == 0) continue;
           const int core = (h.n + ks - 1) / ks;
-          if (L.count + ks > capacity || L.count >= share || in_launch[i] == slaunch.size()) {
+          if (L.count + ks > cut.fill || in_launch[i] == slaunch.size()) {
             slaunch.push_back(L);
             L.first = (int)svec.size();
             L.count = 0;

@@ -32,7 +32,7 @@ void join(Clock* a, const Clock& b) {
 bool has(const Clock& a, int k) { return k < (int)a.size() && a[k]; }
 
 struct Access { int launch; bool write; };
-struct Record { int64_t kind, stream, groups, steps, tag, blocks; };
+struct Record { int64_t kind, stream, groups, steps, tag, blocks, width, jobs; };
 enum { kReg = 0, kSlabs = 1, kTiles = 2, kLds = 3, kLdsSlabs = 4, kLdsTiles = 5, kStream = 6, kRead = 7, kInit = 8 };
 
 struct World {
@@ -200,7 +200,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*,
 hipError_t hipGraphExecDestroy(hipGraphExec_t e) { delete (StubGraph*)e; return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t s) {
   const StubGraph* g = (const StubGraph*)e;
-  launch(s, {{word(g->in), true}, {word(g->out), true}}, {kStream, 0, 0, g->nodes, 0, 0});
+  launch(s, {{word(g->in), true}, {word(g->out), true}}, {kStream, 0, 0, g->nodes, 0, 0, 0, 0});
   w.done[word(g->in)] += g->nodes;
   return hipSuccess;
 }
@@ -218,7 +218,7 @@ hipError_t launch_init_many(bool, const DevInit* recs, int count, int, const Dev
     w.done[recs[k].dst] = 0;
     status[recs[k].inst] = 0;
   }
-  launch(s, what, {kInit, 0, count, 0, 0, 0});
+  launch(s, what, {kInit, 0, count, 0, 0, 0, 0, 0});
   return hipSuccess;
 }
 hipError_t launch_init_one(bool f32, const DevInit& r, const DevCoef* c, int* status, int*, hipStream_t s) {
@@ -232,7 +232,7 @@ hipError_t launch_check_phi(const double* phi, int n, int* words, hipStream_t) {
 hipError_t launch_read(bool, const void* f, double* phi, int n, int, int, double, const int* status, int* words, int seq,
                        const int*, hipStream_t s) {
   reachable(phi, sizeof(double) * n, "phi");
-  launch(s, {{word(f), false}}, {kRead, 0, 0, 0, 0, 0});
+  launch(s, {{word(f), false}}, {kRead, 0, 0, 0, 0, 0, 0, 0});
   words[0] = *status;
   if (inside(w.device, word(phi), 8) || inside(w.pinned, word(phi), 8))
     for (int k = 0; k < n; ++k) phi[k] = (double)w.done[word(f)];
@@ -242,7 +242,7 @@ hipError_t launch_read(bool, const void* f, double* phi, int n, int, int, double
 hipError_t launch_sum(const double*, int, double*, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_bound(int, int, int, void*, int, int, int, int, const double*, const DevCoef*, hipStream_t) { return hipSuccess; }
 hipError_t launch_stream(int, int, int, const void* in, void* out, int, int, const DevCoef*, hipStream_t s) {
-  launch(s, {{word(in), false}, {word(out), true}}, {kStream, 0, 0, 1, 0, 0});
+  launch(s, {{word(in), false}, {word(out), true}}, {kStream, 0, 0, 1, 0, 0, 0, 0});
   w.done[word(out)] = w.done[word(in)] + 1;
   return hipSuccess;
 }
@@ -257,23 +257,27 @@ hipError_t launch_resident(int, int, int, const DevJob* jobs, const DevJobInst* 
       what.push_back({inst[u].addr, true});
       w.done[inst[u].addr] += jobs[k].steps;
     }
-  launch(s, what, {kLds, 0, grid, 0, 0, 0});
+  launch(s, what, {kLds, 0, grid, 0, 0, 0, 0, 0});
   return hipSuccess;
 }
 hipError_t launch_reg(int, int, int, bool, const DevItem* items, int nitems, const DevJob* jobs, const DevSeg* segs, int*,
                       int*, const DevCoef*, int*, long long, int, int grid, int, size_t, hipStream_t s) {
   std::vector<Touch> what;
+  std::set<int> seen;
+  int64_t width = 0;   // the widest job's nodes per lane
   for (int k = 0; k < nitems; ++k) {
     const DevJob& j = jobs[items[k].job];
+    seen.insert(items[k].job);
+    width = width > j.nodes ? width : j.nodes;
     for (int u = j.first; u < j.first + j.count; ++u) {
       what.push_back({segs[u].in, true});
       w.done[segs[u].in] += items[k].steps;
     }
   }
-  launch(s, what, {kReg, 0, grid, 0, 0, 0});
+  launch(s, what, {kReg, 0, grid, 0, 0, 0, width, (int64_t)seen.size()});
   return hipSuccess;
 }
-hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int, int, int sx, bool tile, int turn, void*,
+hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int width, int, int sx, bool tile, int turn, void*,
                       unsigned tag, const DevCoef*, int*, long long, int, int, size_t, hipStream_t s) {
   std::vector<Touch> what;
   std::map<int, std::pair<DevSeg, int64_t>> seen;   // first segment of an instance, nodes so far
@@ -301,7 +305,7 @@ hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int, i
     most = most > st ? most : st;
     blocks = (most + sx - 1) / sx;
   }
-  launch(s, what, {tile ? kTiles : kSlabs, 0, nsegs, most, tag, blocks});
+  launch(s, what, {tile ? kTiles : kSlabs, 0, nsegs, most, tag, blocks, width, 0});
   return hipSuccess;
 }
 hipError_t launch_slab(int, int prec, int, const DevSlab* slabs, int nslabs, const DevTileInst* ti, void* b0, void* b1, int,
@@ -322,7 +326,7 @@ hipError_t launch_slab(int, int prec, int, const DevSlab* slabs, int nslabs, con
     w.done[out] = w.done[in] + t.steps;
     most = most > t.steps ? most : t.steps;
   }
-  launch(s, what, {kLdsSlabs, 0, nslabs, most, 0, 0});
+  launch(s, what, {kLdsSlabs, 0, nslabs, most, 0, 0, 0, 0});
   return hipSuccess;
 }
 hipError_t launch_tile(int, int prec, const DevTile* tiles, int ntiles, const DevTileInst* ti, void* b0, void* b1, int turn,
@@ -343,7 +347,7 @@ hipError_t launch_tile(int, int prec, const DevTile* tiles, int ntiles, const De
     what.push_back({out, true});
     w.done[out] = w.done[in] + st;
   }
-  launch(s, what, {kLdsTiles, 0, ntiles, 0, 0, 0});
+  launch(s, what, {kLdsTiles, 0, ntiles, 0, 0, 0, 0, 0});
   return hipSuccess;
 }
 hipError_t launch_zero_ints(int* p, int n, hipStream_t) { std::memset(p, 0, sizeof(int) * n); return hipSuccess; }

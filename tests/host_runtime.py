@@ -51,10 +51,10 @@ class HostRuntime:
         return n, text.value.decode()
 
     def launches(self, *kinds):
-        """(kind, stream, workgroups, steps, tag, blocks) of the launches since reset()."""
+        """(kind, stream, workgroups, steps, tag, blocks, nodes per lane, jobs) of the launches since reset()."""
         out = []
         for k in range(self.lib.stub_launches()):
-            r = (ctypes.c_int64 * 6)()
+            r = (ctypes.c_int64 * 8)()
             self.lib.stub_launch(k, r)
             if not kinds or r[0] in kinds:
                 out.append(tuple(r))

@@ -75,3 +75,19 @@ def test_random_mixed_batches_do_every_step_in_order(host, seed):
         steps.append(int(np.exp(rng.uniform(0, np.log(8000)))) if seed % 2 else [1000, 4000, 1][int(rng.integers(3))])
     for path in (0, 3, 4):
         advance(host, ps, steps, path)
+
+
+def kawahara_k22(prec):
+    return [W.config4_instance(i, prec=prec).problem for i in range(512)]
+
+
+@pytest.mark.parametrize("prec", [W.F64, W.F32_DEV])
+def test_slab_launches_are_counted_as_they_are_filled(host, prec):
+    """Whole instances fill the launches: none is a short tail, and a group takes at most
+    an eighth more launch time than its workgroups would take on all CUs."""
+    launches = [r for r in advance(host, kawahara_k22(prec), [5000] * 512) if r[0] == H.SLABS]
+    for width in {r[6] for r in launches}:
+        groups = [r[2] for r in launches if r[6] == width]
+        assert 2 * min(groups) >= max(groups), groups
+        work = sum(r[2] * r[3] for r in launches if r[6] == width)
+        assert sum(r[3] for r in launches if r[6] == width) <= max(5000, 1.125 * work / 256), launches
