@@ -91,3 +91,10 @@ def test_slab_launches_are_counted_as_they_are_filled(host, prec):
         assert 2 * min(groups) >= max(groups), groups
         work = sum(r[2] * r[3] for r in launches if r[6] == width)
         assert sum(r[3] for r in launches if r[6] == width) <= max(5000, 1.125 * work / 256), launches
+
+
+@pytest.mark.parametrize("prec", [W.F64, W.F32_DEV])
+def test_whole_instances_have_the_gpu_where_slabs_follow_them(host, prec):
+    launches = advance(host, kawahara_k22(prec), [5000] * 512)
+    assert max(r[2] for r in launches if r[0] == H.SLABS) >= 240
+    assert sum(r[2] for r in launches if r[0] == H.REG) >= 240
