@@ -835,6 +835,20 @@ int seg_count(const SegPlan& p, int q, int n, bool tile) {
   const int top = (all + k - 1) / k + 2 * p.extra, more = (top + cap - 1) / cap;
   return top / more < p.extra + hg + 1 || top / more < 2 * (hl + 1) ? 0 : k;
 }
+// Whether the slab kernel's registers do not hold a lane's R nodes beside what it
+// keeps for its neighbours: the widest lanes of FP64 storage on D1Q5 and of D1Q4
+// tables past degree 5, and with FP32 storage and FP64 arithmetic the widest of
+// the larger tables.  Measured against the step such widths are priced at: 1.4 to
+// 3.4 times in FP64 (128 K(2,2) grids of 16384 nodes, 2500 steps: 13.0 ms with 17
+// nodes per lane, 7.4 ms with 14 or fewer), 1.2 to 1.5 in FP32 storage; the others
+// 0.9 to 1.15.  Whole instances (k_reg) have no such widths.
+bool seg_spills(int q, int prec, int code, int R) {
+  const int D = code & 0xff;
+  const bool dense = (code >> 8) == 0;
+  if (R < (q <= 5 ? 17 : 12) || prec == 2) return false;
+  if (prec == 0) return q == 5 || (dense && D > 5);
+  return q == 7 || (q > 4 && dense && D > 7);
+}
 // The cheapest plan of a group (sizes: node count, instances of it) on `cus`
 // CUs: a step of the waves that share a SIMD, and 1/sx of an exchange or of a
 // tile's way from and to HBM.
@@ -853,6 +867,7 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
     const int widths = reg_menu(q, prec, code, cls != 0, menu), full = reg_waves(cls != 0);
     for (int m = 0; m < widths; ++m) {
       const int k = much ? widths - 1 - m : m;
+      if (seg_spills(q, prec, code, menu[k].R)) continue;
       const double least = std::max(reg_step(menu[k], 1), nodes / (256.0 * menu[k].R * cus) * menu[k].cost);
       if (found && least >= out->est) continue;
       for (int pick = 0; pick < 7; ++pick) {

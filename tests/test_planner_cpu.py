@@ -98,3 +98,12 @@ def test_whole_instances_have_the_gpu_where_slabs_follow_them(host, prec):
     launches = advance(host, kawahara_k22(prec), [5000] * 512)
     assert max(r[2] for r in launches if r[0] == H.SLABS) >= 240
     assert sum(r[2] for r in launches if r[0] == H.REG) >= 240
+
+
+@pytest.mark.parametrize("kind,prec,n,count,widest", [("kdv", W.F64, 16384, 128, 14), ("mkdv", W.F64, 16384, 128, 14),
+                                                      ("kawahara", W.F32_DEV, 20000, 128, 10)])
+def test_slabs_are_not_planned_with_lanes_wider_than_their_registers(host, kind, prec, n, count, widest):
+    """The slab kernels of these tables spill the widest lanes' nodes (2 to 3 times the step)."""
+    for steps in (300, 5000):
+        launches = [r for r in advance(host, [problem(kind, n, prec)] * count, [steps] * count) if r[0] == H.SLABS]
+        assert launches and max(r[6] for r in launches) <= widest
