@@ -707,6 +707,7 @@ constexpr int kChunkItems = 16;        // queue items per workgroup when jobs ou
 constexpr int64_t kMinChunkSteps = 256;
 constexpr int kMaxChunks = 64;
 constexpr int64_t kSlabLaunchSteps = 16;
+constexpr int kMaxSlabChunks = 8;
 constexpr int64_t kMinSlabChunk = 256;   // steps of one chunk of a slab launch
 
 // Lanes a pass spreads its launches over.  HIP runs a process's streams on
@@ -852,9 +853,10 @@ bool seg_spills(int q, int prec, int code, int R) {
 // The cheapest plan of a group (sizes: node count, instances of it) on `cus`
 // CUs: a step of the waves that share a SIMD, and 1/sx of an exchange or of a
 // tile's way from and to HBM.
-// `want`: steps asked for (0: free); `wgs`: workgroups per CU asked for (0: free).
+// `want`: steps asked for (0: free); `wgs`: workgroups per CU asked for (0: free);
+// `chunks`: step chunks that the group's steps can be cut into.
 bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cus, int want, int wgs, bool tile,
-              SegPlan* out) {
+              int chunks, SegPlan* out) {
   const int H = q / 2;
   int64_t nodes = 0;
   for (const auto& [n, times] : sizes) nodes += (int64_t)n * times;
@@ -888,28 +890,32 @@ bool seg_plan(int q, int prec, int code, const std::map<int, int>& sizes, int cu
           p.most = w * cap - 2 * p.extra;
           if (p.most < 1) continue;
           const int hold = full / w;   // workgroups a CU holds
-          auto price = [&](int64_t total) {
+          // (a launch holds whole instances of `count` segments, or of them on average)
+          auto price = [&](int64_t total, double count) {
             p.per_cu = (int)std::min<int64_t>(hold, (total + cus - 1) / cus);
             const int per_simd = (p.per_cu * w + 3) / 4;
-            const double rounds = std::max(1.0, (double)total / ((double)p.per_cu * cus));
+            const int64_t places = (int64_t)p.per_cu * cus;
+            const double held = sizes.size() == 1 ? places - places % (int64_t)count : places - 0.5 * (count - 1.0);
+            double rounds = total <= places ? 1.0 : tile ? std::ceil((double)total / places) : 1e30;
+            for (int c = 1; c <= chunks && !tile && total > places; ++c)
+              rounds = std::min(rounds, (c > 1 ? 1.02 : 1.0) * std::ceil(c * (total / held) - 1e-9) / c);
             const double link = tile ? 3000.0 + 0.4 * (p.per_cu * p.most * p.f.R) * q
                                      : kLinkCost + kLinkShare * (p.per_cu - 1) + (prec != 0 ? 2.0 : 5.0) * p.f.R * q;
-            // (slabs over more than one launch go in up to eight chunks of steps)
-            p.est = (tile ? std::ceil(rounds) : rounds > 1.0 ? 1.02 * std::ceil(8.0 * rounds) / 8.0 : 1.0) *
-                    (reg_step(p.f, per_simd) + link / p.sx);
+            p.est = rounds * (reg_step(p.f, per_simd) + link / p.sx);
           };
-          price(std::max<int64_t>(1, nodes / ((int64_t)p.most * p.f.R)));   // as few segments as there can be
+          price(std::max<int64_t>(1, nodes / ((int64_t)p.most * p.f.R)), 1.0);   // as few segments as there can be
           if (found && p.est >= out->est) continue;
-          int64_t total = 0;
+          int64_t total = 0, instances = 0;
           bool ok = true;
           for (const auto& [n, times] : sizes) {
+            instances += times;
             const int c = seg_count(p, q, n, tile);
             ok = c > 0 && (tile || c <= cus);
             if (!ok) break;
             total += (int64_t)c * times;
           }
           if (!ok) continue;
-          price(total);
+          price(total, (double)total / instances);
           if (!found || p.est < out->est) {
             *out = p;
             found = true;
@@ -994,7 +1000,7 @@ SlabChunks slab_chunks(const std::vector<std::pair<int, int64_t>>& mem, int64_t 
   if (total <= capacity) return out;
   int64_t time = 0, least = INT64_MAX;
   int launches = 0;
-  for (int c = 1; c <= 8 && (c == 1 || longest / c >= kMinSlabChunk); ++c) {
+  for (int c = 1; c <= kMaxSlabChunks && (c == 1 || longest / c >= kMinSlabChunk); ++c) {
     int64_t t;
     const int l = slab_launches(mem, c, capacity, &t);
     if (t + l * kSlabLaunchSteps >= least) continue;
@@ -1096,7 +1102,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     if (it != b->sooner.end()) return it->second;
     if (b->sooner.size() >= 4096) b->sooner.clear();
     SegPlan p;
-    const bool yes = cus > 1 && seg_plan(h.q, h.prec, h.D, {{h.n, 1}}, cus, 0, 0, false, &p) &&
+    const bool yes = cus > 1 && seg_plan(h.q, h.prec, h.D, {{h.n, 1}}, cus, 0, 0, false, 1, &p) &&
                      p.est < 0.95 * ring_step(h.q, h.prec, h.D, h.n);
     return b->sooner[key] = yes;
   };
@@ -1433,10 +1439,15 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       for (int i : g) ++sizes[b->inst[i].n];
       return sizes;
     };
+    auto chunks_of = [&](const std::vector<int>& g) {
+      int64_t longest = 0;
+      for (int i : g) longest = std::max(longest, steps[i]);
+      return (int)std::max<int64_t>(1, std::min<int64_t>(kMaxSlabChunks, longest / kMinSlabChunk));
+    };
     auto plan = [&](const std::tuple<int, int, int>& key, const std::map<int, int>& sizes, int cus, int want, bool tile,
-                    SegPlan* p) {
+                    int chunks, SegPlan* p) {
       // (steps asked for that no segment's halos hold are halved)
-      while (!seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile, p)) {
+      while (!seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile, chunks, p)) {
         if (want <= (tile ? 1 : 2)) return false;
         want = tile ? want / 2 : want / 4 * 2;
       }
@@ -1457,7 +1468,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       }
       SegPlan p;
       const bool whole = b->path == 0 && longest < 1e29 && b->tile_steps == 0 && b->tile_wgs == 0 &&
-                         (!plan(key, sizes_of(it->second), b->lim.cus, slab_steps, false, &p) ||
+                         (!plan(key, sizes_of(it->second), b->lim.cus, slab_steps, false, chunks_of(it->second), &p) ||
                           std::max(longest, sum) < p.est);
       if (whole) {
         std::vector<int>& to = reg[key];
@@ -1471,11 +1482,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       const auto& key = it->first;
       std::vector<int>& g = it->second;
       SegPlan p;
-      if (!plan(key, sizes_of(g), b->lim.cus, slab_steps, false, &p)) {
+      if (!plan(key, sizes_of(g), b->lim.cus, slab_steps, false, chunks_of(g), &p)) {
         std::map<int, bool> cuts;
         for (int i : g) {
           const int n = b->inst[i].n;
-          if (!cuts.count(n)) cuts[n] = plan(key, {{n, 1}}, b->lim.cus, slab_steps, false, &p);
+          if (!cuts.count(n)) cuts[n] = plan(key, {{n, 1}}, b->lim.cus, slab_steps, false, 1, &p);
         }
         std::vector<int> keep;
         for (int i : g) {
@@ -1485,7 +1496,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
             rtile[key].push_back(i);
         }
         g.swap(keep);
-        if (!g.empty() && !plan(key, sizes_of(g), b->lim.cus, slab_steps, false, &p)) {
+        if (!g.empty() && !plan(key, sizes_of(g), b->lim.cus, slab_steps, false, chunks_of(g), &p)) {
           for (int i : g) rtile[key].push_back(i);
           g.clear();
         }
@@ -1516,7 +1527,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       for (const auto& [key, g] : spread) {
         SegPlan p;
         const int cus = std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / all_work));
-        ok = ok && plan(key, sizes_of(g), cus, slab_steps, false, &p);
+        ok = ok && plan(key, sizes_of(g), cus, slab_steps, false, 1, &p);
         shared.push_back(p);
       }
       if (ok && places_of(shared) <= b->lim.cus) {
@@ -1533,7 +1544,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     }
     for (const auto& [key, g] : rtile) {
       SegPlan p;
-      if (!plan(key, sizes_of(g), b->lim.cus, b->tile_steps, true, &p)) return LBM_ERR_UNSUPPORTED;
+      if (!plan(key, sizes_of(g), b->lim.cus, b->tile_steps, true, 1, &p)) return LBM_ERR_UNSUPPORTED;
       lbm_status st = add_segs(key, g, p, false, true);
       if (st != LBM_OK) return st;
     }

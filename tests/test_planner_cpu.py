@@ -107,3 +107,11 @@ def test_slabs_are_not_planned_with_lanes_wider_than_their_registers(host, kind,
     for steps in (300, 5000):
         launches = [r for r in advance(host, [problem(kind, n, prec)] * count, [steps] * count) if r[0] == H.SLABS]
         assert launches and max(r[6] for r in launches) <= widest
+
+
+@pytest.mark.parametrize("prec", [W.F64, W.F32_DEV])
+def test_few_steps_are_planned_without_step_chunks(host, prec):
+    """400 steps cannot be cut into chunks, so that a plan of a little more than one
+    launch would take two launches' time."""
+    launches = [r for r in advance(host, [problem("kawahara", 30000, prec)] * 20, [400] * 20) if r[0] == H.SLABS]
+    assert sum(r[3] for r in launches) == 400, launches
