@@ -1742,30 +1742,43 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     } else if (L.grid >= L.count) {
       for (int k = 0; k < L.count; ++k) parts.push_back(DevItem{k, 0, jobs[k].steps, 0, 0});
     } else {
-      const double span = std::max(L.est_sum / L.grid, L.est_max);
+      // (a job is not split for a few steps, and what that wastes of the even
+      // share must not pile up behind the last workgroup: 300 equal jobs on 256
+      // took two rounds.  So the share is raised until all of them end by it.)
       struct Planned { double start; DevItem item; };
-      std::vector<Planned> plan;
-      double t = 0.0;   // end of the current workgroup's last item
-      int used_wgs = 1;
-      for (int k = 0; k < L.count; ++k) {
-        const int st = jobs[k].steps;
-        int second = 0;   // steps that stay with this workgroup, at its end
-        if (t + est[k] > span * (1.0 + 1e-9) && used_wgs < L.grid) {
-          second = (int)(st * ((span - t) / est[k]));
-          if (second < st / 32 || second < 8) second = 0;
-          if (st - second < st / 32 || st - second < 8) second = st;
-        } else {
-          second = st;
+      std::vector<Planned> plan, trial;
+      double least = 0.0;
+      for (int slack = 0; slack <= 16; ++slack) {
+        const double span = std::max(L.est_sum / L.grid, L.est_max) * (1.0 + 0.01 * slack);
+        double t = 0.0, end = 0.0;   // of the current workgroup's last item; of the latest so far
+        int used_wgs = 1;
+        trial.clear();
+        for (int k = 0; k < L.count; ++k) {
+          const int st = jobs[k].steps;
+          int second = st;   // steps that stay with this workgroup, at its end
+          if (t + est[k] > span * (1.0 + 1e-9) && used_wgs < L.grid) {
+            second = (int)(st * ((span - t) / est[k]));
+            if (second < st / 32 || second < 8) second = 0;
+            if (st - second < st / 32 || st - second < 8) second = st;
+          }
+          const int first = st - second;
+          if (second > 0) {
+            trial.push_back({t, DevItem{k, first > 0 ? 1 : 0, second, first, 0}});
+            t += est[k] * second / st;
+            end = std::max(end, t);
+          }
+          if (first > 0) {
+            trial.push_back({0.0, DevItem{k, 0, first, 0, second > 0 ? 1 : 0}});
+            t = est[k] * first / st;
+            end = std::max(end, t);
+            ++used_wgs;
+          }
         }
-        const int first = st - second;
-        if (second > 0) plan.push_back({t, DevItem{k, first > 0 ? 1 : 0, second, first, 0}});
-        if (first > 0) {
-          plan.push_back({0.0, DevItem{k, 0, first, 0, second > 0 ? 1 : 0}});
-          t = est[k] * first / st;
-          ++used_wgs;
-        } else {
-          t += est[k];
+        if (slack == 0 || end < least) {
+          least = end;
+          plan.swap(trial);
         }
+        if (end <= span * (1.0 + 1e-9)) break;
       }
       std::stable_sort(plan.begin(), plan.end(), [](const Planned& x, const Planned& y) {
         return x.start != y.start ? x.start < y.start : x.item.part < y.item.part;

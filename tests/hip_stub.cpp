@@ -7,6 +7,7 @@
 //    before the next one starts; two launches that touch one buffer, one of them
 //    writing, without such an order are a fault, as is a launch that holds two
 //    step chunks of one instance, or a kernel given memory that is not on the GPU.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -274,7 +275,19 @@ hipError_t launch_reg(int, int, int, bool, const DevItem* items, int nitems, con
       w.done[segs[u].in] += items[k].steps;
     }
   }
-  launch(s, what, {kReg, 0, grid, 0, 0, 0, width, (int64_t)seen.size()});
+  // the launch's length in steps of jobs of equal steps' cost: items in the list's
+  // order to the workgroup that is free first, a job's second part after its first
+  std::vector<int64_t> free(grid, 0);
+  std::map<int, int64_t> over;
+  int64_t end = 0;
+  for (int k = 0; k < nitems; ++k) {
+    auto at = std::min_element(free.begin(), free.end());
+    if (items[k].part > 0) *at = std::max(*at, over[items[k].job]);
+    *at += items[k].steps;
+    over[items[k].job] = *at;
+    end = std::max(end, *at);
+  }
+  launch(s, what, {kReg, 0, grid, end, 0, 0, width, (int64_t)seen.size()});
   return hipSuccess;
 }
 hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int width, int, int sx, bool tile, int turn, void*,

@@ -115,3 +115,10 @@ def test_few_steps_are_planned_without_step_chunks(host, prec):
     launch would take two launches' time."""
     launches = [r for r in advance(host, [problem("kawahara", 30000, prec)] * 20, [400] * 20) if r[0] == H.SLABS]
     assert sum(r[3] for r in launches) == 400, launches
+
+
+@pytest.mark.parametrize("count", [257, 280, 300, 400, 513, 600, 1000, 1025])
+def test_jobs_end_with_the_even_share(host, count):
+    """Equal jobs laid end to end over the workgroups."""
+    r, = [r for r in advance(host, [problem("kdv", 4096)] * count, [2000] * count) if r[0] == H.REG]
+    assert r[3] <= 2000 * max(1.0, r[7] / r[2] + 0.06), r
