@@ -736,14 +736,82 @@ struct RegFit {
   int over = 0;    // nodes by which they exceed the periods
   int waves = 0;
   double cost = 0.0;   // of one wave and step, in VALU operations
-  double lag = 0.0;    // what a lone wave waits for its coefficients beside
+  double lag = 0.0;    // what a lone wave waits for its coefficients beside (many nodes hide it)
 };
 // A step of `waves` waves that share a SIMD: one takes about 1.25 times, two
 // about 1.05 times its operations' time each, unless the wait for coefficients is
-// longer.
+// longer; with one node per lane nothing hides that wait.
 double reg_step(const RegFit& f, int waves) {
   const double slow = waves == 1 ? 1.25 : waves == 2 ? 1.05 : 1.0;
+  if (f.R == 1) return slow * waves * f.cost + f.lag;
   return std::max(slow * waves * f.cost, 1.25 * f.cost + f.lag);
+}
+// What a group of whole instances takes on `cus` CUs, in VALU operations of a wave
+// times steps, when they are packed into jobs of at most `share` waves: whole
+// instances of one width and step count to a job, `full` waves to a CU.  `beside`:
+// the jobs of a CU at once.
+struct RegClass {
+  int64_t steps = 0;
+  RegFit f;
+  int64_t count[17] = {};   // instances of so many waves
+  int least = 16, most = 1; // the waves there are
+};
+double reg_group(const std::vector<RegClass>& classes, int share, int full, double cus, int* beside) {
+  // jobs by the waves they hold: first fit, decreasing
+  struct Jobs { const RegClass* c; int waves; int64_t count; };
+  std::vector<Jobs> jobs;
+  int64_t total = 0;
+  for (const RegClass& c : classes) {
+    int64_t room[17] = {};   // jobs with so much room left
+    for (int w = c.most; w >= c.least; --w) {
+      int64_t left = c.count[w];
+      for (int r = w; r <= share && left > 0; ++r) {
+        const int each = r / w;   // of them a job with this room takes
+        const int64_t filled = std::min(room[r], left / each);
+        room[r] -= filled;
+        room[r - each * w] += filled;
+        left -= filled * each;
+        if (room[r] > 0 && left > 0 && left < each) {
+          --room[r];
+          room[r - (int)left * w] += 1;
+          left = 0;
+        }
+      }
+      if (left > 0) {
+        const int each = share / w;
+        room[share - each * w] += left / each;
+        if (left % each) room[share - (int)(left % each) * w] += 1;
+      }
+    }
+    for (int r = 0; r < share; ++r)
+      if (room[r] > 0) {
+        jobs.push_back({&c, share - r, room[r]});
+        total += room[r];
+      }
+  }
+  // jobs side by side on a CU, as many as end the group sooner; more than that
+  // follow one another, laid end to end
+  double best = 0.0;
+  for (int b = 1; b <= std::max(1, full / share); ++b) {
+    double longest = 0.0, sum = 0.0;
+    for (const Jobs& j : jobs) {
+      // (the waves of one workgroup spread evenly over the SIMDs, those of several
+      // need not: two of two waves each took as long as two waves on one SIMD; and
+      // 600 grids of 2400 nodes, one to a job, two jobs to a CU, took a quarter
+      // more than two to a job)
+      const int per_simd = j.waves == 1 || j.waves == 3 ? (b * j.waves + 3) / 4 : b * ((j.waves + 3) / 4);
+      const double t = (b > 1 ? 1.1 : 1.0) * (double)j.c->steps * reg_step(j.c->f, per_simd);
+      longest = std::max(longest, t);
+      sum += t * j.count / b;
+    }
+    const double t = total <= b * cus ? longest : std::max(longest, 1.02 * sum / cus);
+    if (b == 1 || t < best) {
+      best = t;
+      *beside = b;
+    }
+    if (total <= b * cus) break;
+  }
+  return best;
 }
 int reg_halo(int q, int R, int s) { return (s * (q / 2) + R - 1) / R; }
 // LDS elements of one wave: its exchange strips, or a row of its nodes
@@ -784,7 +852,7 @@ int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
         best.cost = c;
         best.lag = reg_pinned(q, D, code >> 8, arith) || reg_held(q, D, code >> 8, elem, arith, wide, R)
                        ? 0.0
-                       : 37.0 * q * (K - 1) * arith / 64;
+                       : 37.0 * q * (K - 1) * arith / 64 * std::min(1.0, 2.0 / R);
       }
     }
     if (best.R) out[count++] = best;
@@ -796,6 +864,15 @@ int reg_menu(int q, int prec, int code, bool wide, RegFit* out) {
     ++count;
   }
   return count;
+}
+
+// The same width with the narrowest halo, and as many steps between exchanges as
+// that holds: more exchanges, but an instance may need a wave less.
+RegFit reg_tight(int q, int prec, RegFit f) {
+  const int hl = reg_halo(q, f.R, 2), s = std::min(16, hl * f.R / (q / 2) / 2 * 2);
+  f.cost += ((prec != 0 ? 2.0 : 5.0) * f.R * q + 40.0) * (1.0 / s - 1.0 / f.s);
+  f.s = s;
+  return f;
 }
 
 // bounded instances: one width
@@ -1174,7 +1251,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   DevJob* hjobs = b->jobs_host + (size_t)k * b->items_cap;
   DevSeg* hsegs = b->segs_host + (size_t)k * b->items_cap;
   // est_max / est_sum: the longest job's and all jobs' duration estimates
-  struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; bool reg, wide; int grid, part0, parts; int64_t partsteps; };
+  struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; bool reg, wide; int per_cu, grid, part0, parts; int64_t partsteps; };
   std::vector<Launch> launches;
   int used = 0, njobs = 0, nsegs = 0;
   constexpr int kMaxJobInstances = 16;   // instances per job (one wave each at least)
@@ -1260,7 +1337,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       const int slots = jobs_per_cu * b->lim.cus;
       if (!latency && (int)bins.size() < slots && (int)g.size() > (int)bins.size())
         pack(std::max(1, ((int)g.size() + slots - 1) / slots));
-      Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, false, false, 0, 0, 0, 0};
+      Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, false, false, 0, 0, 0, 0, 0};
       struct Planned { const Bin* bin; std::vector<int> waves; double est; };
       std::vector<Planned> plan;
       for (const Bin& bn : bins) {
@@ -1572,13 +1649,19 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     // an instance's last lanes empty and give fewer waves to share the SIMDs.
     // Each instance takes the width with the least wave time among one kernel's
     // (narrow or wide: one launch per group, since a pass's launches run side by
-    // side only while there are hardware queues) up to a bound, and kernel and
-    // bound are those for which the group -- its waves over its CUs, or one job
-    // of the longest waves -- is estimated to end first.
+    // side only while there are hardware queues) up to a bound, or all of them the
+    // same one; kernel, widths and waves per job are those for which the group,
+    // packed, is estimated to end first.  (By its waves alone, 512 grids of 1000
+    // nodes took nine waves each, one to a job of sixteen.)
     std::vector<RegFit> fit(g.size()), trial(g.size());
     double best = 0.0;
-    int job_waves = 4;
+    int job_waves = 4, jobs_per_cu = 1;
     bool wide = false;
+    std::vector<RegClass> classes;
+    std::map<int64_t, int> step_ids;   // of the group's step counts
+    std::vector<int> step_id, class_of;
+    std::vector<RegFit> placed;   // each instance by each width
+    for (int i : g) step_id.push_back(step_ids.insert({steps[i], (int)step_ids.size()}).first->second);
     for (int cls = 0; cls < 2; ++cls) {
       RegFit menu[kRegWidths + 1];
       const int full = reg_waves(cls != 0);
@@ -1589,41 +1672,77 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         menu[0] = bound_fit();
         widths = 1;
       }
-      for (int most = widths - 1; most >= 0; --most) {
-        double sum = 0.0, longest = 0.0, lag = 0.0;
+      // wave time of an instance: that of whole rounds over the SIMDs where no
+      // other has room beside it
+      auto load = [&](const RegFit& f) { return (2 * f.waves > full ? (f.waves + 3) / 4 * 4 : f.waves) * f.cost; };
+      placed.resize(g.size() * widths);
+      for (size_t u = 0; u < g.size(); ++u) {
+        RegFit* at = &placed[u * widths];
+        const int n = b->inst[g[u]].n;
+        if (u > 0 && n == b->inst[g[u - 1]].n) {
+          std::copy(at - widths, at, at);
+          continue;
+        }
+        for (int w = 0; w < widths; ++w) {
+          at[w] = menu[w];
+          reg_place(q, n, &at[w]);
+          if (bounded) continue;
+          RegFit f = reg_tight(q, pr, menu[w]);
+          reg_place(q, n, &f);
+          if (load(f) < load(at[w])) at[w] = f;
+        }
+      }
+      for (int pick = 2 * widths - 1; pick >= 0; --pick) {
+        const int most = pick / 2, from = pick % 2 ? most : 0;
+        if (from == most && most == 0 && pick % 2) continue;
         int64_t waves = 0;
         int top = 1;
         bool ok = true;
+        classes.clear();
+        class_of.assign(step_ids.size() * widths * 2, -1);
         for (size_t u = 0; u < g.size() && ok; ++u) {
           double least = 0.0;
-          for (int w = 0; w <= most; ++w) {
-            RegFit f = menu[w];
-            reg_place(q, b->inst[g[u]].n, &f);
+          int taken = 0;
+          for (int w = from; w <= most; ++w) {
+            const RegFit& f = placed[u * widths + w];
             if (f.waves > full) continue;
-            if (least == 0.0 || f.waves * f.cost < least) {
+            if (least == 0.0 || load(f) < least) {
               trial[u] = f;
-              least = f.waves * f.cost;
+              taken = 2 * w + (f.s != menu[w].s);
+              least = load(f);
             }
           }
           ok = least > 0.0;
           if (!ok) break;
-          sum += least;
           waves += trial[u].waves;
           top = std::max(top, trial[u].waves);
-          longest = std::max(longest, trial[u].cost);
-          lag = std::max(lag, trial[u].lag);
+          int& at = class_of[step_id[u] * widths * 2 + taken];
+          if (at < 0) {
+            at = (int)classes.size();
+            classes.emplace_back();
+            classes[at].steps = steps[g[u]];
+            classes[at].f = trial[u];
+          }
+          RegClass& c = classes[at];
+          ++c.count[trial[u].waves];
+          c.least = std::min(c.least, trial[u].waves);
+          c.most = std::max(c.most, trial[u].waves);
         }
-        if (!ok) break;
-        // waves of a job: all a CU holds, or as many as the waves make for each CU
-        const int share = std::max(top, (int)std::min<double>(full, std::ceil(waves / cus)));
-        const int per_simd = (share + 3) / 4;
-        const double slow = per_simd == 1 ? 1.25 : per_simd == 2 ? 1.05 : 1.0;
-        const double est = std::max({slow * per_simd * longest, slow * sum / (4.0 * cus), 1.25 * longest + lag});
-        if (best == 0.0 || est < best) {
-          best = est;
-          fit = trial;
-          job_waves = share;
-          wide = cls != 0;
+        if (!ok) continue;
+        // waves of a job: as many as the waves make for each CU, all a CU holds,
+        // and (few classes) what lies between
+        const int even = std::max(top, (int)std::min<double>(full, std::ceil(waves / cus)));
+        for (int share = top; share <= full; ++share) {
+          if (share != full && share != even && classes.size() > 64) continue;
+          int beside = 1;
+          const double est = reg_group(classes, share, full, cus, &beside);
+          if (best == 0.0 || est < best) {
+            best = est;
+            fit = trial;
+            job_waves = share;
+            jobs_per_cu = beside;
+            wide = cls != 0;
+          }
         }
       }
     }
@@ -1656,7 +1775,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       return (double)steps[g[bn.members[0]]] * ((bn.waves + 3) / 4) * fit[bn.members[0]].cost;
     };
     std::stable_sort(bins.begin(), bins.end(), [&](const Bin& a, const Bin& c) { return job_est(a) > job_est(c); });
-    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, wide, 0, 0, 0, 0};
+    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, wide, jobs_per_cu, 0, 0, 0, 0};
     for (const Bin& bn : bins) {
       const RegFit& f0 = fit[bn.members[0]];
       const int64_t st = steps[g[bn.members[0]]];
@@ -1724,6 +1843,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     int per_cu = 0;
     LBM_HIP(reg_occupancy(L.q, L.prec, L.code, L.wide, L.block, L.lds, &per_cu));
     if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
+    per_cu = std::min(per_cu, L.per_cu);
     L.grid = std::min<int>(L.count, per_cu * b->lim.cus);
     if (reg_jobs > b->lim.cus)
       L.grid = std::max(1, std::min(L.grid, (int)std::lround(per_cu * b->lim.cus * L.est_sum / reg_est)));

@@ -51,7 +51,8 @@ class HostRuntime:
         return n, text.value.decode()
 
     def launches(self, *kinds):
-        """(kind, stream, workgroups, steps, tag, blocks, nodes per lane, jobs) of the launches since reset()."""
+        """(kind, stream, workgroups, steps, tag, blocks, nodes per lane, jobs) of the launches
+        since reset(); for whole instances, the percentage of a CU's waves filled instead of a tag."""
         out = []
         for k in range(self.lib.stub_launches()):
             r = (ctypes.c_int64 * 8)()

@@ -117,8 +117,17 @@ def test_few_steps_are_planned_without_step_chunks(host, prec):
     assert sum(r[3] for r in launches) == 400, launches
 
 
-@pytest.mark.parametrize("count", [257, 280, 300, 400, 513, 600, 1000, 1025])
+@pytest.mark.parametrize("count", [257, 280, 300, 400, 514, 600, 1000, 1026])
 def test_jobs_end_with_the_even_share(host, count):
     """Equal jobs laid end to end over the workgroups."""
     r, = [r for r in advance(host, [problem("kdv", 4096)] * count, [2000] * count) if r[0] == H.REG]
     assert r[3] <= 2000 * max(1.0, r[7] / r[2] + 0.06), r
+
+
+@pytest.mark.parametrize("kind,prec,n,count", [("kdv", W.F32_DEV_ARITH32, 1000, 512), ("kdv", W.F32_DEV, 1000, 512),
+                                               ("mkdv", W.F32_DEV_ARITH32, 1400, 512), ("kawahara", W.F64, 700, 700)])
+def test_jobs_are_planned_as_whole_instances_fill_them(host, kind, prec, n, count):
+    """Several instances to each CU: jobs that leave no quarter of a CU's waves idle,
+    or one to each CU (nine waves of sixteen, one job to a CU and two rounds, before)."""
+    r, = [r for r in advance(host, [problem(kind, n, prec)] * count, [600] * count) if r[0] == H.REG]
+    assert r[7] <= 256 or r[4] >= 75, r
