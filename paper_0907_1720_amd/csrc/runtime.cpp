@@ -594,10 +594,23 @@ lbm_status load_many(lbm_batch_s* b, const int* idx, const double* const* phi, i
   return LBM_OK;
 }
 
+// Whether kernels may use a caller's array in place: it is this GPU's memory.
+// Another GPU's, which need not be mapped here, and host memory, which a caller
+// may name as well, go by copies.
+bool on_this_gpu(const void* p) {
+  hipPointerAttribute_t at;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();   // (memory the runtime does not know)
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
 // f := f_eq(phi) of instance i from device memory
 lbm_status load_device(lbm_batch_s* b, int i, const double* phi) {
   HostInst& h = b->inst[i];
-  if (h.f32) {   // the rest state is summed on the host
+  if (h.f32 || !on_this_gpu(phi)) {   // the rest state is summed on the host
     std::vector<double> host(h.n);
     LBM_HIP(hipMemcpyAsync(host.data(), phi, sizeof(double) * h.n, hipMemcpyDeviceToHost, b->stream));
     LBM_HIP(hipStreamSynchronize(b->stream));
@@ -2486,7 +2499,8 @@ lbm_status advance(lbm_batch_s* b, const int64_t* steps) {
 }
 
 // phi of instance i, and its status.  Grids up to the stage are summed straight
-// into it (or into device memory); larger ones go by the scratch buffer.
+// into it (or into this GPU's memory); larger ones, and other memory, go by the
+// scratch buffer.
 lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_status* inst_status) {
   HostInst& h = b->inst[i];
   const double rest = h.f32 ? h.mdl.phi_rest : 0.0;
@@ -2494,7 +2508,8 @@ lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_statu
   volatile int* seen = words;
   seen[0] = seen[1] = 0;
   const bool staged = !on_device && sizeof(double) * (size_t)h.n <= b->stage_bytes;
-  double* to = on_device ? out : staged ? reinterpret_cast<double*>(b->stage + kStageHead) : b->scratch;
+  const bool direct = on_device && on_this_gpu(out);
+  double* to = direct ? out : staged ? reinterpret_cast<double*>(b->stage + kStageHead) : b->scratch;
   if (staged && h.n <= 256 * kReadWords) {
     // watched for as long as an idle stream takes; behind an advance that is
     // still running (and on errors) the stream is waited for
@@ -2514,8 +2529,9 @@ lbm_status read_phi(lbm_batch_s* b, int i, double* out, int on_device, lbm_statu
     if (!there) LBM_HIP(hipStreamSynchronize(b->stream));
   } else {
     LBM_HIP(launch_read(h.f32, state_cur(b, h), to, h.n, h.stride, h.q, rest, b->status + i, words, 0, nullptr, b->stream));
-    if (!on_device && !staged)
-      LBM_HIP(hipMemcpyAsync(out, to, sizeof(double) * h.n, hipMemcpyDeviceToHost, b->stream));
+    if (!direct && !staged)
+      LBM_HIP(hipMemcpyAsync(out, to, sizeof(double) * h.n, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                             b->stream));
     LBM_HIP(hipStreamSynchronize(b->stream));
   }
   if (staged) std::memcpy(out, to, sizeof(double) * h.n);

@@ -131,3 +131,25 @@ def test_jobs_are_planned_as_whole_instances_fill_them(host, kind, prec, n, coun
     or one to each CU (nine waves of sixteen, one job to a CU and two rounds, before)."""
     r, = [r for r in advance(host, [problem(kind, n, prec)] * count, [600] * count) if r[0] == H.REG]
     assert r[7] <= 256 or r[4] >= 75, r
+
+
+@pytest.mark.parametrize("where", ["host", "another GPU", "this GPU"])
+@pytest.mark.parametrize("prec", [W.F64, W.F32_DEV])
+def test_device_arrays_that_kernels_cannot_reach_go_by_copies(host, where, prec):
+    """A caller's "device" array may be host memory or another GPU's: a copy takes
+    either, a kernel that is given it faults."""
+    import ctypes
+
+    n = 300
+    keep = np.full(n, 0.5)
+    ptr = keep.ctypes.data if where == "host" else getattr(host.lib, "stub_foreign" if where == "another GPU" else "stub_device")(8 * n)
+    a = np.ctypeslib.as_array(ctypes.cast(ptr, ctypes.POINTER(ctypes.c_double)), (n,))
+    a[:] = 0.5
+    s = lbm.Solver(problem("kdv", n, prec), stream=0)
+    host.reset()
+    assert host.lib.lbm_load_phi(s._h, ptr, 1) == lbm.OK
+    s.advance(7)
+    assert host.lib.lbm_read_phi(s._h, ptr, 1) == lbm.OK
+    s.close()
+    assert host.faults()[0] == 0, host.faults()[1]
+    assert np.all(a == 7.0)
