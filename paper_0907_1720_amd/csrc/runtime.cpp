@@ -1213,6 +1213,16 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     const auto& l = loads[std::make_tuple(h.q, h.prec, h.D)];
     return b->path == 0 && b->res_grid == 0 && b->res_chunks == 0 && b->tile_wgs == 0 && 2.0 * b->lim.cus * l.second > 3.0 * l.first;
   };
+  // (an instance that fits a CU stays whole where there is no memory for the second
+  // state buffer that slabs write to)
+  int room[2] = {-1, -1};
+  auto has_room = [&](bool f32) {
+    if (room[f32] < 0) {
+      room[f32] = ensure_second_buffer(b, f32) == LBM_OK;
+      if (!room[f32]) (void)hipGetLastError();   // (no error of the launches to come)
+    }
+    return room[f32] == 1;
+  };
   const int slab_wgs = b->tile_wgs > 0 ? b->tile_wgs : latency && 4 * all_bytes < lds_all ? 8 : 2;
   for (int i = 0; i < count; ++i) {
     if (steps[i] == 0) continue;
@@ -1242,13 +1252,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       rtile[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else if (b->path == 3)
       til[h.q][h.prec].push_back(i);
-    else if (in_reg && (b->path == 4 || !fits || (latency && spread_sooner(h))))
+    else if (in_reg && (b->path == 4 || !fits || (latency && spread_sooner(h) && has_room(h.f32))))
       spread[std::make_tuple(h.q, h.prec, h.D)].push_back(i);
     else if (b->path == 4 || !fits)
       slb[std::make_tuple(h.q, h.prec, h.D, slab_wgs)].push_back(i);
     else if (!in_reg && latency && h.n >= kSplitNodes)
       slb[std::make_tuple(h.q, h.prec, h.D, 8)].push_back(i);
-    else if (!in_reg && !latency && h.n >= kUnevenNodes && uneven(h))
+    else if (!in_reg && !latency && h.n >= kUnevenNodes && uneven(h) && has_room(h.f32))
       slb[std::make_tuple(h.q, h.prec, h.D, 4)].push_back(i);
     else if (in_reg)
       reg[std::make_tuple(h.q, h.prec, h.D)].push_back(i);

@@ -153,3 +153,20 @@ def test_device_arrays_that_kernels_cannot_reach_go_by_copies(host, where, prec)
     s.close()
     assert host.faults()[0] == 0, host.faults()[1]
     assert np.all(a == 7.0)
+
+
+@pytest.mark.parametrize("kind,sizes", [("power", [256 + 15 * i for i in range(256)]), ("kdv", [900] * 16)])
+def test_instances_that_fit_stay_whole_without_memory_for_a_second_state(host, kind, sizes):
+    ps = [problem(kind, n) for n in sizes]
+    assert any(r[0] in (H.SLABS, H.LDS_SLABS) for r in advance(host, ps, [500] * len(ps)))
+    b = lbm.Batch(ps, stream=0)
+    b.load_phi([np.full(n, 0.5) for n in sizes])
+    host.reset()
+    host.limit(64 << 10)
+    try:
+        b.advance(500)
+    finally:
+        host.limit()
+    assert [b.read_phi(i)[0][0] for i in range(len(ps))] == [500.0] * len(ps)
+    assert not any(r[0] in (H.SLABS, H.LDS_SLABS) for r in host.launches())
+    b.close()
