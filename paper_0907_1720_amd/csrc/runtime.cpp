@@ -2340,12 +2340,16 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     lbm_status gs = pass_gate(gate, gate_need, b->lim.cus, b->stream);
     if (gs != LBM_OK) return gs;
   }
-  int64_t strip_tags = 0;   // of this pass
-  for (const SegLaunch& L : segs) strip_tags += L.blocks;
+  // Tags of this pass: its launches have strips of their own, so that all of them
+  // count from the same tag.
+  int64_t strip_tags = 0;
+  for (const SegLaunch& L : segs) strip_tags = std::max(strip_tags, L.tile ? 0 : L.blocks);
   if (strips_need > 0 && b->strip_tag + strip_tags >= UINT32_MAX) {
     LBM_HIP(hipMemsetAsync(b->strips, 0, sizeof(uint64_t) * b->strips_cap, b->stream));
     b->strip_tag = 1;
   }
+  const uint32_t tag = b->strip_tag;
+  b->strip_tag += (uint32_t)strip_tags;
   if (fork) LBM_HIP(hipEventRecord(b->fork, b->stream));
   const DevSlab* ds = b->slabs + (size_t)k * b->slabs_cap;
   const DevTileInst* dti_all = b->tinsts + (size_t)k * b->tinsts_cap;
@@ -2363,8 +2367,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   };
   auto issue_seg = [&](size_t l, hipStream_t st) -> lbm_status {
     const SegLaunch& L = segs[l];
-    const uint32_t tag = b->strip_tag;
-    if (!L.tile) b->strip_tag += (uint32_t)L.blocks;
     const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
     for (int r = 0; r < L.launches; ++r)
       LBM_HIP(launch_seg(L.q, L.prec, L.code, L.p.f.wide, dxsegs + L.first, L.count, L.p.f.R, L.p.f.s, L.p.sx, L.tile, r,

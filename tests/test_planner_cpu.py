@@ -170,3 +170,23 @@ def test_instances_that_fit_stay_whole_without_memory_for_a_second_state(host, k
     assert [b.read_phi(i)[0][0] for i in range(len(ps))] == [500.0] * len(ps)
     assert not any(r[0] in (H.SLABS, H.LDS_SLABS) for r in host.launches())
     b.close()
+
+
+def test_tags_of_a_pass_do_not_wrap(host):
+    """Strips are cleared to tag 0 and hold the tags of earlier passes: a block's tag
+    must be above both, also in a long pass of many launches."""
+    ps = [problem(kind, 9000, prec) for kind in ("kdv", "mkdv", "kawahara") for prec in range(3)]
+    b = lbm.Batch(ps, stream=0)
+    b.set_tiling(2, 0)
+    b.load_phi([np.full(p.n, 0.5) for p in ps])
+    last = 0
+    for steps in (100, 1 << 30, 1 << 30, 100):
+        host.reset()
+        b.advance(steps)
+        slabs = host.launches(H.SLABS)
+        assert len(slabs) == len(ps)
+        low, high = min(r[4] for r in slabs), max(r[4] + r[5] for r in slabs)
+        assert 1 <= low and high < 1 << 32
+        assert low > last or low == 1   # (1: after a clear)
+        last = high - 1
+    b.close()
