@@ -234,6 +234,16 @@ __device__ __forceinline__ void reg_odd(T (&f)[R][Q], X& relax) {
   reg_scatter<Q, R>(n, f);
 }
 
+// LDS stores of this wave's lanes come before the loads that follow by others of
+// them: a wave's LDS operations complete in order, and the fence keeps the
+// compiler from moving them across (it costs no instruction).
+__device__ __forceinline__ void wave_lds_order() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#endif
+}
+
 template <typename T>
 __device__ __forceinline__ void store_agent(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -461,10 +471,10 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
       }
 #pragma unroll
       for (int r = 0; r < R; ++r) row[r * 64 + lane] = v[r];
-      __builtin_amdgcn_wave_barrier();   // (a wave's LDS operations complete in order)
+      wave_lds_order();
 #pragma unroll
       for (int r = 0; r < R; ++r) f[r][j] = row[lane * R + r];
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_order();
     }
   }
   // in == out for rings: every wave has loaded before the first one stores
@@ -535,8 +545,7 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
 #pragma unroll
         for (int u = 0; u < 4; ++u) next[u] = 4 + u < left ? rows[(int64_t)(at + u) * 2 * nl] : 0.0;
       }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_order();
       reg_even<Q, R, B>(f, relax);
       if (edge) bound.template reset<true, R, 0>(f);
       if (left == 1) break;
@@ -682,14 +691,14 @@ __device__ __forceinline__ void reg_segment(T* __restrict__ L, int steps, int s_
   for (int j = 0; j < Q; ++j) {
 #pragma unroll
     for (int r = 0; r < R; ++r) row[lane * R + r] = f[r][j];
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int x = r * 64 + lane;
       const T v = row[x];
       if (x >= lo && x < hi) out[(int64_t)j * sg.stride + sg.x0 + first + x] = v;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
   }
 }
 
