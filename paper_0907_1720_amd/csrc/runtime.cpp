@@ -118,7 +118,7 @@ struct lbm_batch_s {
   int* slots = nullptr;               // per-workgroup queue slot of the resident kernel
   int counters_cap = 0;
   DevJobInst* items = nullptr;        // two slots of items_cap records (alternating calls)
-  DevJobInst* items_host = nullptr;   // pinned mirror of both slots
+  DevJobInst* items_host = nullptr;   // pinned mirror of both slots (behind the stage, as the next two)
   DevJob* jobs = nullptr;             // two slots of items_cap jobs
   int* done = nullptr;                // per job: chunks published (two slots of items_cap)
   DevJob* jobs_host = nullptr;
@@ -277,14 +277,11 @@ void destroy_batch(lbm_batch_s* b) {
   hipFree(b->counter);
   hipFree(b->slots);
   hipFree(b->items);
-  if (b->items_host) hipHostFree(b->items_host);
   hipFree(b->jobs);
   hipFree(b->done);
   for (StepGraph& g : b->step_graphs) release_graph(&g);
   hipFree(b->bound);
-  if (b->jobs_host) hipHostFree(b->jobs_host);
   hipFree(b->segs);
-  if (b->segs_host) hipHostFree(b->segs_host);
   hipFree(b->parts);
   if (b->parts_host) hipHostFree(b->parts_host);
   hipFree(b->xsegs);
@@ -415,21 +412,21 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want) {
     return LBM_ERR_OUT_OF_MEMORY;
   b->items_cap = count;
   if (hipMalloc(&b->items, sizeof(DevJobInst) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipHostMalloc((void**)&b->items_host, sizeof(DevJobInst) * 2 * count, hipHostMallocDefault) != hipSuccess)
-    return LBM_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&b->jobs, sizeof(DevJob) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&b->done, sizeof(int) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipHostMalloc((void**)&b->jobs_host, sizeof(DevJob) * 2 * count, hipHostMallocDefault) != hipSuccess)
-    return LBM_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&b->segs, sizeof(DevSeg) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipHostMalloc((void**)&b->segs_host, sizeof(DevSeg) * 2 * count, hipHostMallocDefault) != hipSuccess)
-    return LBM_ERR_OUT_OF_MEMORY;
   for (int k = 0; k < 2; ++k) LBM_HIP(hipEventCreateWithFlags(&b->items_done[k], hipEventDisableTiming));
   b->scratch_elems = maxn + 64;
   if (hipMalloc(&b->scratch, sizeof(double) * b->scratch_elems) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   b->stage_bytes = std::min(kStageMost, std::max(kStageLeast, stage_want));
-  if (hipHostMalloc((void**)&b->stage, kStageHead + b->stage_bytes, hipHostMallocDefault) != hipSuccess)
+  // (the tables behind the stage, in one allocation: each takes about 40 us)
+  const size_t items_at = (kStageHead + b->stage_bytes + 255) / 256 * 256;
+  const size_t jobs_at = items_at + sizeof(DevJobInst) * 2 * count, segs_at = jobs_at + sizeof(DevJob) * 2 * count;
+  if (hipHostMalloc((void**)&b->stage, segs_at + sizeof(DevSeg) * 2 * count, hipHostMallocDefault) != hipSuccess)
     return LBM_ERR_OUT_OF_MEMORY;
+  b->items_host = reinterpret_cast<DevJobInst*>(b->stage + items_at);
+  b->jobs_host = reinterpret_cast<DevJob*>(b->stage + jobs_at);
+  b->segs_host = reinterpret_cast<DevSeg*>(b->stage + segs_at);
   LBM_HIP(hipMemsetAsync(b->status, 0, sizeof(int) * count, b->stream));
   LBM_HIP(hipEventCreate(&b->ev0));
   LBM_HIP(hipEventCreate(&b->ev1));

@@ -114,6 +114,7 @@ int stub_launches() { return (int)w.log.size(); }
 void stub_launch(int k, int64_t* out) { std::memcpy(out, &w.log[k], sizeof(Record)); }
 // device memory that may be allocated from now on
 void stub_limit(size_t more) { w.limit = more == ~size_t(0) ? more : w.used + more; }
+int stub_pinned() { return (int)w.pinned.size(); }   // allocations
 // memory of another GPU
 void* stub_foreign(size_t bytes) {
   void* p = calloc(1, bytes);

@@ -190,3 +190,12 @@ def test_tags_of_a_pass_do_not_wrap(host):
         assert low > last or low == 1   # (1: after a clear)
         last = high - 1
     b.close()
+
+
+def test_a_solver_pins_host_memory_twice(host):
+    """Each allocation of pinned memory takes about 40 us of a solver's 700."""
+    before = host.lib.stub_pinned()
+    s = lbm.Solver(problem("kdv", 800), stream=0)
+    assert host.lib.stub_pinned() - before <= 2
+    s.close()
+    assert host.lib.stub_pinned() == before
