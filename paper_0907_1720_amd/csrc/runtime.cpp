@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <tuple>
 #include <new>
@@ -37,8 +38,7 @@ constexpr int kMaxSlabs = 2048;       // workgroups of one slab launch
 constexpr int kUnevenNodes = 256;     // smallest power-sum grid split where its group is uneven
 constexpr int kSplitNodes = 1024;     // smallest power-sum grid split into slabs when the GPU is mostly idle
 constexpr int kMaxResidentGrid = 256 * 8;
-constexpr int kMaxLaunches = 512;     // queue launches per advance pass (one per lattice, precision, variant, kernel)
-constexpr int kMaxResident = 64;      // those of the LDS-resident kernels
+constexpr int kMaxResident = 64;      // LDS-resident launches per advance pass (one per lattice, precision, variant)
 constexpr int kAuxStreams = 16;       // concurrent lanes (resident launches, tiled groups, slab launches)
 constexpr uint64_t kMagic = 0x4c424d4850444531ull;   // "LBMHPDE1"
 
@@ -99,6 +99,30 @@ DeviceLimits query_limits() {
   return L;
 }
 
+// Slab workgroups of all batches of this process on one GPU.  A slab launch ends
+// only if all its workgroups get a place; two launches that each hold places the
+// other waits for would not.  So the launches in flight together never count more
+// workgroups than the GPU has CUs: a workgroup that waits for a place then has an
+// empty CU, or one whose kernel waits for no slab.  A launch that would exceed
+// that waits, on the device, for the other batches' before it.
+struct SlabGate {
+  struct Flight {
+    const lbm_batch_s* owner;
+    hipEvent_t done;
+    int need;          // workgroups, 0 once seen over
+  };
+  std::mutex mu;
+  std::vector<Flight> flight;   // one per batch that has launched slabs
+};
+SlabGate& slab_gate() {
+  static SlabGate gates[64];
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  return gates[dev & 63];
+}
+
+struct PlanMemo;
+
 }  // namespace
 
 struct lbm_batch_s {
@@ -114,26 +138,20 @@ struct lbm_batch_s {
   void* arena[2] = {nullptr, nullptr};  // serving: both state buffers carved from two arenas
   DevCoef* coefs = nullptr;
   int* status = nullptr;              // per instance: 1 = non-finite seen
-  int* counter = nullptr;             // work queue counters (one per group launch)
   int* slots = nullptr;               // per-workgroup queue slot of the resident kernel
-  int counters_cap = 0;
-  DevJobInst* items = nullptr;        // two slots of items_cap records (alternating calls)
-  DevJobInst* items_host = nullptr;   // pinned mirror of both slots (behind the stage, as the next two)
-  DevJob* jobs = nullptr;             // two slots of items_cap jobs
-  int* done = nullptr;                // per job: chunks published (two slots of items_cap)
-  DevJob* jobs_host = nullptr;
-  DevSeg* segs = nullptr;             // register-resident segments: two slots of items_cap records
-  DevSeg* segs_host = nullptr;
-  // whether a (q, prec, variant, nodes) instance on so many CUs advances sooner in slabs
-  std::map<std::tuple<int, int, int, int, int>, bool> sooner;
-  DevSeg* xsegs = nullptr;            // slabs and tiles of the register path: two slots of xsegs_cap
-  DevSeg* xsegs_host = nullptr;
-  int xsegs_cap = 0;
-  DevItem* parts = nullptr;           // queue items of the register launches: two slots of parts_cap
-  DevItem* parts_host = nullptr;
-  int parts_cap = 0;
+  // The tables of a pass (queue words that start at zero, jobs, segments, slabs,
+  // tiles ...), laid out anew for each and uploaded in one copy: two slots of
+  // tables_cap bytes, used in turn, and their pinned mirror.
+  unsigned char* tables = nullptr;
+  unsigned char* tables_host = nullptr;
+  size_t tables_cap = 0;
+  std::vector<DevJobInst> hitems;     // of the pass being planned
+  std::vector<DevJob> hjobs;
+  std::vector<DevSeg> hsegs;
+  SlabGate* gate = nullptr;           // entered with gate_done
+  hipEvent_t gate_done = nullptr;
+  std::shared_ptr<PlanMemo> memo;
   hipEvent_t items_done[2] = {nullptr, nullptr};
-  int items_cap = 0;
   int slot = 0;
   double* scratch = nullptr;          // phi read-out of grids beyond the stage; partial sums
   size_t scratch_elems = 0;
@@ -144,15 +162,6 @@ struct lbm_batch_s {
   int read_seq = 0;                   // read-outs watched so far
   size_t stage_bytes = 0;             // data bytes
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  // temporal blocking tables (two slots like the items)
-  DevTile* tiles = nullptr;
-  DevTile* tiles_host = nullptr;
-  int tiles_cap = 0;
-  DevTileInst* tinsts = nullptr;       // two slots of tinsts_cap records
-  int tinsts_cap = 0;
-  DevSlab* slabs = nullptr;           // two slots of slabs_cap records
-  DevSlab* slabs_host = nullptr;
-  int slabs_cap = 0;
   // halo strips of register slabs: words tagged below strip_tag (0: never written)
   uint64_t* strips = nullptr;
   size_t strips_cap = 0;
@@ -161,7 +170,6 @@ struct lbm_batch_s {
   size_t xbuf_bytes = 0;
   int* sflags = nullptr;              // per-slab block flags
   int sflags_cap = 0;
-  DevTileInst* tinsts_host = nullptr;
   int tile_steps = 0;                 // steps per tiled launch (0 = automatic)
   int tile_wgs = 0;                   // tiled workgroups per CU the LDS budget is split for (0 = automatic)
   int res_grid = 0;                   // cap on the resident grid (0 = automatic)
@@ -261,6 +269,12 @@ size_t elem_size(const HostInst& h) { return h.f32 ? sizeof(float) : sizeof(doub
 void destroy_batch(lbm_batch_s* b) {
   if (!b) return;
   hipStreamSynchronize(b->stream);
+  if (b->gate) {
+    std::lock_guard<std::mutex> hold(b->gate->mu);
+    auto& fl = b->gate->flight;
+    fl.erase(std::find_if(fl.begin(), fl.end(), [&](const SlabGate::Flight& f) { return f.owner == b; }));
+    hipEventDestroy(b->gate_done);
+  }
   if (b->arena[0]) {
     hipFree(b->arena[0]);
     hipFree(b->arena[1]);
@@ -274,28 +288,15 @@ void destroy_batch(lbm_batch_s* b) {
   }
   hipFree(b->coefs);
   hipFree(b->status);
-  hipFree(b->counter);
   hipFree(b->slots);
-  hipFree(b->items);
-  hipFree(b->jobs);
-  hipFree(b->done);
   for (StepGraph& g : b->step_graphs) release_graph(&g);
   hipFree(b->bound);
-  hipFree(b->segs);
-  hipFree(b->parts);
-  if (b->parts_host) hipHostFree(b->parts_host);
-  hipFree(b->xsegs);
-  if (b->xsegs_host) hipHostFree(b->xsegs_host);
+  hipFree(b->tables);
+  if (b->tables_host) hipHostFree(b->tables_host);
   for (int k = 0; k < 2; ++k)
     if (b->items_done[k]) hipEventDestroy(b->items_done[k]);
   hipFree(b->scratch);
   if (b->stage) hipHostFree(b->stage);
-  hipFree(b->tiles);
-  hipFree(b->tinsts);
-  if (b->tiles_host) hipHostFree(b->tiles_host);
-  if (b->tinsts_host) hipHostFree(b->tinsts_host);
-  hipFree(b->slabs);
-  if (b->slabs_host) hipHostFree(b->slabs_host);
   hipFree(b->strips);
   hipFree(b->xbuf);
   hipFree(b->sflags);
@@ -360,6 +361,22 @@ size_t stage_need(int64_t len, bool coefs) {
 
 lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want);
 
+// (each allocation of pinned memory takes about 40 us)
+lbm_status alloc_pass_tables(lbm_batch_s* b, size_t cap) {
+  cap = (cap + 255) / 256 * 256;
+  if (b->tables_cap) {
+    LBM_HIP(hipStreamSynchronize(b->stream));   // earlier passes must be done with them
+    hipFree(b->tables);
+    hipHostFree(b->tables_host);
+    b->tables = b->tables_host = nullptr;
+    b->tables_cap = 0;
+  }
+  if (hipMalloc(&b->tables, 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+  if (hipHostMalloc((void**)&b->tables_host, 2 * cap, hipHostMallocDefault) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+  b->tables_cap = cap;
+  return LBM_OK;
+}
+
 lbm_status alloc_batch(lbm_batch_s* b, void* dev_buf, size_t buf_bytes) {
   size_t n64 = 0, n32 = 0, maxn = 0, stage = 0;
   for (HostInst& h : b->inst) {
@@ -396,8 +413,6 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want) {
   const int count = (int)b->inst.size();
   if (hipMalloc(&b->coefs, sizeof(DevCoef) * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   if (hipMalloc(&b->status, sizeof(int) * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  b->counters_cap = 2 * kMaxLaunches;   // 2 item slots x up to kMaxLaunches launches
-  if (hipMalloc(&b->counter, sizeof(int) * b->counters_cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   // one queue slot per workgroup of each resident launch
   if (hipMalloc(&b->slots, sizeof(int) * kMaxResidentGrid * 2 * kMaxResident) != hipSuccess)
     return LBM_ERR_OUT_OF_MEMORY;
@@ -406,27 +421,16 @@ lbm_status alloc_tables(lbm_batch_s* b, size_t maxn, size_t stage_want) {
     LBM_HIP(hipEventCreateWithFlags(&b->join[k], hipEventDisableTiming));
   }
   LBM_HIP(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
-  b->tinsts_cap = count;
-  if (hipMalloc(&b->tinsts, sizeof(DevTileInst) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipHostMalloc((void**)&b->tinsts_host, sizeof(DevTileInst) * 2 * count, hipHostMallocDefault) != hipSuccess)
-    return LBM_ERR_OUT_OF_MEMORY;
-  b->items_cap = count;
-  if (hipMalloc(&b->items, sizeof(DevJobInst) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipMalloc(&b->jobs, sizeof(DevJob) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipMalloc(&b->done, sizeof(int) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-  if (hipMalloc(&b->segs, sizeof(DevSeg) * 2 * count) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
+  // (a job, its instance and segment, and two queue items of each instance)
+  const lbm_status ts = alloc_pass_tables(
+      b, 4096 + (size_t)count * (sizeof(int) + sizeof(DevJob) + sizeof(DevJobInst) + sizeof(DevSeg) + 2 * sizeof(DevItem)));
+  if (ts != LBM_OK) return ts;
   for (int k = 0; k < 2; ++k) LBM_HIP(hipEventCreateWithFlags(&b->items_done[k], hipEventDisableTiming));
   b->scratch_elems = maxn + 64;
   if (hipMalloc(&b->scratch, sizeof(double) * b->scratch_elems) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
   b->stage_bytes = std::min(kStageMost, std::max(kStageLeast, stage_want));
-  // (the tables behind the stage, in one allocation: each takes about 40 us)
-  const size_t items_at = (kStageHead + b->stage_bytes + 255) / 256 * 256;
-  const size_t jobs_at = items_at + sizeof(DevJobInst) * 2 * count, segs_at = jobs_at + sizeof(DevJob) * 2 * count;
-  if (hipHostMalloc((void**)&b->stage, segs_at + sizeof(DevSeg) * 2 * count, hipHostMallocDefault) != hipSuccess)
+  if (hipHostMalloc((void**)&b->stage, kStageHead + b->stage_bytes, hipHostMallocDefault) != hipSuccess)
     return LBM_ERR_OUT_OF_MEMORY;
-  b->items_host = reinterpret_cast<DevJobInst*>(b->stage + items_at);
-  b->jobs_host = reinterpret_cast<DevJob*>(b->stage + jobs_at);
-  b->segs_host = reinterpret_cast<DevSeg*>(b->stage + segs_at);
   LBM_HIP(hipMemsetAsync(b->status, 0, sizeof(int) * count, b->stream));
   LBM_HIP(hipEventCreate(&b->ev0));
   LBM_HIP(hipEventCreate(&b->ev1));
@@ -1107,52 +1111,171 @@ SlabChunks slab_chunks(const std::vector<std::pair<int, int64_t>>& mem, int64_t 
   return out;
 }
 
-// Slab workgroups of all batches of this process on one GPU.  A slab launch ends
-// only if all its workgroups get a place; two launches that each hold places the
-// other waits for would not.  So the launches in flight together never count more
-// workgroups than the GPU has CUs: a workgroup that waits for a place then has an
-// empty CU, or one whose kernel waits for no slab.  A launch that would exceed
-// that waits, on the device, for the ones issued before it.
-struct SlabGate {
-  std::mutex mu;
-  std::vector<std::pair<hipEvent_t, int>> flight;   // (done, workgroups), in the order of issue
-};
-SlabGate& slab_gate() {
-  static SlabGate gates[64];
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  return gates[dev & 63];
-}
-// waits of `stream` before a launch of `need` workgroups (gate held)
-lbm_status pass_gate(SlabGate& gate, int need, int cus, hipStream_t stream) {
-  auto& fl = gate.flight;
+// waits of b's stream before launches of `need` workgroups (gate held)
+lbm_status pass_gate(SlabGate& gate, lbm_batch_s* b, int need) {
   int sum = 0;
-  for (size_t k = 0; k < fl.size();) {
-    if (hipEventQuery(fl[k].first) == hipSuccess) {
-      LBM_HIP(hipEventDestroy(fl[k].first));
-      fl.erase(fl.begin() + k);
-    } else {
-      sum += fl[k++].second;
+  for (SlabGate::Flight& f : gate.flight) {
+    // (b's own earlier passes come before on its stream)
+    if (f.need == 0 || (f.owner == b && f.need <= need)) continue;
+    if (hipEventQuery(f.done) == hipSuccess)
+      f.need = 0;
+    else
+      (void)hipGetLastError();   // (not ready is no error)
+    if (f.owner != b) sum += f.need;
+  }
+  for (const SlabGate::Flight& f : gate.flight) {
+    if (sum + need <= b->lim.cus) break;
+    if (f.owner == b || f.need == 0) continue;
+    LBM_HIP(hipStreamWaitEvent(b->stream, f.done, 0));
+    sum -= f.need;
+  }
+  return LBM_OK;
+}
+// b's launches have been issued; until they are over, its entry counts the most of
+// them and of b's earlier ones
+lbm_status enter_gate(SlabGate& gate, lbm_batch_s* b, int need) {
+  if (!b->gate) {
+    LBM_HIP(hipEventCreateWithFlags(&b->gate_done, hipEventDisableTiming));
+    gate.flight.push_back({b, b->gate_done, 0});
+    b->gate = &gate;
+  }
+  LBM_HIP(hipEventRecord(b->gate_done, b->stream));
+  for (SlabGate::Flight& f : gate.flight)
+    if (f.owner == b) f.need = std::max(f.need, need);
+  return LBM_OK;
+}
+
+// Plans depend on sizes and step counts alone, and a program that advances a few
+// steps at a time asks for the same ones again: 300 sizes beyond one LDS cost 160
+// us of planning for 130 us of steps.  A batch keeps the latest, by everything
+// they were made from.
+struct RingPlan {
+  std::vector<RegFit> fit;
+  int job_waves = 4, jobs_per_cu = 1;
+  bool wide = false, found = false;
+};
+struct PlanMemo {
+  std::map<std::vector<int64_t>, std::pair<bool, SegPlan>> segs;
+  std::map<std::vector<int64_t>, RingPlan> rings;
+  size_t ring_instances = 0;   // of all of them
+  std::map<std::tuple<int, int, int, int>, std::pair<double, double>> ring_steps;   // by (q, prec, code, nodes)
+  // whether a (q, prec, variant, nodes) instance on so many CUs advances sooner in slabs
+  std::map<std::tuple<int, int, int, int, int>, bool> sooner;
+};
+
+// Nodes per lane: few spend more on halos and lane edges, many leave more of
+// an instance's last lanes empty and give fewer waves to share the SIMDs.
+// Each instance takes the width with the least wave time among one kernel's
+// (narrow or wide: one launch per group, since a pass's launches run side by
+// side only while there are hardware queues) up to a bound, or all of them the
+// same one; kernel, widths and waves per job are those for which the group,
+// packed, is estimated to end first.  (By its waves alone, 512 grids of 1000
+// nodes took nine waves each, one to a job of sixteen.)
+bool plan_rings(const lbm_batch_s* b, int q, int pr, int code, const std::vector<int>& g, const int64_t* steps, double cus,
+                RingPlan* out) {
+  std::vector<RegFit>& fit = out->fit;
+  fit.resize(g.size());
+  std::vector<RegFit> trial(g.size());
+  const bool bounded = (code >> 16) != 0;
+  double best = 0.0;
+  std::vector<RegClass> classes;
+  std::map<int64_t, int> step_ids;   // of the group's step counts
+  std::vector<int> step_id, class_of;
+  std::vector<RegFit> placed;   // each instance by each width
+  for (int i : g) step_id.push_back(step_ids.insert({steps[i], (int)step_ids.size()}).first->second);
+  for (int cls = 0; cls < 2; ++cls) {
+    RegFit menu[kRegWidths + 1];
+    const int full = reg_waves(cls != 0);
+    int widths = 0;
+    if (!bounded) {
+      widths = reg_menu(q, pr, code, cls != 0, menu);
+    } else if (cls == 0) {
+      menu[0] = bound_fit();
+      widths = 1;
+    }
+    if (widths == 0) continue;
+    // wave time of an instance: that of whole rounds over the SIMDs where no
+    // other has room beside it
+    auto load = [&](const RegFit& f) { return (2 * f.waves > full ? (f.waves + 3) / 4 * 4 : f.waves) * f.cost; };
+    placed.resize(g.size() * widths);
+    for (size_t u = 0; u < g.size(); ++u) {
+      RegFit* at = &placed[u * widths];
+      const int n = b->inst[g[u]].n;
+      if (u > 0 && n == b->inst[g[u - 1]].n) {
+        std::copy(at - widths, at, at);
+        continue;
+      }
+      for (int w = 0; w < widths; ++w) {
+        at[w] = menu[w];
+        reg_place(q, n, &at[w]);
+        if (bounded) continue;
+        RegFit f = reg_tight(q, pr, menu[w]);
+        reg_place(q, n, &f);
+        if (load(f) < load(at[w])) at[w] = f;
+      }
+    }
+    for (int pick = 2 * widths - 1; pick >= 0; --pick) {
+      const int most = pick / 2, from = pick % 2 ? most : 0;
+      if (from == most && most == 0 && pick % 2) continue;
+      int64_t waves = 0;
+      int top = 1;
+      bool ok = true;
+      classes.clear();
+      class_of.assign(step_ids.size() * widths * 2, -1);
+      for (size_t u = 0; u < g.size() && ok; ++u) {
+        double least = 0.0;
+        int taken = 0;
+        for (int w = from; w <= most; ++w) {
+          const RegFit& f = placed[u * widths + w];
+          if (f.waves > full) continue;
+          if (least == 0.0 || load(f) < least) {
+            trial[u] = f;
+            taken = 2 * w + (f.s != menu[w].s);
+            least = load(f);
+          }
+        }
+        ok = least > 0.0;
+        if (!ok) break;
+        waves += trial[u].waves;
+        top = std::max(top, trial[u].waves);
+        int& at = class_of[step_id[u] * widths * 2 + taken];
+        if (at < 0) {
+          at = (int)classes.size();
+          classes.emplace_back();
+          classes[at].steps = steps[g[u]];
+          classes[at].f = trial[u];
+        }
+        RegClass& c = classes[at];
+        ++c.count[trial[u].waves];
+        c.least = std::min(c.least, trial[u].waves);
+        c.most = std::max(c.most, trial[u].waves);
+      }
+      if (!ok) continue;
+      // waves of a job: as many as the waves make for each CU, all a CU holds,
+      // and (few classes) what lies between
+      const int even = std::max(top, (int)std::min<double>(full, std::ceil(waves / cus)));
+      for (int share = top; share <= full; ++share) {
+        if (share != full && share != even && classes.size() > 64) continue;
+        int beside = 1;
+        const double est = reg_group(classes, share, full, cus, &beside);
+        if (best == 0.0 || est < best) {
+          best = est;
+          fit = trial;
+          out->job_waves = share;
+          out->jobs_per_cu = beside;
+          out->wide = cls != 0;
+        }
+      }
     }
   }
-  (void)hipGetLastError();   // (an event that is not ready is no error)
-  for (size_t k = 0; k < fl.size() && sum + need > cus; ++k) {
-    LBM_HIP(hipStreamWaitEvent(stream, fl[k].first, 0));
-    sum -= fl[k].second;
-  }
-  return LBM_OK;
-}
-lbm_status enter_gate(SlabGate& gate, int need, hipStream_t stream) {
-  hipEvent_t done;
-  LBM_HIP(hipEventCreateWithFlags(&done, hipEventDisableTiming));
-  LBM_HIP(hipEventRecord(done, stream));
-  gate.flight.push_back({done, need});
-  return LBM_OK;
+  return best > 0.0;
 }
 
 // One pass: every instance advances by steps[i] <= kMaxStepsPerLaunch.
 lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const int count = (int)b->inst.size();
+  if (!b->memo) b->memo = std::make_shared<PlanMemo>();
+  PlanMemo& memo = *b->memo;
   // resident groups by (q, precision, variant); the rest streams through HBM
   // (q, prec, variant code, bounded)
   std::map<std::tuple<int, int, int, int>, std::vector<int>> res;
@@ -1185,13 +1308,13 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   auto spread_sooner = [&](const HostInst& h) {
     const int cus = b->lim.cus / std::max(1, sharing);
     const auto key = std::make_tuple(h.q, h.prec, h.D, h.n, cus);
-    const auto it = b->sooner.find(key);
-    if (it != b->sooner.end()) return it->second;
-    if (b->sooner.size() >= 4096) b->sooner.clear();
+    const auto it = memo.sooner.find(key);
+    if (it != memo.sooner.end()) return it->second;
+    if (memo.sooner.size() >= 4096) memo.sooner.clear();
     SegPlan p;
     const bool yes = cus > 1 && seg_plan(h.q, h.prec, h.D, {{h.n, 1}}, cus, 0, 0, false, 1, &p) &&
                      p.est < 0.95 * ring_step(h.q, h.prec, h.D, h.n);
-    return b->sooner[key] = yes;
+    return memo.sooner[key] = yes;
   };
   // Power sums in LDS: an instance is one CU's work, so that a group ends with its
   // largest one.  Where that takes more than one and a half times the even share
@@ -1267,9 +1390,12 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const int k = b->slot;
   b->slot ^= 1;
   LBM_HIP(hipEventSynchronize(b->items_done[k]));
-  DevJobInst* hitems = b->items_host + (size_t)k * b->items_cap;
-  DevJob* hjobs = b->jobs_host + (size_t)k * b->items_cap;
-  DevSeg* hsegs = b->segs_host + (size_t)k * b->items_cap;
+  std::vector<DevJobInst>& hitems = b->hitems;
+  std::vector<DevJob>& hjobs = b->hjobs;
+  std::vector<DevSeg>& hsegs = b->hsegs;
+  hitems.clear();
+  hjobs.clear();
+  hsegs.clear();
   // est_max / est_sum: the longest job's and all jobs' duration estimates
   struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; bool reg, wide; int per_cu, grid, part0, parts; int64_t partsteps; };
   std::vector<Launch> launches;
@@ -1397,7 +1523,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         L.maxsteps = std::max<int64_t>(L.maxsteps, bn.steps);
         L.est_max = std::max(L.est_max, pl.est);
         L.est_sum += pl.est;
-        DevJob& jb = hjobs[njobs++];
+        DevJob& jb = (++njobs, hjobs.emplace_back());
         jb.first = used;
         jb.count = m;
         jb.steps = (int)bn.steps;
@@ -1408,7 +1534,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         for (int u = 0; u < m; ++u) {
           const int i = bn.members[u];
           const HostInst& h = b->inst[i];
-          DevJobInst& it = hitems[used++];
+          DevJobInst& it = (++used, hitems.emplace_back());
           it.addr = (uint64_t)(uintptr_t)state_cur(b, h);
           it.n = h.n;
           it.stride = h.stride;
@@ -1543,23 +1669,47 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     };
     auto plan = [&](const std::tuple<int, int, int>& key, const std::map<int, int>& sizes, int cus, int want, bool tile,
                     int chunks, SegPlan* p) {
-      // (steps asked for that no segment's halos hold are halved)
-      while (!seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile, chunks, p)) {
-        if (want <= (tile ? 1 : 2)) return false;
-        want = tile ? want / 2 : want / 4 * 2;
+      std::vector<int64_t> from{std::get<0>(key), std::get<1>(key), std::get<2>(key), cus, want, b->tile_wgs, tile, chunks};
+      for (const auto& [n, times] : sizes) {
+        from.push_back(n);
+        from.push_back(times);
       }
-      return true;
+      const auto it = memo.segs.find(from);
+      if (it == memo.segs.end()) {
+        // (steps asked for that no segment's halos hold are halved)
+        bool found;
+        while (!(found = seg_plan(std::get<0>(key), std::get<1>(key), std::get<2>(key), sizes, cus, want, b->tile_wgs, tile,
+                                  chunks, p)) &&
+               want > (tile ? 1 : 2))
+          want = tile ? want / 2 : want / 4 * 2;
+        if (memo.segs.size() >= 256) memo.segs.clear();
+        memo.segs[std::move(from)] = {found, *p};
+        return found;
+      }
+      *p = it->second.second;
+      return it->second.first;
+    };
+    auto ring_time = [&](const std::tuple<int, int, int>& key, int n, double* step) {
+      const auto of = std::make_tuple(std::get<0>(key), std::get<1>(key), std::get<2>(key), n);
+      auto it = memo.ring_steps.find(of);
+      if (it == memo.ring_steps.end()) {
+        if (memo.ring_steps.size() >= 4096) memo.ring_steps.clear();
+        std::pair<double, double> t;
+        t.first = ring_step(std::get<0>(key), std::get<1>(key), std::get<2>(key), n, &t.second);
+        it = memo.ring_steps.insert({of, t}).first;
+      }
+      *step = it->second.second;
+      return it->second.first;
     };
     // Whole instances instead where enough of them fill the GPU: the group's
     // waves over the CUs, no exchange between workgroups and no rounds of
     // launches.
     for (auto it = spread.begin(); it != spread.end();) {
       const auto& key = it->first;
-      const int q = std::get<0>(key), pr = std::get<1>(key), code = std::get<2>(key);
       double longest = 0.0, sum = 0.0;
       for (int i : it->second) {
         double step = 0.0;
-        const double one = ring_step(q, pr, code, b->inst[i].n, &step);
+        const double one = ring_time(key, b->inst[i].n, &step);
         longest = std::max(longest, one);
         sum += step / b->lim.cus;
       }
@@ -1665,108 +1815,20 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     const bool bounded = (code >> 16) != 0;
     // the CUs that are this group's by its share of the pass's work
     const double cus = std::max(1.0, b->lim.cus * work_of(group.first, group.second) / all_work);
-    // Nodes per lane: few spend more on halos and lane edges, many leave more of
-    // an instance's last lanes empty and give fewer waves to share the SIMDs.
-    // Each instance takes the width with the least wave time among one kernel's
-    // (narrow or wide: one launch per group, since a pass's launches run side by
-    // side only while there are hardware queues) up to a bound, or all of them the
-    // same one; kernel, widths and waves per job are those for which the group,
-    // packed, is estimated to end first.  (By its waves alone, 512 grids of 1000
-    // nodes took nine waves each, one to a job of sixteen.)
-    std::vector<RegFit> fit(g.size()), trial(g.size());
-    double best = 0.0;
-    int job_waves = 4, jobs_per_cu = 1;
-    bool wide = false;
-    std::vector<RegClass> classes;
-    std::map<int64_t, int> step_ids;   // of the group's step counts
-    std::vector<int> step_id, class_of;
-    std::vector<RegFit> placed;   // each instance by each width
-    for (int i : g) step_id.push_back(step_ids.insert({steps[i], (int)step_ids.size()}).first->second);
-    for (int cls = 0; cls < 2; ++cls) {
-      RegFit menu[kRegWidths + 1];
-      const int full = reg_waves(cls != 0);
-      int widths = 0;
-      if (!bounded) {
-        widths = reg_menu(q, pr, code, cls != 0, menu);
-      } else if (cls == 0) {
-        menu[0] = bound_fit();
-        widths = 1;
-      }
-      // wave time of an instance: that of whole rounds over the SIMDs where no
-      // other has room beside it
-      auto load = [&](const RegFit& f) { return (2 * f.waves > full ? (f.waves + 3) / 4 * 4 : f.waves) * f.cost; };
-      placed.resize(g.size() * widths);
-      for (size_t u = 0; u < g.size(); ++u) {
-        RegFit* at = &placed[u * widths];
-        const int n = b->inst[g[u]].n;
-        if (u > 0 && n == b->inst[g[u - 1]].n) {
-          std::copy(at - widths, at, at);
-          continue;
-        }
-        for (int w = 0; w < widths; ++w) {
-          at[w] = menu[w];
-          reg_place(q, n, &at[w]);
-          if (bounded) continue;
-          RegFit f = reg_tight(q, pr, menu[w]);
-          reg_place(q, n, &f);
-          if (load(f) < load(at[w])) at[w] = f;
-        }
-      }
-      for (int pick = 2 * widths - 1; pick >= 0; --pick) {
-        const int most = pick / 2, from = pick % 2 ? most : 0;
-        if (from == most && most == 0 && pick % 2) continue;
-        int64_t waves = 0;
-        int top = 1;
-        bool ok = true;
-        classes.clear();
-        class_of.assign(step_ids.size() * widths * 2, -1);
-        for (size_t u = 0; u < g.size() && ok; ++u) {
-          double least = 0.0;
-          int taken = 0;
-          for (int w = from; w <= most; ++w) {
-            const RegFit& f = placed[u * widths + w];
-            if (f.waves > full) continue;
-            if (least == 0.0 || load(f) < least) {
-              trial[u] = f;
-              taken = 2 * w + (f.s != menu[w].s);
-              least = load(f);
-            }
-          }
-          ok = least > 0.0;
-          if (!ok) break;
-          waves += trial[u].waves;
-          top = std::max(top, trial[u].waves);
-          int& at = class_of[step_id[u] * widths * 2 + taken];
-          if (at < 0) {
-            at = (int)classes.size();
-            classes.emplace_back();
-            classes[at].steps = steps[g[u]];
-            classes[at].f = trial[u];
-          }
-          RegClass& c = classes[at];
-          ++c.count[trial[u].waves];
-          c.least = std::min(c.least, trial[u].waves);
-          c.most = std::max(c.most, trial[u].waves);
-        }
-        if (!ok) continue;
-        // waves of a job: as many as the waves make for each CU, all a CU holds,
-        // and (few classes) what lies between
-        const int even = std::max(top, (int)std::min<double>(full, std::ceil(waves / cus)));
-        for (int share = top; share <= full; ++share) {
-          if (share != full && share != even && classes.size() > 64) continue;
-          int beside = 1;
-          const double est = reg_group(classes, share, full, cus, &beside);
-          if (best == 0.0 || est < best) {
-            best = est;
-            fit = trial;
-            job_waves = share;
-            jobs_per_cu = beside;
-            wide = cls != 0;
-          }
-        }
-      }
+    std::vector<int64_t> from{q, pr, code, (int64_t)std::lround(64.0 * cus)};
+    for (int i : g) {
+      from.push_back(b->inst[i].n);
+      from.push_back(steps[i]);
     }
-    if (best == 0.0) return LBM_ERR_UNSUPPORTED;
+    if (memo.ring_instances > 65536) {
+      memo.rings.clear();
+      memo.ring_instances = 0;
+    }
+    memo.ring_instances += g.size();
+    RingPlan& ring = memo.rings[std::move(from)];
+    if (!ring.found) ring.found = plan_rings(b, q, pr, code, g, steps, cus, &ring);
+    if (!ring.found) return LBM_ERR_UNSUPPORTED;
+    const std::vector<RegFit>& fit = ring.fit;
     std::vector<int> order(g.size());
     for (size_t u = 0; u < g.size(); ++u) order[u] = (int)u;
     std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
@@ -1786,7 +1848,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
           fit[u].s != fit[order[o - 1]].s)
         for (size_t& v : open) v = bins.size();
       size_t& v = open[w];
-      while (v < bins.size() && bins[v].waves + w > job_waves) ++v;
+      while (v < bins.size() && bins[v].waves + w > ring.job_waves) ++v;
       if (v == bins.size()) bins.push_back(Bin{0, {}});
       bins[v].waves += w;
       bins[v].members.push_back(u);
@@ -1795,7 +1857,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       return (double)steps[g[bn.members[0]]] * ((bn.waves + 3) / 4) * fit[bn.members[0]].cost;
     };
     std::stable_sort(bins.begin(), bins.end(), [&](const Bin& a, const Bin& c) { return job_est(a) > job_est(c); });
-    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, wide, jobs_per_cu, 0, 0, 0, 0};
+    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, ring.wide, ring.jobs_per_cu, 0, 0, 0, 0};
     for (const Bin& bn : bins) {
       const RegFit& f0 = fit[bn.members[0]];
       const int64_t st = steps[g[bn.members[0]]];
@@ -1803,7 +1865,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       L.maxsteps = std::max<int64_t>(L.maxsteps, st);
       L.est_max = std::max(L.est_max, est);
       L.est_sum += est;
-      DevJob& jb = hjobs[njobs++];
+      DevJob& jb = (++njobs, hjobs.emplace_back());
       jb = DevJob{};
       jb.first = nsegs;
       jb.count = (int)bn.members.size();
@@ -1815,7 +1877,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       for (int u : bn.members) {
         const int i = g[u];
         const HostInst& h = b->inst[i];
-        DevSeg& sg = hsegs[nsegs++];
+        DevSeg& sg = (++nsegs, hsegs.emplace_back());
         sg = DevSeg{};
         sg.in = sg.out = (uint64_t)(uintptr_t)state_cur(b, h);
         sg.n = sg.len = h.n;
@@ -1840,7 +1902,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     L.count = njobs - L.first;
     reg_est += L.est_sum;
     reg_jobs += L.count;
-    if ((int)launches.size() >= kMaxLaunches) return LBM_ERR_UNSUPPORTED;
     launches.push_back(L);
     for (const Bin& bn : bins) reg_job_est.push_back(job_est(bn));
   }
@@ -1869,7 +1930,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       L.grid = std::max(1, std::min(L.grid, (int)std::lround(per_cu * b->lim.cus * L.est_sum / reg_est)));
     if (b->res_grid > 0) L.grid = std::min(L.grid, b->res_grid);
     L.part0 = (int)parts.size();
-    const DevJob* jobs = hjobs + L.first;
+    const DevJob* jobs = hjobs.data() + L.first;
     if (b->res_chunks > 0) {   // chunks as asked, chunk by chunk
       for (int c = 0; c < b->res_chunks; ++c)
         for (int k = 0; k < L.count; ++k) {
@@ -1927,19 +1988,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     }
     L.parts = (int)parts.size() - L.part0;
     for (int k = L.part0; k < (int)parts.size(); ++k) L.partsteps = std::max<int64_t>(L.partsteps, parts[k].steps);
-  }
-  if ((int)parts.size() > b->parts_cap) {
-    LBM_HIP(hipStreamSynchronize(b->stream));   // earlier passes must be done with them
-    hipFree(b->parts);
-    if (b->parts_host) hipHostFree(b->parts_host);
-    b->parts = nullptr;
-    b->parts_host = nullptr;
-    b->parts_cap = 0;
-    const int cap = (int)parts.size() * 2;
-    if (hipMalloc(&b->parts, sizeof(DevItem) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-    if (hipHostMalloc((void**)&b->parts_host, sizeof(DevItem) * 2 * cap, hipHostMallocDefault) != hipSuccess)
-      return LBM_ERR_OUT_OF_MEMORY;
-    b->parts_cap = cap;
   }
   // temporal blocking plan per (q, prec) group
   struct TileGroup { int q; int prec; int first, ntiles, tfirst, tcount, s, halo, launches, block; size_t lds; double est; };
@@ -2084,9 +2132,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     slab_side_by_side = false;
   }
   if (!svec.empty() || !xsv.empty()) {
-    if ((int)svec.size() > b->slabs_cap || xbuf_need > b->xbuf_bytes || flags_need > b->sflags_cap ||
-        (int)xsv.size() > b->xsegs_cap || strips_need > b->strips_cap) {
-      // grow the slab tables and exchange buffers; earlier passes must be done with them
+    if (xbuf_need > b->xbuf_bytes || flags_need > b->sflags_cap || strips_need > b->strips_cap) {
+      // grow the exchange buffers; earlier passes must be done with them
       LBM_HIP(hipStreamSynchronize(b->stream));
       if (strips_need > b->strips_cap) {
         hipFree(b->strips);
@@ -2095,30 +2142,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         if (hipMalloc(&b->strips, sizeof(uint64_t) * strips_need) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
         b->strips_cap = strips_need;
         b->strip_tag = UINT32_MAX;   // to be cleared
-      }
-      if ((int)xsv.size() > b->xsegs_cap) {
-        hipFree(b->xsegs);
-        if (b->xsegs_host) hipHostFree(b->xsegs_host);
-        b->xsegs = nullptr;
-        b->xsegs_host = nullptr;
-        b->xsegs_cap = 0;
-        const int cap = (int)xsv.size() * 2;
-        if (hipMalloc(&b->xsegs, sizeof(DevSeg) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-        if (hipHostMalloc((void**)&b->xsegs_host, sizeof(DevSeg) * 2 * cap, hipHostMallocDefault) != hipSuccess)
-          return LBM_ERR_OUT_OF_MEMORY;
-        b->xsegs_cap = cap;
-      }
-      if ((int)svec.size() > b->slabs_cap) {
-        hipFree(b->slabs);
-        if (b->slabs_host) hipHostFree(b->slabs_host);
-        b->slabs = nullptr;
-        b->slabs_host = nullptr;
-        b->slabs_cap = 0;
-        const int cap = (int)svec.size() * 2;
-        if (hipMalloc(&b->slabs, sizeof(DevSlab) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-        if (hipHostMalloc((void**)&b->slabs_host, sizeof(DevSlab) * 2 * cap, hipHostMallocDefault) != hipSuccess)
-          return LBM_ERR_OUT_OF_MEMORY;
-        b->slabs_cap = cap;
       }
       if (xbuf_need > b->xbuf_bytes) {
         hipFree(b->xbuf);
@@ -2135,10 +2158,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
         b->sflags_cap = flags_need;
       }
     }
-    if (!xsv.empty())
-      std::memcpy(b->xsegs_host + (size_t)k * b->xsegs_cap, xsv.data(), sizeof(DevSeg) * xsv.size());
-    if (!svec.empty())
-      std::memcpy(b->slabs_host + (size_t)k * b->slabs_cap, svec.data(), sizeof(DevSlab) * svec.size());
     for (const auto& group : slb) {
       lbm_status st = ensure_second_buffer(b, std::get<1>(group.first) != 0);
       if (st != LBM_OK) return st;
@@ -2200,22 +2219,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     }
   }
   if (!tvec.empty()) {
-    if ((int)tvec.size() > b->tiles_cap) {
-      // grow the tile tables (both slots); previous users of the buffers must be done
-      LBM_HIP(hipStreamSynchronize(b->stream));
-      hipFree(b->tiles);
-      if (b->tiles_host) hipHostFree(b->tiles_host);
-      b->tiles = nullptr;
-      b->tiles_host = nullptr;
-      b->tiles_cap = 0;
-      const int cap = (int)tvec.size() * 2;
-      if (hipMalloc(&b->tiles, sizeof(DevTile) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-      if (hipHostMalloc((void**)&b->tiles_host, sizeof(DevTile) * 2 * cap, hipHostMallocDefault) != hipSuccess)
-        return LBM_ERR_OUT_OF_MEMORY;
-      b->tiles_cap = cap;
-    }
-    std::memcpy(b->tiles_host + (size_t)k * b->tiles_cap, tvec.data(), sizeof(DevTile) * tvec.size());
-    for (int i : str) (void)i;
     for (int qq = 4; qq < 8; ++qq)
       for (int pr = 0; pr < 3; ++pr) {
         lbm_status st = til[qq][pr].empty() ? LBM_OK : ensure_second_buffer(b, pr != 0);
@@ -2223,58 +2226,49 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       }
   }
 
+  // every table of the pass in one copy (five copies and clears took 10 us more)
+  size_t need = 0;
+  auto place = [&](size_t bytes) {
+    const size_t at = need;
+    need += (bytes + 15) / 16 * 16;
+    return at;
+  };
+  const size_t words = launches.size() + (size_t)njobs;   // a counter of each launch, parts done of each job
+  const size_t words_at = place(sizeof(int) * words), jobs_at = place(sizeof(DevJob) * hjobs.size());
+  const size_t items_at = place(sizeof(DevJobInst) * hitems.size()), segs_at = place(sizeof(DevSeg) * hsegs.size());
+  const size_t parts_at = place(sizeof(DevItem) * parts.size()), xsegs_at = place(sizeof(DevSeg) * xsv.size());
+  const size_t slabs_at = place(sizeof(DevSlab) * svec.size()), tiles_at = place(sizeof(DevTile) * tvec.size());
+  const size_t tinsts_at = place(sizeof(DevTileInst) * htin.size());
+  if (need > b->tables_cap) {
+    const lbm_status ts = alloc_pass_tables(b, 2 * need);
+    if (ts != LBM_OK) return ts;
+  }
+  unsigned char* th = b->tables_host + (size_t)k * b->tables_cap;
+  unsigned char* td = b->tables + (size_t)k * b->tables_cap;
+  auto fill = [&](size_t at, const auto& v) {
+    if (!v.empty()) std::memcpy(th + at, v.data(), sizeof(v[0]) * v.size());
+  };
+  std::memset(th + words_at, 0, sizeof(int) * words);
+  fill(jobs_at, hjobs);
+  fill(items_at, hitems);
+  fill(segs_at, hsegs);
+  fill(parts_at, parts);
+  fill(xsegs_at, xsv);
+  fill(slabs_at, svec);
+  fill(tiles_at, tvec);
+  fill(tinsts_at, htin);
   LBM_HIP(hipEventRecord(b->ev0, b->stream));
-  if (!tvec.empty()) {
-    DevTile* dt = b->tiles + (size_t)k * b->tiles_cap;
-    LBM_HIP(hipMemcpyAsync(dt, b->tiles_host + (size_t)k * b->tiles_cap, sizeof(DevTile) * tvec.size(),
-                           hipMemcpyHostToDevice, b->stream));
-  }
-  DevSeg* dxsegs = b->xsegs + (size_t)k * b->xsegs_cap;
-  if (!xsv.empty())
-    LBM_HIP(hipMemcpyAsync(dxsegs, b->xsegs_host + (size_t)k * b->xsegs_cap, sizeof(DevSeg) * xsv.size(),
-                           hipMemcpyHostToDevice, b->stream));
-  if (!svec.empty()) {
-    DevSlab* ds = b->slabs + (size_t)k * b->slabs_cap;
-    LBM_HIP(hipMemcpyAsync(ds, b->slabs_host + (size_t)k * b->slabs_cap, sizeof(DevSlab) * svec.size(),
-                           hipMemcpyHostToDevice, b->stream));
-  }
-  if (tin_used) {
-    if (tin_used > b->tinsts_cap) {
-      // grow both slots; earlier passes must be done with them
-      LBM_HIP(hipStreamSynchronize(b->stream));
-      hipFree(b->tinsts);
-      hipHostFree(b->tinsts_host);
-      b->tinsts = nullptr;
-      b->tinsts_host = nullptr;
-      b->tinsts_cap = 0;
-      const int cap = 2 * tin_used;
-      if (hipMalloc(&b->tinsts, sizeof(DevTileInst) * 2 * cap) != hipSuccess) return LBM_ERR_OUT_OF_MEMORY;
-      if (hipHostMalloc((void**)&b->tinsts_host, sizeof(DevTileInst) * 2 * cap, hipHostMallocDefault) != hipSuccess)
-        return LBM_ERR_OUT_OF_MEMORY;
-      b->tinsts_cap = cap;
-    }
-    DevTileInst* hti = b->tinsts_host + (size_t)k * b->tinsts_cap;
-    std::memcpy(hti, htin.data(), sizeof(DevTileInst) * tin_used);
-    DevTileInst* dti = b->tinsts + (size_t)k * b->tinsts_cap;
-    LBM_HIP(hipMemcpyAsync(dti, hti, sizeof(DevTileInst) * tin_used, hipMemcpyHostToDevice, b->stream));
-  }
-  DevJobInst* ditems = b->items + (size_t)k * b->items_cap;
-  DevJob* djobs = b->jobs + (size_t)k * b->items_cap;
-  int* counters = b->counter + k * kMaxLaunches;
-  if (used) LBM_HIP(hipMemcpyAsync(ditems, hitems, sizeof(DevJobInst) * used, hipMemcpyHostToDevice, b->stream));
-  DevSeg* dsegs = b->segs + (size_t)k * b->items_cap;
-  DevItem* dparts = b->parts + (size_t)k * b->parts_cap;
-  if (nsegs) {
-    DevItem* hparts = b->parts_host + (size_t)k * b->parts_cap;
-    std::memcpy(hparts, parts.data(), sizeof(DevItem) * parts.size());
-    LBM_HIP(hipMemcpyAsync(dparts, hparts, sizeof(DevItem) * parts.size(), hipMemcpyHostToDevice, b->stream));
-    LBM_HIP(hipMemcpyAsync(dsegs, hsegs, sizeof(DevSeg) * nsegs, hipMemcpyHostToDevice, b->stream));
-  }
-  if (njobs) {
-    LBM_HIP(hipMemcpyAsync(djobs, hjobs, sizeof(DevJob) * njobs, hipMemcpyHostToDevice, b->stream));
-    LBM_HIP(hipMemsetAsync(counters, 0, sizeof(int) * kMaxLaunches, b->stream));
-    LBM_HIP(hipMemsetAsync(b->done + (size_t)k * b->items_cap, 0, sizeof(int) * njobs, b->stream));
-  }
+  if (need > 0) LBM_HIP(hipMemcpyAsync(td, th, need, hipMemcpyHostToDevice, b->stream));
+  int* counters = reinterpret_cast<int*>(td + words_at);
+  int* done_all = counters + launches.size();
+  const DevJob* djobs = reinterpret_cast<const DevJob*>(td + jobs_at);
+  const DevJobInst* ditems = reinterpret_cast<const DevJobInst*>(td + items_at);
+  const DevSeg* dsegs = reinterpret_cast<const DevSeg*>(td + segs_at);
+  const DevItem* dparts = reinterpret_cast<const DevItem*>(td + parts_at);
+  const DevSeg* dxsegs = reinterpret_cast<const DevSeg*>(td + xsegs_at);
+  const DevSlab* ds = reinterpret_cast<const DevSlab*>(td + slabs_at);
+  const DevTile* dtiles = reinterpret_cast<const DevTile*>(td + tiles_at);
+  const DevTileInst* dti_all = reinterpret_cast<const DevTileInst*>(td + tinsts_at);
   // Lanes: every resident launch, every tiled group and every slab launch (or
   // the chain of slab launches, when they cannot run side by side) is one
   // item; with more items than lanes, each item in order of its duration
@@ -2334,7 +2328,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   gate_need = std::min(gate_need, b->lim.cus);
   if (gate_need > 0) {
     gate_lock = std::unique_lock<std::mutex>(gate.mu);
-    lbm_status gs = pass_gate(gate, gate_need, b->lim.cus, b->stream);
+    lbm_status gs = pass_gate(gate, b, gate_need);
     if (gs != LBM_OK) return gs;
   }
   // Tags of this pass: its launches have strips of their own, so that all of them
@@ -2348,8 +2342,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const uint32_t tag = b->strip_tag;
   b->strip_tag += (uint32_t)strip_tags;
   if (fork) LBM_HIP(hipEventRecord(b->fork, b->stream));
-  const DevSlab* ds = b->slabs + (size_t)k * b->slabs_cap;
-  const DevTileInst* dti_all = b->tinsts + (size_t)k * b->tinsts_cap;
   auto issue_slab = [&](size_t l, hipStream_t st) -> lbm_status {
     const SlabLaunch& L = slaunch[l];
     void* b0 = L.prec ? (void*)b->f32[0] : (void*)b->f64[0];
@@ -2387,7 +2379,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     if (it.kind == 0) {
       const int l = it.idx;
       const Launch& L = launches[l];
-      int* done = b->done + (size_t)k * b->items_cap + L.first;
+      int* done = done_all + L.first;
       if (L.reg) {
         const int stall = (b->test_stall == 1 && l == 0 && L.parts > L.count) ? 0 : -1;
         LBM_HIP(launch_reg(L.q, L.prec, L.code, L.wide, dparts + L.part0, L.parts, djobs + L.first, dsegs, counters + l,
@@ -2417,12 +2409,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
                               b->coefs, b->status, ticks, stall, grid, L.block, L.lds, st));
     } else if (it.kind == 1) {
       const TileGroup& G = tgroups[it.idx];
-      DevTile* dt = b->tiles + (size_t)k * b->tiles_cap + G.first;
-      DevTileInst* dti = b->tinsts + (size_t)k * b->tinsts_cap;
+      const DevTile* dt = dtiles + G.first;
       void* b0 = G.prec ? (void*)b->f32[0] : (void*)b->f64[0];
       void* b1 = G.prec ? (void*)b->f32[1] : (void*)b->f64[1];
       for (int l = 0; l < G.launches; ++l)
-        LBM_HIP(launch_tile(G.q, G.prec, dt, G.ntiles, dti, b0, b1, l, G.s, G.halo, b->coefs, b->status, G.block,
+        LBM_HIP(launch_tile(G.q, G.prec, dt, G.ntiles, dti_all, b0, b1, l, G.s, G.halo, b->coefs, b->status, G.block,
                             G.lds, st));
       for (int t = G.tfirst; t < G.tfirst + G.tcount; ++t) {
         HostInst& h = b->inst[htin[t].inst];
@@ -2460,7 +2451,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   }
   LBM_HIP(hipEventRecord(b->items_done[k], b->stream));
   if (gate_need > 0) {
-    lbm_status gs = enter_gate(gate, gate_need, b->stream);
+    lbm_status gs = enter_gate(gate, b, gate_need);
     if (gs != LBM_OK) return gs;
     gate_lock.unlock();
   }

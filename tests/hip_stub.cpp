@@ -46,6 +46,8 @@ struct World {
   std::map<uint64_t, size_t> device, pinned, foreign;
   size_t used = 0, limit = ~size_t(0);
   std::vector<Record> log;
+  std::vector<std::pair<int, int>> slabs;   // (launch, workgroups)
+  int copies = 0;
   int faults = 0;
   std::string first;
 };
@@ -82,6 +84,13 @@ void launch(hipStream_t s, const std::vector<Touch>& what, Record r) {
         fault("launches %d and %d touch the state at %llx in no order", a.launch, me, (unsigned long long)t.at);
     w.access[t.at].push_back({me, t.write});
   }
+  if (r.kind == kSlabs) {   // (a launch may hold several workgroups of a CU, launches together may not)
+    int64_t together = r.groups;
+    for (const auto& [other, groups] : w.slabs)
+      if (!has(before, other)) together += groups;
+    if (together > 256 && together > r.groups) fault("%lld slab workgroups in flight together", (long long)together);
+    w.slabs.push_back({me, (int)r.groups});
+  }
   before.resize(me + 1);
   before[me] = true;
   w.streams[s] = before;
@@ -103,13 +112,14 @@ extern "C" {
 void stub_reset() {
   w.log.clear();
   w.access.clear();
-  w.faults = 0;
+  w.faults = w.copies = 0;
   w.first.clear();
 }
 int stub_faults(char* text, int cap) {
   if (text && cap > 0) snprintf(text, cap, "%s", w.first.c_str());
   return w.faults;
 }
+int stub_copies() { return w.copies; }   // and clears, on a stream
 int stub_launches() { return (int)w.log.size(); }
 void stub_launch(int k, int64_t* out) { std::memcpy(out, &w.log[k], sizeof(Record)); }
 // device memory that may be allocated from now on
@@ -168,8 +178,16 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
   return hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  ++w.copies;
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
+  ++w.copies;
+  std::memset(d, v, n);
+  return hipSuccess;
+}
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)calloc(1, 8); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { w.streams.erase(s); free(s); return hipSuccess; }

@@ -199,3 +199,37 @@ def test_a_solver_pins_host_memory_twice(host):
     assert host.lib.stub_pinned() - before <= 2
     s.close()
     assert host.lib.stub_pinned() == before
+
+
+@pytest.mark.parametrize("sizes", [[300], [20000], [300, 5000, 9000, 16000] * 16])
+def test_a_pass_uploads_its_tables_in_one_copy(host, sizes):
+    """Each copy or clear on the stream adds some 4 us to a short advance."""
+    b = lbm.Batch([problem("kdv", n) for n in sizes], stream=0)
+    b.load_phi([np.full(n, 0.5) for n in sizes])
+    b.advance(2)
+    host.reset()
+    b.advance(2)
+    assert host.lib.stub_copies() == 1
+    b.close()
+
+
+def test_slab_launches_of_two_batches_wait_for_each_other(host):
+    """Together they would hold more workgroups than there are CUs (on two streams)."""
+    sizes = [[200003], [9001] * 90, [5000]]
+    streams = [0x10, 0x20, 0x30]
+    batches = []
+    for ns, s in zip(sizes, streams):
+        b = lbm.Batch([problem("kdv", n) for n in ns], stream=s)
+        b.load_phi([np.full(n, 0.5) for n in ns])
+        batches.append(b)
+    host.reset()
+    for steps in (100, 7, 100, 300):
+        for b in batches:
+            b.advance(steps)
+    assert host.faults()[0] == 0, host.faults()[1]
+    assert all(b.read_phi(0)[0][0] == 507.0 for b in batches)
+    batches[1].close()
+    for b in batches[::2]:
+        b.advance(5)
+        b.close()
+    assert host.faults()[0] == 0, host.faults()[1]
