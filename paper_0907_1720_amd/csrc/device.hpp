@@ -50,7 +50,7 @@ struct DevJob {
   int32_t steps;             // steps of this launch
   int32_t degree;            // kernel variant shared by all instances of the job
   int32_t bounded;           // 1: the instances reset their boundary layers after every step
-  int32_t nodes;             // register kernels: nodes per lane (2, 4 or 8)
+  int32_t nodes;             // register kernels: nodes per lane (one of reg_width's)
   int32_t s_per;             // register kernels: steps between wave exchanges (even)
   int32_t pad_;
 };

@@ -74,8 +74,8 @@ inline int variant_code(int D, int parity) { return D | (parity << 8); }
 hipError_t launch_init_many(bool f32, const DevInit* recs, int count, int longest, const DevCoef* coefs, int* status,
                             hipStream_t s);
 hipError_t launch_init_one(bool f32, const DevInit& rec, const DevCoef* coefs, int* status, int* bad, hipStream_t s);
-// words[0] |= 1 if any phi is not finite, |= 2 if any is negative (device or
-// pinned host memory)
+// words[0] := 1 if any phi is not finite, words[1] := 1 if any is negative (two
+// words in device or pinned host memory, left alone otherwise)
 hipError_t launch_check_phi(const double* phi, int n, int* words, hipStream_t s);
 // slabs: one launch no larger than the GPU holds at once, one workgroup per
 // slab; flags[0 .. nslabs) start at 0; xbuf holds 4 Q halo values per slab;
@@ -109,7 +109,9 @@ hipError_t launch_resident(int q, int prec, int code, const DevJob* jobs, const 
 // The narrow kernels fit 128 registers (four waves per SIMD), the wide ones 256
 // (two); the i-th width of either, 0 past the last.  (Multiples of four on D1Q4
 // and D1Q5 cost the narrow kernels a register move for every sixth operation;
-// large tables, which few problems use, are built for fewer widths.)
+// large tables, which few problems use, are built for fewer widths; without three
+// nodes per lane 512 D1Q7 grids of 1000 nodes with cubic fluxes, FP32 arithmetic,
+// took 1.2 times the LDS kernels' time.)
 constexpr int kRegWidths = 6;
 constexpr int reg_width(int q, int elem, int degree, int parity, bool wide, int i) {
   constexpr int w[8][2][kRegWidths] = {{{1, 2, 3, 5, 6}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP64
@@ -117,9 +119,9 @@ constexpr int reg_width(int q, int elem, int degree, int parity, bool wide, int 
                                        {{1, 2, 3, 5, 8}, {5, 8, 10, 12, 14, 17}},   // D1Q4 / D1Q5, FP32 storage
                                        {{2, 3, 6}, {1, 3, 6, 8, 10, 12}},           // D1Q6 / D1Q7, FP32 storage
                                        {{3, 6}, {1, 6, 10, 17}},                    // the same, large tables
-                                       {{2, 4}, {1, 4, 8}},
+                                       {{2, 3, 4}, {1, 4, 8}},
                                        {{3, 6}, {1, 6, 10, 17}},
-                                       {{2, 4}, {1, 4, 8, 12}}};
+                                       {{2, 3, 4}, {1, 4, 8, 12}}};
   const bool large = parity == 0 ? degree >= 9 : degree >= 13;
   return w[(large ? 4 : 0) + (elem == 8 ? 0 : 2) + (q >= 6 ? 1 : 0)][wide ? 1 : 0][i];
 }

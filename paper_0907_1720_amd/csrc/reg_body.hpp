@@ -397,7 +397,7 @@ struct RegBound {
 //   wall clock marks the instance (status bit 2) and is the wave's last: it runs
 //   on without waiting, so that every kernel ends.
 //  Bounded: the whole instance, no ring; after every step the outer layers are
-//   reset from the exact solution (reg_reset).
+//   reset from the exact solution (RegBound::reset).
 //  (A tile is a slab of at most `sx` steps, which meets no exchange with
 //   neighbours.)
 // State moves between memory order and lane order through a row of LDS per wave,

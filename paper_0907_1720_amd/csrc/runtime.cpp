@@ -1320,7 +1320,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // largest one.  Where that takes more than one and a half times the even share
   // of the CUs, the group goes in slabs of a quarter of an LDS (256 grids of 256
   // to 4096 nodes, 2.9 times: 4.80 -> 2.49 ms per 1000 steps; half-LDS slabs
-  // 4.11, an eighth 2.62; 1024 such grids, 0.7 times, stay whole).
+  // 4.11, an eighth 2.62; 1024 such grids, 0.7 times, stay whole).  Over ranges of
+  // sizes, powers and step counts with shares of 1.9 to 4 the slabs took 0.52 to
+  // 0.70 of the whole instances' time in FP64 and 0.62 to 0.9 in FP32 storage; 300
+  // grids of 128 to 1024 nodes, 2.0 times, the same time.
   std::map<std::tuple<int, int, int>, std::pair<int64_t, int64_t>> loads;   // steps x nodes: all, largest
   for (int i = 0; i < count; ++i) {
     const HostInst& h = b->inst[i];
@@ -1443,9 +1446,9 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       // pass more than the rest and every step waits for them.  Where two jobs
       // share each CU (eight waves per SIMD: the step is bound by VALU issue) a
       // job therefore admits a member only while the members' waves at that
-      // pass count fit (the 4096-instance FP32 batch: 46.5 -> 45.3 ms).  One
-      // job per CU is bound by the step's latency instead, and fuller jobs pay
-      // there (the FP64 batch ran 1.5% slower with the rule).
+      // pass count fit.  One job per CU is bound by the step's latency instead,
+      // and fuller jobs pay there.  (Measured on 4096 KdV and mKdV grids while
+      // those ran in LDS: FP32 storage 46.5 -> 45.3 ms, FP64 1.5% slower.)
       const bool wave_budget = !latency && jobs_per_cu >= 2;
       const int full_passes = std::max<int>(
           std::max(1, kNodesPerWave / 64),
@@ -1558,12 +1561,10 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       launches.push_back(L);
     }
   }
-  // register-resident jobs: ring segments of one variant, step count and width,
-  // bin-packed by waves
-  // Slabs and tiles.  Every group takes its share of the CUs, so that the
-  // launches run side by side; where one needs more workgroups than that at
-  // once, the launches run one after another, each over the whole GPU.  What
-  // cannot be cut into that many slabs is advanced tile by tile.
+  // Register-resident slabs and tiles.  Groups go side by side, each by its plan
+  // for the whole GPU or for its share of the CUs, where every workgroup of all of
+  // them finds a CU; else one after another, each over the whole GPU.  What cannot
+  // be cut into slabs is advanced tile by tile.
   struct SegLaunch { int q; int prec; int code; SegPlan p; bool tile; int first, count, launches; size_t lds, at; int64_t blocks; double est; };
   std::vector<SegLaunch> segs;
   std::vector<DevSeg> xsv;
@@ -1796,7 +1797,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       if (st != LBM_OK) return st;
     }
   }
-  // Whole instances share the GPU with slabs only where those leave it to them:
+  // Register-resident jobs: whole instances of one variant, step count and width,
+  // bin-packed by waves.  They share the GPU with slabs only where those leave it:
   // slab launches that fill it start when the whole instances have ended (512
   // Kawahara and K(2,2) grids, FP32 storage, 5000 steps: the 2048-node half took
   // 15.5 ms on a third of the CUs with slabs waiting, 9.8 ms on all of them; the
@@ -2803,8 +2805,8 @@ lbm_status lbm_advance(lbm_problem h, int64_t steps) {
 
 // lbm_create + lbm_load_phi + lbm_advance + lbm_read_phi of one periodic
 // problem whose state fits one workgroup's LDS, with every device buffer in
-// the fixed per-device scratch (noalloc.hip): the same kernels (k_init, one
-// resident launch per 2^30 steps, k_phi), so the result is bitwise that of the
+// the fixed per-device scratch (noalloc.hip): the same kernels (k_init_one, one
+// resident launch per 2^30 steps, k_read), so the result is bitwise that of the
 // handle path.  Host-side buffers live on this call's stack.
 //
 // Short calls are bound by their launches, copies and waits: 257 nodes and 101
