@@ -105,11 +105,22 @@ DeviceLimits query_limits() {
 // workgroups than the GPU has CUs: a workgroup that waits for a place then has an
 // empty CU, or one whose kernel waits for no slab.  A launch that would exceed
 // that waits, on the device, for the other batches' before it.
+//
+// The places are those of an XCD's 32 CUs: a launch hands its workgroups to the
+// XCDs in turn, whether they have room or not, and begins at any of them (of 108
+// and 148 workgroups side by side that take a CU each, three had to wait).
+constexpr int kXcdCus = 32;
+int xcd_count(int cus) { return std::max(1, cus / kXcdCus); }
+// a launch's workgroups, as many to each XCD as to the one that gets the most
+int64_t even_places(int64_t workgroups, int cus) {
+  const int x = xcd_count(cus);
+  return (workgroups + x - 1) / x * x;
+}
 struct SlabGate {
   struct Flight {
     const lbm_batch_s* owner;
     hipEvent_t done;
-    int need;          // workgroups, 0 once seen over
+    int need;          // workgroups (even_places), 0 once seen over
   };
   std::mutex mu;
   std::vector<Flight> flight;   // one per batch that has launched slabs
@@ -1570,7 +1581,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   std::vector<DevSeg> xsv;
   std::vector<std::pair<int, int>> flips;   // (instance, buffer exchanges)
   size_t strips_need = 0;  // words
-  int slab_cus = 0;        // workgroups of all slab launches
+  int slab_cus = 0;        // workgroups of all slab launches (even_places)
   double all_work = 1.0;   // node updates x operations of all register groups
   auto work_of = [&](const std::tuple<int, int, int>& key, const std::vector<int>& g) {
     double w = 0.0;
@@ -1606,7 +1617,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       if (!tile) {
         L.at = strips_need;
         strips_need += (size_t)L.count * 4 * (hg + 1) * R * q * (es / 4);
-        slab_cus += L.count;
+        slab_cus += (int)even_places(L.count, b->lim.cus);
       }
       segs.push_back(L);
       L.first = (int)xsv.size();
@@ -1763,19 +1774,38 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       int64_t total = 0;
       size_t at = 0;
       for (const auto& [key, g] : spread) {
-        for (int i : g) total += seg_count(ps[at], std::get<0>(key), b->inst[i].n, false);
+        int64_t wgs = 0;
+        for (int i : g) wgs += seg_count(ps[at], std::get<0>(key), b->inst[i].n, false);
+        total += even_places(wgs, b->lim.cus);
         ++at;
       }
       return total;
     };
     bool together = places_of(plans) <= b->lim.cus;
     if (spread.size() > 1 && !together) {
+      // (shares in whole CUs of every XCD, the largest cut while they exceed the GPU)
+      const int unit = xcd_count(b->lim.cus);
       std::vector<SegPlan> shared;
-      bool ok = true;
+      std::vector<int> share, least;
+      int sum = 0;
+      for (const auto& [key, g] : spread) {
+        least.push_back((int)even_places(g.size(), b->lim.cus));
+        const double part = b->lim.cus * work_of(key, g) / all_work / unit;
+        share.push_back(std::max(least.back(), unit * (int)std::lround(part)));
+        sum += share.back();
+      }
+      while (sum > b->lim.cus) {
+        size_t top = share.size();
+        for (size_t k = 0; k < share.size(); ++k)
+          if (share[k] > least[k] && (top == share.size() || share[k] > share[top])) top = k;
+        if (top == share.size()) break;
+        share[top] -= unit;
+        sum -= unit;
+      }
+      bool ok = sum <= b->lim.cus;
       for (const auto& [key, g] : spread) {
         SegPlan p;
-        const int cus = std::max<int>((int)g.size(), (int)(b->lim.cus * work_of(key, g) / all_work));
-        ok = ok && plan(key, sizes_of(g), cus, slab_steps, false, 1, &p);
+        ok = ok && plan(key, sizes_of(g), share[shared.size()], slab_steps, false, 1, &p);
         shared.push_back(p);
       }
       if (ok && places_of(shared) <= b->lim.cus) {
@@ -2111,13 +2141,15 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   }
   // side by side only while all their workgroups fit the GPU twice over;
   // otherwise one after another (each launch alone fits by construction)
-  int64_t total_slabs = 0, total_cap = 0;
+  int64_t total_slabs = 0, total_places = 0, total_cap = 0;
   for (const SlabLaunch& S : slaunch) {
     total_slabs += S.count;
+    total_places += even_places(S.count, b->lim.cus);
     total_cap += S.cap;
   }
   bool slab_side_by_side =
-      segs.empty() && slaunch.size() > 1 && 2 * total_slabs <= (int64_t)min_per_cu * b->lim.cus;
+      segs.empty() && slaunch.size() > 1 && 2 * total_slabs <= (int64_t)min_per_cu * b->lim.cus &&
+      total_places <= (int64_t)min_per_cu * b->lim.cus;
   // A small pass (a serving round) whose slab launches would run one after
   // another, each less than half full on average, is bound by that sequence of
   // mostly idle launches; temporal blocking has no co-residency condition, so
@@ -2325,8 +2357,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   std::unique_lock<std::mutex> gate_lock;
   int gate_need = 0;
   for (const SegLaunch& L : segs)
-    if (!L.tile) gate_need = segs_side_by_side ? slab_cus : std::max(gate_need, L.count);
-  for (const SlabLaunch& L : slaunch) gate_need += L.count;
+    if (!L.tile) gate_need = segs_side_by_side ? slab_cus : std::max(gate_need, (int)even_places(L.count, b->lim.cus));
+  for (const SlabLaunch& L : slaunch) gate_need += (int)even_places(L.count, b->lim.cus);
   gate_need = std::min(gate_need, b->lim.cus);
   if (gate_need > 0) {
     gate_lock = std::unique_lock<std::mutex>(gate.mu);

@@ -85,10 +85,12 @@ void launch(hipStream_t s, const std::vector<Touch>& what, Record r) {
     w.access[t.at].push_back({me, t.write});
   }
   if (r.kind == kSlabs) {   // (a launch may hold several workgroups of a CU, launches together may not)
-    int64_t together = r.groups;
+    // (each hands its workgroups to the eight XCDs of 32 CUs in turn, from any of them on)
+    int64_t together = (r.groups + 7) / 8;
+    const int64_t alone = together;
     for (const auto& [other, groups] : w.slabs)
-      if (!has(before, other)) together += groups;
-    if (together > 256 && together > r.groups) fault("%lld slab workgroups in flight together", (long long)together);
+      if (!has(before, other)) together += (groups + 7) / 8;
+    if (together > 32 && together > alone) fault("%lld slab workgroups in flight together on an XCD", (long long)together);
     w.slabs.push_back({me, (int)r.groups});
   }
   before.resize(me + 1);

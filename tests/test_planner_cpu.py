@@ -233,3 +233,24 @@ def test_slab_launches_of_two_batches_wait_for_each_other(host):
         b.advance(5)
         b.close()
     assert host.faults()[0] == 0, host.faults()[1]
+
+
+def test_slab_launches_side_by_side_have_a_cu_for_every_workgroup_of_an_xcd(host):
+    """Counted over the whole GPU, launches of 108 and 148 workgroups leave no room for one of them on
+    three of the XCDs, and each may wait there for a place that the other holds."""
+    P = problem
+    for few in range(1, 7):
+        for many in (20, 24, 27, 30):
+            advance(host, [P("kdv", 20000)] * few + [P("mkdv", 9000 + 100 * few)] * many + [P("kawahara", 5000)] * 3,
+                    [300] * (few + many + 3))
+    streams, batches = [0x10, 0x20], []
+    for ns, s in zip(([6001], [9001] * 2), streams):   # 94 and 162 workgroups
+        b = lbm.Batch([P("kdv", n) for n in ns], stream=s)
+        b.load_phi([np.full(n, 0.5) for n in ns])
+        batches.append(b)
+    host.reset()
+    for b in batches:
+        b.advance(100)
+    assert host.faults()[0] == 0, host.faults()[1]
+    for b in batches:
+        b.close()
