@@ -1122,6 +1122,23 @@ SlabChunks slab_chunks(const std::vector<std::pair<int, int64_t>>& mem, int64_t 
   return out;
 }
 
+// The GPU's CUs over launches side by side, in whole CUs of every XCD (even_places):
+// each next one to the launch that would end last, none beyond its `most`
+// workgroups.  Empty: more launches than an XCD has CUs.
+std::vector<int> cu_shares(const std::vector<double>& work, const std::vector<int>& most, int cus) {
+  const int unit = xcd_count(cus), units = cus / unit;
+  if ((int)work.size() > units) return {};
+  std::vector<int> share(work.size(), unit);
+  for (int u = (int)work.size(); u < units; ++u) {
+    size_t top = work.size();
+    for (size_t k = 0; k < work.size(); ++k)
+      if (share[k] < most[k] && (top == work.size() || work[k] / share[k] > work[top] / share[top])) top = k;
+    if (top == work.size()) break;
+    share[top] += unit;
+  }
+  return share;
+}
+
 // waits of b's stream before launches of `need` workgroups (gate held)
 lbm_status pass_gate(SlabGate& gate, lbm_batch_s* b, int need) {
   int sum = 0;
@@ -1411,7 +1428,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   hjobs.clear();
   hsegs.clear();
   // est_max / est_sum: the longest job's and all jobs' duration estimates
-  struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; bool reg, wide; int per_cu, grid, part0, parts; int64_t partsteps; };
+  struct Launch { int q; int prec; int code; int first, count; size_t lds; int block; int64_t maxsteps; double est_max, est_sum; bool reg, wide; int per_cu, grid, part0, parts; int64_t partsteps; double issue; };
   std::vector<Launch> launches;
   int used = 0, njobs = 0, nsegs = 0;
   constexpr int kMaxJobInstances = 16;   // instances per job (one wave each at least)
@@ -1497,7 +1514,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       const int slots = jobs_per_cu * b->lim.cus;
       if (!latency && (int)bins.size() < slots && (int)g.size() > (int)bins.size())
         pack(std::max(1, ((int)g.size() + slots - 1) / slots));
-      Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, false, false, 0, 0, 0, 0, 0};
+      Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, false, false, 0, 0, 0, 0, 0, 0.0};
       struct Planned { const Bin* bin; std::vector<int> waves; double est; };
       std::vector<Planned> plan;
       for (const Bin& bn : bins) {
@@ -1889,7 +1906,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       return (double)steps[g[bn.members[0]]] * ((bn.waves + 3) / 4) * fit[bn.members[0]].cost;
     };
     std::stable_sort(bins.begin(), bins.end(), [&](const Bin& a, const Bin& c) { return job_est(a) > job_est(c); });
-    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, ring.wide, ring.jobs_per_cu, 0, 0, 0, 0};
+    Launch L{q, pr, code, njobs, 0, 0, 64, 0, 0.0, 0.0, true, ring.wide, ring.jobs_per_cu, 0, 0, 0, 0, 0.0};
     for (const Bin& bn : bins) {
       const RegFit& f0 = fit[bn.members[0]];
       const int64_t st = steps[g[bn.members[0]]];
@@ -1897,6 +1914,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
       L.maxsteps = std::max<int64_t>(L.maxsteps, st);
       L.est_max = std::max(L.est_max, est);
       L.est_sum += est;
+      L.issue += (double)st * bn.waves * (f0.cost - f0.R * q);
       DevJob& jb = (++njobs, hjobs.emplace_back());
       jb = DevJob{};
       jb.first = nsegs;
@@ -1947,19 +1965,34 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   // 1959; fixed step chunks, with a queue barely longer than the workgroups,
   // spent a third of the time waiting for the chunk before).  Items are taken
   // in the order of their planned start.
+  // The work by which launches share the CUs is the operations their waves issue: a
+  // step is priced with q operations more per node (a population's update is two
+  // operations, issued as one FMA), which is a larger part of a small table's (4096
+  // KdV and mKdV grids, FP32 arithmetic: 48.5 ms shared by price, 45.3 by issue).
   std::vector<DevItem> parts;
-  size_t job0 = 0;
+  std::vector<double> issue;
+  std::vector<int> most;
+  for (Launch& L : launches) {
+    if (!L.reg) continue;
+    int per_cu = 0;
+    LBM_HIP(reg_occupancy(L.q, L.prec, L.code, L.wide, L.block, L.lds, &per_cu));
+    if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
+    L.per_cu = std::min(per_cu, L.per_cu);
+    issue.push_back(L.issue);
+    most.push_back((L.count + L.per_cu - 1) / L.per_cu);
+  }
+  const std::vector<int> shares = cu_shares(issue, most, b->lim.cus);
+  size_t job0 = 0, nth = 0;
   for (Launch& L : launches) {
     if (!L.reg) continue;
     const double* est = &reg_job_est[job0];
     job0 += L.count;
-    int per_cu = 0;
-    LBM_HIP(reg_occupancy(L.q, L.prec, L.code, L.wide, L.block, L.lds, &per_cu));
-    if (per_cu < 1) return LBM_ERR_UNSUPPORTED;
-    per_cu = std::min(per_cu, L.per_cu);
+    const int per_cu = L.per_cu;
     L.grid = std::min<int>(L.count, per_cu * b->lim.cus);
     if (reg_jobs > b->lim.cus)
-      L.grid = std::max(1, std::min(L.grid, (int)std::lround(per_cu * b->lim.cus * L.est_sum / reg_est)));
+      L.grid = std::max(1, std::min(L.grid, shares.empty() ? (int)std::lround(per_cu * b->lim.cus * L.est_sum / reg_est)
+                                                           : per_cu * shares[nth]));
+    ++nth;
     if (b->res_grid > 0) L.grid = std::min(L.grid, b->res_grid);
     L.part0 = (int)parts.size();
     const DevJob* jobs = hjobs.data() + L.first;
@@ -2348,6 +2381,19 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   }
   if (chain) items.push_back({2, -1, chain_est});
   const bool fork = items.size() > 1;
+  // Workgroups of launches side by side that can have a CU each shall have one: a
+  // launch begins with the same CUs of an XCD as the one before it, as long as its
+  // workgroups fit beside that one's (108 and 148 small ones left 30 to 42 CUs idle;
+  // 4096 KdV and mKdV grids with FP32 arithmetic took 55 ms on shared CUs, 48.5 ms
+  // on their own).  None fits beside one with more than half of the LDS.
+  int64_t side = segs_side_by_side ? slab_cus : 0;
+  for (const Launch& L : launches) side += even_places(L.reg ? L.grid : L.count, b->lim.cus);
+  for (const SegLaunch& L : segs) side += L.tile ? even_places(L.count, b->lim.cus) : 0;
+  for (const TileGroup& G : tgroups) side += even_places(G.ntiles, b->lim.cus);
+  for (const SlabLaunch& S : slaunch) side += even_places(S.count, b->lim.cus);
+  if (fork && side <= b->lim.cus)
+    for (Launch& L : launches)
+      if (L.reg) L.lds = std::max(L.lds, b->lim.lds_max / 2 + 16);
   const int nlanes = std::min<int>((int)items.size(), b->lanes > 0 ? b->lanes : hw_lanes());
   if ((int)items.size() > nlanes)
     std::stable_sort(items.begin(), items.end(), [](const LaneItem& x, const LaneItem& y) { return x.est > y.est; });

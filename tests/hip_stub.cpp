@@ -283,7 +283,7 @@ hipError_t launch_resident(int, int, int, const DevJob* jobs, const DevJobInst* 
   return hipSuccess;
 }
 hipError_t launch_reg(int, int, int, bool wide, const DevItem* items, int nitems, const DevJob* jobs, const DevSeg* segs, int*,
-                      int*, const DevCoef*, int*, long long, int, int grid, int block, size_t, hipStream_t s) {
+                      int*, const DevCoef*, int*, long long, int, int grid, int block, size_t lds, hipStream_t s) {
   std::vector<Touch> what;
   std::set<int> seen;
   int64_t width = 0;   // the widest job's nodes per lane
@@ -310,7 +310,7 @@ hipError_t launch_reg(int, int, int, bool wide, const DevItem* items, int nitems
   }
   // the part of a CU's waves that jobs of this size fill, in percent
   const int waves = block / 64, filled = 100 * (reg_waves(wide) / waves * waves) / reg_waves(wide);
-  launch(s, what, {kReg, 0, grid, end, filled, 0, width, (int64_t)seen.size()});
+  launch(s, what, {kReg, 0, grid, end, filled, (int64_t)lds, width, (int64_t)seen.size()});
   return hipSuccess;
 }
 hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int width, int, int sx, bool tile, int turn, void*,

@@ -52,7 +52,8 @@ class HostRuntime:
 
     def launches(self, *kinds):
         """(kind, stream, workgroups, steps, tag, blocks, nodes per lane, jobs) of the launches
-        since reset(); for whole instances, the percentage of a CU's waves filled instead of a tag."""
+        since reset(); for whole instances, the percentage of a CU's waves filled instead of a tag, and
+        bytes of LDS instead of blocks."""
         out = []
         for k in range(self.lib.stub_launches()):
             r = (ctypes.c_int64 * 8)()

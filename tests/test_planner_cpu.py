@@ -254,3 +254,16 @@ def test_slab_launches_side_by_side_have_a_cu_for_every_workgroup_of_an_xcd(host
     assert host.faults()[0] == 0, host.faults()[1]
     for b in batches:
         b.close()
+
+
+@pytest.mark.parametrize("groups", [[("kdv", 774, W.F32_DEV, 415), ("mkdv", 758, W.F32_DEV_ARITH32, 267)],
+                                    [("kdv", 1204, W.F32_DEV_ARITH32, 303), ("kawahara", 900, W.F32_DEV, 263)],
+                                    [("kdv", 2000, W.F64, 150), ("mkdv", 2100, W.F32_DEV, 130), ("kawahara", 700, W.F64, 250)]])
+def test_launches_side_by_side_have_cus_of_their_own(host, groups):
+    """Whole CUs of every XCD each, and no other workgroup fits beside one."""
+    problems = [problem(kind, n, prec) for kind, n, prec, count in groups for _ in range(count)]
+    launches = [l for l in advance(host, problems, [400] * len(problems)) if l[0] == H.REG]
+    assert len(launches) == len(groups)
+    assert sum((wgs + 7) // 8 for _, _, wgs, *_ in launches) <= 32
+    assert all(wgs % 8 == 0 or wgs == jobs for _, _, wgs, _, _, _, _, jobs in launches)
+    assert all(lds > 163840 // 2 for _, _, _, _, _, lds, _, _ in launches)
