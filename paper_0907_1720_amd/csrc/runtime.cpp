@@ -2422,6 +2422,11 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const uint32_t tag = b->strip_tag;
   b->strip_tag += (uint32_t)strip_tags;
   if (fork) LBM_HIP(hipEventRecord(b->fork, b->stream));
+  // Steps that whole instances of this pass may keep CUs from a slab launch, part of
+  // which waits for the rest meanwhile (10 s of them passed for a time-out).
+  int64_t ahead = 0;
+  for (const Launch& L : launches)
+    ahead += L.reg ? (L.parts + L.grid - 1) / L.grid * L.partsteps : (L.count + b->lim.cus - 1) / b->lim.cus * L.maxsteps;
   auto issue_slab = [&](size_t l, hipStream_t st) -> lbm_status {
     const SlabLaunch& L = slaunch[l];
     void* b0 = L.prec ? (void*)b->f32[0] : (void*)b->f64[0];
@@ -2430,7 +2435,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     LBM_HIP(hipMemsetAsync(flags, 0, sizeof(int) * L.count, st));
     const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
     LBM_HIP(launch_slab(L.q, L.prec, L.code, ds + L.first, L.count, dti_all, b0, b1, L.s, L.halo,
-                        (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.s), mute,
+                        (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.s + ahead), mute,
                         L.block, L.lds, st));
     return LBM_OK;
   };
@@ -2439,7 +2444,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
     for (int r = 0; r < L.launches; ++r)
       LBM_HIP(launch_seg(L.q, L.prec, L.code, L.p.f.wide, dxsegs + L.first, L.count, L.p.f.R, L.p.f.s, L.p.sx, L.tile, r,
-                         b->strips + L.at, tag, b->coefs, b->status, wait_ticks(b, L.p.sx), mute, 64 * L.p.waves, L.lds, st));
+                         b->strips + L.at, tag, b->coefs, b->status, wait_ticks(b, L.p.sx + ahead), mute, 64 * L.p.waves, L.lds, st));
     return LBM_OK;
   };
   for (size_t ii = 0; ii < items.size(); ++ii) {

@@ -48,6 +48,7 @@ struct World {
   std::vector<Record> log;
   std::vector<std::pair<int, int>> slabs;   // (launch, workgroups)
   int copies = 0;
+  long long slab_wait = 0;                  // ticks, of the latest slab launch
   int faults = 0;
   std::string first;
 };
@@ -122,6 +123,7 @@ int stub_faults(char* text, int cap) {
   return w.faults;
 }
 int stub_copies() { return w.copies; }   // and clears, on a stream
+long long stub_slab_wait() { return w.slab_wait; }
 int stub_launches() { return (int)w.log.size(); }
 void stub_launch(int k, int64_t* out) { std::memcpy(out, &w.log[k], sizeof(Record)); }
 // device memory that may be allocated from now on
@@ -314,7 +316,8 @@ hipError_t launch_reg(int, int, int, bool wide, const DevItem* items, int nitems
   return hipSuccess;
 }
 hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int width, int, int sx, bool tile, int turn, void*,
-                      unsigned tag, const DevCoef*, int*, long long, int, int, size_t, hipStream_t s) {
+                      unsigned tag, const DevCoef*, int*, long long wait, int, int, size_t, hipStream_t s) {
+  w.slab_wait = wait;
   std::vector<Touch> what;
   std::map<int, std::pair<DevSeg, int64_t>> seen;   // first segment of an instance, nodes so far
   int64_t most = 0, blocks = 0;
@@ -345,7 +348,8 @@ hipError_t launch_seg(int, int, int, bool, const DevSeg* segs, int nsegs, int wi
   return hipSuccess;
 }
 hipError_t launch_slab(int, int prec, int, const DevSlab* slabs, int nslabs, const DevTileInst* ti, void* b0, void* b1, int,
-                       int, void*, int*, const DevCoef*, int*, long long, int, int, size_t, hipStream_t s) {
+                       int, void*, int*, const DevCoef*, int*, long long wait, int, int, size_t, hipStream_t s) {
+  w.slab_wait = wait;
   const size_t es = prec ? 4 : 8;
   std::vector<Touch> what;
   std::map<int, int> seen;   // the step chunk of an instance

@@ -31,6 +31,7 @@ class HostRuntime:
         lbm.LIB_PATH, lbm._lib = path, None
         self.lib = lbm.library()
         self.lib.stub_limit.argtypes = [ctypes.c_size_t]
+        self.lib.stub_slab_wait.restype = ctypes.c_longlong
         for name in ("stub_foreign", "stub_device"):
             getattr(self.lib, name).argtypes = [ctypes.c_size_t]
             getattr(self.lib, name).restype = ctypes.c_void_p

@@ -267,3 +267,14 @@ def test_launches_side_by_side_have_cus_of_their_own(host, groups):
     assert sum((wgs + 7) // 8 for _, _, wgs, *_ in launches) <= 32
     assert all(wgs % 8 == 0 or wgs == jobs for _, _, wgs, _, _, _, _, jobs in launches)
     assert all(lds > 163840 // 2 for _, _, _, _, _, lds, _, _ in launches)
+
+
+@pytest.mark.parametrize("kinds,n,large", [(("kdv", "kawahara"), 2048, 16384), (("power", "power"), 800, 30000)])
+def test_slabs_wait_as_long_as_whole_instances_may_keep_their_cus(host, kinds, n, large):
+    """Part of a slab launch may have its places while the rest waits for launches beside it to end."""
+    steps = 10 ** 7
+    problems = [problem(k, n) for k in kinds for _ in range(128)] + [problem(k, large) for k in kinds for _ in range(64)]
+    launches = advance(host, problems, [steps] * len(problems))
+    assert {H.REG, H.LDS} & {l[0] for l in launches} and {H.SLABS, H.LDS_SLABS} & {l[0] for l in launches}
+    us = host.lib.stub_slab_wait() / 100.0   # (ticks of a 100 MHz clock)
+    assert us >= 10 ** 7 + 20.0 * steps
