@@ -116,14 +116,21 @@ int64_t even_places(int64_t workgroups, int cus) {
   const int x = xcd_count(cus);
   return (workgroups + x - 1) / x * x;
 }
+//
+// That kernel may be another batch's whole instances for many steps, while part of
+// a slab launch has its places and waits: the gate also knows how many, so that the
+// slabs' waits are given as much longer (passes beyond kLongPass; a shorter one
+// takes less than a second, and leaves its CUs to slabs when it ends).
+constexpr int64_t kLongPass = 1 << 15;
 struct SlabGate {
   struct Flight {
     const lbm_batch_s* owner;
     hipEvent_t done;
     int need;          // workgroups (even_places), 0 once seen over
+    int64_t ahead;     // steps of whole instances, 0 once seen over
   };
   std::mutex mu;
-  std::vector<Flight> flight;   // one per batch that has launched slabs
+  std::vector<Flight> flight;   // one per batch that has launched slabs or a long pass
 };
 SlabGate& slab_gate() {
   static SlabGate gates[64];
@@ -1139,18 +1146,25 @@ std::vector<int> cu_shares(const std::vector<double>& work, const std::vector<in
   return share;
 }
 
-// waits of b's stream before launches of `need` workgroups (gate held)
-lbm_status pass_gate(SlabGate& gate, lbm_batch_s* b, int need) {
+// waits of b's stream before slab launches of `need` workgroups (gate held); ahead:
+// the steps of other batches' whole instances in flight
+lbm_status pass_gate(SlabGate& gate, lbm_batch_s* b, int need, int64_t* ahead) {
   int sum = 0;
+  *ahead = 0;
   for (SlabGate::Flight& f : gate.flight) {
     // (b's own earlier passes come before on its stream)
-    if (f.need == 0 || (f.owner == b && f.need <= need)) continue;
-    if (hipEventQuery(f.done) == hipSuccess)
+    if ((f.need == 0 && f.ahead == 0) || (f.owner == b && f.need <= need && f.ahead == 0)) continue;
+    if (hipEventQuery(f.done) == hipSuccess) {
       f.need = 0;
-    else
+      f.ahead = 0;
+    } else {
       (void)hipGetLastError();   // (not ready is no error)
-    if (f.owner != b) sum += f.need;
+    }
+    if (f.owner == b) continue;
+    sum += f.need;
+    *ahead += f.ahead;
   }
+  if (need == 0) return LBM_OK;
   for (const SlabGate::Flight& f : gate.flight) {
     if (sum + need <= b->lim.cus) break;
     if (f.owner == b || f.need == 0) continue;
@@ -1160,16 +1174,19 @@ lbm_status pass_gate(SlabGate& gate, lbm_batch_s* b, int need) {
   return LBM_OK;
 }
 // b's launches have been issued; until they are over, its entry counts the most of
-// them and of b's earlier ones
-lbm_status enter_gate(SlabGate& gate, lbm_batch_s* b, int need) {
+// the workgroups of them and of b's earlier ones, and all their steps
+lbm_status enter_gate(SlabGate& gate, lbm_batch_s* b, int need, int64_t ahead) {
   if (!b->gate) {
     LBM_HIP(hipEventCreateWithFlags(&b->gate_done, hipEventDisableTiming));
-    gate.flight.push_back({b, b->gate_done, 0});
+    gate.flight.push_back({b, b->gate_done, 0, 0});
     b->gate = &gate;
   }
   LBM_HIP(hipEventRecord(b->gate_done, b->stream));
   for (SlabGate::Flight& f : gate.flight)
-    if (f.owner == b) f.need = std::max(f.need, need);
+    if (f.owner == b) {
+      f.need = std::max(f.need, need);
+      f.ahead += ahead;
+    }
   return LBM_OK;
 }
 
@@ -2406,11 +2423,19 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     if (!L.tile) gate_need = segs_side_by_side ? slab_cus : std::max(gate_need, (int)even_places(L.count, b->lim.cus));
   for (const SlabLaunch& L : slaunch) gate_need += (int)even_places(L.count, b->lim.cus);
   gate_need = std::min(gate_need, b->lim.cus);
-  if (gate_need > 0) {
+  // Steps that whole instances may keep CUs from a slab launch, part of which waits
+  // for the rest meanwhile (10 s of them passed for a time-out): this pass's, and
+  // those of other batches' passes in flight.
+  int64_t ahead = 0, others = 0;
+  for (const Launch& L : launches)
+    ahead += L.reg ? (L.parts + L.grid - 1) / L.grid * L.partsteps : (L.count + b->lim.cus - 1) / b->lim.cus * L.maxsteps;
+  const bool gated = gate_need > 0 || ahead > kLongPass;
+  if (gated) {
     gate_lock = std::unique_lock<std::mutex>(gate.mu);
-    lbm_status gs = pass_gate(gate, b, gate_need);
+    lbm_status gs = pass_gate(gate, b, gate_need, &others);
     if (gs != LBM_OK) return gs;
   }
+  const int64_t slab_ahead = ahead + others;
   // Tags of this pass: its launches have strips of their own, so that all of them
   // count from the same tag.
   int64_t strip_tags = 0;
@@ -2422,11 +2447,6 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
   const uint32_t tag = b->strip_tag;
   b->strip_tag += (uint32_t)strip_tags;
   if (fork) LBM_HIP(hipEventRecord(b->fork, b->stream));
-  // Steps that whole instances of this pass may keep CUs from a slab launch, part of
-  // which waits for the rest meanwhile (10 s of them passed for a time-out).
-  int64_t ahead = 0;
-  for (const Launch& L : launches)
-    ahead += L.reg ? (L.parts + L.grid - 1) / L.grid * L.partsteps : (L.count + b->lim.cus - 1) / b->lim.cus * L.maxsteps;
   auto issue_slab = [&](size_t l, hipStream_t st) -> lbm_status {
     const SlabLaunch& L = slaunch[l];
     void* b0 = L.prec ? (void*)b->f32[0] : (void*)b->f64[0];
@@ -2435,7 +2455,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     LBM_HIP(hipMemsetAsync(flags, 0, sizeof(int) * L.count, st));
     const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
     LBM_HIP(launch_slab(L.q, L.prec, L.code, ds + L.first, L.count, dti_all, b0, b1, L.s, L.halo,
-                        (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.s + ahead), mute,
+                        (unsigned char*)b->xbuf + L.xoff, flags, b->coefs, b->status, wait_ticks(b, L.s + slab_ahead), mute,
                         L.block, L.lds, st));
     return LBM_OK;
   };
@@ -2444,7 +2464,7 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     const int mute = (b->test_stall == 2 && l == 0) ? 0 : -1;
     for (int r = 0; r < L.launches; ++r)
       LBM_HIP(launch_seg(L.q, L.prec, L.code, L.p.f.wide, dxsegs + L.first, L.count, L.p.f.R, L.p.f.s, L.p.sx, L.tile, r,
-                         b->strips + L.at, tag, b->coefs, b->status, wait_ticks(b, L.p.sx + ahead), mute, 64 * L.p.waves, L.lds, st));
+                         b->strips + L.at, tag, b->coefs, b->status, wait_ticks(b, L.p.sx + slab_ahead), mute, 64 * L.p.waves, L.lds, st));
     return LBM_OK;
   };
   for (size_t ii = 0; ii < items.size(); ++ii) {
@@ -2535,8 +2555,8 @@ lbm_status advance_pass(lbm_batch_s* b, const int64_t* steps) {
     }
   }
   LBM_HIP(hipEventRecord(b->items_done[k], b->stream));
-  if (gate_need > 0) {
-    lbm_status gs = enter_gate(gate, b, gate_need);
+  if (gated) {
+    lbm_status gs = enter_gate(gate, b, gate_need, ahead > kLongPass ? ahead : 0);
     if (gs != LBM_OK) return gs;
     gate_lock.unlock();
   }

@@ -278,3 +278,23 @@ def test_slabs_wait_as_long_as_whole_instances_may_keep_their_cus(host, kinds, n
     assert {H.REG, H.LDS} & {l[0] for l in launches} and {H.SLABS, H.LDS_SLABS} & {l[0] for l in launches}
     us = host.lib.stub_slab_wait() / 100.0   # (ticks of a 100 MHz clock)
     assert us >= 10 ** 7 + 20.0 * steps
+
+
+def test_slabs_wait_as_long_as_another_batch_may_keep_their_cus(host):
+    """Whole instances of another batch, ten million steps on another stream."""
+    many = lbm.Batch([problem("kdv", 1000)] * 300, stream=0x10)
+    many.load_phi([np.full(1000, 0.5)] * 300)
+    lone = lbm.Batch([problem("kdv", 15001)], stream=0x20)
+    lone.load_phi([np.full(15001, 0.5)])
+    us = []
+    for _ in range(2):
+        many.advance(10 ** 7)
+        lone.advance(100)
+        us.append(host.lib.stub_slab_wait() / 100.0)
+        many.last_advance_ms()
+        lone.advance(100)
+        us.append(host.lib.stub_slab_wait() / 100.0)
+    assert all(u >= 10 ** 7 + 20.0 * 10 ** 7 for u in us[::2])
+    assert all(u < 1.01 * 10 ** 7 for u in us[1::2])   # over, and not counted any more
+    for b in (many, lone):
+        b.close()
