@@ -34,6 +34,11 @@ bool has(const Clock& a, int k) { return k < (int)a.size() && a[k]; }
 
 struct Access { int launch; bool write; };
 struct Record { int64_t kind, stream, groups, steps, tag, blocks, width, jobs; };
+// A slab launch: the workgroups that an XCD gets at most (a launch hands them to
+// the eight XCDs of 32 CUs in turn, from any of them on), and what is over before
+// it starts.
+struct SlabRun { int launch; int64_t wgs; Clock before; };
+bool ordered(const SlabRun& a, const SlabRun& b) { return has(a.before, b.launch) || has(b.before, a.launch); }
 enum { kReg = 0, kSlabs = 1, kTiles = 2, kLds = 3, kLdsSlabs = 4, kLdsTiles = 5, kStream = 6, kRead = 7, kInit = 8 };
 
 struct World {
@@ -46,7 +51,7 @@ struct World {
   std::map<uint64_t, size_t> device, pinned, foreign;
   size_t used = 0, limit = ~size_t(0);
   std::vector<Record> log;
-  std::vector<std::pair<int, int>> slabs;   // (launch, workgroups)
+  std::vector<SlabRun> slabs;
   int copies = 0;
   long long slab_wait = 0;                  // ticks, of the latest slab launch
   int faults = 0;
@@ -73,6 +78,19 @@ void reachable(const void* p, size_t bytes, const char* what) {
   if (!inside(w.device, a, bytes) && !inside(w.pinned, a, bytes)) fault("%s: a kernel given memory that is not on the GPU", what);
 }
 
+// the most slab workgroups that launches of `from` have on an XCD together, no two of
+// which are kept apart by an order; `taken`: of those chosen so far
+void in_flight(const std::vector<const SlabRun*>& from, int64_t taken, int64_t* most) {
+  *most = std::max(*most, taken);
+  int64_t left = taken;
+  for (const SlabRun* r : from) left += r->wgs;
+  if (left <= *most) return;
+  std::vector<const SlabRun*> rest(from.begin() + 1, from.end()), beside;
+  for (const SlabRun* r : rest)
+    if (!ordered(*from[0], *r)) beside.push_back(r);
+  in_flight(beside, taken + from[0]->wgs, most);
+  if (beside.size() < rest.size()) in_flight(rest, taken, most);
+}
 // one launch on `s` that reads and writes the states at these addresses
 struct Touch { uint64_t at; bool write; };
 void launch(hipStream_t s, const std::vector<Touch>& what, Record r) {
@@ -85,14 +103,17 @@ void launch(hipStream_t s, const std::vector<Touch>& what, Record r) {
         fault("launches %d and %d touch the state at %llx in no order", a.launch, me, (unsigned long long)t.at);
     w.access[t.at].push_back({me, t.write});
   }
-  if (r.kind == kSlabs) {   // (a launch may hold several workgroups of a CU, launches together may not)
-    // (each hands its workgroups to the eight XCDs of 32 CUs in turn, from any of them on)
-    int64_t together = (r.groups + 7) / 8;
-    const int64_t alone = together;
-    for (const auto& [other, groups] : w.slabs)
-      if (!has(before, other)) together += (groups + 7) / 8;
-    if (together > 32 && together > alone) fault("%lld slab workgroups in flight together on an XCD", (long long)together);
-    w.slabs.push_back({me, (int)r.groups});
+  if (r.kind == kSlabs) {   // (a launch alone may hold several workgroups of a CU, launches together may not)
+    w.slabs.erase(std::remove_if(w.slabs.begin(), w.slabs.end(), [](const SlabRun& o) { return has(w.host, o.launch); }),
+                  w.slabs.end());
+    w.slabs.push_back({me, (r.groups + 7) / 8, before});
+    const SlabRun& run = w.slabs.back();
+    std::vector<const SlabRun*> beside;
+    for (const SlabRun& o : w.slabs)
+      if (o.launch != me && !ordered(o, run)) beside.push_back(&o);
+    int64_t most = 0;
+    in_flight(beside, run.wgs, &most);
+    if (most > 32 && most > run.wgs) fault("%lld slab workgroups in flight together on an XCD", (long long)most);
   }
   before.resize(me + 1);
   before[me] = true;
